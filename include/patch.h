@@ -60,15 +60,14 @@ typedef struct {
                  /* prefill: K slices per output tile, one workgroup each, whose partial             */
                  /* products go to `workspace` and are summed in slice order by a second launch;     */
                  /* 0 = auto (1 unless the tile grid would leave a third of the chip idle; with a    */
-                 /* workspace a part-filled last round of at most half the chip is split on its own - */
-                 /* tile 128 only),                                                                   */
+                 /* workspace a part-filled last round of at most half the chip is split on its own),  */
                  /* 1 = no split.  Never more slices than the workspace holds: without one, no split. */
     int variant; /* kernel variant within the path, 0 = default.  Prefill: 1 = simple 128 x 128 kernel, */
                  /* 2 = 256 x 256 LDS-staged kernel (tile 128 beyond the limits of 3), 3 = 256 x 256 weights-in- */
-                 /* registers kernel (the default for tile 128 where K <= 32768 and M K 2 < 4 GB), 4 = the  */
+                 /* registers kernel (the 256-row default where K <= 16384 and M K 2 < 4 GB), 4 = the       */
                  /* LDS-staged kernel with blocks of 256 features x 128 rows, 5 = blocks of 128 rows with  */
                  /* the weights loaded straight into registers, 6 = the same with 256 rows (tile 64 only:  */
-                 /* its 256-row default).                                                                  */
+                 /* its 256-row default beyond the limits of 3).                                           */
                  /* Blocks of 128 rows (5) are the default, with no split requested, where estimated       */
                  /* faster (up to a few hundred rows).  Decode: 2 / 3 = 8 / 4                              */
                  /* K-steps per wavefront of the 16-feature-strip kernel; 4 = the kernel with 64         */

@@ -402,7 +402,7 @@ static bool use_mid_kernel(int rows, int variant, int split_k, int mid_chunks, i
 // measurements; it reproduces the crossovers above - M = 192 at 4096 x 4096, 128 from 5120 features - and also holds
 // for long-K weights of few features such as 4096 x 11008, where 16 output tiles run 172 steps each: 144 us, against
 // 45 us for a 64-row pass):
-//   unsplit prefill launch  rounds x 64-column steps x 1.0 us (tile 64 on the LDS-staged kernel: 1.45 us), or with
+//   unsplit prefill launch  rounds x 64-column steps x 1.0 us (tile 64 beyond K = 16384: 1.45 us), or with
 //                           blocks of 128 rows x 0.70 us (tile 64: 0.75), whichever is less (launch_prefill makes the
 //                           same choice)
 //   pass of up to 64 rows   steps x 0.3 us x (1 + 0.4 min(1, feature groups / 256)) x max(1, feature groups / 256)
@@ -423,7 +423,7 @@ static int auto_path(int64_t M, const patch_packed* P, const patch_gemm_opts* op
     const double rounds = (double)((tiles + P->n_cus - 1) / P->n_cus);
     const int64_t tiles128 = ((P->N + 255) / 256) * ((M + 127) / 128);   // blocks of 128 rows: 0.70 / 0.75 us per step
     const double us128 = (double)((tiles128 + P->n_cus - 1) / P->n_cus) * steps * (P->tile == 128 ? 0.70 : 0.75);
-    const double us256 = rounds * steps * (P->tile == 128 ? 1.0 : 1.45);
+    const double us256 = rounds * steps * (P->tile == 128 || P->K <= 16384 ? 1.0 : 1.45);
     const double prefill_us = us128 < us256 ? us128 : us256;
     const double groups = (double)(P->N / 64);
     // (a weight of more feature groups than the chip takes at once - 65536 features - costs that many times more)
@@ -709,9 +709,12 @@ size_t patch_gemm_workspace_bytes(int64_t M, const patch_packed* P, const patch_
     if (variant == 1) return 0;
     if (variant == 0 && split_k == 0) {
         int split128 = 1;
-        if (prefill_prefers_128_rows(a, &split128)) return split128 > 1 ? (size_t)split128 * (size_t)M * (size_t)P->N * sizeof(float) : 0;
+        // (mask tile 64: what the library asks for here, and with it which calls patch_gemm_static accepts, is the split of
+        // prefill_kernel_areg at either block height; prefill_kernel_w64 takes the slices, and the split of a part-filled
+        // last round, that fit into what it is given)
+        if (prefill_prefers_128_rows(a, &split128, true)) return split128 > 1 ? (size_t)split128 * (size_t)M * (size_t)P->N * sizeof(float) : 0;
     }
-    if (variant == 2 || variant == 4 || variant == 5 || (variant == 6 && a.tile == 64) || !prefill_wreg_supports(a)) {   // whole-launch K split only (same for both 256-row kernels)
+    if (variant == 2 || variant == 4 || variant == 5 || a.tile == 64 || !prefill_wreg_supports(a)) {   // whole-launch K split only (same for both 256-row kernels)
         const int sl = prefill_lds_split(a, split_k, variant == 4 || variant == 5 ? 128 : 256);
         return sl > 1 ? (size_t)sl * (size_t)M * (size_t)P->N * sizeof(float) : 0;
     }

@@ -695,11 +695,12 @@ int prefill_lds_split(const GemmArgs& a, int requested, int bm) {
 // estimated from measured rates:
 //     us = rounds x K-steps per workgroup x t_step + 3 + (split > 1 ? 3 + (2 split + 1) M N 4 B / 5.5 TB/s : 0)
 // A step is slower the fuller the chip (shared L2 bandwidth, power): t_step = t0 + t1 x min(1, workgroups / compute
-// units), with (t0, t1) = (0.90, 0.35) us for prefill_kernel_wreg, (1.26, 0.33) for the 256-row kernels of mask tile 64
-// and of long K, and for prefill_kernel_areg with 128 rows (0.70, 0.24) on mask tile 128, (0.75, 0.22) on mask tile 64 (fitted
+// units), with (t0, t1) = (0.90, 0.35) us for prefill_kernel_wreg and prefill_kernel_w64, (1.26, 0.33) for the 256-row
+// kernels beyond their limits, and for prefill_kernel_areg with 128 rows (0.70, 0.24) on mask tile 128, (0.75, 0.22) on mask tile 64 (fitted
 // to unsplit launches of 16 and of 256 workgroups at f = 0.6).  The 256-row side takes the
 // split its launcher would take; the 128-row side its best split of at most 8 slices of at least 512 columns that the
-// workspace holds.  Returns true, and the split, when 128 rows are estimated at least 3 % faster.
+// workspace holds.  Returns true, and the split, when 128 rows are estimated at least 3 % faster.  no_w64: mask tile 64 as if its
+// 256-row kernel were prefill_kernel_areg (see patch_gemm_workspace_bytes).
 static double pf_estimate(const GemmArgs& a, int blocks, int split, double t0, double t1) {
     const int rounds = (blocks * split + a.n_cus - 1) / a.n_cus;
     const int steps = ((a.Tk + split - 1) / split) * (a.tile / kStepCols);
@@ -709,10 +710,10 @@ static double pf_estimate(const GemmArgs& a, int blocks, int split, double t0, d
     return us;
 }
 
-bool prefill_prefers_128_rows(const GemmArgs& a, int* split) {
+bool prefill_prefers_128_rows(const GemmArgs& a, int* split, bool no_w64) {
     const int tiles_n = (int)((a.N + kPfBN - 1) / kPfBN);
     const int b256 = tiles_n * (int)((a.M + 255) / 256), b128 = tiles_n * (int)((a.M + 127) / 128);
-    const bool wreg = a.tile == 128 && prefill_wreg_supports(a);
+    const bool wreg = prefill_wreg_supports(a) && !(no_w64 && a.tile == 64);
     const double us256 = pf_estimate(a, b256, wreg ? prefill_wreg_split(a, 0) : prefill_lds_split(a, 0, 256), wreg ? 0.90 : 1.26,
                                      wreg ? 0.35 : 0.33);
     const size_t per_slice = (size_t)a.M * (size_t)a.N * sizeof(float);
@@ -728,9 +729,9 @@ bool prefill_prefers_128_rows(const GemmArgs& a, int* split) {
 }
 
 // Kernel choice.  variant 0 (default): prefill_kernel_areg with blocks of 128 rows where prefill_prefers_128_rows says so
-// (no split requested); else 256 rows: tile 128 -> prefill_kernel_wreg where its limits hold, else prefill_kernel_lds;
-// tile 64 -> prefill_kernel_areg.  variant 1 forces prefill_kernel_v0, 2 prefill_kernel_lds (256 rows), 3
-// prefill_kernel_wreg, 4 prefill_kernel_lds with 128 rows, 5 prefill_kernel_areg with 128 rows, 6 prefill_kernel_areg
+// (no split requested); else 256 rows: prefill_kernel_wreg (tile 128) or prefill_kernel_w64 (tile 64) where their limits
+// hold, else tile 128 -> prefill_kernel_lds, tile 64 -> prefill_kernel_areg.  variant 1 forces prefill_kernel_v0, 2
+// prefill_kernel_lds (256 rows), 3 prefill_kernel_wreg / prefill_kernel_w64, 4 prefill_kernel_lds with 128 rows, 5 prefill_kernel_areg with 128 rows, 6 prefill_kernel_areg
 // with 256 rows (mask tile 64 only); each falls back to the default choice where it does not apply.
 template <int TILE, int BM>
 static void launch_prefill_lds(const GemmArgs& a, int split_k, hipStream_t stream) {
@@ -764,7 +765,7 @@ void launch_prefill(const GemmArgs& a, int variant, int split_k, hipStream_t str
             return;
         }
     }
-    if (a.tile == 128 && (variant == 0 || variant == 3) && prefill_wreg_supports(a)) { launch_prefill_wreg(a, split_k, stream); return; }
+    if ((variant == 0 || variant == 3) && prefill_wreg_supports(a)) { launch_prefill_wreg(a, split_k, stream); return; }
     if (variant == 5) {   // 128 rows, weights in registers
         if (a.tile == 128) launch_prefill_areg<128, 128>(a, split_k, stream);
         else launch_prefill_areg<64, 128>(a, split_k, stream);

@@ -1,5 +1,11 @@
-// Prefill-shaped hybrid GEMM for tile = 128 with the weights loaded straight into registers (Section 4 /
-// Appendix A of the paper: the product for the prefill input, dense and 2:4 tiles mixed inside one launch).
+// Prefill-shaped hybrid GEMM with the weights loaded straight into registers (Section 4 / Appendix A of the paper: the
+// product for the prefill input, dense and 2:4 tiles mixed inside one launch): prefill_kernel_wreg for mask tile 128,
+// which the following describes, and prefill_kernel_w64 for mask tile 64 - the same loop with every step a tile of its
+// own and every wavefront a tile row of its own.  Mask tile 64 used to run on prefill_kernel_areg<64, 256> (8 wavefronts,
+// 32 x 32 matrix instructions, every wavefront reading all of X from LDS: 1.4 - 1.6 us per 64-column step, compiler-scheduled);
+// a step takes 1.0 - 1.1 us here.  f = 0.6, fp32 output, before -> after: 11008 x 4096 at M = 1003 / 2048 / 4096 92 / 190 / 308 ->
+// 69 / 148 / 240 us, 4096 x 11008 98 / 170 / 283 -> 88 / 134 / 212 us; a set runs as one launch (two 11008 x 4096 at M = 512
+// 124 -> 74 us, three 4096 x 4096 at M = 66 50 -> 32 us).
 //
 // Workgroup = 256 output features (two tile rows) x 256 rows of X, 4 wavefronts (one per SIMD).  Wavefront w owns
 // 64 features (4 strips of tile row w / 2) x ALL 256 rows of X: its weight fragments are private, so they go
@@ -45,6 +51,8 @@ constexpr int kWrStage = kWrBM * 128;   // 256 rows of X x 64 columns, swizzled
 constexpr int kWrRing = 4 * kWrStage;   // 128 KB: the four X stages
 constexpr int kWrOut = 4096;            // per wavefront: 16 rows x 64 features fp32 of the output stage
 constexpr int kWrLds = kWrRing + 4 * kWrOut;   // 144 KB
+constexpr int kWrEntries = 320;         // mask tile 64: table entries per wavefront kept in LDS (256 tiles and three more), whole lanes
+constexpr int kWrLds64 = kWrLds + 4 * kWrEntries * 4;   // 149 KB
 
 typedef __attribute__((address_space(3))) void* wr_lptr_t;
 
@@ -103,7 +111,9 @@ typedef __attribute__((address_space(3))) void* wr_lptr_t;
 //
 // ---- weight load of slot I (0..7) of the step two ahead into buffer ABN: one instruction in column block I
 #define PATCH_WR_WLOAD_03(ABN, I) "global_load_dwordx4 " PATCH_WR_VA(ABN, I) ", v[228+" #I "], s[84:85]\n\t"
-#define PATCH_WR_WLOAD_47(ABN, I) "global_load_dwordx4 " PATCH_WR_VA(ABN, I) ", v[228+" #I "], s[96:97]\n\t"
+#define PATCH_WR_WLOAD_47(ABN, I, PAR) "global_load_dwordx4 " PATCH_WR_VA(ABN, I) ", v[228+" #I "], " PATCH_WR_B47_##PAR "\n\t"
+#define PATCH_WR_B47_0 "s[96:97]"
+#define PATCH_WR_B47_1 "s[96:97]"
 // X load SLOT (0..7) of the step three ahead: 16 bytes per lane, global -> LDS at m0 + lane * 16
 #define PATCH_WR_X3(SLOT) "s_add_u32 m0, s91, 4096*" #SLOT "\n\t"
 #define PATCH_WR_X4(SLOT) "global_load_lds_dwordx4 %[xo" #SLOT "], s[82:83]\n\t"
@@ -124,22 +134,22 @@ typedef __attribute__((address_space(3))) void* wr_lptr_t;
 #define PATCH_WR_LD3_13(ABN) PATCH_WR_X3(5)
 #define PATCH_WR_LD3_14(ABN) PATCH_WR_X3(6)
 #define PATCH_WR_LD3_15(ABN) PATCH_WR_X3(7)
-#define PATCH_WR_LD4_0(ABN) PATCH_WR_WLOAD_03(ABN, 0)
-#define PATCH_WR_LD4_1(ABN) PATCH_WR_WLOAD_03(ABN, 1)
-#define PATCH_WR_LD4_2(ABN) PATCH_WR_WLOAD_03(ABN, 2)
-#define PATCH_WR_LD4_3(ABN) PATCH_WR_WLOAD_03(ABN, 3)
-#define PATCH_WR_LD4_4(ABN) PATCH_WR_WLOAD_47(ABN, 4)
-#define PATCH_WR_LD4_5(ABN) PATCH_WR_WLOAD_47(ABN, 5)
-#define PATCH_WR_LD4_6(ABN) PATCH_WR_WLOAD_47(ABN, 6)
-#define PATCH_WR_LD4_7(ABN) PATCH_WR_WLOAD_47(ABN, 7)
-#define PATCH_WR_LD4_8(ABN) PATCH_WR_X4(0)
-#define PATCH_WR_LD4_9(ABN) PATCH_WR_X4(1)
-#define PATCH_WR_LD4_10(ABN) PATCH_WR_X4(2)
-#define PATCH_WR_LD4_11(ABN) PATCH_WR_X4(3)
-#define PATCH_WR_LD4_12(ABN) PATCH_WR_X4(4)
-#define PATCH_WR_LD4_13(ABN) PATCH_WR_X4(5)
-#define PATCH_WR_LD4_14(ABN) PATCH_WR_X4(6)
-#define PATCH_WR_LD4_15(ABN) PATCH_WR_X4(7)
+#define PATCH_WR_LD4_0(ABN, PAR) PATCH_WR_WLOAD_03(ABN, 0)
+#define PATCH_WR_LD4_1(ABN, PAR) PATCH_WR_WLOAD_03(ABN, 1)
+#define PATCH_WR_LD4_2(ABN, PAR) PATCH_WR_WLOAD_03(ABN, 2)
+#define PATCH_WR_LD4_3(ABN, PAR) PATCH_WR_WLOAD_03(ABN, 3)
+#define PATCH_WR_LD4_4(ABN, PAR) PATCH_WR_WLOAD_47(ABN, 4, PAR)
+#define PATCH_WR_LD4_5(ABN, PAR) PATCH_WR_WLOAD_47(ABN, 5, PAR)
+#define PATCH_WR_LD4_6(ABN, PAR) PATCH_WR_WLOAD_47(ABN, 6, PAR)
+#define PATCH_WR_LD4_7(ABN, PAR) PATCH_WR_WLOAD_47(ABN, 7, PAR)
+#define PATCH_WR_LD4_8(ABN, PAR) PATCH_WR_X4(0)
+#define PATCH_WR_LD4_9(ABN, PAR) PATCH_WR_X4(1)
+#define PATCH_WR_LD4_10(ABN, PAR) PATCH_WR_X4(2)
+#define PATCH_WR_LD4_11(ABN, PAR) PATCH_WR_X4(3)
+#define PATCH_WR_LD4_12(ABN, PAR) PATCH_WR_X4(4)
+#define PATCH_WR_LD4_13(ABN, PAR) PATCH_WR_X4(5)
+#define PATCH_WR_LD4_14(ABN, PAR) PATCH_WR_X4(6)
+#define PATCH_WR_LD4_15(ABN, PAR) PATCH_WR_X4(7)
 
 // ---- lane LDS addresses by step parity PAR: column blocks 0-8 read ahead inside the step's own stage (address pair
 // "cur"), column blocks 9-15 into the next stage ("nxt")
@@ -259,6 +269,126 @@ typedef __attribute__((address_space(3))) void* wr_lptr_t;
 #define PATCH_WR_K1_15_1 "v_cndmask_b32_e64 v235, v243, v251, s[92:93]\n\t"
 #define PATCH_WR_K2_15_1 "s_mov_b64 s[84:85], s[74:75]\n\ts_mov_b64 s[96:97], s[74:75]\n\t"
 #define PATCH_WR_K3_15_1 "s_add_i32 s80, s80, 1\n\t"
+// ---- mask tile 64 (prefill_kernel_w64): a step is a tile of its own, so every step does what an odd step does above, once:
+// "parities" 2 / 3 are the even / odd steps of that loop.  Besides the registers above (s[74:75], s86, s[96:97] and
+// v236-v247 have no use or another one there):
+//   s[84:85]  address of the tile the weight loads of this step fetch: tile s + 2
+//   s77, s78  types of the tiles of steps s + 1 / s + 2 (a queue that ends in s87)
+//   v228-v231 lane offsets of weight-load slots 0-3, the same for either type; v232-v235 those of slots 4-7 for the type of the
+//             tile being loaded, selected from v240-v243 (dense) and v248-v251 (2:4: 16 bytes starting at the dword that holds
+//             the 16-bit position words of the lane and of its neighbour)
+//   v238      16 for odd lanes, 0 for even ones: a 2:4 step shifts its four position dwords down by it before the first use
+//   v236      LDS address of entry s + 3 of the tile row's list of table entries (a copy in LDS, one ds_read_b32 per step in
+//             block 3, taken from v237 in block 10: six blocks' reads, twelve in number, were requested after it, so
+//             the block's own wait for all but twelve covers it; before that the wait is stricter by one read).  v_readlane,
+//             as above, would need four registers of entries and three selects at K = 16384.
+//   blocks 10-14: entry s76 of tile s + 3, its address, the four lane offsets, the type queue (all after the last weight load, block 7)
+#define PATCH_WR_B47_2 "s[84:85]"
+#define PATCH_WR_B47_3 "s[84:85]"
+#define PATCH_WR_CURL_2 PATCH_WR_CURL_0
+#define PATCH_WR_CURH_2 PATCH_WR_CURH_0
+#define PATCH_WR_NXTL_2 PATCH_WR_NXTL_0
+#define PATCH_WR_NXTH_2 PATCH_WR_NXTH_0
+#define PATCH_WR_CURL_3 PATCH_WR_CURL_1
+#define PATCH_WR_CURH_3 PATCH_WR_CURH_1
+#define PATCH_WR_NXTL_3 PATCH_WR_NXTL_1
+#define PATCH_WR_NXTH_3 PATCH_WR_NXTH_1
+#define PATCH_WR_K1_0_2 "s_add_i32 s88, s80, 3\n\t"
+#define PATCH_WR_K2_0_2 "s_min_i32 s89, s88, %[sm1]\n\t"
+#define PATCH_WR_K3_0_2 "s_lshl_b32 s89, s89, 7\n\t"
+#define PATCH_WR_K1_1_2 "s_add_u32 s82, %[xlo], s89\n\ts_addc_u32 s83, %[xhi], 0\n\t"
+#define PATCH_WR_K2_1_2 "s_and_b32 s88, s88, 3\n\t"
+#define PATCH_WR_K3_1_2 "s_lshl_b32 s88, s88, 15\n\t"
+#define PATCH_WR_K1_2_2 "s_add_u32 s91, %[ldsw], s88\n\t"
+#define PATCH_WR_K2_2_2 ""
+#define PATCH_WR_K3_2_2 ""
+#define PATCH_WR_K1_3_2 "ds_read_b32 v237, v236\n\t"
+#define PATCH_WR_K2_3_2 "v_add_u32 v236, 4, v236\n\t"
+#define PATCH_WR_K3_3_2 ""
+#define PATCH_WR_K1_4_2 ""
+#define PATCH_WR_K2_4_2 ""
+#define PATCH_WR_K3_4_2 ""
+#define PATCH_WR_K1_5_2 ""
+#define PATCH_WR_K2_5_2 ""
+#define PATCH_WR_K3_5_2 ""
+#define PATCH_WR_K1_6_2 ""
+#define PATCH_WR_K2_6_2 ""
+#define PATCH_WR_K3_6_2 ""
+#define PATCH_WR_K1_7_2 ""
+#define PATCH_WR_K2_7_2 ""
+#define PATCH_WR_K3_7_2 ""
+#define PATCH_WR_K1_8_2 ""
+#define PATCH_WR_K2_8_2 ""
+#define PATCH_WR_K3_8_2 ""
+#define PATCH_WR_K1_9_2 "s_add_i32 s88, s80, 2\n\t"
+#define PATCH_WR_K2_9_2 "s_and_b32 s88, s88, 3\n\t"
+#define PATCH_WR_K3_9_2 "s_lshl_b32 s88, s88, 15\n\t"
+#define PATCH_WR_K1_10_2 "v_add_u32 v224, s88, %[bl0]\n\t"
+#define PATCH_WR_K2_10_2 "v_add_u32 v225, s88, %[bh0]\n\t"
+#define PATCH_WR_K3_10_2 "v_readfirstlane_b32 s76, v237\n\t"
+#define PATCH_WR_K1_11_2 "s_lshr_b32 s95, s76, 25\n\t"
+#define PATCH_WR_K2_11_2 "s_lshl_b32 s94, s76, 7\n\t"
+#define PATCH_WR_K3_11_2 "s_bitset0_b32 s94, 7\n\t"
+#define PATCH_WR_K1_12_2 "s_add_u32 s84, %[plo], s94\n\ts_addc_u32 s85, %[phi], s95\n\t"
+#define PATCH_WR_K2_12_2 "s_bitcmp1_b32 s76, 0\n\ts_cselect_b64 s[92:93], -1, 0\n\t"
+#define PATCH_WR_K3_12_2 "v_cndmask_b32_e64 v232, v240, v248, s[92:93]\n\t"
+#define PATCH_WR_K1_13_2 "v_cndmask_b32_e64 v233, v241, v249, s[92:93]\n\t"
+#define PATCH_WR_K2_13_2 "v_cndmask_b32_e64 v234, v242, v250, s[92:93]\n\t"
+#define PATCH_WR_K3_13_2 "v_cndmask_b32_e64 v235, v243, v251, s[92:93]\n\t"
+#define PATCH_WR_K1_14_2 "s_mov_b32 s87, s77\n\t"
+#define PATCH_WR_K2_14_2 "s_mov_b32 s77, s78\n\t"
+#define PATCH_WR_K3_14_2 "s_and_b32 s78, s76, %[live]\n\t"
+#define PATCH_WR_K1_15_2 ""
+#define PATCH_WR_K2_15_2 ""
+#define PATCH_WR_K3_15_2 "s_add_i32 s80, s80, 1\n\t"
+#define PATCH_WR_K1_0_3 "s_add_i32 s88, s80, 3\n\t"
+#define PATCH_WR_K2_0_3 "s_min_i32 s89, s88, %[sm1]\n\t"
+#define PATCH_WR_K3_0_3 "s_lshl_b32 s89, s89, 7\n\t"
+#define PATCH_WR_K1_1_3 "s_add_u32 s82, %[xlo], s89\n\ts_addc_u32 s83, %[xhi], 0\n\t"
+#define PATCH_WR_K2_1_3 "s_and_b32 s88, s88, 3\n\t"
+#define PATCH_WR_K3_1_3 "s_lshl_b32 s88, s88, 15\n\t"
+#define PATCH_WR_K1_2_3 "s_add_u32 s91, %[ldsw], s88\n\t"
+#define PATCH_WR_K2_2_3 ""
+#define PATCH_WR_K3_2_3 ""
+#define PATCH_WR_K1_3_3 "ds_read_b32 v237, v236\n\t"
+#define PATCH_WR_K2_3_3 "v_add_u32 v236, 4, v236\n\t"
+#define PATCH_WR_K3_3_3 ""
+#define PATCH_WR_K1_4_3 ""
+#define PATCH_WR_K2_4_3 ""
+#define PATCH_WR_K3_4_3 ""
+#define PATCH_WR_K1_5_3 ""
+#define PATCH_WR_K2_5_3 ""
+#define PATCH_WR_K3_5_3 ""
+#define PATCH_WR_K1_6_3 ""
+#define PATCH_WR_K2_6_3 ""
+#define PATCH_WR_K3_6_3 ""
+#define PATCH_WR_K1_7_3 ""
+#define PATCH_WR_K2_7_3 ""
+#define PATCH_WR_K3_7_3 ""
+#define PATCH_WR_K1_8_3 ""
+#define PATCH_WR_K2_8_3 ""
+#define PATCH_WR_K3_8_3 ""
+#define PATCH_WR_K1_9_3 "s_add_i32 s88, s80, 2\n\t"
+#define PATCH_WR_K2_9_3 "s_and_b32 s88, s88, 3\n\t"
+#define PATCH_WR_K3_9_3 "s_lshl_b32 s88, s88, 15\n\t"
+#define PATCH_WR_K1_10_3 "v_add_u32 v226, s88, %[bl0]\n\t"
+#define PATCH_WR_K2_10_3 "v_add_u32 v227, s88, %[bh0]\n\t"
+#define PATCH_WR_K3_10_3 "v_readfirstlane_b32 s76, v237\n\t"
+#define PATCH_WR_K1_11_3 "s_lshr_b32 s95, s76, 25\n\t"
+#define PATCH_WR_K2_11_3 "s_lshl_b32 s94, s76, 7\n\t"
+#define PATCH_WR_K3_11_3 "s_bitset0_b32 s94, 7\n\t"
+#define PATCH_WR_K1_12_3 "s_add_u32 s84, %[plo], s94\n\ts_addc_u32 s85, %[phi], s95\n\t"
+#define PATCH_WR_K2_12_3 "s_bitcmp1_b32 s76, 0\n\ts_cselect_b64 s[92:93], -1, 0\n\t"
+#define PATCH_WR_K3_12_3 "v_cndmask_b32_e64 v232, v240, v248, s[92:93]\n\t"
+#define PATCH_WR_K1_13_3 "v_cndmask_b32_e64 v233, v241, v249, s[92:93]\n\t"
+#define PATCH_WR_K2_13_3 "v_cndmask_b32_e64 v234, v242, v250, s[92:93]\n\t"
+#define PATCH_WR_K3_13_3 "v_cndmask_b32_e64 v235, v243, v251, s[92:93]\n\t"
+#define PATCH_WR_K1_14_3 "s_mov_b32 s87, s77\n\t"
+#define PATCH_WR_K2_14_3 "s_mov_b32 s77, s78\n\t"
+#define PATCH_WR_K3_14_3 "s_and_b32 s78, s76, %[live]\n\t"
+#define PATCH_WR_K1_15_3 ""
+#define PATCH_WR_K2_15_3 ""
+#define PATCH_WR_K3_15_3 "s_add_i32 s80, s80, 1\n\t"
 // block 8 starts with the step's barrier: this wavefront's share of X(s+1) has landed (the loads issued after it: A(s+1),
 // X(s+2), A(s+2)); past the barrier all of X(s+1) is visible (first read in block 9) and every read of stage (s-1) % 4
 // has completed, so the loads of X(s+3) (one per block 8-15) may overwrite it
@@ -327,7 +457,7 @@ typedef __attribute__((address_space(3))) void* wr_lptr_t;
     "v_mfma_f32_16x16x32_bf16 " PATCH_WR_C(2, CB) ", " PATCH_WR_VA(AB, 4) ", " PATCH_WR_VBL(SET) ", " PATCH_WR_C(2, CB) "\n\t" \
     PATCH_WR_LD3_##CB(ABN)                                                                                         \
     "v_mfma_f32_16x16x32_bf16 " PATCH_WR_C(3, CB) ", " PATCH_WR_VA(AB, 6) ", " PATCH_WR_VBL(SET) ", " PATCH_WR_C(3, CB) "\n\t" \
-    PATCH_WR_LD4_##CB(ABN)                                                                                         \
+    PATCH_WR_LD4_##CB(ABN, PAR)                                                                                         \
     "v_mfma_f32_16x16x32_bf16 " PATCH_WR_C(0, CB) ", " PATCH_WR_VA(AB, 1) ", " PATCH_WR_VBH(SET) ", " PATCH_WR_C(0, CB) "\n\t" \
     PATCH_WR_K1_##CB##_##PAR                                                                                       \
     "v_mfma_f32_16x16x32_bf16 " PATCH_WR_C(1, CB) ", " PATCH_WR_VA(AB, 3) ", " PATCH_WR_VBH(SET) ", " PATCH_WR_C(1, CB) "\n\t" \
@@ -346,7 +476,7 @@ typedef __attribute__((address_space(3))) void* wr_lptr_t;
     PATCH_WR_LD3_##CB(ABN)                                                                                         \
     PATCH_WR_K1_##CB##_##PAR                                                                                       \
     "v_smfmac_f32_16x16x64_bf16 " PATCH_WR_C(2, CB) ", " PATCH_WR_VA(AB, 2) ", " PATCH_WR_VB(SET) ", " PATCH_WR_VI(AB, 2) " abid:" #J "\n\t" \
-    PATCH_WR_LD4_##CB(ABN)                                                                                         \
+    PATCH_WR_LD4_##CB(ABN, PAR)                                                                                         \
     PATCH_WR_K2_##CB##_##PAR                                                                                       \
     "v_smfmac_f32_16x16x64_bf16 " PATCH_WR_C(3, CB) ", " PATCH_WR_VA(AB, 3) ", " PATCH_WR_VB(SET) ", " PATCH_WR_VI(AB, 3) " abid:" #J "\n\t" \
     PATCH_WR_K3_##CB##_##PAR
@@ -426,7 +556,7 @@ __device__ __forceinline__ void wr_tile_of(int t, int tiles_n, int tiles_m, int&
 // Sum of the partial tiles of a MODE 2 launch (slot (t - t0) * slices + y, 256 rows x 256 features each, slice 0
 // first) into Y.  Block = 16 rows of one tile; thread = 4 x 4 features of one row.
 __global__ __launch_bounds__(256) void wr_tail_reduce_kernel(const float* __restrict__ ws, int slices, int t0, int tiles_n, int tiles_m,
-                                                             int64_t M, int Tk_all, const WeightSet set, int ybf16) {
+                                                             int64_t M, int Tk_all, int tile, const WeightSet set, int ybf16) {
     const int j = blockIdx.x >> 4, chunk = blockIdx.x & 15;
     int bn, bm;
     wr_tile_of(t0 + j, tiles_n, tiles_m, bn, bm);
@@ -444,15 +574,21 @@ __global__ __launch_bounds__(256) void wr_tail_reduce_kernel(const float* __rest
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const int f = (threadIdx.x & 15) * 4 + 64 * u;   // feature inside the 256-feature block
-        const int row = pairs[2 * bn + (f >> 7)];
-        if (row < 0) continue;                           // no second tile row
+        int64_t n;                                       // feature of the weight
+        if (tile == 128) {
+            const int row = pairs[2 * bn + (f >> 7)];
+            n = row < 0 ? N : (int64_t)row * 128 + (f & 127);
+        } else {
+            n = (int64_t)bn * kWrBN + f;
+        }
+        if (n >= N) continue;                            // no such tile row
         const float* src = ws + (int64_t)j * slices * (kWrBM * kWrBN) + r * kWrBN + f;
         wr_f32x4 acc = *reinterpret_cast<const wr_f32x4*>(src);
         for (int y = 1; y < slices; ++y) {
             const wr_f32x4 v = *reinterpret_cast<const wr_f32x4*>(src + (int64_t)y * (kWrBM * kWrBN));
             acc[0] += v[0]; acc[1] += v[1]; acc[2] += v[2]; acc[3] += v[3];
         }
-        store4(Y, m * N + (int64_t)row * 128 + (f & 127), acc, ybf16);
+        store4(Y, m * N + n, acc, ybf16);
     }
 }
 
@@ -463,16 +599,17 @@ __global__ __launch_bounds__(256) void wr_tail_reduce_kernel(const float* __rest
 // MODE 2: the same split for the last few tiles of a launch whose tile count is a little more than a multiple of the
 //         CU count (a part-filled last round): slice y of tile t writes a 256 x 256 partial tile to slot
 //         (t - t0) * gridDim.y + y of the workspace, wr_tail_reduce_kernel sums the slots into Y.
-template <int MODE>
-__global__ __launch_bounds__(256) void prefill_kernel_wreg(const uint16_t* __restrict__ X, int64_t M, int64_t K, int Tk_all, int tiles_n,
-                                                           int tiles_m, int t0, int cnt, const WeightSet set, int ybf16) {
+// TILE 128: wavefronts 0, 1 own one tile row, 2, 3 the other; TILE 64: every wavefront owns a tile row (rows 4 bn + w).
+template <int MODE, int TILE>
+__device__ __forceinline__ void wr_body(const uint16_t* __restrict__ X, int64_t M, int64_t K, int Tk_all, int tiles_n, int tiles_m, int t0, int cnt,
+                                        const WeightSet& set, int ybf16) {
     constexpr bool SPLIT = MODE != 0;
-    constexpr int TILE = 128;
+    constexpr int KPT = TILE / kStepCols;   // K-steps per tile
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tr = w >> 1, sh = w & 1;  // tile row of the block, half (4 strips) of the tile
+    const int tr = TILE == 128 ? w >> 1 : w, sh = TILE == 128 ? w & 1 : 0;  // tile row of the block, half (4 strips) of the tile
     const int col = lane & 15, q = lane >> 4;
 
     // ---- block -> tile of the launch order.  Consecutive blocks go to different XCDs (hardware round-robin), each
@@ -518,11 +655,20 @@ __global__ __launch_bounds__(256) void prefill_kernel_wreg(const uint16_t* __res
     // barriers like the others, read the first row's weights (valid addresses) and multiply nothing.
     // (read through the constant address space: a scalar load; the table pointer came out of scalar selects, after
     // which the compiler no longer knows its address space and would use flat vector loads)
-    const __attribute__((address_space(4))) int32_t* pairs =
-        reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(table)) + (N / TILE) * (int64_t)Tk_all;
-    const int row0 = pairs[2 * bn], row1 = pairs[2 * bn + 1];
-    const bool live = tr == 0 || row1 >= 0;
-    const int64_t nrow = (int64_t)__builtin_amdgcn_readfirstlane((tr == 0 || row1 < 0) ? row0 : row1) * TILE;  // first feature of this wavefront's tile row
+    // Mask tile 64 has no such list: a block is four adjacent tile rows, of which the last block may lack up to three.
+    bool live;
+    int64_t nrow;   // first feature of this wavefront's tile row
+    if constexpr (TILE == 128) {
+        const __attribute__((address_space(4))) int32_t* pairs =
+            reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(table)) + (N / TILE) * (int64_t)Tk_all;
+        const int row0 = pairs[2 * bn], row1 = pairs[2 * bn + 1];
+        live = tr == 0 || row1 >= 0;
+        nrow = (int64_t)__builtin_amdgcn_readfirstlane((tr == 0 || row1 < 0) ? row0 : row1) * TILE;
+    } else {
+        const int64_t n0 = (int64_t)bn * kWrBN;
+        live = n0 + w * TILE < N;
+        nrow = n0 + (live ? w * TILE : 0);
+    }
     // this workgroup's K slice, in tiles: to the rest of the kernel it is a product with a shorter K
     const int t_begin = SPLIT ? (int)((int64_t)blockIdx.y * Tk_all / gridDim.y) : 0;
     const int Tk = SPLIT ? (int)((int64_t)(blockIdx.y + 1) * Tk_all / gridDim.y) - t_begin : Tk_all;
@@ -555,8 +701,11 @@ __global__ __launch_bounds__(256) void prefill_kernel_wreg(const uint16_t* __res
     //   2:4 slot 4 + s  : 16 bytes starting at the lane's position dword of strip s (the first register is the
     //                     dword, the rest is ignored; the last lanes read up to 12 bytes into the next tile or the
     //                     zeroed slack behind the payload)
-    const uint32_t vlane16 = lane * 16, vlane4 = lane * 4;
+    const uint32_t vlane16 = lane * 16, vlane4 = TILE == 128 ? lane * 4 : (lane >> 1) * 4;
+    // (mask tile 64: one K-step per tile, and a lane's 16-bit position word shares its dword with the neighbour's)
     auto a_base = [&](int slot, int j, uint32_t e) -> const uint8_t* {
+        if constexpr (TILE == 64)
+            return payload + entry_offset(e) + (slot >= 4 && entry_sparse(e) ? sparse_vals_bytes(TILE) + (slot - 4) * 64 * 2 : slot * 1024);
         const int cd = sh * 4 * 2 * kDenseFragBytes + (slot >> 1) * 2 * kDenseFragBytes + j * kDenseFragBytes + (slot & 1) * 1024;
         const int cs = slot < 4 ? sh * 4 * 2 * kSparseFragBytes + slot * 2 * kSparseFragBytes + j * kSparseFragBytes
                                 : sparse_vals_bytes(TILE) + (4 * sh + slot - 4) * 64 * 4;
@@ -581,18 +730,27 @@ __global__ __launch_bounds__(256) void prefill_kernel_wreg(const uint16_t* __res
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0v), "v"(xoff[slot]), "s"(xb) : "memory");
     };
 
-    const int S = 2 * Tk;  // 64-column steps
+    const int S = KPT * Tk;  // 64-column steps
     // the tile row's table entries: lane l of ent[i] holds tile 64 i + l; the loop fetches them with v_readlane (a
     // scalar load in the loop would be waited for with lgkmcnt(0), i.e. together with every LDS read in flight).
     // Tk <= 128 (prefill_wreg_supports).
-    uint32_t ent[2];
+    // Mask tile 64: Tk <= 256, the entries (three more of the last one: the loop looks up to three tiles ahead) go to the
+    // wavefront's own list in LDS instead.
+    constexpr int kEnt = TILE == 128 ? 2 : kWrEntries / 64;
+    uint32_t ent[kEnt];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < kEnt; ++i) {
         const int t = 64 * i + lane;
         ent[i] = trow[t < Tk ? t : Tk - 1];
     }
     // a use right here: the compiler waits for these loads now
-    asm volatile("" : "+v"(ent[0]), "+v"(ent[1]));
+#pragma unroll
+    for (int i = 0; i < kEnt; ++i) asm volatile("" : "+v"(ent[i]));
+    if constexpr (TILE == 64) {
+        uint32_t* const list = reinterpret_cast<uint32_t*>(lds + kWrLds) + w * kWrEntries;
+#pragma unroll
+        for (int i = 0; i < kEnt; ++i) list[64 * i + lane] = ent[i];
+    }
 
     // accumulators: zero
 #define PATCH_WR_ZERO(CB, SET, NSET)                                                                               \
@@ -609,7 +767,8 @@ __global__ __launch_bounds__(256) void prefill_kernel_wreg(const uint16_t* __res
 
     // ---- prologue, in the order the steady state would have produced: X(0) | A(0) X(1) | A(1) X(2)
     {
-        const uint32_t e0 = __builtin_amdgcn_readlane(ent[0], 0);   // tile 0: steps 0 and 1
+        const uint32_t e0 = __builtin_amdgcn_readlane(ent[0], 0);   // tile of step 0 (tile 128: and of step 1)
+        const uint32_t e1 = TILE == 128 ? e0 : __builtin_amdgcn_readlane(ent[0], 1);
         const int s1 = S > 1 ? 1 : 0, s2 = S > 2 ? 2 : S - 1;
 #pragma unroll
         for (int i = 0; i < 8; ++i) load_x_slot(i, 0, 0);
@@ -619,7 +778,7 @@ __global__ __launch_bounds__(256) void prefill_kernel_wreg(const uint16_t* __res
 #pragma unroll
         for (int i = 0; i < 8; ++i) load_x_slot(i, s1, 1);
         asm volatile("" ::: "memory");
-        PATCH_WR_LOAD_STEP(1, 1, e0)
+        PATCH_WR_LOAD_STEP(1, (TILE == 128 ? 1 : 0), e1)
         asm volatile("" ::: "memory");
 #pragma unroll
         for (int i = 0; i < 8; ++i) load_x_slot(i, s2, 2);
@@ -639,7 +798,7 @@ __global__ __launch_bounds__(256) void prefill_kernel_wreg(const uint16_t* __res
 
     // lane offsets of the weight loads inside a tile: dense operands, 2:4 values, 2:4 position dwords
     const uint32_t vd = lane * 16 + sh * 4 * 2 * kDenseFragBytes, vs = lane * 16 + sh * 4 * 2 * kSparseFragBytes;
-    const uint32_t vm = lane * 4 + sh * 4 * 64 * 4;
+    const uint32_t vm = vlane4 + sh * 4 * 64 * 4;
 // LDS offset of the column block seven ahead
 #define PATCH_WR_OFF_0 14336
 #define PATCH_WR_OFF_1 16384
@@ -672,6 +831,19 @@ __global__ __launch_bounds__(256) void prefill_kernel_wreg(const uint16_t* __res
 #define PATCH_WR_BODY_S_3(CB, SET, NSET) PATCH_WR_PIECE_SPARSE(CB, SET, NSET, 0, 2, 1, 1, PATCH_WR_OFF_##CB)
 #define PATCH_WR_BODY_S_4(CB, SET, NSET) PATCH_WR_PIECE_SPARSE(CB, SET, NSET, 1, 0, 0, 0, PATCH_WR_OFF_##CB)
 #define PATCH_WR_BODY_S_5(CB, SET, NSET) PATCH_WR_PIECE_SPARSE(CB, SET, NSET, 2, 1, 1, 1, PATCH_WR_OFF_##CB)
+// mask tile 64: K-step 0 of its tile in every step
+#define PATCH_WR_BODY_D64_0(CB, SET, NSET) PATCH_WR_PIECE_DENSE(CB, SET, NSET, 0, 2, 0, 2, PATCH_WR_OFF_##CB)
+#define PATCH_WR_BODY_D64_1(CB, SET, NSET) PATCH_WR_PIECE_DENSE(CB, SET, NSET, 1, 0, 0, 3, PATCH_WR_OFF_##CB)
+#define PATCH_WR_BODY_D64_2(CB, SET, NSET) PATCH_WR_PIECE_DENSE(CB, SET, NSET, 2, 1, 0, 2, PATCH_WR_OFF_##CB)
+#define PATCH_WR_BODY_D64_3(CB, SET, NSET) PATCH_WR_PIECE_DENSE(CB, SET, NSET, 0, 2, 0, 3, PATCH_WR_OFF_##CB)
+#define PATCH_WR_BODY_D64_4(CB, SET, NSET) PATCH_WR_PIECE_DENSE(CB, SET, NSET, 1, 0, 0, 2, PATCH_WR_OFF_##CB)
+#define PATCH_WR_BODY_D64_5(CB, SET, NSET) PATCH_WR_PIECE_DENSE(CB, SET, NSET, 2, 1, 0, 3, PATCH_WR_OFF_##CB)
+#define PATCH_WR_BODY_S64_0(CB, SET, NSET) PATCH_WR_PIECE_SPARSE(CB, SET, NSET, 0, 2, 0, 2, PATCH_WR_OFF_##CB)
+#define PATCH_WR_BODY_S64_1(CB, SET, NSET) PATCH_WR_PIECE_SPARSE(CB, SET, NSET, 1, 0, 0, 3, PATCH_WR_OFF_##CB)
+#define PATCH_WR_BODY_S64_2(CB, SET, NSET) PATCH_WR_PIECE_SPARSE(CB, SET, NSET, 2, 1, 0, 2, PATCH_WR_OFF_##CB)
+#define PATCH_WR_BODY_S64_3(CB, SET, NSET) PATCH_WR_PIECE_SPARSE(CB, SET, NSET, 0, 2, 0, 3, PATCH_WR_OFF_##CB)
+#define PATCH_WR_BODY_S64_4(CB, SET, NSET) PATCH_WR_PIECE_SPARSE(CB, SET, NSET, 1, 0, 0, 2, PATCH_WR_OFF_##CB)
+#define PATCH_WR_BODY_S64_5(CB, SET, NSET) PATCH_WR_PIECE_SPARSE(CB, SET, NSET, 2, 1, 0, 3, PATCH_WR_OFF_##CB)
 // The dense steps of a round lie one behind the other, and so do the 2:4 steps: a step whose tile has the type of
 // the one before is entered by falling through, and only a change of type (at most once per tile) takes a branch - a
 // taken branch is a bubble in the matrix pipe.  Head of step SS in either chain: an even step ends the loop when
@@ -686,12 +858,25 @@ __global__ __launch_bounds__(256) void prefill_kernel_wreg(const uint16_t* __res
     "WR_S" #SS "_%=:\n\t" PATCH_WR_END_CHECK_##EVEN "s_waitcnt vmcnt(24)\n\t"                                       \
     "s_cmp_eq_u32 s87, 0\n\ts_cbranch_scc1 WR_DB" #SS "_%=\n\t"                                                    \
     "WR_SB" #SS "_%=:\n\t" PATCH_WR_16(PATCH_WR_BODY_S_##SS)
+// mask tile 64: the tile count may be odd, so every step checks for the end; a 2:4 step brings its position words down to
+// the low half (two wait states from a vector write to a matrix instruction that reads it)
+#define PATCH_WR_STEP_D64(SS)                                                                                      \
+    "WR_D" #SS "_%=:\n\t" PATCH_WR_END_CHECK_0 "s_waitcnt vmcnt(24)\n\t"                                           \
+    "s_cmp_lg_u32 s87, 0\n\ts_cbranch_scc1 WR_SB" #SS "_%=\n\t"                                                    \
+    "WR_DB" #SS "_%=:\n\t" PATCH_WR_16(PATCH_WR_BODY_D64_##SS)
+#define PATCH_WR_STEP_S64(SS, AB)                                                                                  \
+    "WR_S" #SS "_%=:\n\t" PATCH_WR_END_CHECK_0 "s_waitcnt vmcnt(24)\n\t"                                           \
+    "s_cmp_eq_u32 s87, 0\n\ts_cbranch_scc1 WR_DB" #SS "_%=\n\t"                                                    \
+    "WR_SB" #SS "_%=:\n\t" PATCH_WR_SHIFT(AB, 0) PATCH_WR_SHIFT(AB, 1) PATCH_WR_SHIFT(AB, 2) PATCH_WR_SHIFT(AB, 3) "s_nop 1\n\t" \
+    PATCH_WR_16(PATCH_WR_BODY_S64_##SS)
+#define PATCH_WR_SHIFT(AB, S) "v_lshrrev_b32 " PATCH_WR_VI(AB, S) ", v238, " PATCH_WR_VI(AB, S) "\n\t"
     {
         const uint64_t xb64 = reinterpret_cast<uint64_t>(xbase), pl64 = reinterpret_cast<uint64_t>(payload);
         const uint32_t xlo = (uint32_t)xb64, xhi = (uint32_t)(xb64 >> 32), plo = (uint32_t)pl64, phi = (uint32_t)(pl64 >> 32);
         const uint32_t ldsw = lds0 + w * 1024;
         const int sm1 = S - 1, tkm1 = Tk - 1;
         const int live_i = __builtin_amdgcn_readfirstlane(live ? 1 : 0);
+        if constexpr (TILE == 128)
         asm volatile(
             // ---- lane offsets of the eight weight-load slots for either tile type
             "v_mov_b32 v236, %[vd]\n\tv_add_u32 v237, 1024, %[vd]\n\tv_add_u32 v238, 4096, %[vd]\n\tv_add_u32 v239, 5120, %[vd]\n\t"
@@ -729,6 +914,42 @@ __global__ __launch_bounds__(256) void prefill_kernel_wreg(const uint16_t* __res
               "v238", "v239", "v240", "v241", "v242", "v243", "v244", "v245", "v246", "v247", "v248", "v249", "v250", "v251", "s74", "s75", "s76",
               "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s88", "s89", "s90", "s91", "s92", "s93", "s94", "s95", "s96", "s97",
               PATCH_WR_CLOBBER);
+        else {
+            const uint32_t list3 = lds0 + kWrLds + w * (kWrEntries * 4) + 12;   // entry 3 of the wavefront's list
+            const uint32_t e0 = __builtin_amdgcn_readlane(ent[0], 0), e1 = __builtin_amdgcn_readlane(ent[0], 1), e2 = __builtin_amdgcn_readlane(ent[0], 2);
+            const uint32_t odd = (lane & 1) * 16;
+            asm volatile(
+                // ---- lane offsets: slots 0-3 of either type, slots 4-7 of a dense and of a 2:4 tile
+                "v_mov_b32 v228, %[vd]\n\tv_add_u32 v229, 1024, %[vd]\n\tv_add_u32 v230, 2048, %[vd]\n\tv_add_u32 v231, 3072, %[vd]\n\t"
+                "v_add_u32 v240, 4096, %[vd]\n\tv_add_u32 v241, 5120, %[vd]\n\tv_add_u32 v242, 6144, %[vd]\n\tv_add_u32 v243, 7168, %[vd]\n\t"
+                "v_add_u32 v248, 4096, %[vm]\n\tv_add_u32 v249, 4224, %[vm]\n\tv_add_u32 v250, 4352, %[vm]\n\tv_add_u32 v251, 4480, %[vm]\n\t"
+                "v_mov_b32 v236, %[list3]\n\tv_mov_b32 v238, %[odd]\n\t"
+                // ---- state of step 0: stages 0 / 1, the weight loads fetch tile min(2, Tk - 1), tile 0 is multiplied
+                "s_mov_b32 s80, 0\n\t"
+                "v_mov_b32 v224, %[bl0]\n\tv_mov_b32 v225, %[bh0]\n\t"
+                "v_add_u32 v226, 0x8000, %[bl0]\n\tv_add_u32 v227, 0x8000, %[bh0]\n\t"
+                "s_and_b32 s87, %[e0], %[live]\n\ts_and_b32 s77, %[e1], %[live]\n\ts_and_b32 s78, %[e2], %[live]\n\t"
+                "s_lshr_b32 s95, %[e2], 25\n\ts_lshl_b32 s94, %[e2], 7\n\ts_bitset0_b32 s94, 7\n\t"
+                "s_add_u32 s84, %[plo], s94\n\ts_addc_u32 s85, %[phi], s95\n\t"
+                "s_bitcmp1_b32 %[e2], 0\n\ts_cselect_b64 s[92:93], -1, 0\n\t"
+                "v_cndmask_b32_e64 v232, v240, v248, s[92:93]\n\tv_cndmask_b32_e64 v233, v241, v249, s[92:93]\n\t"
+                "v_cndmask_b32_e64 v234, v242, v250, s[92:93]\n\tv_cndmask_b32_e64 v235, v243, v251, s[92:93]\n\t"
+                // ---- the loop, as for mask tile 128
+                PATCH_WR_STEP_D64(0) PATCH_WR_STEP_D64(1) PATCH_WR_STEP_D64(2) PATCH_WR_STEP_D64(3) PATCH_WR_STEP_D64(4) PATCH_WR_STEP_D64(5)
+                "s_branch WR_D0_%=\n\t"
+                PATCH_WR_STEP_S64(0, 0) PATCH_WR_STEP_S64(1, 1) PATCH_WR_STEP_S64(2, 2) PATCH_WR_STEP_S64(3, 0) PATCH_WR_STEP_S64(4, 1) PATCH_WR_STEP_S64(5, 2)
+                "s_branch WR_S0_%=\n\t"
+                "WR_END_%=:"
+                :
+                : [S] "s"(S), [sm1] "s"(sm1), [live] "s"(live_i), [xlo] "s"(xlo), [xhi] "s"(xhi), [plo] "s"(plo), [phi] "s"(phi), [ldsw] "s"(ldsw),
+                  [e0] "s"(e0), [e1] "s"(e1), [e2] "s"(e2), [bl0] "v"(bl0), [bh0] "v"(bh0), [vd] "v"(vd), [vm] "v"(vm), [list3] "v"(list3),
+                  [odd] "v"(odd), [xo0] "v"(xoff[0]), [xo1] "v"(xoff[1]), [xo2] "v"(xoff[2]), [xo3] "v"(xoff[3]), [xo4] "v"(xoff[4]),
+                  [xo5] "v"(xoff[5]), [xo6] "v"(xoff[6]), [xo7] "v"(xoff[7])
+                : "memory", "scc", "v224", "v225", "v226", "v227", "v228", "v229", "v230", "v231", "v232", "v233", "v234", "v235", "v236", "v237",
+                  "v238", "v240", "v241", "v242", "v243", "v248", "v249", "v250", "v251", "s76", "s77", "s78", "s80", "s82", "s83", "s84", "s85",
+                  "s87", "s88", "s89", "s91", "s92", "s93", "s94", "s95", PATCH_WR_CLOBBER);
+            (void)vs; (void)tkm1;
+        }
     }
 #undef PATCH_WR_STEP_D
 #undef PATCH_WR_STEP_S
@@ -768,7 +989,7 @@ __global__ __launch_bounds__(256) void prefill_kernel_wreg(const uint16_t* __res
             const int r = 4 * j + rr; /* row inside the column block */                                            \
             const int64_t m = m0 + 16 * CB + r;                                                                    \
             /* element offset of this lane's four features: a workspace slot (MODE 2), a workspace slice (MODE 1), Y */ \
-            const int64_t ye = MODE == 2 ? ((int64_t)(bid - t0) * gridDim.y + blockIdx.y) * (kWrBM * kWrBN) + (16 * CB + r) * kWrBN + 128 * tr + 64 * sh + 4 * ch \
+            const int64_t ye = MODE == 2 ? ((int64_t)(bid - t0) * gridDim.y + blockIdx.y) * (kWrBM * kWrBN) + (16 * CB + r) * kWrBN + 64 * w + 4 * ch \
                                          : (MODE == 1 ? (int64_t)blockIdx.y * M * N : 0) + m * N + nrow + 64 * sh + 4 * ch;     \
             if (MODE == 2 || m < M) store4(Y, ye, o[j], PATCH_WR_YB);                                                       \
         }                                                                                                          \
@@ -789,14 +1010,31 @@ __global__ __launch_bounds__(256) void prefill_kernel_wreg(const uint16_t* __res
     }
 }
 
-// Limits of the kernel: 32-bit lane offsets into X, two registers of table entries per tile row (128 tiles).
-bool prefill_wreg_supports(const GemmArgs& a) {
-    return a.tile == 128 && a.M > 0 && a.K <= 128 * 128 && (uint64_t)a.M * (uint64_t)a.K * 2 < (1ull << 32);
+template <int MODE>
+__global__ __launch_bounds__(256) void prefill_kernel_wreg(const uint16_t* __restrict__ X, int64_t M, int64_t K, int Tk_all, int tiles_n,
+                                                           int tiles_m, int t0, int cnt, const WeightSet set, int ybf16) {
+    wr_body<MODE, 128>(X, M, K, Tk_all, tiles_n, tiles_m, t0, cnt, set, ybf16);
 }
+
+// The same for mask tile 64.
+template <int MODE>
+__global__ __launch_bounds__(256) void prefill_kernel_w64(const uint16_t* __restrict__ X, int64_t M, int64_t K, int Tk_all, int tiles_n,
+                                                          int tiles_m, int t0, int cnt, const WeightSet set, int ybf16) {
+    wr_body<MODE, 64>(X, M, K, Tk_all, tiles_n, tiles_m, t0, cnt, set, ybf16);
+}
+
+// Limits of the kernel: 32-bit lane offsets into X; tile 128: two registers of table entries per tile row (128 tiles); tile 64:
+// a list of 256 entries per wavefront in LDS.
+bool prefill_wreg_supports(const GemmArgs& a) {
+    return a.M > 0 && a.K <= 128 * 128 && (uint64_t)a.M * (uint64_t)a.K * 2 < (1ull << 32);
+}
+
+// most K slices of at least 512 columns
+static int wr_longest(const GemmArgs& a) { return (int)((int64_t)a.Tk * a.tile / 512); }
 
 // K slices per output tile: as many as the workspace a.ws holds partial products for (M N fp32 each), at most
 // `requested` if > 0, else as many as fill the chip when the tile grid covers less than about two thirds of it -
-// each slice at least four tiles (eight steps) long, at most 8.  1 = no split (no workspace needed).
+// each slice at least 512 columns (eight steps) long, at most 8.  1 = no split (no workspace needed).
 int prefill_wreg_split(const GemmArgs& a, int requested) {
     const int tiles = (int)(((a.N + kWrBN - 1) / kWrBN) * ((a.M + kWrBM - 1) / kWrBM));
     int s = requested;
@@ -804,7 +1042,7 @@ int prefill_wreg_split(const GemmArgs& a, int requested) {
         s = 1;
         if (tiles < (a.n_cus * 2) / 3) {
             s = a.n_cus / tiles;
-            if (s > a.Tk / 4) s = a.Tk / 4;
+            if (s > wr_longest(a)) s = wr_longest(a);
             if (s > 8) s = 8;
         }
     }
@@ -830,7 +1068,7 @@ int prefill_wreg_tail_of(int tiles, const GemmArgs& a, int* tail) {
     if (!a.ws || tiles < a.n_cus || t == 0 || 2 * t > a.n_cus) return 1;
     int s = a.n_cus / t;
     if (s > 8) s = 8;
-    if (s > a.Tk / 4) s = a.Tk / 4;
+    if (s > wr_longest(a)) s = wr_longest(a);
     const size_t per_slot = (size_t)kWrBM * kWrBN * sizeof(float);
     while (s >= 2 && (size_t)t * (size_t)s * per_slot > a.ws_bytes) --s;
     if (s < 2) return 1;
@@ -839,24 +1077,28 @@ int prefill_wreg_tail_of(int tiles, const GemmArgs& a, int* tail) {
     // a K-step costs 0.9 us on a nearly empty chip and 1.25 us on a full one: the part-filled round is shorter than a
     // full round to begin with, and its slices run on a fuller chip
     const double fill = (double)t / a.n_cus, fill_s = (double)t * s / a.n_cus;
-    const double round_us = 2.0 * a.Tk * (0.9 + 0.35 * fill) * (tiles / a.n_cus > 3 ? 0.4 : 1.0);
-    const double gain_us = round_us - 2.0 * a.Tk / s * (0.9 + 0.35 * (fill_s < 1.0 ? fill_s : 1.0)) * (tiles / a.n_cus > 3 ? 0.4 : 1.0);
+    const double steps = (double)a.Tk * (a.tile / kStepCols);
+    const double round_us = steps * (0.9 + 0.35 * fill) * (tiles / a.n_cus > 3 ? 0.4 : 1.0);
+    const double gain_us = round_us - steps / s * (0.9 + 0.35 * (fill_s < 1.0 ? fill_s : 1.0)) * (tiles / a.n_cus > 3 ? 0.4 : 1.0);
     const double cost_us = 2.0 * (double)t * s * per_slot / 3.0e6 + 8.0;
     if (gain_us <= cost_us) return 1;
     *tail = t;
     return s;
 }
 
-static void wr_grant_lds() {
-    static const hipError_t granted0 = hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_kernel_wreg<0>),
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, kWrLds);
-    static const hipError_t granted1 = hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_kernel_wreg<1>),
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, kWrLds);
-    static const hipError_t granted2 = hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_kernel_wreg<2>),
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, kWrLds);
-    (void)granted0;
-    (void)granted1;
-    (void)granted2;
+// One launch of the kernel of a.tile: tiles t0 .. t0 + cnt - 1 of the order, `slices` K slices each (MODE 1, 2).
+template <int MODE>
+static void wr_launch(const GemmArgs& a, const WeightSet& set, int tiles_m, int t0, int cnt, int slices, int ybf16, hipStream_t stream) {
+    const auto kernel = a.tile == 128 ? &prefill_kernel_wreg<MODE> : &prefill_kernel_w64<MODE>;
+    const int lds_bytes = a.tile == 128 ? kWrLds : kWrLds64;
+    static const hipError_t granted128 = hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_kernel_wreg<MODE>),
+                                                             hipFuncAttributeMaxDynamicSharedMemorySize, kWrLds);
+    static const hipError_t granted64 = hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_kernel_w64<MODE>),
+                                                            hipFuncAttributeMaxDynamicSharedMemorySize, kWrLds64);
+    (void)granted128;
+    (void)granted64;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(((cnt + 7) / 8) * 8), (unsigned)slices), dim3(256), lds_bytes, stream, a.X, a.M, a.K, a.Tk,
+                       set.units, tiles_m, t0, cnt, set, ybf16);
 }
 
 void wr_reduce(const float* ws, size_t n4, int slices, float* Y, int ybf16, hipStream_t stream) {
@@ -865,46 +1107,45 @@ void wr_reduce(const float* ws, size_t n4, int slices, float* Y, int ybf16, hipS
                        reinterpret_cast<const wr_f32x4*>(ws), n4, slices, Y, ybf16);
 }
 
+// An unsplit launch; with a.ws and a part-filled last round worth it, all full rounds unsplit, then the last tiles in K
+// slices over the whole chip, then their sum.
+static void wr_launch_whole(const GemmArgs& a, const WeightSet& set, int tiles_m, bool may_split_tail, hipStream_t stream) {
+    const int nblk = set.units * tiles_m;
+    int tail = 0;
+    const int tail_split = may_split_tail ? prefill_wreg_tail_of(nblk, a, &tail) : 1;   // 1 without a.ws
+    if (tail_split < 2) {
+        wr_launch<0>(a, set, tiles_m, 0, nblk, 1, a.ybf16, stream);
+        return;
+    }
+    const int body = nblk - tail;
+    wr_launch<0>(a, set, tiles_m, 0, body, 1, a.ybf16, stream);
+    WeightSet part = set;
+    for (int i = 0; i < kMaxMany; ++i) part.Y[i] = a.ws;   // partial tiles go to workspace slots, whatever the weight
+    wr_launch<2>(a, part, tiles_m, body, tail, tail_split, 0, stream);
+    hipLaunchKernelGGL(wr_tail_reduce_kernel, dim3(tail * 16), dim3(256), 0, stream, a.ws, tail_split, body, set.units, tiles_m, a.M, a.Tk,
+                       a.tile, set, a.ybf16);
+}
+
 void launch_prefill_wreg(const GemmArgs& a, int split_k, hipStream_t stream) {
-    wr_grant_lds();
     const int tiles_n = (int)((a.N + kWrBN - 1) / kWrBN), tiles_m = (int)((a.M + kWrBM - 1) / kWrBM);
-    const int nblk = tiles_n * tiles_m;
-    const int grid = ((nblk + 7) / 8) * 8;
     const int split = prefill_wreg_split(a, split_k);
     WeightSet set = {};
     set.payload[0] = a.payload;
     set.table[0] = a.table;
+    set.Y[0] = a.Y;
     set.N[0] = a.N;
     set.count = 1;
     set.units = tiles_n;
-    int tail = 0;
-    const int tail_split = (split == 1 && split_k == 0) ? prefill_wreg_tail(a, &tail) : 1;
-    if (split == 1 && tail_split > 1) {
-        // all full rounds unsplit, then the part-filled round in K slices over the whole chip, then their sum
-        const int body = nblk - tail;
-        set.Y[0] = a.Y;
-        hipLaunchKernelGGL(prefill_kernel_wreg<0>, dim3(((body + 7) / 8) * 8), dim3(256), kWrLds, stream, a.X, a.M, a.K, a.Tk, tiles_n,
-                           tiles_m, 0, body, set, a.ybf16);
-        set.Y[0] = a.ws;
-        hipLaunchKernelGGL(prefill_kernel_wreg<2>, dim3(((tail + 7) / 8) * 8, tail_split), dim3(256), kWrLds, stream, a.X, a.M, a.K,
-                           a.Tk, tiles_n, tiles_m, body, tail, set, 0);
-        set.Y[0] = a.Y;
-        hipLaunchKernelGGL(wr_tail_reduce_kernel, dim3(tail * 16), dim3(256), 0, stream, a.ws, tail_split, body, tiles_n, tiles_m, a.M,
-                           a.Tk, set, a.ybf16);
-    } else if (split == 1) {
-        set.Y[0] = a.Y;
-        hipLaunchKernelGGL(prefill_kernel_wreg<0>, dim3(grid), dim3(256), kWrLds, stream, a.X, a.M, a.K, a.Tk, tiles_n, tiles_m, 0, nblk,
-                           set, a.ybf16);
+    if (split == 1) {
+        wr_launch_whole(a, set, tiles_m, split_k == 0, stream);
     } else {
         set.Y[0] = a.ws;
-        hipLaunchKernelGGL(prefill_kernel_wreg<1>, dim3(grid, split), dim3(256), kWrLds, stream, a.X, a.M, a.K, a.Tk, tiles_n,
-                           tiles_m, 0, nblk, set, 0);
+        wr_launch<1>(a, set, tiles_m, 0, tiles_n * tiles_m, split, 0, stream);
         wr_reduce(a.ws, (size_t)a.M * (size_t)a.N / 4, split, a.Y, a.ybf16, stream);
     }
 }
 
 void launch_prefill_wreg_set(const GemmArgs& a, const WeightSet& set, hipStream_t stream) {
-    wr_grant_lds();
     const int tiles_m = (int)((a.M + kWrBM - 1) / kWrBM);
     const int nblk = set.units * tiles_m;
     // A set whose tile grid covers less than about two thirds of the chip (q / k / v of a 13B layer at M = 512: 120
@@ -915,7 +1156,7 @@ void launch_prefill_wreg_set(const GemmArgs& a, const WeightSet& set, hipStream_
         int64_t out_floats = 0;
         for (int i = 0; i < set.count; ++i) out_floats += a.M * set.N[i];
         int split = a.n_cus / nblk;
-        if (split > a.Tk / 4) split = a.Tk / 4;
+        if (split > wr_longest(a)) split = wr_longest(a);
         if (split > 8) split = 8;
         const size_t fit = out_floats ? a.ws_bytes / ((size_t)out_floats * sizeof(float)) : 0;
         if ((size_t)split > fit) split = (int)fit;
@@ -931,31 +1172,14 @@ void launch_prefill_wreg_set(const GemmArgs& a, const WeightSet& set, hipStream_
                 if (red.n4[i] > n4_max) n4_max = red.n4[i];
                 off += (size_t)split * (size_t)a.M * (size_t)set.N[i];
             }
-            hipLaunchKernelGGL(prefill_kernel_wreg<1>, dim3(((nblk + 7) / 8) * 8, split), dim3(256), kWrLds, stream, a.X, a.M, a.K, a.Tk,
-                               set.units, tiles_m, 0, nblk, part, 0);
+            wr_launch<1>(a, part, tiles_m, 0, nblk, split, 0, stream);
             const size_t blocks = (n4_max + 255) / 256;
             hipLaunchKernelGGL(wr_reduce_set_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048), (unsigned)set.count), dim3(256), 0, stream,
                                red, split, a.ybf16);
             return;
         }
     }
-    int tail = 0;
-    const int tail_split = prefill_wreg_tail_of(nblk, a, &tail);   // 1 without a.ws
-    if (tail_split > 1) {
-        const int body = nblk - tail;
-        hipLaunchKernelGGL(prefill_kernel_wreg<0>, dim3(((body + 7) / 8) * 8), dim3(256), kWrLds, stream, a.X, a.M, a.K, a.Tk, set.units,
-                           tiles_m, 0, body, set, a.ybf16);
-        WeightSet part = set;
-        for (int i = 0; i < kMaxMany; ++i) part.Y[i] = a.ws;   // partial tiles go to workspace slots, whatever the weight
-        hipLaunchKernelGGL(prefill_kernel_wreg<2>, dim3(((tail + 7) / 8) * 8, tail_split), dim3(256), kWrLds, stream, a.X, a.M, a.K,
-                           a.Tk, set.units, tiles_m, body, tail, part, 0);
-        hipLaunchKernelGGL(wr_tail_reduce_kernel, dim3(tail * 16), dim3(256), 0, stream, a.ws, tail_split, body, set.units, tiles_m, a.M,
-                           a.Tk, set, a.ybf16);
-        return;
-    }
-    const int grid = ((nblk + 7) / 8) * 8;
-    hipLaunchKernelGGL(prefill_kernel_wreg<0>, dim3(grid), dim3(256), kWrLds, stream, a.X, a.M, a.K, a.Tk, set.units, tiles_m, 0, nblk,
-                       set, a.ybf16);
+    wr_launch_whole(a, set, tiles_m, true, stream);
 }
 
 }  // namespace patch

@@ -262,6 +262,28 @@ def test_wreg_kernel_keeps_named_registers_to_itself(tmp_path):
     assert len(re.findall(r"\.agpr_count:\s+256", text)) >= 3
 
 
+def test_w64_kernel_keeps_named_registers_to_itself(tmp_path):
+    """prefill_kernel_w64 (the same loop for mask tile 64) names the same registers: outside its asm statements the compiler
+    touches no accumulation register, no v64 - v251 and not m0, spills nothing, and the step loop is one statement."""
+    import re
+    from paper_2509_23410_amd import build
+    text = open(build.device_asm("gemm_prefill_wreg.hip", str(tmp_path / "w64.s"))).read()
+    bodies = re.findall(r"^_ZN5patch18prefill_kernel_w64\w*:[^\n]*\n(.*?)^\.Lfunc_end\d+:", text, re.S | re.M)
+    assert len(bodies) == 3, "expected the instantiations <0>, <1>, <2>"
+    for body in bodies:
+        loop = re.search(r"WR_D0_\d+:(.*?)WR_END_\d+:", body, re.S)
+        assert loop and "#ASMEND" not in loop.group(1), "the step loop must be a single asm statement"
+        outside = re.sub(r"#ASMSTART.*?#ASMEND", "", body, flags=re.S)
+        code = "\n".join(line.split(";")[0] for line in outside.splitlines() if not line.strip().startswith("."))
+        assert not re.search(r"\ba\[?\d|accvgpr|\bm0\b", code)
+        used = [int(v) for v in re.findall(r"\bv(\d+)\b", code)] + [int(v) for r in re.findall(r"\bv\[(\d+):(\d+)\]", code) for v in r]
+        assert used and all(v < 64 or v > 251 for v in used)
+    kernels = [k for k in re.split(r"(?m)^  - \.a", text[text.index("amdhsa.kernels"):]) if "prefill_kernel_w64" in k]
+    assert len(kernels) == 3
+    for k in kernels:
+        assert re.search(r"\.vgpr_spill_count:\s+0\b", k)
+
+
 @pytest.mark.parametrize("source,kernel,at_least", [("gemm_decode.hip", "decode_kernel", 4), ("gemm_mid.hip", "mid_kernel", 4),
                                                    ("gemm_prefill.hip", "prefill_kernel_lds", 2), ("gemm_prefill.hip", "prefill_kernel_areg", 6), ("quant4.hip", "prefill4_kernel", 8)])
 def test_kernels_with_untracked_loads_do_not_spill(source, kernel, at_least):
