@@ -57,11 +57,19 @@ __host__ __device__ constexpr int64_t q4_scale_index(int64_t strip, int Tk, int 
 
 __device__ __forceinline__ float q4_bf16_to_float(uint32_t bits) { return __uint_as_float(bits << 16); }
 
-// 4-bit code of w for scale s (s > 0), as a nibble
-__device__ __forceinline__ uint32_t q4_code(uint16_t w_bits, float s) {
-    float r = rintf(__fdiv_rn(q4_bf16_to_float(w_bits), s));
-    r = fminf(fmaxf(r, -7.0f), 7.0f);
-    return (uint32_t)((int)r) & 0xFu;
+// 4-bit code of w for scale s (s > 0), as a nibble: rint(w / s) clamped, the quotient correctly rounded.  Where s is well
+// inside the exponent range, w inv refined once rounds to the same integer as the division (about a dozen instructions):
+// w and s are bf16 (8-bit significands), so their quotient is a half-integer exactly - which the refinement then
+// reproduces, its residual being exact - or at least 2^-10 away from one.  inv = 1 / s to a few units in the last place.
+// The quotient is at most 7 (1 + 2^-8) (s = max |w| / 7 rounded to bf16), so it needs no clamp there, and adding 1.5 x 2^23
+// rounds it to an integer, ties to even, whose low bits are the sum's.
+__device__ __forceinline__ uint32_t q4_code(uint16_t w_bits, float s, float inv, bool plain) {
+    const float w = q4_bf16_to_float(w_bits);
+    if (plain) {
+        const float q0 = w * inv;
+        return __float_as_uint(__builtin_fmaf(__builtin_fmaf(-q0, s, w), inv, q0) + 0x1.8p23f) & 0xFu;
+    }
+    return (uint32_t)((int)fminf(fmaxf(rintf(__fdiv_rn(w, s)), -7.0f), 7.0f)) & 0xFu;
 }
 
 // 8 codes of a dword -> 8 bf16 values bf16(q s), element e from bits [4e+3 : 4e].  v_cvt_off_f32_i4 turns the low nibble
@@ -91,143 +99,153 @@ __device__ __forceinline__ q4_u32x4 q4_dequant8(uint32_t codes, float s) {
 
 __device__ __forceinline__ bool q4_nonzero(uint16_t h) { return (h & 0x7FFFu) != 0; }
 
-// One workgroup per tile: scales, then codes (and, for a 2:4 tile, the kept positions of the unquantized weights).
+// One workgroup per tile: scales and codes (and, for a 2:4 tile, the kept positions of the unquantized weights).  Bound by
+// memory (2 bytes read, 0.4 - 0.5 written per weight): a thread holds its 16-byte pieces of the tile in registers, so W is read
+// once, in whole rows (consecutive lanes take consecutive pieces of a row); the lanes of a row find its maximum among
+// themselves; the codes are put together in LDS and leave as one contiguous run.  A first version (one thread per row for the
+// maximum, the tile read again in fragment order, a division per weight) took 76 us on 11008 x 4096, tile 128, f = 0.5, and 31 us on
+// 4096 x 4096, tile 64; this one 41 and 17 us (about half of that is arithmetic: eight instructions per code).
+template <int TILE>
 __global__ __launch_bounds__(256) void pack4_kernel(const uint16_t* __restrict__ W, int64_t K, const uint32_t* __restrict__ table, int Tk,
-                                                    int tile, uint8_t* __restrict__ payload, uint16_t* __restrict__ scales,
-                                                    int* __restrict__ err) {
-    __shared__ float sc[128];
+                                                    uint8_t* __restrict__ payload, uint16_t* __restrict__ scales, int* __restrict__ err) {
+    constexpr int KPT = TILE / kStepCols, SPT = TILE / kStripRows;
+    constexpr int CPR = TILE / 8, RPP = 256 / CPR, PASSES = TILE / RPP;   // pieces per row, rows per pass, passes
+    __shared__ __attribute__((aligned(16))) uint8_t stage[q4_dense_tile(TILE)];
     const int t = blockIdx.x;
     const int tn = t / Tk, tk = t % Tk;
     const uint32_t e = table[t];
     const bool sparse = entry_sparse(e);
-    uint8_t* base = payload + entry_offset(e);
-    const int64_t n0 = (int64_t)tn * tile, k0 = (int64_t)tk * tile;
-    const int KPT = tile / kStepCols, SPT = tile / kStripRows;
-    for (int r = threadIdx.x; r < tile; r += blockDim.x) {
-        const uint16_t* row = W + (n0 + r) * K + k0;
+    const int kc = threadIdx.x % CPR, r0 = threadIdx.x / CPR;   // piece of the row, first row
+    const int j = kc >> 3;                                      // K-step of the piece
+    union Piece { q4_u32x4 v; uint16_t h[8]; } in[PASSES];
+    const uint16_t* src = W + ((int64_t)tn * TILE + r0) * K + (int64_t)tk * TILE + 8 * kc;
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) in[p].v = *reinterpret_cast<const q4_u32x4*>(src + (int64_t)p * RPP * K);
+    bool ok = true;
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        const int row = r0 + p * RPP, strip = row >> 4, i = row & 15;
         uint32_t amax = 0;   // |w| compares like its bit pattern
-        for (int k = 0; k < tile; k += 8) {
-            union { q4_u32x4 v; uint16_t h[8]; } in;
-            in.v = *reinterpret_cast<const q4_u32x4*>(row + k);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) { const uint32_t a = in.h[i] & 0x7FFFu; amax = a > amax ? a : amax; }
-        }
+        for (int k = 0; k < 8; ++k) { const uint32_t a = in[p].h[k] & 0x7FFFu; amax = a > amax ? a : amax; }
+#pragma unroll
+        for (int x = 1; x < CPR; x <<= 1) { const uint32_t a = __shfl_xor(amax, x); amax = a > amax ? a : amax; }
         const uint32_t sb = bf16_rne_bits(__fdiv_rn(q4_bf16_to_float(amax), 7.0f));
-        scales[q4_scale_index((int64_t)tn * SPT + r / 16, Tk, tk, r % 16)] = (uint16_t)sb;
-        sc[r] = q4_bf16_to_float(sb);
-    }
-    __syncthreads();
-    if (!sparse) {
-        const int nchunks = tile * tile / 16;   // one lane of one fragment: 16 elements -> 2 dwords
-        for (int c = threadIdx.x; c < nchunks; c += blockDim.x) {
-            const int lane = c & 63, sj = c >> 6;
-            const int j = sj % KPT, s = sj / KPT, i = lane & 15, q = lane >> 4;
-            const float scl = sc[16 * s + i];
-            uint32_t d[2];
+        if (kc == 0) scales[q4_scale_index((int64_t)tn * SPT + strip, Tk, tk, i)] = (uint16_t)sb;
+        const float scl = q4_bf16_to_float(sb), inv = __builtin_amdgcn_rcpf(scl);
+        const bool some = scl > 0.f, plain = scl >= 0x1p-100f && scl <= 0x1p100f;
+        if (!sparse) {
+            // operand h of the fragment, k = 8 q + element: one dword of eight codes
+            const int h = (kc >> 2) & 1, q = kc & 3;
+            uint32_t codes = 0;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                union { q4_u32x4 v; uint16_t hh[8]; } in;
-                in.v = *reinterpret_cast<const q4_u32x4*>(W + (n0 + 16 * s + i) * K + k0 + 64 * j + 32 * h + 8 * q);
-                uint32_t w = 0;
-#pragma unroll
-                for (int el = 0; el < 8; ++el) w |= (scl > 0.f ? q4_code(in.hh[el], scl) : 0u) << (4 * el);
-                d[h] = w;
-            }
-            *reinterpret_cast<uint2*>(base + (size_t)c * 8) = uint2{d[0], d[1]};
-        }
-    } else {
-        const int nchunks = tile * tile / 16;   // one lane of one fragment: 16 elements -> 8 kept codes
-        uint16_t* meta = reinterpret_cast<uint16_t*>(base + q4_sparse_codes(tile));
-        bool ok = true;
-        for (int c = threadIdx.x; c < nchunks; c += blockDim.x) {
-            const int lane = c & 63, sj = c >> 6;
-            const int j = sj % KPT, s = sj / KPT, i = lane & 15, qa = lane >> 4;
-            const float scl = sc[16 * s + i];
-            union { q4_u32x4 v[2]; uint16_t h[16]; } in;
-            const uint16_t* src = W + (n0 + 16 * s + i) * K + k0 + 64 * j + 16 * qa;
-            in.v[0] = *reinterpret_cast<const q4_u32x4*>(src);
-            in.v[1] = *reinterpret_cast<const q4_u32x4*>(src + 8);
+            for (int k = 0; k < 8; ++k) codes |= (some ? q4_code(in[p].h[k], scl, inv, plain) : 0u) << (4 * k);
+            *reinterpret_cast<uint32_t*>(stage + (strip * KPT + j) * 512 + (16 * q + i) * 8 + 4 * h) = codes;
+        } else {
+            // half of the 16 columns of a fragment's lane: two groups of four -> four kept codes, eight position bits
+            const int lane = 16 * ((kc & 7) >> 1) + i, half = kc & 1;
             uint32_t codes = 0, idx = 0;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
+            for (int g = 0; g < 2; ++g) {
                 // kept positions: the nonzeros, padded with the lowest-index zeros (the rule of the bf16 packer)
                 bool keep[4];
                 int nnz = 0;
 #pragma unroll
-                for (int p = 0; p < 4; ++p) { keep[p] = q4_nonzero(in.h[4 * g + p]); nnz += keep[p] ? 1 : 0; }
+                for (int c = 0; c < 4; ++c) { keep[c] = q4_nonzero(in[p].h[4 * g + c]); nnz += keep[c] ? 1 : 0; }
                 if (nnz > 2) ok = false;
 #pragma unroll
-                for (int p = 0; p < 4; ++p)
-                    if (!keep[p] && nnz < 2) { keep[p] = true; ++nnz; }
-                int p0 = -1, p1 = -1;
+                for (int c = 0; c < 4; ++c)
+                    if (!keep[c] && nnz < 2) { keep[c] = true; ++nnz; }
+                int p0 = 0, p1 = 1;   // first and second kept position (the others exist when ok)
+                uint16_t w0 = in[p].h[4 * g], w1 = in[p].h[4 * g + 1];
+                int seen = 0;
 #pragma unroll
-                for (int p = 0; p < 4; ++p)
-                    if (keep[p]) { if (p0 < 0) p0 = p; else if (p1 < 0) p1 = p; }
-                if (p1 < 0) { p0 = 0; p1 = 1; }
-                const uint32_t c0 = scl > 0.f ? q4_code(in.h[4 * g + p0], scl) : 0u, c1 = scl > 0.f ? q4_code(in.h[4 * g + p1], scl) : 0u;
+                for (int c = 0; c < 4; ++c)
+                    if (keep[c]) {
+                        if (seen == 0) { p0 = c; w0 = in[p].h[4 * g + c]; }
+                        else if (seen == 1) { p1 = c; w1 = in[p].h[4 * g + c]; }
+                        ++seen;
+                    }
+                const uint32_t c0 = some ? q4_code(w0, scl, inv, plain) : 0u, c1 = some ? q4_code(w1, scl, inv, plain) : 0u;
                 codes |= (c0 | (c1 << 4)) << (8 * g);
                 idx |= (uint32_t)(p0 | (p1 << 2)) << (4 * g);
             }
-            *reinterpret_cast<uint32_t*>(base + (size_t)c * 4) = codes;
-            meta[(s * 64 + lane) * KPT + j] = (uint16_t)idx;
+            *reinterpret_cast<uint16_t*>(stage + (strip * KPT + j) * 256 + lane * 4 + 2 * half) = (uint16_t)codes;
+            stage[q4_sparse_codes(TILE) + ((strip * 64 + lane) * KPT + j) * 2 + half] = (uint8_t)idx;
         }
-        if (!ok) atomicOr(err, 1);
     }
+    if (!ok) atomicOr(err, 1);
+    __syncthreads();
+    q4_u32x4* out = reinterpret_cast<q4_u32x4*>(payload + entry_offset(e));
+    const int n16 = (sparse ? q4_sparse_tile(TILE) : q4_dense_tile(TILE)) / 16;
+    for (int c = threadIdx.x; c < n16; c += 256) out[c] = reinterpret_cast<const q4_u32x4*>(stage)[c];
 }
 
-// The inverse: the dequantized bf16 matrix and / or the codes (int8, 0 at dropped positions) and scales in matrix order.
+// The inverse: the dequantized bf16 matrix and / or the codes (int8, 0 at dropped positions) and scales in matrix order.  Bound
+// by memory, mostly by what it writes: the tile's codes pass through LDS, then a thread turns eight consecutive columns of a row
+// into one 16-byte and one 8-byte store, consecutive lanes side by side (4096 x 4096, tile 64, all three outputs: 14 us, 4.2 TB/s; with
+// 2-byte and 1-byte stores 62 us; 11008 x 4096, tile 128: 30 us against 161).  `codes_out` has no alignment of its own: where it is not 8-byte aligned its bytes go one by one.
+template <int TILE>
 __global__ __launch_bounds__(256) void unpack4_kernel(const uint8_t* __restrict__ payload, const uint16_t* __restrict__ scales,
-                                                      const uint32_t* __restrict__ table, int Tk, int tile, int64_t K,
-                                                      uint16_t* __restrict__ W_deq, int8_t* __restrict__ codes_out,
-                                                      uint16_t* __restrict__ scales_out) {
+                                                      const uint32_t* __restrict__ table, int Tk, int64_t K, uint16_t* __restrict__ W_deq,
+                                                      int8_t* __restrict__ codes_out, uint16_t* __restrict__ scales_out) {
+    constexpr int KPT = TILE / kStepCols, SPT = TILE / kStripRows;
+    constexpr int CPR = TILE / 8, RPP = 256 / CPR, PASSES = TILE / RPP;
+    __shared__ __attribute__((aligned(16))) uint8_t stage[q4_dense_tile(TILE)];
     const int t = blockIdx.x;
     const int tn = t / Tk, tk = t % Tk;
     const uint32_t e = table[t];
     const bool sparse = entry_sparse(e);
-    const uint8_t* base = payload + entry_offset(e);
-    const int64_t n0 = (int64_t)tn * tile, k0 = (int64_t)tk * tile;
-    const int KPT = tile / kStepCols, SPT = tile / kStripRows;
+    const q4_u32x4* src = reinterpret_cast<const q4_u32x4*>(payload + entry_offset(e));
+    const int n16 = (sparse ? q4_sparse_tile(TILE) : q4_dense_tile(TILE)) / 16;
+    for (int c = threadIdx.x; c < n16; c += 256) reinterpret_cast<q4_u32x4*>(stage)[c] = src[c];
+    // the tile columns of a tile row share the rows of the scale matrix among them: whole rows, contiguous stores
     if (scales_out)
-        for (int r = threadIdx.x; r < tile; r += blockDim.x)
-            scales_out[(n0 + r) * Tk + tk] = scales[q4_scale_index((int64_t)tn * SPT + r / 16, Tk, tk, r % 16)];
-    const int nchunks = tile * tile / 16;
-    const uint16_t* meta = reinterpret_cast<const uint16_t*>(base + q4_sparse_codes(tile));
-    for (int c = threadIdx.x; c < nchunks; c += blockDim.x) {
-        const int lane = c & 63, sj = c >> 6;
-        const int j = sj % KPT, s = sj / KPT, i = lane & 15, q = lane >> 4;
-        const float scl = q4_bf16_to_float(scales[q4_scale_index((int64_t)tn * SPT + s, Tk, tk, i)]);
-        int qv[16];
-        int64_t kk[16];
+        for (int r = tk; r < TILE; r += Tk)
+            for (int c = threadIdx.x; c < Tk; c += 256)
+                scales_out[((int64_t)tn * TILE + r) * Tk + c] = scales[q4_scale_index((int64_t)tn * SPT + (r >> 4), Tk, c, r & 15)];
+    __syncthreads();
+    const int kc = threadIdx.x % CPR, r0 = threadIdx.x / CPR, j = kc >> 3;
+    const bool bytewise = (reinterpret_cast<uintptr_t>(codes_out) & 7u) != 0;
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        const int row = r0 + p * RPP, strip = row >> 4, i = row & 15;
+        const float scl = q4_bf16_to_float(scales[q4_scale_index((int64_t)tn * SPT + strip, Tk, tk, i)]);
+        int qv[8];
         if (!sparse) {
-            const uint2 d = *reinterpret_cast<const uint2*>(base + (size_t)c * 8);
+            const int h = (kc >> 2) & 1, q = kc & 3;
+            const uint32_t d = *reinterpret_cast<const uint32_t*>(stage + (strip * KPT + j) * 512 + (16 * q + i) * 8 + 4 * h);
 #pragma unroll
-            for (int el = 0; el < 8; ++el) {
-                qv[el] = ((int)(d.x << (28 - 4 * el))) >> 28;
-                qv[8 + el] = ((int)(d.y << (28 - 4 * el))) >> 28;
-                kk[el] = 64 * j + 8 * q + el;
-                kk[8 + el] = 64 * j + 32 + 8 * q + el;
-            }
+            for (int k = 0; k < 8; ++k) qv[k] = ((int)(d << (28 - 4 * k))) >> 28;
         } else {
-            const uint32_t d = *reinterpret_cast<const uint32_t*>(base + (size_t)c * 4);
-            const uint32_t idx = meta[(s * 64 + lane) * KPT + j];
+            const int lane = 16 * ((kc & 7) >> 1) + i, half = kc & 1;
+            const uint32_t d = *reinterpret_cast<const uint16_t*>(stage + (strip * KPT + j) * 256 + lane * 4 + 2 * half);
+            const uint32_t idx = stage[q4_sparse_codes(TILE) + ((strip * 64 + lane) * KPT + j) * 2 + half];
 #pragma unroll
-            for (int el = 0; el < 16; ++el) { qv[el] = 0; kk[el] = 64 * j + 16 * q + el; }
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
+            for (int g = 0; g < 2; ++g) {
                 const int p0 = (idx >> (4 * g)) & 3, p1 = (idx >> (4 * g + 2)) & 3;
                 const int c0 = ((int)(d << (28 - 8 * g))) >> 28, c1 = ((int)(d << (24 - 8 * g))) >> 28;
 #pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    if (p == p0) qv[4 * g + p] = c0;
-                    if (p == p1) qv[4 * g + p] = c1;
-                }
+                for (int c = 0; c < 4; ++c) qv[4 * g + c] = c == p1 ? c1 : c == p0 ? c0 : 0;
             }
         }
+        const int64_t at = ((int64_t)tn * TILE + row) * K + (int64_t)tk * TILE + 8 * kc;
+        if (W_deq) {
+            q4_u32x4 w;
 #pragma unroll
-        for (int el = 0; el < 16; ++el) {
-            const int64_t at = (n0 + 16 * s + i) * K + k0 + kk[el];
-            if (W_deq) W_deq[at] = (uint16_t)bf16_rne_bits((float)qv[el] * scl);
-            if (codes_out) codes_out[at] = (int8_t)qv[el];
+            for (int k = 0; k < 4; ++k) w[k] = bf16_rne_bits((float)qv[2 * k] * scl) | (bf16_rne_bits((float)qv[2 * k + 1] * scl) << 16);
+            *reinterpret_cast<q4_u32x4*>(W_deq + at) = w;
+        }
+        if (codes_out) {
+            if (bytewise) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) codes_out[at + k] = (int8_t)qv[k];
+            } else {
+                q4_u32x2 b = {0u, 0u};
+#pragma unroll
+                for (int k = 0; k < 8; ++k) b[k >> 2] |= ((uint32_t)qv[k] & 0xFFu) << (8 * (k & 3));
+                *reinterpret_cast<q4_u32x2*>(codes_out + at) = b;
+            }
         }
     }
 }
@@ -857,8 +875,8 @@ patch_status patch_pack4(const void* W_hat, int64_t N, int64_t K, const uint8_t*
     }
     hipError_t e = hipMemsetAsync(d_err, 0, sizeof(int), s);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(pack4_kernel, dim3((unsigned)T), dim3(256), 0, s, static_cast<const uint16_t*>(W_hat), K, P->d_table, P->Tk, tile,
-                           P->d_payload, P->d_scales, d_err);
+        hipLaunchKernelGGL(tile == 128 ? &pack4_kernel<128> : &pack4_kernel<64>, dim3((unsigned)T), dim3(256), 0, s,
+                           static_cast<const uint16_t*>(W_hat), K, P->d_table, P->Tk, P->d_payload, P->d_scales, d_err);
         e = hipGetLastError();
     }
     int h_err = 0;
@@ -960,8 +978,9 @@ patch_status patch_deserialize4(const void* buf, size_t bytes, void* stream, pat
 patch_status patch_unpack4(const patch_packed4* P, void* W_deq, void* codes, void* scales, void* stream) {
     if (!P || (!W_deq && !codes && !scales)) return PATCH_ERR_ARG;
     if ((W_deq && !q4_aligned16(W_deq)) || (scales && (reinterpret_cast<uintptr_t>(scales) & 1u))) return PATCH_ERR_ARG;
-    hipLaunchKernelGGL(unpack4_kernel, dim3((unsigned)(P->Tn * P->Tk)), dim3(256), 0, static_cast<hipStream_t>(stream), P->d_payload, P->d_scales,
-                       P->d_table, P->Tk, P->tile, P->K, static_cast<uint16_t*>(W_deq), static_cast<int8_t*>(codes), static_cast<uint16_t*>(scales));
+    hipLaunchKernelGGL(P->tile == 128 ? &unpack4_kernel<128> : &unpack4_kernel<64>, dim3((unsigned)(P->Tn * P->Tk)), dim3(256), 0,
+                       static_cast<hipStream_t>(stream), P->d_payload, P->d_scales, P->d_table, P->Tk, P->K, static_cast<uint16_t*>(W_deq),
+                       static_cast<int8_t*>(codes), static_cast<uint16_t*>(scales));
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) { patch_note_hip_error((int)e); return PATCH_ERR_HIP; }
     return PATCH_OK;
