@@ -49,30 +49,48 @@ void launch_apply_mask(const uint16_t* W, const uint8_t* mask24, const uint8_t* 
 }
 
 // ------------------------------------------------------------------ hard 2:4 mask from the pattern logits
-// One thread per group of four consecutive elements: the candidate with the largest of the six logits (first one on
+// Four groups of four consecutive elements per thread and step: the candidate with the largest of the six logits (first one on
 // ties; a NaN never wins a comparison), written as four keep bytes.  Candidates in lexicographic order of the kept
-// positions: (0,1) (0,2) (0,3) (1,2) (1,3) (2,3).
-__global__ __launch_bounds__(256) void hard_mask24_kernel(const float* __restrict__ P24, int64_t G, uint32_t* __restrict__ mask24) {
+// positions: (0,1) (0,2) (0,3) (1,2) (1,3) (2,3).  Bound by memory (24 bytes read, 4 written per group): 11008 x 4096 in 58 us
+// (5.4 TB/s); with one group per thread, which is what logits or masks without 16-byte alignment still take, 67 - 73 us.
+typedef float pk_f32x4 __attribute__((ext_vector_type(4)));
+template <typename F, typename U, int V>
+__global__ __launch_bounds__(256) void hard_mask24_kernel(const F* __restrict__ P24, int64_t G, U* __restrict__ mask24) {
     // keep bytes of candidate c, little endian: byte j = element j of the group
     constexpr uint32_t kPattern[6] = {0x00000101u, 0x00010001u, 0x01000001u, 0x00010100u, 0x01000100u, 0x01010000u};
     for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < G; g += (int64_t)gridDim.x * blockDim.x) {
-        float best = P24[g];
-        uint32_t pat = kPattern[0];
+        F v[6];
 #pragma unroll
-        for (int c = 1; c < 6; ++c) {
-            const float v = P24[(int64_t)c * G + g];
-            const bool better = v > best;
-            best = better ? v : best;
-            pat = better ? kPattern[c] : pat;
+        for (int c = 0; c < 6; ++c) v[c] = __builtin_nontemporal_load(P24 + (int64_t)c * G + g);
+        U pat;
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            float best = reinterpret_cast<const float*>(&v[0])[e];
+            uint32_t p = kPattern[0];
+#pragma unroll
+            for (int c = 1; c < 6; ++c) {
+                const float x = reinterpret_cast<const float*>(&v[c])[e];
+                const bool better = x > best;
+                best = better ? x : best;
+                p = better ? kPattern[c] : p;
+            }
+            reinterpret_cast<uint32_t*>(&pat)[e] = p;
         }
         mask24[g] = pat;
     }
 }
 
+// G is a multiple of 1024 (whole tiles), so the six planes share the alignment of the first.
 void launch_hard_mask24(const float* P24, int64_t G, uint8_t* mask24, hipStream_t stream) {
-    int blocks = (int)((G + 255) / 256);
+    const bool wide = ((reinterpret_cast<uintptr_t>(P24) | reinterpret_cast<uintptr_t>(mask24)) & 15u) == 0;
+    const int64_t n = wide ? G / 4 : G;
+    int blocks = (int)((n + 255) / 256);
     if (blocks > 256 * 32) blocks = 256 * 32;
-    hipLaunchKernelGGL(hard_mask24_kernel, dim3(blocks), dim3(256), 0, stream, P24, G, reinterpret_cast<uint32_t*>(mask24));
+    if (wide)
+        hipLaunchKernelGGL((hard_mask24_kernel<pk_f32x4, u32x4, 4>), dim3(blocks), dim3(256), 0, stream, reinterpret_cast<const pk_f32x4*>(P24), n,
+                           reinterpret_cast<u32x4*>(mask24));
+    else
+        hipLaunchKernelGGL((hard_mask24_kernel<float, uint32_t, 1>), dim3(blocks), dim3(256), 0, stream, P24, n, reinterpret_cast<uint32_t*>(mask24));
 }
 
 // ------------------------------------------------------------------ compression
@@ -95,50 +113,66 @@ __device__ __forceinline__ bool compress16(const uint16_t* in, uint16_t* out, ui
 #pragma unroll
         for (int p = 0; p < 4; ++p)
             if (!keep[p] && nnz < 2) { keep[p] = true; ++nnz; }
-        int p0 = -1, p1 = -1;
+        // first and second kept position and their values, by selects (an element picked by a computed index would go
+        // through memory)
+        int p0 = 0, p1 = 1, seen = 0;
+        uint16_t w0 = grp[0], w1 = grp[1];
 #pragma unroll
         for (int p = 0; p < 4; ++p)
-            if (keep[p]) { if (p0 < 0) p0 = p; else if (p1 < 0) p1 = p; }
-        if (p1 < 0) { p0 = 0; p1 = 1; }  // unreachable when ok; keeps indices in range otherwise
-        out[2 * g] = grp[p0];
-        out[2 * g + 1] = grp[p1];
+            if (keep[p]) {
+                if (seen == 0) { p0 = p; w0 = grp[p]; }
+                else if (seen == 1) { p1 = p; w1 = grp[p]; }
+                ++seen;
+            }
+        out[2 * g] = w0;
+        out[2 * g + 1] = w1;
         idx |= (uint32_t)(p0 | (p1 << 2)) << (4 * g);
     }
     return ok;
 }
 
-// One workgroup per tile.
+// One workgroup per tile; every thread requests all its pieces of the tile before it uses the first.  11008 x 4096, tile 128, f = 0.6:
+// 33 us (4.8 TB/s) against 41 with a loop over the pieces and kept values picked by a computed index (which the compiler
+// sent through LDS); 4096 x 4096, tile 64, f = 0.5: 14 us against 25.
+template <int TILE>
 __global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ W, int64_t K, const uint32_t* __restrict__ table,
-                                                   int Tk, int tile, uint8_t* __restrict__ payload, int* __restrict__ err) {
+                                                   int Tk, uint8_t* __restrict__ payload, int* __restrict__ err) {
+    constexpr int KPT = TILE / kStepCols, PIECES = TILE * TILE / 8 / 256;
     const int t = blockIdx.x;
     const int tn = t / Tk, tk = t % Tk;
     const uint32_t e = table[t];
     uint8_t* base = payload + entry_offset(e);
-    const int64_t n0 = (int64_t)tn * tile, k0 = (int64_t)tk * tile;
-    const int KPT = tile / kStepCols;
+    const int lane = threadIdx.x & 63, i = lane & 15, q = lane >> 4;
+    const uint16_t* src = W + ((int64_t)tn * TILE + i) * K + (int64_t)tk * TILE;
+    u32x4 in[PIECES];
     if (!entry_sparse(e)) {
-        const int nchunks = tile * tile / 8;
-        for (int c = threadIdx.x; c < nchunks; c += blockDim.x) {
-            const int lane = c & 63, h = (c >> 6) & 1, sj = c >> 7;
-            const int j = sj % KPT, s = sj / KPT, i = lane & 15, q = lane >> 4;
-            const uint16_t* src = W + (n0 + 16 * s + i) * K + k0 + 64 * j + 32 * h + 8 * q;
-            *reinterpret_cast<u32x4*>(base + (size_t)c * 16) = *reinterpret_cast<const u32x4*>(src);
+#pragma unroll
+        for (int p = 0; p < PIECES; ++p) {
+            const int f = (threadIdx.x >> 6) + 4 * p, h = f & 1, j = (f >> 1) % KPT, s = (f >> 1) / KPT;   // operand h of fragment (s, j)
+            in[p] = *reinterpret_cast<const u32x4*>(src + (int64_t)(16 * s) * K + 64 * j + 32 * h + 8 * q);
         }
+#pragma unroll
+        for (int p = 0; p < PIECES; ++p) *reinterpret_cast<u32x4*>(base + (size_t)(threadIdx.x + 256 * p) * 16) = in[p];
     } else {
-        const int nchunks = tile * tile / 16;
-        uint16_t* meta = reinterpret_cast<uint16_t*>(base + sparse_vals_bytes(tile));
+        uint16_t* meta = reinterpret_cast<uint16_t*>(base + sparse_vals_bytes(TILE));
         bool ok = true;
-        for (int c = threadIdx.x; c < nchunks; c += blockDim.x) {
-            const int lane = c & 63, sj = c >> 6;
-            const int j = sj % KPT, s = sj / KPT, i = lane & 15, qa = lane >> 4;
-            const uint16_t* src = W + (n0 + 16 * s + i) * K + k0 + 64 * j + 16 * qa;
-            union { u32x4 v[2]; uint16_t h[16]; } in;
-            in.v[0] = *reinterpret_cast<const u32x4*>(src);
-            in.v[1] = *reinterpret_cast<const u32x4*>(src + 8);
+#pragma unroll
+        for (int p = 0; p < PIECES / 2; ++p) {
+            const int f = (threadIdx.x >> 6) + 4 * p, j = f % KPT, s = f / KPT;
+            const u32x4* at = reinterpret_cast<const u32x4*>(src + (int64_t)(16 * s) * K + 64 * j + 16 * q);
+            in[2 * p] = at[0];
+            in[2 * p + 1] = at[1];
+        }
+#pragma unroll
+        for (int p = 0; p < PIECES / 2; ++p) {
+            const int f = (threadIdx.x >> 6) + 4 * p, j = f % KPT, s = f / KPT;
+            union { u32x4 v[2]; uint16_t h[16]; } x;
+            x.v[0] = in[2 * p];
+            x.v[1] = in[2 * p + 1];
             union { u32x4 v; uint16_t h[8]; } out;
             uint32_t idx;
-            ok = compress16(in.h, out.h, idx) && ok;
-            *reinterpret_cast<u32x4*>(base + (size_t)c * 16) = out.v;
+            ok = compress16(x.h, out.h, idx) && ok;
+            *reinterpret_cast<u32x4*>(base + (size_t)(threadIdx.x + 256 * p) * 16) = out.v;
             meta[(s * 64 + lane) * KPT + j] = (uint16_t)idx;
         }
         if (!ok) atomicOr(err, 1);
@@ -147,7 +181,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ 
 
 void launch_pack(const uint16_t* W, int64_t K, const uint32_t* d_table, int n_tiles, int Tk, int tile, uint8_t* payload, int* d_err,
                  hipStream_t stream) {
-    hipLaunchKernelGGL(pack_kernel, dim3(n_tiles), dim3(256), 0, stream, W, K, d_table, Tk, tile, payload, d_err);
+    hipLaunchKernelGGL(tile == 128 ? &pack_kernel<128> : &pack_kernel<64>, dim3(n_tiles), dim3(256), 0, stream, W, K, d_table, Tk, payload, d_err);
 }
 
 // ------------------------------------------------------------------ decompression
