@@ -24,7 +24,9 @@ struct patch_packed {
     int Tn = 0, Tk = 0;
     int64_t n_sparse = 0;
     size_t payload_bytes = 0;   // sum of tile payloads (no alignment slack: tiles are granule multiples)
+    // one allocation: payload | zeroed slack | status word of the 2:4 check | table | pairs
     uint8_t* d_payload = nullptr;
+    int* d_err = nullptr;
     uint32_t* d_table = nullptr;
     std::vector<uint8_t> tile_map;   // host copy, 1 = dense
     std::vector<uint32_t> table;     // host copy of the offset / type table
@@ -65,29 +67,46 @@ static std::vector<int32_t> pair_tile_rows(const std::vector<uint8_t>& tile_map,
     out.reserve((size_t)Tn + 1);
     std::vector<int> carry;  // rows left single by earlier windows
     constexpr int kWindow = 256;
-    struct Cand { int agree, a, b; };  // agree = steps in which both rows are 2:4
+    // the 2:4 tiles of a row as a bit set (86 rows of 32 tiles, 3655 pairs: 40 us, byte by byte and with a comparison sort 300)
+    const int words = (Tk + 63) / 64;
+    std::vector<uint64_t> bits((size_t)Tn * words, 0);
+    for (int r = 0; r < Tn; ++r)
+        for (int k = 0; k < Tk; ++k) bits[(size_t)r * words + k / 64] |= (uint64_t)(tile_map[(size_t)r * Tk + k] == 0) << (k % 64);
+    const auto common = [&](int a, int b) {   // steps in which both rows are 2:4
+        int n = 0;
+        for (int i = 0; i < words; ++i) n += __builtin_popcountll(bits[(size_t)a * words + i] & bits[(size_t)b * words + i]);
+        return n;
+    };
+    std::vector<uint32_t> cand, sorted;   // pairs of positions in the window, i << 16 | j
+    std::vector<int> agree, first((size_t)Tk + 2);
     for (int w0 = 0; w0 < Tn; w0 += kWindow) {
         std::vector<int> rows = carry;
         carry.clear();
         for (int r = w0; r < Tn && r < w0 + kWindow; ++r) rows.push_back(r);
         const int n = (int)rows.size();
-        std::vector<Cand> cand;
-        cand.reserve((size_t)n * (size_t)(n - 1) / 2);
+        cand.clear();
+        agree.clear();
+        std::fill(first.begin(), first.end(), 0);
         for (int i = 0; i < n; ++i)
             for (int j = i + 1; j < n; ++j) {
-                const uint8_t* ra = &tile_map[(size_t)rows[i] * Tk];
-                const uint8_t* rb = &tile_map[(size_t)rows[j] * Tk];
-                int agree = 0;
-                for (int k = 0; k < Tk; ++k) agree += ra[k] == 0 && rb[k] == 0;
-                cand.push_back(Cand{agree, i, j});
+                const int c = common(rows[i], rows[j]);
+                cand.push_back((uint32_t)i << 16 | (uint32_t)j);
+                agree.push_back(c);
+                ++first[Tk - c + 1];
             }
-        std::stable_sort(cand.begin(), cand.end(), [](const Cand& x, const Cand& y) { return x.agree > y.agree; });
+        // most common steps first, pairs of equal count in their order (a counting sort)
+        for (int c = 0; c <= Tk; ++c) first[c + 1] += first[c];
+        sorted.resize(cand.size());
+        for (size_t p = 0; p < cand.size(); ++p) sorted[first[Tk - agree[p]]++] = cand[p];
         std::vector<char> used((size_t)n, 0);
-        for (const Cand& c : cand) {
-            if (used[c.a] || used[c.b]) continue;
-            used[c.a] = used[c.b] = 1;
-            out.push_back(rows[c.a]);
-            out.push_back(rows[c.b]);
+        int left = n;
+        for (size_t p = 0; p < sorted.size() && left > 1; ++p) {
+            const int a = (int)(sorted[p] >> 16), b = (int)(sorted[p] & 0xFFFFu);
+            if (used[a] || used[b]) continue;
+            used[a] = used[b] = 1;
+            left -= 2;
+            out.push_back(rows[a]);
+            out.push_back(rows[b]);
         }
         for (int i = 0; i < n; ++i)
             if (!used[i]) carry.push_back(rows[i]);
@@ -103,9 +122,7 @@ static std::vector<int32_t> pair_tile_rows(const std::vector<uint8_t>& tile_map,
     std::vector<std::pair<int, size_t>> cost(np);
     for (size_t p = 0; p < np; ++p) {
         const int a = out[2 * p], b2 = out[2 * p + 1];
-        int both = 0;
-        for (int k = 0; k < Tk; ++k) both += tile_map[(size_t)a * Tk + k] == 0 && (b2 < 0 || tile_map[(size_t)b2 * Tk + k] == 0);
-        cost[p] = {both, p};  // more common 2:4 steps = lighter
+        cost[p] = {common(a, b2 < 0 ? a : b2), p};  // more common 2:4 steps = lighter
     }
     std::stable_sort(cost.begin(), cost.end(), [](const auto& x, const auto& y) { return x.first < y.first; });
     std::vector<int32_t> ordered;
@@ -204,22 +221,26 @@ patch_status patch_hard_masks(const float* P_tile, const void* P_24, int64_t N, 
 void patch_free(patch_packed* P) {
     if (!P) return;
     if (P->d_payload) (void)hipFree(P->d_payload);
-    if (P->d_table) (void)hipFree(P->d_table);
     delete P;
 }
 
-// The host side of a packed weight (tile map, offset / type table, tile-row pairs) and its device buffers, the table
-// uploaded on `s`, the payload not yet written.  Shared by patch_pack (which fills the payload from the matrix) and
-// patch_deserialize (which copies a saved one).
-static patch_status new_packed(int64_t N, int64_t K, const uint8_t* tile_map, int tile, hipStream_t s, patch_packed** out) {
+// The host side of a packed weight (tile map, offset / type table) and its device buffers - one allocation, everything in
+// front of the tile-row pairs but the payload in one upload on `s` - the payload not yet written.  Shared by patch_pack (which
+// fills the payload from the matrix) and patch_deserialize (which copies a saved one).  `staging` is the upload's source:
+// it must live until `s` has been waited for.
+static patch_status new_packed(int64_t N, int64_t K, const uint8_t* tile_map, int tile, hipStream_t s, std::vector<uint32_t>& staging, patch_packed** out) {
     patch_packed* P = new (std::nothrow) patch_packed();
     if (!P) return PATCH_ERR_ALLOC;
     P->N = N; P->K = K; P->tile = tile;
     P->Tn = (int)(N / tile); P->Tk = (int)(K / tile);
     const size_t T = (size_t)P->Tn * (size_t)P->Tk;
+    // (a kilobyte of zeroed slack behind the payload keeps any over-read of the last tile inside the allocation; the
+    // status word has 16 bytes)
+    constexpr size_t kFront = kZeroPad / sizeof(uint32_t) + 4;
     try {
         P->tile_map.resize(T);
         P->table.resize(T);
+        staging.assign(kFront + T, 0);
     } catch (...) { delete P; return PATCH_ERR_ALLOC; }
     uint64_t off = 0;
     for (size_t i = 0; i < T; ++i) {
@@ -231,9 +252,7 @@ static patch_status new_packed(int64_t N, int64_t K, const uint8_t* tile_map, in
     }
     P->payload_bytes = off;
     if ((off / kGranule) >> 31) { delete P; return PATCH_ERR_SHAPE; }
-    try {
-        if (tile == 128) P->pairs = pair_tile_rows(P->tile_map, P->Tn, P->Tk);  // read by prefill_kernel_wreg only
-    } catch (...) { delete P; return PATCH_ERR_ALLOC; }
+    memcpy(staging.data() + kFront, P->table.data(), T * sizeof(uint32_t));
 
     int dev = 0;
     hipDeviceProp_t prop;
@@ -245,18 +264,15 @@ static patch_status new_packed(int64_t N, int64_t K, const uint8_t* tile_map, in
     P->device = dev;
     P->n_cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
 
-    // a kilobyte of slack behind the payload keeps any over-read of the last tile inside the allocation
-    const bool ok = hipMalloc(&P->d_payload, P->payload_bytes + kZeroPad) == hipSuccess &&
-                    hipMalloc(&P->d_table, (T + P->pairs.size()) * sizeof(uint32_t)) == hipSuccess;
-    if (!ok) {
+    const size_t n_pairs = tile == 128 ? 2 * (((size_t)P->Tn + 1) / 2) : 0;
+    if (hipMalloc(&P->d_payload, P->payload_bytes + (kFront + T + n_pairs) * sizeof(uint32_t)) != hipSuccess) {
         (void)hipGetLastError();
         patch_free(P);
         return PATCH_ERR_ALLOC;
     }
-    hipError_t e = hipMemcpyAsync(P->d_table, P->table.data(), T * sizeof(uint32_t), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(P->d_table + T, P->pairs.data(), P->pairs.size() * sizeof(int32_t), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemsetAsync(P->d_payload + P->payload_bytes, 0, kZeroPad, s);
+    P->d_err = reinterpret_cast<int*>(P->d_payload + P->payload_bytes + kZeroPad);
+    P->d_table = reinterpret_cast<uint32_t*>(P->d_payload + P->payload_bytes) + kFront;
+    const hipError_t e = hipMemcpyAsync(P->d_payload + P->payload_bytes, staging.data(), staging.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) {
         g_last_hip_error = (int)e;
         (void)hipStreamSynchronize(s);
@@ -264,6 +280,16 @@ static patch_status new_packed(int64_t N, int64_t K, const uint8_t* tile_map, in
         return PATCH_ERR_HIP;
     }
     *out = P;
+    return PATCH_OK;
+}
+
+// The tile-row pairs of a new packed weight, uploaded on `s` (tile 128 only: prefill_kernel_wreg reads them).
+static patch_status add_pairs(patch_packed* P, hipStream_t s) {
+    if (P->tile != 128) return PATCH_OK;
+    try {
+        P->pairs = pair_tile_rows(P->tile_map, P->Tn, P->Tk);
+    } catch (...) { return PATCH_ERR_ALLOC; }
+    HIP_TRY(hipMemcpyAsync(P->d_table + P->table.size(), P->pairs.data(), P->pairs.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
     return PATCH_OK;
 }
 
@@ -275,34 +301,21 @@ patch_status patch_pack(const void* W_hat, int64_t N, int64_t K, const uint8_t* 
     if (!aligned16(W_hat)) return PATCH_ERR_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
     patch_packed* P = nullptr;
-    st = new_packed(N, K, tile_map, tile, s, &P);
+    std::vector<uint32_t> staging;
+    st = new_packed(N, K, tile_map, tile, s, staging, &P);
     if (st != PATCH_OK) return st;
-    const size_t T = (size_t)P->Tn * (size_t)P->Tk;
-    int* d_err = nullptr;
-    if (hipMalloc(&d_err, sizeof(int)) != hipSuccess) {
-        (void)hipGetLastError();
-        (void)hipStreamSynchronize(s);
-        patch_free(P);
-        return PATCH_ERR_ALLOC;
-    }
-    hipError_t e = hipMemsetAsync(d_err, 0, sizeof(int), s);
-    if (e == hipSuccess) {
-        launch_pack(static_cast<const uint16_t*>(W_hat), K, P->d_table, (int)T, P->Tk, tile, P->d_payload, d_err, s);
-        e = hipGetLastError();
-    }
+    launch_pack(static_cast<const uint16_t*>(W_hat), K, P->d_table, (int)P->table.size(), P->Tk, tile, P->d_payload, P->d_err, s);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) st = add_pairs(P, s);   // on the host while the kernel runs
     int h_err = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&h_err, d_err, sizeof(int), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess && st == PATCH_OK) e = hipMemcpyAsync(&h_err, P->d_err, sizeof(int), hipMemcpyDeviceToHost, s);
     const hipError_t e_sync = hipStreamSynchronize(s);
     if (e == hipSuccess) e = e_sync;
-    (void)hipFree(d_err);
-    if (e != hipSuccess) {
-        g_last_hip_error = (int)e;
+    if (e != hipSuccess && st == PATCH_OK) { g_last_hip_error = (int)e; st = PATCH_ERR_HIP; }
+    if (st == PATCH_OK && h_err) st = PATCH_ERR_NOT_24;
+    if (st != PATCH_OK) {
         patch_free(P);
-        return PATCH_ERR_HIP;
-    }
-    if (h_err) {
-        patch_free(P);
-        return PATCH_ERR_NOT_24;
+        return st;
     }
     *out = P;
     return PATCH_OK;
@@ -355,7 +368,8 @@ patch_status patch_deserialize(const void* buf, size_t bytes, void* stream, patc
     if (fnv1a(b + pay_at, (size_t)h.payload_bytes, fnv1a(b + map_at, (size_t)T, kFnvBasis)) != h.checksum) return PATCH_ERR_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
     patch_packed* P = nullptr;
-    const patch_status st = new_packed(h.N, h.K, b + map_at, (int)h.tile, s, &P);
+    std::vector<uint32_t> staging;
+    patch_status st = new_packed(h.N, h.K, b + map_at, (int)h.tile, s, staging, &P);
     if (st != PATCH_OK) return st;
     if (P->payload_bytes != h.payload_bytes) {   // the map decides the size: a header that disagrees is not ours
         (void)hipStreamSynchronize(s);
@@ -363,12 +377,13 @@ patch_status patch_deserialize(const void* buf, size_t bytes, void* stream, patc
         return PATCH_ERR_ARG;
     }
     hipError_t e = hipMemcpyAsync(P->d_payload, b + pay_at, P->payload_bytes, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) st = add_pairs(P, s);
     const hipError_t e_sync = hipStreamSynchronize(s);   // the caller's buffer is free to go when the call returns
     if (e == hipSuccess) e = e_sync;
-    if (e != hipSuccess) {
-        g_last_hip_error = (int)e;
+    if (e != hipSuccess && st == PATCH_OK) { g_last_hip_error = (int)e; st = PATCH_ERR_HIP; }
+    if (st != PATCH_OK) {
         patch_free(P);
-        return PATCH_ERR_HIP;
+        return st;
     }
     *out = P;
     return PATCH_OK;

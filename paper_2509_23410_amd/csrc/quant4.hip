@@ -790,9 +790,11 @@ struct patch_packed4 {
     int64_t n_sparse = 0;
     size_t algorithmic_bytes = 0;   // codes + positions + scales, without alignment padding
     size_t payload_bytes = 0;
+    // one allocation: payload | status word of the 2:4 check | table | scales
     uint8_t* d_payload = nullptr;   // codes and positions
-    uint16_t* d_scales = nullptr;   // N x Tk bf16, strip-major
+    int* d_err = nullptr;
     uint32_t* d_table = nullptr;
+    uint16_t* d_scales = nullptr;   // N x Tk bf16, strip-major
     std::vector<uint8_t> tile_map;  // host copy, 1 = dense
     int n_cus = 256;
 };
@@ -804,26 +806,28 @@ extern "C" {
 void patch_free4(patch_packed4* P) {
     if (!P) return;
     if (P->d_payload) (void)hipFree(P->d_payload);
-    if (P->d_scales) (void)hipFree(P->d_scales);
-    if (P->d_table) (void)hipFree(P->d_table);
     delete P;
 }
 
-// The host side of a 4-bit packed weight and its device buffers: table uploaded on `s`, payload zeroed (its alignment
-// padding reads as zero), codes and scales not yet written.  Shared by patch_pack4 and patch_deserialize4.
-static patch_status new_packed4(int64_t N, int64_t K, const uint8_t* tile_map, int tile, hipStream_t s, patch_packed4** out) {
+// The host side of a 4-bit packed weight and its device buffers - one allocation, status word and table in one upload on `s` -
+// payload and scales not yet written (a tile has no alignment padding at either size, so that whoever fills them writes every
+// byte).  Shared by patch_pack4 and patch_deserialize4.  `staging` is the upload's source: it must live until `s` has been waited for.
+static_assert(q4_dense_tile(64) == q4_dense_codes(64) && q4_dense_tile(128) == q4_dense_codes(128) &&
+              q4_sparse_tile(64) == q4_sparse_codes(64) + q4_sparse_pos(64) && q4_sparse_tile(128) == q4_sparse_codes(128) + q4_sparse_pos(128),
+              "a tile with padding would have to be cleared");
+static patch_status new_packed4(int64_t N, int64_t K, const uint8_t* tile_map, int tile, hipStream_t s, std::vector<uint32_t>& staging, patch_packed4** out) {
     patch_packed4* P = new (std::nothrow) patch_packed4();
     if (!P) return PATCH_ERR_ALLOC;
     P->N = N; P->K = K; P->tile = tile;
     P->Tn = (int)(N / tile); P->Tk = (int)(K / tile);
     const size_t T = (size_t)P->Tn * (size_t)P->Tk;
-    std::vector<uint32_t> table;
-    try { table.resize(T); P->tile_map.resize(T); } catch (...) { delete P; return PATCH_ERR_ALLOC; }
+    constexpr size_t kFront = 4;   // the status word, 16 bytes
+    try { staging.assign(kFront + T, 0); P->tile_map.resize(T); } catch (...) { delete P; return PATCH_ERR_ALLOC; }
     uint64_t off = 0;
     for (size_t i = 0; i < T; ++i) {
         const bool sparse = tile_map[i] == 0;
         P->tile_map[i] = sparse ? 0 : 1;
-        table[i] = make_entry(off, sparse);
+        staging[kFront + i] = make_entry(off, sparse);
         off += sparse ? q4_sparse_tile(tile) : q4_dense_tile(tile);
         P->algorithmic_bytes += sparse ? q4_sparse_codes(tile) + q4_sparse_pos(tile) + 2 * tile : q4_dense_codes(tile) + 2 * tile;
         if (sparse) ++P->n_sparse;
@@ -838,19 +842,19 @@ static patch_status new_packed4(int64_t N, int64_t K, const uint8_t* tile_map, i
         return PATCH_ERR_HIP;
     }
     P->n_cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-    const bool ok = hipMalloc(&P->d_payload, P->payload_bytes) == hipSuccess && hipMalloc(&P->d_table, T * sizeof(uint32_t)) == hipSuccess &&
-                    hipMalloc(&P->d_scales, (size_t)N * P->Tk * sizeof(uint16_t)) == hipSuccess;
-    if (!ok) {
+    const size_t scales_at = ((kFront + T) * sizeof(uint32_t) + kGranule - 1) / kGranule * kGranule;
+    if (hipMalloc(&P->d_payload, P->payload_bytes + scales_at + (size_t)N * P->Tk * sizeof(uint16_t)) != hipSuccess) {
         (void)hipGetLastError();
         patch_free4(P);
         return PATCH_ERR_ALLOC;
     }
-    hipError_t e = hipMemcpyAsync(P->d_table, table.data(), T * sizeof(uint32_t), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemsetAsync(P->d_payload, 0, P->payload_bytes, s);
-    const hipError_t e_sync = hipStreamSynchronize(s);   // the host table goes out of scope here
-    if (e == hipSuccess) e = e_sync;
+    P->d_err = reinterpret_cast<int*>(P->d_payload + P->payload_bytes);
+    P->d_table = reinterpret_cast<uint32_t*>(P->d_err) + kFront;
+    P->d_scales = reinterpret_cast<uint16_t*>(P->d_payload + P->payload_bytes + scales_at);
+    const hipError_t e = hipMemcpyAsync(P->d_err, staging.data(), staging.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) {
         patch_note_hip_error((int)e);
+        (void)hipStreamSynchronize(s);
         patch_free4(P);
         return PATCH_ERR_HIP;
     }
@@ -864,26 +868,16 @@ patch_status patch_pack4(const void* W_hat, int64_t N, int64_t K, const uint8_t*
     if (!q4_aligned16(W_hat)) return PATCH_ERR_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
     patch_packed4* P = nullptr;
-    const patch_status st = new_packed4(N, K, tile_map, tile, s, &P);
+    std::vector<uint32_t> staging;
+    const patch_status st = new_packed4(N, K, tile_map, tile, s, staging, &P);
     if (st != PATCH_OK) return st;
-    const size_t T = (size_t)P->Tn * (size_t)P->Tk;
-    int* d_err = nullptr;
-    if (hipMalloc(&d_err, sizeof(int)) != hipSuccess) {
-        (void)hipGetLastError();
-        patch_free4(P);
-        return PATCH_ERR_ALLOC;
-    }
-    hipError_t e = hipMemsetAsync(d_err, 0, sizeof(int), s);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(tile == 128 ? &pack4_kernel<128> : &pack4_kernel<64>, dim3((unsigned)T), dim3(256), 0, s,
-                           static_cast<const uint16_t*>(W_hat), K, P->d_table, P->Tk, P->d_payload, P->d_scales, d_err);
-        e = hipGetLastError();
-    }
+    hipLaunchKernelGGL(tile == 128 ? &pack4_kernel<128> : &pack4_kernel<64>, dim3((unsigned)(P->Tn * P->Tk)), dim3(256), 0, s,
+                       static_cast<const uint16_t*>(W_hat), K, P->d_table, P->Tk, P->d_payload, P->d_scales, P->d_err);
+    hipError_t e = hipGetLastError();
     int h_err = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&h_err, d_err, sizeof(int), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(&h_err, P->d_err, sizeof(int), hipMemcpyDeviceToHost, s);
     const hipError_t e_sync = hipStreamSynchronize(s);
     if (e == hipSuccess) e = e_sync;
-    (void)hipFree(d_err);
     if (e != hipSuccess) {
         patch_note_hip_error((int)e);
         patch_free4(P);
@@ -956,9 +950,11 @@ patch_status patch_deserialize4(const void* buf, size_t bytes, void* stream, pat
         return PATCH_ERR_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
     patch_packed4* P = nullptr;
-    const patch_status st = new_packed4(h.N, h.K, b + map_at, (int)h.tile, s, &P);
+    std::vector<uint32_t> staging;
+    const patch_status st = new_packed4(h.N, h.K, b + map_at, (int)h.tile, s, staging, &P);
     if (st != PATCH_OK) return st;
     if (P->payload_bytes != h.payload_bytes) {   // the map decides the size: a header that disagrees is not ours
+        (void)hipStreamSynchronize(s);
         patch_free4(P);
         return PATCH_ERR_ARG;
     }
