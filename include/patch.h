@@ -42,10 +42,10 @@ typedef enum {
 } patch_status;
 
 /* Which kernel family patch_gemm_ex uses.  DECODE handles M in passes of up to 64 rows (the weight is streamed
- * once per pass: 16-feature strips per workgroup for few rows, 64 features per wavefront for more rows where that
+ * once per pass: 16-feature strips per workgroup for few rows, 64 or 128 features per workgroup for more where that
  * fills the chip), PREFILL in blocks of 256 rows (128 where an estimate of both says so: few rows, or a weight of
- * few feature blocks that would otherwise need a deep K split).  AUTO (measured crossovers): decode up to M = 64 (with a
- * workspace, a single weight of at least 10240 features goes to prefill from M = 33); beyond, with a
+ * few feature blocks that would otherwise need a deep K split).  AUTO (measured crossovers): decode up to M = 64 (without
+ * a workspace, a single weight wider than the chip goes to prefill from M = 33); beyond, with a
  * workspace for at least two slices (see patch_gemm_opts) prefill, whose K split then fills the chip; without one
  * the cheaper of repeated passes and one unsplit prefill launch by an estimate from the launch geometry (passes up to
  * M = 192 at 4096 x 4096, up to M = 128 from 5120 features, further for long-K weights of few features). */
@@ -72,11 +72,12 @@ typedef struct {
                  /* faster (up to a few hundred rows).  Decode: 2 / 3 = 8 / 4                              */
                  /* K-steps per wavefront of the 16-feature-strip kernel; 4 = the kernel with 64         */
                  /* features per wavefront (its split_k = K chunks over `workspace`, 0 = auto; the       */
-                 /* default for passes of 17 .. 64 rows when a workspace allows chunks or N >= 4608, and */
-                 /* for 12 .. 16 rows when N >= 10240); 5 / 6 = the strip kernel with two X loads per    */
-                 /* step / with one X load for several steps (up to 8 rows; the default picks 6 where at */
-                 /* least a quarter of the tiles are 2:4).  A variant that does not apply falls back to  */
-                 /* the default.                                                                         */
+                 /* default for passes of 8 .. 64 rows where estimated fastest); 5 / 6 = the strip kernel */
+                 /* with two X loads per step / with one X load for several steps (up to 8 rows; the     */
+                 /* default picks 6 where at least a quarter of the tiles are 2:4); 7 = the kernel with  */
+                 /* 128 features per workgroup (its split_k = K chunks over `workspace`, 0 = auto; the   */
+                 /* default for passes of 8 .. 64 rows where estimated fastest, with a workspace in      */
+                 /* chunks).  A variant that does not apply falls back to the default.                   */
     void* workspace;        /* DEVICE, 16-byte aligned, caller-owned scratch for launches that split K   */
                             /* over workgroups (prefill; decode passes of 17 .. 64 rows), or NULL.  The  */
                             /* library never allocates in a product call.  Launches that may run         */

@@ -389,48 +389,80 @@ patch_status patch_deserialize(const void* buf, size_t bytes, void* stream, patc
     return PATCH_OK;
 }
 
-// A pass on the decode path runs the 64-features-per-wavefront kernel (gemm_mid.hip) when asked for (variant 4) or,
-// by default, when it can fill the chip and X is a large part of the traffic:
-//   17 .. 64 rows: with K-chunks over a workspace, or with at least 72 groups of 64 features (measured at M = 32,
-//     unsplit: 4096 x 4096, 64 groups, 19.6 us against 12.9 for the strip kernel; 5120 x 5120, 80 groups, 24.1
-//     against 25.2; 13824 x 5120 25.7 against 46.3; at M = 64: 4864 x 896, 76 groups, 9.1 against 10.5);
-//   12 .. 16 rows: with at least 160 groups (M = 16: 11008 x 4096 17.9 us against 19.9, 13824 x 5120 22.4 against
-//     29.8; M = 8: 18.2 against 15.9 and 22.9 against 24.3; 4096 x 4096: the strip kernel at every M <= 16).
-//     (a set of three 4096 x 4096 weights, 192 groups: from 8 rows, 20.0 us against 20.5; equal at M = 1)
-static bool use_mid_kernel(int rows, int variant, int split_k, int mid_chunks, int64_t groups, bool set = false) {
-    if (variant == 4) return true;
-    if (variant != 0 || split_k != 0) return false;
-    if (rows <= 16) return rows >= (set ? 8 : 12) && groups >= 160;
-    return mid_chunks > 1 || groups >= 72;
+// Which kernel a pass of `rows` rows (at most 64) takes, and in how many K chunks.  Three kernels share this range: the strip kernel
+// (gemm_decode.hip: 16 features per workgroup), mid_kernel (64 features) and batch_kernel (128 features).  A launch is bound by
+// what one compute unit draws, so each is estimated as
+//     base + rounds x K-steps per workgroup x step,   rounds = ceil(workgroups / compute units),
+// with step = us per 64 columns, a little more the fuller the chip, fitted to launches of 7 .. 344 workgroups of 8 .. 216 steps at
+// f = 0.5 (mostly within 10 %; us measured):
+//     strip  up to 16 rows  3.0 + (0.027 + 0.0030 rows) (1 + 0.3 fill)     1024 x 8192, 12 / 16 rows 11.1 / 12.4; 4096 x 4096, 16 rows 9.1
+//            up to 64       4.3 + (0.113 + 0.0019 rows) (1 + 0.2 fill)     4096 x 4096, 33 / 64 rows 16.8 / 20.9; 896 x 4864 16.9 / 22.4
+//     mid    up to 16 rows  4.0 + (0.11 + 0.0047 rows) (1 + 0.25 fill)     three 4096 x 4096, 8 / 16 rows 16.1 / 17.1
+//            up to 32       4.0 + (0.10 + 0.0037 rows) (1 + 0.25 fill)     three 4096 x 4096 20.3; 5120 x 13824, 20 rows 44
+//            up to 64       5.5 + (0.19 + 0.0022 rows) (1 + 0.25 fill)     three 4096 x 4096, 33 / 64 rows 24.1 / 28.7; 896 x 4864, 64 rows 29.5
+//     batch                 5.2 + (0.235 + 0.0018 rows) (1 + 0.33 fill)    three 4096 x 4096, 16 / 32 / 33 / 64 rows 24.2 / 26.0 / 26.5 / 29.8, in two
+//                           chunks 20.5 / 20.9 / 22.4 / 25.2; 896 x 896, 64 rows 9.8; gate and up of 4096 / 11008 27.2 / 29.4 / 29.2 / 32.9 (mid: two rounds, 31.1 / 37.1 / 41.4 / 52.6)
+// (every further round: strip 0.7, mid 2 us more; batch has to be 0.5 us ahead) and none takes less than its weights at 6.6 TB/s.  A split costs a second launch (5 us) and its partial sums twice through memory
+// (5 TB/s).  Up to 7 rows (11 for a single weight) the strip kernel's X is small and it is always taken.
+struct DecodePlan { int kernel, chunks; double us; };   // kernel: 0 strip, 1 mid, 2 batch
+struct DecodeShape { int64_t N; int strips, groups64, groups128; size_t payload; int count; };   // of a weight or a whole set
+
+static DecodePlan decode_plan(const GemmArgs& a, const DecodeShape& d, int rows, bool only_wide = false) {
+    const double steps = (double)a.K / kStepCols, hbm = (double)d.payload / 6.6e6;
+    const auto us = [&](double base, int64_t groups, int chunks, double step, double by_fill) {
+        const int64_t wg = groups * chunks, rounds = (wg + a.n_cus - 1) / a.n_cus;
+        const double fill = wg < a.n_cus ? (double)wg / a.n_cus : 1.0, t = (double)rounds * steps / chunks * step * (1.0 + by_fill * fill);
+        return base + (t > hbm ? t : hbm) + (chunks > 1 ? 5.0 + 2.0 * chunks * rows * (double)d.N * 4.0 / 5.0e6 : 0.0);
+    };
+    const double strip_more = 0.7 * (double)((d.strips - 1) / a.n_cus);
+    DecodePlan best = {0, 1, rows <= 16 ? us(3.0 + strip_more, d.strips, 1, 0.027 + 0.0030 * rows, 0.3) : us(4.3 + strip_more, d.strips, 1, 0.113 + 0.0019 * rows, 0.2)};
+    if (rows < (d.count > 1 ? 8 : 12) && !only_wide) return best;
+    const auto consider = [&](int kernel, int chunks, double t) { if (t < best.us) best = DecodePlan{kernel, chunks, t}; };
+    const size_t per_chunk = (size_t)rows * (size_t)d.N * sizeof(float);
+    const int fit = a.ws ? (int)(a.ws_bytes / per_chunk < 8 ? a.ws_bytes / per_chunk : 8) : 1;
+    const double mid0 = rows <= 32 ? 4.0 : 5.5, mid = rows <= 16 ? 0.11 + 0.0047 * rows : rows <= 32 ? 0.10 + 0.0037 * rows : 0.19 + 0.0022 * rows, batch = 0.235 + 0.0018 * rows;
+    consider(1, 1, us(mid0 + 2.0 * (double)((d.groups64 - 1) / a.n_cus), d.groups64, 1, mid, 0.25));
+    if (d.count == 1 && rows > 16) {
+        const int c = mid_split(a, rows, 0);
+        if (c > 1) consider(1, c, us(mid0, d.groups64, c, mid, 0.25));
+    }
+    // (at most 8 chunks of at least four units of 128 columns; beyond one workgroup per compute unit a split only adds partial sums)
+    DecodePlan wide = {2, 1, us(5.2, d.groups128, 1, batch, 0.33)};
+    for (int c = 2; c <= fit && d.groups128 * c <= a.n_cus && c * 512 <= a.K; ++c) {
+        const double t = us(5.2, d.groups128, c, batch, 0.33);
+        if (t < wide.us) wide = DecodePlan{2, c, t};
+    }
+    return only_wide || wide.us + 0.5 < best.us ? wide : best;
 }
 
-// Measured crossovers between decode-path passes (up to 64 rows each; every pass streams the whole weight) and the
-// 256 x 256-tile prefill kernel, f = 0.5, us at M = 32 / 64 / 128:
-//   with a workspace (K split over otherwise idle compute units on either path):
-//     4096 x 4096    passes 12.4 / 16.1 / 31.3    split prefill 21.1 / 21.7 / 24.4
-//     5120 x 5120    passes 15.9 / 21.5 / 42.5    split prefill 23.4 / 25.2 / 28.2
-//     13824 x 5120   passes 25.7 / 34.6 / 69.9    split prefill 35.2 / 39.6 / 42.9
-//     5120 x 13824   passes 27.8 / 36.8 / 72.5    split prefill 42.1 / 43.0 / 45.9
-//   without one the prefill grid is too small to fill the chip (66 - 93 us on these shapes) and the passes cost
-//     4096 x 4096 12.9 / 20.7 / 41.2 (strip kernel), 5120 x 5120 24.1 / 32.9 / 66.1, 13824 x 5120 25.7 / 34.8 / 70.3.
-// Without a workspace the choice is an estimate of both sides from the launch geometry (fitted to the same
-// measurements; it reproduces the crossovers above - M = 192 at 4096 x 4096, 128 from 5120 features - and also holds
-// for long-K weights of few features such as 4096 x 11008, where 16 output tiles run 172 steps each: 144 us, against
-// 45 us for a 64-row pass):
+// batch_kernel on request (variant 7): `requested` K chunks as far as they exist and the workspace holds them, 0 = the plan's
+static DecodePlan batch_plan(const GemmArgs& a, const DecodeShape& d, int rows, int requested) {
+    if (requested == 0) return decode_plan(a, d, rows, true);
+    const size_t per_chunk = (size_t)rows * (size_t)d.N * sizeof(float);
+    int c = requested;
+    if (c > (a.K + 127) / 128) c = (int)((a.K + 127) / 128);
+    const size_t fit = a.ws ? a.ws_bytes / per_chunk : 1;
+    if ((size_t)c > fit) c = (int)fit;
+    return DecodePlan{2, c < 1 ? 1 : c, 0.0};
+}
+
+static DecodeShape decode_shape(const patch_packed* P) {
+    return DecodeShape{P->N, (int)(P->N / 16), (int)(P->N / 64), (int)((P->N + 127) / 128), P->payload_bytes, 1};
+}
+
+// Passes of up to 64 rows, each streaming the whole weight, or one prefill launch?  With a workspace the prefill path's K
+// split fills the chip at any number of rows, and from 65 rows one launch of it beats two passes (4096 x 4096, us at M = 128: passes
+// 31, split prefill 18; 13824 x 5120: 70 and 34), while up to 64 rows a pass is ahead (decode_plan; 11008 x 4096 at 33 / 64 rows
+// 19 / 22 us against 21 / 23).  Without one the prefill grid may be too small to fill the chip, and both sides are estimated:
 //   unsplit prefill launch  rounds x 64-column steps x 1.0 us (tile 64 beyond K = 16384: 1.45 us), or with
 //                           blocks of 128 rows x 0.70 us (tile 64: 0.75), whichever is less (launch_prefill makes the
 //                           same choice)
-//   pass of up to 64 rows   steps x 0.3 us x (1 + 0.4 min(1, feature groups / 256)) x max(1, feature groups / 256)
-// From 33 rows on the same estimate also decides a single pass against an unsplit prefill launch: only weights wider
-// than the chip change side (65536 x 4096 at M = 64: 109 us in a pass, 90 us on the 128-row prefill kernel).
+//   passes                  decode_plan's estimate of a full pass, and of the last one by its rows
+// From 33 rows on the estimate also decides a single pass against an unsplit prefill launch: only weights wider
+// than the chip change side (65536 x 4096 at M = 64: 109 us in a pass of mid_kernel, 90 us on the 128-row prefill kernel).
 static int auto_path(int64_t M, const patch_packed* P, const patch_gemm_opts* opts, bool single = true) {
     const bool ws = opts && opts->workspace && opts->workspace_bytes >= 2 * (size_t)M * (size_t)P->N * sizeof(float);
     if (M <= 16) return PATCH_PATH_DECODE;
-    // With a workspace, 33 .. 64 rows and a single weight of at least 160 feature groups (10240 features: the pass then
-    // runs unsplit on the 64-features-per-wavefront kernel): the split prefill launch with 128-row blocks is ahead, e.g.
-    // M = 33 / 64: 11008 x 4096 20.7 / 23.0 us against 21.2 / 26.6, 32000 x 4096 36.8 / 39.8 against 43.5 / 54.1 (8192 x
-    // 4096 breaks even at 64 rows; 4096 features and fewer stay on the pass).
-    if (ws && single && M > 32 && M <= kDecodeRows && P->N / 64 >= 160) return PATCH_PATH_PREFILL;
     if (ws) return M <= kDecodeRows ? PATCH_PATH_DECODE : PATCH_PATH_PREFILL;
     if (M <= 32 || (M <= kDecodeRows && !single)) return PATCH_PATH_DECODE;
     const double steps = (double)P->K / 64.0;
@@ -440,13 +472,12 @@ static int auto_path(int64_t M, const patch_packed* P, const patch_gemm_opts* op
     const double us128 = (double)((tiles128 + P->n_cus - 1) / P->n_cus) * steps * (P->tile == 128 ? 0.70 : 0.75);
     const double us256 = rounds * steps * (P->tile == 128 || P->K <= 16384 ? 1.0 : 1.45);
     const double prefill_us = us128 < us256 ? us128 : us256;
-    const double groups = (double)(P->N / 64);
-    // (a weight of more feature groups than the chip takes at once - 65536 features - costs that many times more)
-    const double pass_us = steps * 0.3 * (1.0 + 0.4 * (groups < 256.0 ? groups / 256.0 : 1.0)) * (groups > 256.0 ? groups / 256.0 : 1.0);
-    // a last pass of r < 64 rows costs about (1 + r / 64) / 2 of a full one (11008 x 4096: 12.8 us for 1 row, 26.7 for 64)
+    GemmArgs a = {};
+    a.N = P->N; a.K = P->K; a.tile = P->tile; a.Tk = P->Tk; a.n_cus = P->n_cus;
+    const DecodeShape d = decode_shape(P);
     const int64_t full = M / kDecodeRows, rest = M % kDecodeRows;
-    const double passes = (double)full + (rest ? 0.5 + 0.5 * (double)rest / kDecodeRows : 0.0);
-    return passes * pass_us < prefill_us ? PATCH_PATH_DECODE : PATCH_PATH_PREFILL;
+    const double passes_us = (full ? (double)full * decode_plan(a, d, kDecodeRows).us : 0.0) + (rest ? decode_plan(a, d, (int)rest).us : 0.0);
+    return passes_us < prefill_us ? PATCH_PATH_DECODE : PATCH_PATH_PREFILL;
 }
 
 patch_status patch_gemm_ex(const void* X, int64_t M, const patch_packed* P, void* Y, void* stream, const patch_gemm_opts* opts) {
@@ -473,11 +504,16 @@ patch_status patch_gemm_ex(const void* X, int64_t M, const patch_packed* P, void
         WeightSet one = {};
         one.payload[0] = a.payload; one.table[0] = a.table; one.Y[0] = a.Y; one.N[0] = a.N;
         one.count = 1;
-        one.units = (int)(a.N / 64);
+        const DecodeShape d = decode_shape(P);
         for (int64_t m0 = 0; m0 < M; m0 += kDecodeRows) {
             const int rows = (int)((M - m0 < kDecodeRows) ? M - m0 : kDecodeRows);
-            const int chunks = (rows > 16 || variant == 4) ? mid_split(a, rows, variant == 4 ? split_k : 0) : 1;
-            if (use_mid_kernel(rows, variant, split_k, chunks, a.N / 64)) launch_mid_set(a, one, m0, rows, chunks, s);
+            DecodePlan plan = {0, 1, 0.0};
+            if (variant == 4) plan = DecodePlan{1, mid_split(a, rows, split_k), 0.0};
+            else if (variant == 7) plan = batch_plan(a, d, rows, split_k);
+            else if (variant == 0 && split_k == 0) plan = decode_plan(a, d, rows);
+            one.units = plan.kernel == 2 ? d.groups128 : d.groups64;
+            if (plan.kernel == 2) launch_batch_set(a, one, m0, rows, plan.chunks, s);
+            else if (plan.kernel == 1) launch_mid_set(a, one, m0, rows, plan.chunks, s);
             else launch_decode(a, m0, rows, split_k, variant, s);
         }
     } else {
@@ -514,6 +550,8 @@ patch_status patch_tune_all(const void* X, int64_t M, const patch_packed* P, voi
             if (workspace)
                 for (int sk : {2, 3, 4, 6, 8})
                     if ((size_t)sk * per_slice <= workspace_bytes && sk <= P->Tk) add(PATCH_PATH_DECODE, sk, 4, true);
+            add(PATCH_PATH_DECODE, 1, 7, false);   // 128 features per workgroup, unsplit and in the planned number of chunks
+            if (workspace) add(PATCH_PATH_DECODE, 0, 7, true);
         }
     }
     const size_t per_slice = (size_t)M * (size_t)P->N * sizeof(float);
@@ -714,12 +752,18 @@ size_t patch_gemm_workspace_bytes(int64_t M, const patch_packed* P, const patch_
     a.ws = reinterpret_cast<float*>(16);  // "enough": ask for the unconstrained choice
     a.ws_bytes = ~(size_t)0;
     if (path == PATCH_PATH_DECODE) {
-        // passes of 17 .. 64 rows may cut K into chunks over the workspace (the largest pass decides)
+        // passes of 12 .. 64 rows may cut K into chunks over the workspace (the largest pass decides)
         const int rows = (int)(M < kDecodeRows ? M : kDecodeRows);
-        if (rows <= 16 && variant != 4) return 0;
-        const int chunks = mid_split(a, rows, variant == 4 ? split_k : 0);
-        if (!use_mid_kernel(rows, variant, split_k, chunks, a.N / 64) || chunks < 2) return 0;
-        return (size_t)chunks * (size_t)rows * (size_t)P->N * sizeof(float);
+        int chunks = 1;
+        if (variant == 4) chunks = mid_split(a, rows, split_k);
+        else if (variant == 7) chunks = batch_plan(a, decode_shape(P), rows, split_k).chunks;
+        else if (variant == 0 && split_k == 0) {
+            // (from 17 rows at least what mid_kernel would take, whichever kernel the plan prefers: a caller that asked before
+            // and one that asks now get no smaller a buffer)
+            chunks = decode_plan(a, decode_shape(P), rows).chunks;
+            if (rows > 16) chunks = std::max(chunks, mid_split(a, rows, 0));
+        }
+        return chunks < 2 ? 0 : (size_t)chunks * (size_t)rows * (size_t)P->N * sizeof(float);
     }
     if (variant == 1) return 0;
     if (variant == 0 && split_k == 0) {
@@ -812,17 +856,25 @@ patch_status patch_gemm_many(const void* X, int64_t M, const patch_packed* const
     }
     set.count = count;
     set.units = strips;
-    // the same set in units of 64-feature groups, for passes of more than 16 rows
-    WeightSet wide = set;
-    int groups = 0;
+    // the same set in groups of 64 and of 128 features
+    WeightSet wide64 = set, wide128 = set;
+    DecodeShape d = {0, strips, 0, 0, 0, count};
     for (int i = 0; i < count; ++i) {
-        wide.first[i] = groups;
-        groups += (int)(P[i]->N / 64);
+        const DecodeShape w = decode_shape(P[i]);
+        wide64.first[i] = d.groups64;
+        wide128.first[i] = d.groups128;
+        d.N += w.N; d.groups64 += w.groups64; d.groups128 += w.groups128; d.payload += w.payload;
     }
-    wide.units = groups;
+    wide64.units = d.groups64;
+    wide128.units = d.groups128;
     for (int64_t m0 = 0; m0 < M; m0 += kDecodeRows) {
         const int rows = (int)((M - m0 < kDecodeRows) ? M - m0 : kDecodeRows);
-        if (use_mid_kernel(rows, variant, split_k, 1, groups, true)) launch_mid_set(a, wide, m0, rows, 1, s);
+        DecodePlan plan = {0, 1, 0.0};
+        if (variant == 4) plan.kernel = 1;
+        else if (variant == 7) plan = batch_plan(a, d, rows, split_k);
+        else if (variant == 0 && split_k == 0) plan = decode_plan(a, d, rows);
+        if (plan.kernel == 2) launch_batch_set(a, wide128, m0, rows, plan.chunks, s);
+        else if (plan.kernel == 1) launch_mid_set(a, wide64, m0, rows, 1, s);
         else launch_decode_set(a, set, m0, rows, split_k, variant, s);
     }
     HIP_TRY(hipGetLastError());

@@ -508,11 +508,6 @@ __global__ __launch_bounds__(256) void wr_reduce_kernel(const wr_f32x4* __restri
 }
 
 // The same for a set of weights in one launch: blockIdx.y = weight; its slices lie one behind the other at ws[y].
-struct WrReduceSet {
-    const float* ws[kMaxMany];
-    float* Y[kMaxMany];
-    size_t n4[kMaxMany];
-};
 __global__ __launch_bounds__(256) void wr_reduce_set_kernel(const WrReduceSet set, int slices, int ybf16) {
     const int y = blockIdx.y;
     const wr_f32x4* ws = reinterpret_cast<const wr_f32x4*>(set.ws[0]);
@@ -1107,6 +1102,14 @@ void wr_reduce(const float* ws, size_t n4, int slices, float* Y, int ybf16, hipS
                        reinterpret_cast<const wr_f32x4*>(ws), n4, slices, Y, ybf16);
 }
 
+void wr_reduce_set(const WrReduceSet& red, int count, int slices, int ybf16, hipStream_t stream) {
+    size_t n4 = 0;
+    for (int i = 0; i < count; ++i) n4 = red.n4[i] > n4 ? red.n4[i] : n4;
+    const size_t blocks = (n4 + 255) / 256;
+    hipLaunchKernelGGL(wr_reduce_set_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048), (unsigned)count), dim3(256), 0, stream, red, slices,
+                       ybf16);
+}
+
 // An unsplit launch; with a.ws and a part-filled last round worth it, all full rounds unsplit, then the last tiles in K
 // slices over the whole chip, then their sum.
 static void wr_launch_whole(const GemmArgs& a, const WeightSet& set, int tiles_m, bool may_split_tail, hipStream_t stream) {
@@ -1163,19 +1166,16 @@ void launch_prefill_wreg_set(const GemmArgs& a, const WeightSet& set, hipStream_
         if (split >= 2) {
             WeightSet part = set;
             WrReduceSet red = {};
-            size_t off = 0, n4_max = 0;
+            size_t off = 0;
             for (int i = 0; i < set.count; ++i) {
                 part.Y[i] = a.ws + off;
                 red.ws[i] = a.ws + off;
                 red.Y[i] = set.Y[i];
                 red.n4[i] = (size_t)a.M * (size_t)set.N[i] / 4;
-                if (red.n4[i] > n4_max) n4_max = red.n4[i];
                 off += (size_t)split * (size_t)a.M * (size_t)set.N[i];
             }
             wr_launch<1>(a, part, tiles_m, 0, nblk, split, 0, stream);
-            const size_t blocks = (n4_max + 255) / 256;
-            hipLaunchKernelGGL(wr_reduce_set_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048), (unsigned)set.count), dim3(256), 0, stream,
-                               red, split, a.ybf16);
+            wr_reduce_set(red, set.count, split, a.ybf16, stream);
             return;
         }
     }

@@ -71,6 +71,17 @@ void launch_mid_set(const GemmArgs& a, const WeightSet& set, int64_t m0, int row
 // Y[i] = sum over the slices of ws[slice * n4 + i] (float4 units), slice 0 first
 void wr_reduce(const float* ws, size_t n4, int slices, float* Y, int ybf16, hipStream_t stream);
 
+// the same for a set: the slices of weight i, n4[i] float4 each, one behind the other at ws[i]
+struct WrReduceSet {
+    const float* ws[kMaxMany];
+    float* Y[kMaxMany];
+    size_t n4[kMaxMany];
+};
+void wr_reduce_set(const WrReduceSet& red, int count, int slices, int ybf16, hipStream_t stream);
+// Up to kDecodeRows rows of X starting at row m0: 128 features per workgroup.  set.units / first[] count groups of 128
+// features, each weight rounded up; split > 1 needs a.ws with room for split x rows x N floats of every weight.
+void launch_batch_set(const GemmArgs& a, const WeightSet& set, int64_t m0, int rows, int split, hipStream_t stream);
+
 // Any M (prefill shape).
 void launch_prefill(const GemmArgs& a, int variant, int split_k, hipStream_t stream);
 bool prefill_wreg_supports(const GemmArgs& a);                  // K <= 16384, M * K * 2 < 4 GB
