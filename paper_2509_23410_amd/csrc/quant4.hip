@@ -30,6 +30,7 @@
 #include <vector>
 
 #include "../../include/patch.h"
+#include "batch_parts.h"
 #include "epilogue.h"
 #include "kernels.h"
 #include "layout.h"
@@ -551,6 +552,104 @@ static int q4_strips_per_group(int strips, int n_cus, int rows) {
 }
 
 // ------------------------------------------------------------------------------------------------------
+// Batched decoding from the 4-bit storage: the workgroup of batch_kernel (gemm_batch.hip: 128 features, X through LDS, two
+// wavefront groups taking the 128-column units in turn), the codes becoming operands as they are multiplied.  decode4_kernel draws
+// all of X once per 16 R <= 48 features, which at 64 rows is 10 - 30 times a strip's codes; here X is drawn once per 128.
+// No load is conditional: of a 2:4 tile, whose fragment lanes are 4 bytes apart, the second dword is the neighbour's (in the tile:
+// positions follow the codes), and a dense tile's "positions" are its first codes; neither is used.
+// ------------------------------------------------------------------------------------------------------
+typedef unsigned int b4_pair_t __attribute__((ext_vector_type(2), aligned(4)));   // two dwords at a dword's alignment
+
+struct Bt4 {
+    template <int TILE>
+    struct Unit {
+        static constexpr int KPT = TILE / kStepCols, NT = 2 / KPT;   // steps per tile, tiles per unit
+        b4_pair_t d[2][2];               // [strip][step]
+        uint32_t pos[2][NT], sc[2][NT];  // [strip][tile]
+        __device__ __forceinline__ void load(bt_bytes_ptr payload, bt_halves_ptr srow, int Tk, uint32_t e0, uint32_t e1, int t0, int t1, int s0, int lane) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const uint32_t e = j == 0 ? e0 : e1;
+                const bool sp = entry_sparse(e);
+                const bt_bytes_ptr base = payload + entry_offset(e);
+                const int each = sp ? 4 : 8;
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    const int f = (s0 + s) * KPT + (TILE == 128 ? j : 0);   // fragment
+                    d[s][j] = __builtin_nontemporal_load(reinterpret_cast<const PATCH_BT_GLOBAL b4_pair_t*>(base + f * 64 * each + lane * each));
+                    if (j < NT) {
+                        const bt_bytes_ptr pb = base + (sp ? q4_sparse_codes(TILE) : 0) + ((s0 + s) * 64 + lane) * (2 * KPT);
+                        if constexpr (KPT == 2) pos[s][j] = *reinterpret_cast<const PATCH_BT_GLOBAL uint32_t*>(pb);
+                        else pos[s][j] = *reinterpret_cast<bt_halves_ptr>(pb);
+                        sc[s][j] = srow[(s * Tk + (j == 0 ? t0 : t1)) * 16];
+                    }
+                }
+            }
+        }
+        __device__ __forceinline__ bt_u32x4 operand(int s, int j, int h) const { return q4_dequant8(d[s][j][h], q4_bf16_to_float(sc[s][NT == 1 ? 0 : j])); }
+        __device__ __forceinline__ uint32_t positions(int s, int j, int) const { return NT == 1 ? pos[s][0] >> (16 * j) : pos[s][j]; }
+    };
+};
+
+// Up to kMaxMany weights that share one X; first[i] counts groups of 128 features, each weight rounded up.
+struct Q4Wide {
+    const uint8_t* payload[kMaxMany];
+    const uint16_t* scales[kMaxMany];
+    const uint32_t* table[kMaxMany];
+    float* Y[kMaxMany];
+    int64_t N[kMaxMany];
+    int first[kMaxMany];
+    int count, units;
+};
+
+template <int TILE, int RB, bool SPLIT>
+__global__ __launch_bounds__(256 * kBtGroups) void batch4_kernel(const uint16_t* __restrict__ X, int64_t m0, int rows, int64_t K, int Tk, const Q4Wide set) {
+    uint64_t payload = reinterpret_cast<uint64_t>(set.payload[0]), scales = reinterpret_cast<uint64_t>(set.scales[0]);
+    uint64_t table = reinterpret_cast<uint64_t>(set.table[0]), Y = reinterpret_cast<uint64_t>(set.Y[0]);
+    int64_t N = set.N[0];
+    int first = 0;
+    if (set.count > 1)
+#pragma unroll
+        for (int i = 1; i < kMaxMany; ++i) {
+            const bool here = i < set.count && (int)blockIdx.x >= set.first[i];
+            payload = here ? reinterpret_cast<uint64_t>(set.payload[i]) : payload;
+            scales = here ? reinterpret_cast<uint64_t>(set.scales[i]) : scales;
+            table = here ? reinterpret_cast<uint64_t>(set.table[i]) : table;
+            Y = here ? reinterpret_cast<uint64_t>(set.Y[i]) : Y;
+            N = here ? set.N[i] : N;
+            first = here ? set.first[i] : first;
+        }
+    batch_body<Bt4, TILE, RB, SPLIT>(X, m0, rows, K, Tk, reinterpret_cast<bt_bytes_ptr>(bt_uniform64(payload)),
+                                     reinterpret_cast<bt_table_ptr>(bt_uniform64(table)), reinterpret_cast<bt_halves_ptr>(bt_uniform64(scales)),
+                                     reinterpret_cast<float*>(bt_uniform64(Y)), (int64_t)bt_uniform64((uint64_t)N),
+                                     (int)blockIdx.x - __builtin_amdgcn_readfirstlane(first), 0);
+}
+
+template <int TILE, bool SPLIT>
+static void launch_batch4_t(const uint16_t* X, int64_t m0, int rows, int64_t K, int Tk, const Q4Wide& set, int split, hipStream_t s) {
+    const dim3 grid((unsigned)set.units, (unsigned)split), block(256 * kBtGroups);
+    if (rows <= 16) hipLaunchKernelGGL((batch4_kernel<TILE, 1, SPLIT>), grid, block, 0, s, X, m0, rows, K, Tk, set);
+    else if (rows <= 32) hipLaunchKernelGGL((batch4_kernel<TILE, 2, SPLIT>), grid, block, 0, s, X, m0, rows, K, Tk, set);
+    else if (rows <= 48) hipLaunchKernelGGL((batch4_kernel<TILE, 3, SPLIT>), grid, block, 0, s, X, m0, rows, K, Tk, set);
+    else hipLaunchKernelGGL((batch4_kernel<TILE, 4, SPLIT>), grid, block, 0, s, X, m0, rows, K, Tk, set);
+}
+
+// Up to 64 rows of X starting at row m0.  split > 1 (a set of one; at most ceil(K / 128)): K chunks, partial sums in ws (split x rows x N floats).
+static void launch_batch4(const uint16_t* X, int64_t m0, int rows, int64_t K, int tile, const Q4Wide& set, int split, float* ws, hipStream_t s) {
+    const int Tk = (int)(K / tile);
+    if (split < 2) {
+        if (tile == 128) launch_batch4_t<128, false>(X, m0, rows, K, Tk, set, 1, s);
+        else launch_batch4_t<64, false>(X, m0, rows, K, Tk, set, 1, s);
+        return;
+    }
+    Q4Wide part = set;
+    part.Y[0] = ws;
+    if (tile == 128) launch_batch4_t<128, true>(X, m0, rows, K, Tk, part, split, s);
+    else launch_batch4_t<64, true>(X, m0, rows, K, Tk, part, split, s);
+    wr_reduce(ws, (size_t)rows * (size_t)set.N[0] / 4, split, set.Y[0] + m0 * set.N[0], 0, s);
+}
+
+// ------------------------------------------------------------------------------------------------------
 // Prefill-shaped product from the 4-bit storage: the structure of prefill_kernel_areg - blocks of 256
 // features x 128 or 256 rows, a wavefront owns 32 features x all rows, X through two LDS stages - with the weight operands
 // dequantized in registers.  A lane loads the codes of its pieces of the stored fragments one step ahead (dense: two
@@ -982,6 +1081,40 @@ patch_status patch_unpack4(const patch_packed4* P, void* W_deq, void* codes, voi
     return PATCH_OK;
 }
 
+// A pass of `rows` rows (at most 64) over all weights of a set (N features of a single weight, whose K may be split over ws_bytes of
+// workspace; 0 = none): the strip kernel or batch4_kernel, and in how many K chunks.  Both are estimated, in us with steps = 64-column steps
+// (fitted to launches of 16 .. 1728 strips at f = 0.5, mostly within 12 %; measured in brackets, strip / batch):
+//   strip   3 + share x (0.6 R + 0.2 + 0.04 rows) x 0.05 x steps up to 16 rows, beyond with 1.09 + 0.076 (rows - 17), from 33 rows
+//           2.23 + 0.068 (rows - 32) in place of the last two terms; R = strips per workgroup, share = workgroups / compute units where more
+//           than one (then 15 % more: they share a compute unit), else 1; x (0.55 + 0.6 kept share of the weights), 1 at f = 0.5.  (Finer
+//           than the estimate R is chosen by.)
+//   batch   5 + rounds x steps / chunks x (0.17 + 0.041 blocks of 16 rows) (1 + 0.12 fill), mask tile 64 8 % more (two scales and
+//           position loads per unit), and 1.2 (up to 8 rows 3) to be worth it; a split 2.7 for the second launch, and its partial sums twice at 5 TB/s
+// gate and up of 4096 / 11008 at 1 / 16 / 32 / 64 rows (17.4 / 19.6, 19.6 / 19.5, 25.8 / 22.5, 41.9 / 28.2), of 5120 / 13824 (26.1 / 23.8, 31.3 / 23.6,
+// 41.8 / 27.7, 78.0 / 35.0); three 4096 x 4096 (9.8 / 19.5, 11.1 / 19.3, 15.9 / 22.0, 22.7 / 27.5); 4096 x 11008 in 8 chunks at 8 / 16 / 40 rows (12.1 / 13.3,
+// 16.4 / 13.9, 29.9 / 17.2).
+struct Q4Plan { bool wide; int chunks; double us; };
+static Q4Plan q4_pass_plan(int strips, int groups128, int64_t N, int64_t K, int tile, int rows, int n_cus, double kept, size_t ws_bytes) {
+    const double steps = (double)K / kStepCols;
+    const int R = q4_strips_per_group(strips, n_cus, rows);
+    const double x = rows <= 16 ? 0.2 + 0.04 * rows : rows <= 32 ? 1.09 + 0.076 * (rows - 17) : 2.23 + 0.068 * (rows - 32);
+    const double share = (double)((strips + R - 1) / R) / n_cus;
+    Q4Plan best = {false, 1, 3.0 + (share > 1.0 ? 1.15 * share : 1.0) * (0.6 * R + x) * (0.55 + 0.6 * kept) * 0.05 * steps};
+    const double margin = rows <= 8 ? 3.0 : 1.2;
+    const double step = (0.17 + 0.041 * ((rows + 15) / 16)) * (tile == 64 ? 1.08 : 1.0);
+    const size_t fit = ws_bytes / ((size_t)rows * (size_t)N * sizeof(float));
+    for (int c = 1; c == 1 || (c <= 8 && (size_t)c <= fit && groups128 * c <= n_cus && c * 512 <= K); ++c) {
+        const int wg = groups128 * c, rounds = (wg + n_cus - 1) / n_cus;
+        const double fill = wg < n_cus ? (double)wg / n_cus : 1.0;
+        const double us = (best.wide ? 5.0 : 5.0 + margin) + rounds * steps / c * step * (1.0 + 0.12 * fill) + (c > 1 ? 2.7 + 2.0 * c * rows * (double)N * 4.0 / 5.0e6 : 0.0);
+        if (us < best.us) best = Q4Plan{true, c, best.wide ? us : us - margin};
+    }
+    return best;
+}
+
+static patch_status q4_passes(const void* X, int64_t M, const patch_packed4* const* P, void* const* Y, int count, float* ws, size_t ws_bytes,
+                              hipStream_t s);
+
 patch_status patch_gemm4_many(const void* X, int64_t M, const patch_packed4* const* P, void* const* Y, int count, void* stream) {
     if (!X || !P || !Y || M < 0 || count < 1 || count > PATCH_MAX_MANY) return PATCH_ERR_ARG;
     static_assert(PATCH_MAX_MANY == kMaxMany, "header and kernels disagree");
@@ -991,7 +1124,13 @@ patch_status patch_gemm4_many(const void* X, int64_t M, const patch_packed4* con
         if (P[i]->K != P[0]->K || P[i]->tile != P[0]->tile) return PATCH_ERR_SHAPE;
     }
     if (M == 0) return PATCH_OK;
-    hipStream_t s = static_cast<hipStream_t>(stream);
+    return q4_passes(X, M, P, Y, count, nullptr, 0, static_cast<hipStream_t>(stream));
+}
+
+// Passes of up to 64 rows over all weights, which share X (checked by the callers): the strip kernel or batch4_kernel, whichever is
+// estimated faster.  A single weight may split K over a workspace.
+static patch_status q4_passes(const void* X, int64_t M, const patch_packed4* const* P, void* const* Y, int count, float* ws, size_t ws_bytes,
+                              hipStream_t s) {
     const patch_packed4* P0 = P[0];
     const int total = P0->Tk * (P0->tile / kStepCols);
     int first[kMaxMany], total_strips = 0;
@@ -999,10 +1138,32 @@ patch_status patch_gemm4_many(const void* X, int64_t M, const patch_packed4* con
         first[i] = total_strips;
         total_strips += (int)(P[i]->N / kStripRows);
     }
+    Q4Wide wide = {};
+    for (int i = 0; i < count; ++i) {
+        wide.payload[i] = P[i]->d_payload;
+        wide.scales[i] = P[i]->d_scales;
+        wide.table[i] = P[i]->d_table;
+        wide.Y[i] = static_cast<float*>(Y[i]);
+        wide.N[i] = P[i]->N;
+        wide.first[i] = wide.units;
+        wide.units += (int)((P[i]->N + kBtFeatures - 1) / kBtFeatures);
+    }
+    wide.count = count;
+    double sparse_tiles = 0.0, tiles = 0.0;
+    for (int i = 0; i < count; ++i) {
+        sparse_tiles += (double)P[i]->n_sparse;
+        tiles += (double)P[i]->Tn * P[i]->Tk;
+    }
+    const double kept = 1.0 - 0.5 * sparse_tiles / tiles;
     // One launch per pass of up to 64 rows (1, 2 or 4 blocks of 16), R strips per workgroup (q4_strips_per_group).
     auto run = [&](const auto& set) {
         for (int64_t m0 = 0; m0 < M; m0 += kQ4Rows) {
             const int rows = (int)(M - m0 < kQ4Rows ? M - m0 : kQ4Rows);
+            const Q4Plan plan = q4_pass_plan(total_strips, wide.units, P0->N, P0->K, P0->tile, rows, P0->n_cus, kept, count == 1 ? ws_bytes : 0);
+            if (plan.wide) {
+                launch_batch4(static_cast<const uint16_t*>(X), m0, rows, P0->K, P0->tile, wide, plan.chunks, ws, s);
+                continue;
+            }
             const int RB = rows <= 16 ? 1 : rows <= 32 ? 2 : 4;
             const int R = q4_strips_per_group(total_strips, P0->n_cus, rows);
             const int groups = (total_strips + R - 1) / R;
@@ -1050,30 +1211,24 @@ patch_status patch_gemm4(const void* X, int64_t M, const patch_packed4* P, void*
     return patch_gemm4_ex(X, M, P, Y, nullptr, 0, stream);
 }
 
-// Passes of up to 64 rows (the decode-shaped kernel) or the prefill-shaped kernel?  Both sides are
-// estimated from measured rates, as for the bf16 kernels:
-//   pass of r rows   rounds x (x(r) + R) x 0.05 us x 64-column steps, the terms of q4_strips_per_group (a workgroup
-//                    loads all of X whatever R is); 64 rows: 4096^2 17.8 us, 11008 x 4096 21.9, 13824 x 5120 44.5
+// Passes of up to 64 rows or the prefill-shaped kernel?  Both sides are estimated from measured rates, as for the bf16 kernels:
+//   passes           q4_pass_plan's estimate of a full pass, and of the last one by its rows
 //   prefill kernel   rounds x steps per workgroup x (t0 + t1 fill) us + 3, fill = min(1, workgroups / compute units),
 //                    for blocks of 128 and of 256 rows (the dequantization makes a step 0.2 - 0.4 us longer than the
 //                    bf16 kernel's), + for a split 3 + (2 split + 1) M N 4 B / 5.5 TB/s; splits of at most 8 slices of at
 //                    least 512 columns
 // Returns the split to launch the prefill kernel with (and the block height), or 0 for passes.
-static double q4_pass_us(int strips, int n_cus, int rows, int steps) {
-    const int R = q4_strips_per_group(strips, n_cus, rows);
-    const int groups = (strips + R - 1) / R;
-    const double x = rows <= 16 ? 0.15 + 0.045 * rows : rows <= 32 ? 1.7 : 1.7 + 2.8 * (rows - 32) / 32.0;   // 4.5 at 64 rows
-    const double rounds = groups <= 2 * n_cus ? (double)((groups + n_cus - 1) / n_cus) : (double)groups / n_cus + 0.5;
-    return rounds * (x + R) * 0.05 * steps;
-}
-
 static int q4_prefill_split(int64_t M, const patch_packed4* P, const GemmArgs& a, int* bm_out) {
     *bm_out = 128;
     if (M <= 16) return 0;
-    const int kpt = P->tile / 64, steps = P->Tk * kpt, strips = (int)(P->N / 16);
+    const int kpt = P->tile / 64, strips = (int)(P->N / 16);
     const int64_t full = M / kQ4Rows;
     const int rest = (int)(M % kQ4Rows);
-    const double passes_us = (double)full * q4_pass_us(strips, P->n_cus, kQ4Rows, steps) + (rest ? q4_pass_us(strips, P->n_cus, rest, steps) : 0.0);
+    const auto pass_us = [&](int rows) {
+        return q4_pass_plan(strips, (int)((P->N + kBtFeatures - 1) / kBtFeatures), P->N, P->K, P->tile, rows, P->n_cus,
+                            1.0 - 0.5 * (double)P->n_sparse / ((double)P->Tn * P->Tk), a.ws ? a.ws_bytes : 0).us;
+    };
+    const double passes_us = (full ? (double)full * pass_us(kQ4Rows) : 0.0) + (rest ? pass_us(rest) : 0.0);
     const size_t per_slice = (size_t)M * (size_t)P->N * sizeof(float);
     const int fit = a.ws ? (int)(a.ws_bytes / per_slice < 8 ? a.ws_bytes / per_slice : 8) : 1;
     const int longest = P->Tk * P->tile / 512;
@@ -1110,8 +1265,8 @@ patch_status patch_gemm4_ex(const void* X, int64_t M, const patch_packed4* P, vo
     if (ws) { a.ws = static_cast<float*>(workspace); a.ws_bytes = workspace_bytes; }
     int bm = 128;
     const int split = q4_prefill_split(M, P, a, &bm);
-    if (split == 0) return patch_gemm4_many(X, M, &P, &Y, 1, stream);
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (split == 0) return q4_passes(X, M, &P, &Y, 1, a.ws, a.ws_bytes, s);
     const int tiles_n = (int)((P->N + kP4BN - 1) / kP4BN), tiles_m = (int)((M + bm - 1) / bm);
     const int grid = ((tiles_n * tiles_m + 7) / 8) * 8;
     const int lds_bytes = 2 * bm * 128;
