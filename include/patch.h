@@ -45,7 +45,8 @@ typedef enum {
  * once per pass: 16-feature strips per workgroup for few rows, 64 or 128 features per workgroup for more where that
  * fills the chip), PREFILL in blocks of 256 rows (128 where an estimate of both says so: few rows, or a weight of
  * few feature blocks that would otherwise need a deep K split).  AUTO (measured crossovers): decode up to M = 64 (without
- * a workspace, a single weight wider than the chip goes to prefill from M = 33); beyond, with a
+ * a workspace, a single weight wider than the chip goes to prefill from M = 33) and, as one pass, up to M = 128
+ * where estimated ahead of a prefill launch; beyond, with a
  * workspace for at least two slices (see patch_gemm_opts) prefill, whose K split then fills the chip; without one
  * the cheaper of repeated passes and one unsplit prefill launch by an estimate from the launch geometry (passes up to
  * M = 192 at 4096 x 4096, up to M = 128 from 5120 features, further for long-K weights of few features). */
@@ -77,7 +78,7 @@ typedef struct {
                  /* default picks 6 where at least a quarter of the tiles are 2:4); 7 = the kernel with  */
                  /* 128 features per workgroup (its split_k = K chunks over `workspace`, 0 = auto; the   */
                  /* default for passes of 8 .. 64 rows where estimated fastest, with a workspace in      */
-                 /* chunks).  A variant that does not apply falls back to the default.                   */
+                 /* chunks; up to 128 rows a pass).  A variant that does not apply falls back to the default.                   */
     void* workspace;        /* DEVICE, 16-byte aligned, caller-owned scratch for launches that split K   */
                             /* over workgroups (prefill; decode passes of 17 .. 64 rows), or NULL.  The  */
                             /* library never allocates in a product call.  Launches that may run         */

@@ -399,10 +399,11 @@ patch_status patch_deserialize(const void* buf, size_t bytes, void* stream, patc
 //            up to 64       4.3 + (0.113 + 0.0019 rows) (1 + 0.2 fill)     4096 x 4096, 33 / 64 rows 16.8 / 20.9; 896 x 4864 16.9 / 22.4
 //     mid    up to 16 rows  4.0 + (0.11 + 0.0047 rows) (1 + 0.25 fill)     three 4096 x 4096, 8 / 16 rows 16.1 / 17.1
 //            up to 32       4.0 + (0.10 + 0.0037 rows) (1 + 0.25 fill)     three 4096 x 4096 20.3; 5120 x 13824, 20 rows 44
-//            up to 64       5.5 + (0.19 + 0.0022 rows) (1 + 0.25 fill)     three 4096 x 4096, 33 / 64 rows 24.1 / 28.7; 896 x 4864, 64 rows 29.5
+//            up to 64       6.5 + (0.165 + 0.0016 rows) (1 + 0.38 fill)    three 4096 x 4096, 33 / 64 rows 24.1 / 28.7; three 5120 x 5120, 64 rows
+//                           35.8; 5120 x 13824, 48 / 64 rows 65 / 73; 13824 x 512, 64 rows 11.6; in chunks 1.5 less: 896 x 4864, 64 rows (8) 13.2
 //     batch                 5.2 + (0.235 + 0.0018 rows) (1 + 0.33 fill)    three 4096 x 4096, 16 / 32 / 33 / 64 rows 24.2 / 26.0 / 26.5 / 29.8, in two
 //                           chunks 20.5 / 20.9 / 22.4 / 25.2; 896 x 896, 64 rows 9.8; gate and up of 4096 / 11008 27.2 / 29.4 / 29.2 / 32.9 (mid: two rounds, 31.1 / 37.1 / 41.4 / 52.6)
-// (every further round: strip 0.7, mid 2 us more; batch has to be 0.5 us ahead) and none takes less than its weights at 6.6 TB/s.  A split costs a second launch (5 us) and its partial sums twice through memory
+// (every further round: strip 0.7, mid 2 us more; batch has to be 0.7 us ahead) and none takes less than its weights at 6.6 TB/s.  A split costs a second launch (5 us) and its partial sums twice through memory
 // (5 TB/s).  Up to 7 rows (11 for a single weight) the strip kernel's X is small and it is always taken.
 struct DecodePlan { int kernel, chunks; double us; };   // kernel: 0 strip, 1 mid, 2 batch
 struct DecodeShape { int64_t N; int strips, groups64, groups128; size_t payload; int count; };   // of a weight or a whole set
@@ -420,19 +421,37 @@ static DecodePlan decode_plan(const GemmArgs& a, const DecodeShape& d, int rows,
     const auto consider = [&](int kernel, int chunks, double t) { if (t < best.us) best = DecodePlan{kernel, chunks, t}; };
     const size_t per_chunk = (size_t)rows * (size_t)d.N * sizeof(float);
     const int fit = a.ws ? (int)(a.ws_bytes / per_chunk < 8 ? a.ws_bytes / per_chunk : 8) : 1;
-    const double mid0 = rows <= 32 ? 4.0 : 5.5, mid = rows <= 16 ? 0.11 + 0.0047 * rows : rows <= 32 ? 0.10 + 0.0037 * rows : 0.19 + 0.0022 * rows, batch = 0.235 + 0.0018 * rows;
-    consider(1, 1, us(mid0 + 2.0 * (double)((d.groups64 - 1) / a.n_cus), d.groups64, 1, mid, 0.25));
+    const double mid0 = rows <= 32 ? 4.0 : 6.5, mid_fill = rows <= 32 ? 0.25 : 0.38;
+    const double mid = rows <= 16 ? 0.11 + 0.0047 * rows : rows <= 32 ? 0.10 + 0.0037 * rows : 0.165 + 0.0016 * rows;
+    const double batch = rows <= kDecodeRows ? 0.235 + 0.0018 * rows : 0.09 + 0.064 * (rows <= 80 ? 5 : rows <= 96 ? 6 : 8);
+    consider(1, 1, us(mid0 + 2.0 * (double)((d.groups64 - 1) / a.n_cus), d.groups64, 1, mid, mid_fill));
     if (d.count == 1 && rows > 16) {
         const int c = mid_split(a, rows, 0);
-        if (c > 1) consider(1, c, us(mid0, d.groups64, c, mid, 0.25));
+        if (c > 1) consider(1, c, us(mid0 - 1.5, d.groups64, c, mid, mid_fill));
     }
     // (at most 8 chunks of at least four units of 128 columns; beyond one workgroup per compute unit a split only adds partial sums)
+    // (beyond 64 rows a second launch is a smaller part of the whole: half of it is hidden)
+    const double again = rows > kDecodeRows ? 2.5 : 0.0;
     DecodePlan wide = {2, 1, us(5.2, d.groups128, 1, batch, 0.33)};
     for (int c = 2; c <= fit && d.groups128 * c <= a.n_cus && c * 512 <= a.K; ++c) {
-        const double t = us(5.2, d.groups128, c, batch, 0.33);
+        const double t = us(5.2 - again, d.groups128, c, batch, 0.33);
         if (t < wide.us) wide = DecodePlan{2, c, t};
     }
-    return only_wide || wide.us + 0.5 < best.us ? wide : best;
+    return only_wide || wide.us + 0.7 < best.us ? wide : best;
+}
+
+// 65 .. 128 rows, nothing asked for: one pass of batch_kernel (5, 6 or 8 blocks of 16 rows, one wavefront group) against the prefill launch
+// - whose K split writes and reads its partial products more often, or which leaves compute units idle - and, without a workspace, two
+// passes.  Step 0.09 + 0.064 blocks there, a split's second launch 2.5 us; the prefill estimates run 12 % low at so few rows,
+// and do not know the share f of 2:4 tiles (10 % less at f = 1).  f = 0.5, prefill
+// -> pass, 80 / 128 rows: three 4096 x 4096 40.4 / 40.4 -> 27.0 / 35.4 us, gate and up of 4096 / 11008 48.2 / 52.1 -> 36.5 / 49.7, of 5120 / 13824
+// 68.4 / 74.2 -> 46.6 / 62.0, of 896 / 4864 21.7 / 22.0 -> 11.9 / 15.5, 4096 x 11008 32.9 / 35.3 -> 24.4 / 28.7 (4096 x 4096 17.2 / 18.4 against 16.8 / 22.4:
+// the prefill launch from 81 rows).
+static bool takes_wide_pass(const GemmArgs& a, const DecodeShape& d, double prefill_us, DecodePlan* plan) {   // kDecodeRows < a.M <= kBatchRows
+    *plan = decode_plan(a, d, (int)a.M, true);
+    double other = 1.12 * prefill_us * std::min(1.0, 1.1 - 0.002 * a.sparse_pct);
+    if (!a.ws) other = std::min(other, decode_plan(a, d, kDecodeRows).us + decode_plan(a, d, (int)a.M - kDecodeRows).us);
+    return plan->us + 0.8 + 0.15 * plan->chunks < other;
 }
 
 // batch_kernel on request (variant 7): `requested` K chunks as far as they exist and the workspace holds them, 0 = the plan's
@@ -456,7 +475,7 @@ static DecodeShape decode_shape(const patch_packed* P) {
 // 19 / 22 us against 21 / 23).  Without one the prefill grid may be too small to fill the chip, and both sides are estimated:
 //   unsplit prefill launch  rounds x 64-column steps x 1.0 us (tile 64 beyond K = 16384: 1.45 us), or with
 //                           blocks of 128 rows x 0.70 us (tile 64: 0.75), whichever is less (launch_prefill makes the
-//                           same choice)
+//                           same choice), + 4.2 us for the launch (896 x 896 at M = 66: 14.0 us)
 //   passes                  decode_plan's estimate of a full pass, and of the last one by its rows
 // From 33 rows on the estimate also decides a single pass against an unsplit prefill launch: only weights wider
 // than the chip change side (65536 x 4096 at M = 64: 109 us in a pass of mid_kernel, 90 us on the 128-row prefill kernel).
@@ -471,7 +490,7 @@ static int auto_path(int64_t M, const patch_packed* P, const patch_gemm_opts* op
     const int64_t tiles128 = ((P->N + 255) / 256) * ((M + 127) / 128);   // blocks of 128 rows: 0.70 / 0.75 us per step
     const double us128 = (double)((tiles128 + P->n_cus - 1) / P->n_cus) * steps * (P->tile == 128 ? 0.70 : 0.75);
     const double us256 = rounds * steps * (P->tile == 128 || P->K <= 16384 ? 1.0 : 1.45);
-    const double prefill_us = us128 < us256 ? us128 : us256;
+    const double prefill_us = (us128 < us256 ? us128 : us256) + 4.2;
     GemmArgs a = {};
     a.N = P->N; a.K = P->K; a.tile = P->tile; a.Tk = P->Tk; a.n_cus = P->n_cus;
     const DecodeShape d = decode_shape(P);
@@ -488,7 +507,6 @@ patch_status patch_gemm_ex(const void* X, int64_t M, const patch_packed* P, void
     if (path < PATCH_PATH_AUTO || path > PATCH_PATH_PREFILL || split_k < 0 || split_k > 16 || variant < 0) return PATCH_ERR_ARG;
     if (opts && opts->workspace && !aligned16(opts->workspace)) return PATCH_ERR_ARG;
     if (M == 0) return PATCH_OK;  // an empty batch: nothing to launch, Y has no rows
-    if (path == PATCH_PATH_AUTO) path = auto_path(M, P, opts);
     hipStream_t s = static_cast<hipStream_t>(stream);
     GemmArgs a;
     a.X = static_cast<const uint16_t*>(X);
@@ -500,13 +518,21 @@ patch_status patch_gemm_ex(const void* X, int64_t M, const patch_packed* P, void
     a.sparse_pct = (int)(100 * P->n_sparse / ((int64_t)P->Tn * P->Tk));
     if (opts && opts->workspace) { a.ws = static_cast<float*>(opts->workspace); a.ws_bytes = opts->workspace_bytes; }
     a.ybf16 = (opts && opts->y_bf16) ? 1 : 0;
+    WeightSet one = {};
+    one.payload[0] = a.payload; one.table[0] = a.table; one.Y[0] = a.Y; one.N[0] = a.N;
+    one.count = 1;
+    const DecodeShape d = decode_shape(P);
+    DecodePlan wide = {2, 1, 0.0};
+    if (path == PATCH_PATH_AUTO && variant == 0 && split_k == 0 && M > kDecodeRows && M <= kBatchRows && takes_wide_pass(a, d, prefill_estimate(a), &wide)) {
+        one.units = d.groups128;
+        launch_batch_set(a, one, 0, (int)M, wide.chunks, s);
+        HIP_TRY(hipGetLastError());
+        return PATCH_OK;
+    }
+    if (path == PATCH_PATH_AUTO) path = auto_path(M, P, opts);
     if (path == PATCH_PATH_DECODE) {
-        WeightSet one = {};
-        one.payload[0] = a.payload; one.table[0] = a.table; one.Y[0] = a.Y; one.N[0] = a.N;
-        one.count = 1;
-        const DecodeShape d = decode_shape(P);
-        for (int64_t m0 = 0; m0 < M; m0 += kDecodeRows) {
-            const int rows = (int)((M - m0 < kDecodeRows) ? M - m0 : kDecodeRows);
+        for (int64_t m0 = 0; m0 < M; m0 += (variant == 7 ? kBatchRows : kDecodeRows)) {
+            const int rows = (int)((M - m0 < (variant == 7 ? kBatchRows : kDecodeRows)) ? M - m0 : (variant == 7 ? kBatchRows : kDecodeRows));
             DecodePlan plan = {0, 1, 0.0};
             if (variant == 4) plan = DecodePlan{1, mid_split(a, rows, split_k), 0.0};
             else if (variant == 7) plan = batch_plan(a, d, rows, split_k);
@@ -743,6 +769,7 @@ size_t patch_gemm_workspace_bytes(int64_t M, const patch_packed* P, const patch_
     int path = PATCH_PATH_AUTO, split_k = 0, variant = 0;
     if (opts) { path = opts->path; split_k = opts->split_k; variant = opts->variant; }
     patch_gemm_opts enough = {path, split_k, variant, reinterpret_cast<void*>(16), ~(size_t)0, 0};  // the choice given enough
+    const bool any = path == PATCH_PATH_AUTO && variant == 0 && split_k == 0;
     if (path == PATCH_PATH_AUTO) path = auto_path(M, P, &enough);
     GemmArgs a;
     a.X = nullptr; a.M = M; a.N = P->N; a.K = P->K;
@@ -751,6 +778,10 @@ size_t patch_gemm_workspace_bytes(int64_t M, const patch_packed* P, const patch_
     a.n_cus = P->n_cus;
     a.ws = reinterpret_cast<float*>(16);  // "enough": ask for the unconstrained choice
     a.ws_bytes = ~(size_t)0;
+    // 65 .. 128 rows: what one pass would use, and no less than the prefill launch it stands in for (below)
+    size_t least = 0;
+    DecodePlan wide = {2, 1, 0.0};
+    if (any && M > kDecodeRows && M <= kBatchRows && takes_wide_pass(a, decode_shape(P), prefill_estimate(a), &wide) && wide.chunks > 1) least = (size_t)wide.chunks * (size_t)M * (size_t)P->N * sizeof(float);
     if (path == PATCH_PATH_DECODE) {
         // passes of 12 .. 64 rows may cut K into chunks over the workspace (the largest pass decides)
         const int rows = (int)(M < kDecodeRows ? M : kDecodeRows);
@@ -771,18 +802,18 @@ size_t patch_gemm_workspace_bytes(int64_t M, const patch_packed* P, const patch_
         // (mask tile 64: what the library asks for here, and with it which calls patch_gemm_static accepts, is the split of
         // prefill_kernel_areg at either block height; prefill_kernel_w64 takes the slices, and the split of a part-filled
         // last round, that fit into what it is given)
-        if (prefill_prefers_128_rows(a, &split128, true)) return split128 > 1 ? (size_t)split128 * (size_t)M * (size_t)P->N * sizeof(float) : 0;
+        if (prefill_prefers_128_rows(a, &split128, true)) return std::max(least, split128 > 1 ? (size_t)split128 * (size_t)M * (size_t)P->N * sizeof(float) : (size_t)0);
     }
     if (variant == 2 || variant == 4 || variant == 5 || a.tile == 64 || !prefill_wreg_supports(a)) {   // whole-launch K split only (same for both 256-row kernels)
         const int sl = prefill_lds_split(a, split_k, variant == 4 || variant == 5 ? 128 : 256);
-        return sl > 1 ? (size_t)sl * (size_t)M * (size_t)P->N * sizeof(float) : 0;
+        return std::max(least, sl > 1 ? (size_t)sl * (size_t)M * (size_t)P->N * sizeof(float) : (size_t)0);
     }
     const int s = prefill_wreg_split(a, split_k);
-    if (s > 1) return (size_t)s * (size_t)M * (size_t)P->N * sizeof(float);
+    if (s > 1) return std::max(least, (size_t)s * (size_t)M * (size_t)P->N * sizeof(float));
     if (split_k != 0) return 0;
     int tail = 0;
     const int ts = prefill_wreg_tail(a, &tail);   // K slices for the part-filled last round only
-    return ts > 1 ? (size_t)ts * (size_t)tail * 256 * 256 * sizeof(float) : 0;
+    return std::max(least, ts > 1 ? (size_t)ts * (size_t)tail * 256 * 256 * sizeof(float) : (size_t)0);
 }
 
 patch_status patch_gemm_many(const void* X, int64_t M, const patch_packed* const* P, void* const* Y, int count, void* stream,
@@ -798,6 +829,7 @@ patch_status patch_gemm_many(const void* X, int64_t M, const patch_packed* const
     if (opts) { path = opts->path; split_k = opts->split_k; variant = opts->variant; }
     if (path < PATCH_PATH_AUTO || path > PATCH_PATH_PREFILL || split_k < 0 || split_k > 16 || variant < 0) return PATCH_ERR_ARG;
     if (M == 0) return PATCH_OK;
+    const bool any = path == PATCH_PATH_AUTO && variant == 0 && split_k == 0;
     if (path == PATCH_PATH_AUTO) path = auto_path(M, P[0], opts, count == 1);
     hipStream_t s = static_cast<hipStream_t>(stream);
     GemmArgs a = {};
@@ -817,33 +849,6 @@ patch_status patch_gemm_many(const void* X, int64_t M, const patch_packed* const
     a.ybf16 = (opts && opts->y_bf16) ? 1 : 0;
     if (opts && opts->workspace && !aligned16(opts->workspace)) return PATCH_ERR_ARG;
     if (opts && opts->workspace && split_k == 0) { a.ws = static_cast<float*>(opts->workspace); a.ws_bytes = opts->workspace_bytes; }
-    if (path == PATCH_PATH_PREFILL && count > 1 && (variant == 0 || variant == 3) && split_k <= 1 && prefill_wreg_supports(a)) {
-        // one launch over the feature blocks of all weights (with a workspace and few blocks: K in slices over the
-        // whole set, see launch_prefill_wreg_set)
-        int blocks = 0;
-        WeightSet set = {};
-        for (int i = 0; i < count; ++i) {
-            set.payload[i] = P[i]->d_payload;
-            set.table[i] = P[i]->d_table;
-            set.Y[i] = static_cast<float*>(Y[i]);
-            set.N[i] = P[i]->N;
-            set.first[i] = blocks;
-            blocks += (int)((P[i]->N + 255) / 256);
-        }
-        set.count = count;
-        set.units = blocks;
-        launch_prefill_wreg_set(a, set, s);
-        HIP_TRY(hipGetLastError());
-        return PATCH_OK;
-    }
-    if (path == PATCH_PATH_PREFILL || count == 1) {
-        patch_gemm_opts o = {path, split_k, variant, opts ? opts->workspace : nullptr, opts ? opts->workspace_bytes : 0, a.ybf16};
-        for (int i = 0; i < count; ++i) {
-            const patch_status st = patch_gemm_ex(X, M, P[i], Y[i], stream, &o);
-            if (st != PATCH_OK) return st;
-        }
-        return PATCH_OK;
-    }
     DecodeSet set = {};
     int strips = 0;
     for (int i = 0; i < count; ++i) {
@@ -867,8 +872,54 @@ patch_status patch_gemm_many(const void* X, int64_t M, const patch_packed* const
     }
     wide64.units = d.groups64;
     wide128.units = d.groups128;
-    for (int64_t m0 = 0; m0 < M; m0 += kDecodeRows) {
-        const int rows = (int)((M - m0 < kDecodeRows) ? M - m0 : kDecodeRows);
+    if (any && count > 1 && M > kDecodeRows && M <= kBatchRows) {
+        int units = 0;
+        for (int i = 0; i < count; ++i) units += (int)((P[i]->N + 255) / 256);
+        // (beyond the limits of the set launch the weights go one by one: priced as one launch after the other)
+        double prefill_us = 0.0;
+        if (prefill_wreg_supports(a)) prefill_us = prefill_set_estimate(a, units, d.N);
+        else
+            for (int i = 0; i < count; ++i) {
+                GemmArgs b = a;
+                b.N = P[i]->N;
+                prefill_us += prefill_estimate(b);
+            }
+        DecodePlan plan = {2, 1, 0.0};
+        if (takes_wide_pass(a, d, prefill_us, &plan)) {
+            launch_batch_set(a, wide128, 0, (int)M, plan.chunks, s);
+            HIP_TRY(hipGetLastError());
+            return PATCH_OK;
+        }
+    }
+    if (path == PATCH_PATH_PREFILL && count > 1 && (variant == 0 || variant == 3) && split_k <= 1 && prefill_wreg_supports(a)) {
+        // one launch over the feature blocks of all weights (with a workspace and few blocks: K in slices over the
+        // whole set, see launch_prefill_wreg_set)
+        int blocks = 0;
+        WeightSet set = {};
+        for (int i = 0; i < count; ++i) {
+            set.payload[i] = P[i]->d_payload;
+            set.table[i] = P[i]->d_table;
+            set.Y[i] = static_cast<float*>(Y[i]);
+            set.N[i] = P[i]->N;
+            set.first[i] = blocks;
+            blocks += (int)((P[i]->N + 255) / 256);
+        }
+        set.count = count;
+        set.units = blocks;
+        launch_prefill_wreg_set(a, set, s);
+        HIP_TRY(hipGetLastError());
+        return PATCH_OK;
+    }
+    if (path == PATCH_PATH_PREFILL || count == 1) {
+        patch_gemm_opts o = {any && count == 1 ? PATCH_PATH_AUTO : path, split_k, variant, opts ? opts->workspace : nullptr, opts ? opts->workspace_bytes : 0, a.ybf16};
+        for (int i = 0; i < count; ++i) {
+            const patch_status st = patch_gemm_ex(X, M, P[i], Y[i], stream, &o);
+            if (st != PATCH_OK) return st;
+        }
+        return PATCH_OK;
+    }
+    for (int64_t m0 = 0; m0 < M; m0 += (variant == 7 ? kBatchRows : kDecodeRows)) {
+        const int rows = (int)((M - m0 < (variant == 7 ? kBatchRows : kDecodeRows)) ? M - m0 : (variant == 7 ? kBatchRows : kDecodeRows));
         DecodePlan plan = {0, 1, 0.0};
         if (variant == 4) plan.kernel = 1;
         else if (variant == 7) plan = batch_plan(a, d, rows, split_k);

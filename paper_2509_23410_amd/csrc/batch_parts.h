@@ -25,7 +25,8 @@ typedef const PATCH_BT_GLOBAL uint16_t* bt_halves_ptr;
 
 constexpr int kBtFeatures = 128;   // per workgroup: 4 wavefronts x 2 strips
 constexpr int kBtUnit = 128;       // columns per unit
-constexpr int kBtGroups = 2;       // wavefront groups: each takes every second unit
+// wavefront groups, each taking every kth unit: two up to 64 rows; beyond, the accumulators of 128 rows leave room for one
+constexpr int bt_groups(int RB) { return RB > 4 ? 1 : 2; }
 
 __device__ __forceinline__ uint64_t bt_uniform64(uint64_t v) {
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
@@ -38,7 +39,7 @@ __device__ __forceinline__ uint64_t bt_uniform64(uint64_t v) {
 template <class Weight, int TILE, int RB, bool SPLIT>
 __device__ __forceinline__ void batch_body(const uint16_t* __restrict__ X, int64_t m0, int rows, int64_t K, int Tk, bt_bytes_ptr payload,
                                            bt_table_ptr table, bt_halves_ptr scales, float* Y, int64_t N, int grp, int ybf16) {
-    constexpr int KG = kBtGroups;
+    constexpr int KG = bt_groups(RB);
     constexpr int kStage = 2 * RB * 16 * 128;   // two steps x rows x 128 bytes
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[KG * 2 * kStage];
     const int tid = threadIdx.x & 255, lane = tid & 63;

@@ -1,4 +1,4 @@
-// Hybrid GEMM for batched decoding: up to 64 rows of X per launch (the product Y = X * W_hat^T of Section 4 / Appendix A
+// Hybrid GEMM for batched decoding: up to 128 rows of X per launch (the product Y = X * W_hat^T of Section 4 / Appendix A
 // of the paper between its decoding input, a few rows, and its prefill input, thousands).
 //
 // What bounds it: a compute unit draws about 50 GB/s through its vector L1 here, however many wavefronts ask (one group of
@@ -10,6 +10,9 @@
 // columns and wr_reduce_set_kernel adds their partial sums in order; that second launch costs about 4 us, which is why
 // decode_plan (api.hip) weighs it.  f = 0.5, 47 rows, before -> now: gate and up of 4096 / 11008 (172 workgroups, no split) 46.7 -> 31.4 us
 // (4.5 TB/s of weights), of 5120 / 13824 59.0 -> 41.4; 4096 x 11008 (8 chunks) 23.9 -> 21.8; 5120 x 13824 at 16 rows (6 chunks) 37.3 -> 23.5.
+//
+// Beyond 64 rows, up to 128, one wavefront group per workgroup (80 - 128 accumulators and operands of up to eight row blocks per
+// lane: 272 - 384 registers): X then costs as much as the weights, still once per 128 features.
 //
 // Weights go straight into registers in the stored order, one unit ahead, always eight 16-byte loads per wavefront and unit:
 // of a 2:4 tile the second load of a step starts at the lane's position word (its first register; the rest is ignored; the
@@ -53,7 +56,7 @@ struct BtBf16 {
 };
 
 template <int TILE, int RB, bool SPLIT>
-__global__ __launch_bounds__(256 * kBtGroups) void batch_kernel(const uint16_t* __restrict__ X, int64_t m0, int rows, int64_t K, int Tk, const WeightSet set, int ybf16) {
+__global__ __launch_bounds__(256 * bt_groups(RB)) void batch_kernel(const uint16_t* __restrict__ X, int64_t m0, int rows, int64_t K, int Tk, const WeightSet set, int ybf16) {
     uint64_t payload64 = reinterpret_cast<uint64_t>(set.payload[0]), table64 = reinterpret_cast<uint64_t>(set.table[0]), Y64 = reinterpret_cast<uint64_t>(set.Y[0]);
     int64_t N = set.N[0];
     int first = 0;
@@ -77,14 +80,17 @@ __global__ __launch_bounds__(256 * kBtGroups) void batch_kernel(const uint16_t* 
 
 template <int TILE, bool SPLIT>
 static void launch_batch_t(const GemmArgs& a, const WeightSet& set, int64_t m0, int rows, int split, int ybf16, hipStream_t stream) {
-    const dim3 grid((unsigned)set.units, (unsigned)split), block(256 * kBtGroups);
-    if (rows <= 16) hipLaunchKernelGGL((batch_kernel<TILE, 1, SPLIT>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, ybf16);
-    else if (rows <= 32) hipLaunchKernelGGL((batch_kernel<TILE, 2, SPLIT>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, ybf16);
-    else if (rows <= 48) hipLaunchKernelGGL((batch_kernel<TILE, 3, SPLIT>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, ybf16);
-    else hipLaunchKernelGGL((batch_kernel<TILE, 4, SPLIT>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, ybf16);
+    const dim3 grid((unsigned)set.units, (unsigned)split);
+#define PATCH_BT_CASE(rb)                                                                                                             \
+    if (rows <= 16 * rb) {                                                                                                            \
+        hipLaunchKernelGGL((batch_kernel<TILE, rb, SPLIT>), grid, dim3(256 * bt_groups(rb)), 0, stream, a.X, m0, rows, a.K, a.Tk, set, ybf16); \
+        return;                                                                                                                       \
+    }
+    PATCH_BT_CASE(1) PATCH_BT_CASE(2) PATCH_BT_CASE(3) PATCH_BT_CASE(4) PATCH_BT_CASE(5) PATCH_BT_CASE(6) PATCH_BT_CASE(8)
+#undef PATCH_BT_CASE
 }
 
-// Up to 64 rows of X starting at row m0.  set.units / first[] count groups of 128 features, each weight rounded up.  A K split
+// Up to kBatchRows rows of X starting at row m0.  set.units / first[] count groups of 128 features, each weight rounded up.  A K split
 // (split > 1, at most ceil(K / 128)) needs a.ws with room for split x rows x N floats of every weight.
 void launch_batch_set(const GemmArgs& a, const WeightSet& set, int64_t m0, int rows, int split, hipStream_t stream) {
     if (split < 2) {

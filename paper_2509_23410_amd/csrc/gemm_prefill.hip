@@ -710,7 +710,7 @@ static double pf_estimate(const GemmArgs& a, int blocks, int split, double t0, d
     return us;
 }
 
-bool prefill_prefers_128_rows(const GemmArgs& a, int* split, bool no_w64) {
+static bool pf_prefers_128(const GemmArgs& a, int* split, bool no_w64, double* us) {
     const int tiles_n = (int)((a.N + kPfBN - 1) / kPfBN);
     const int b256 = tiles_n * (int)((a.M + 255) / 256), b128 = tiles_n * (int)((a.M + 127) / 128);
     const bool wreg = prefill_wreg_supports(a) && !(no_w64 && a.tile == 64);
@@ -725,7 +725,21 @@ bool prefill_prefers_128_rows(const GemmArgs& a, int* split, bool no_w64) {
         const double us = pf_estimate(a, b128, sp, a.tile == 128 ? 0.70 : 0.75, a.tile == 128 ? 0.24 : 0.22);
         if (sp == 1 || us < best) { best = us; *split = sp; }
     }
+    *us = best < 0.97 * us256 ? best : us256;
     return best < 0.97 * us256;
+}
+
+bool prefill_prefers_128_rows(const GemmArgs& a, int* split, bool no_w64) {
+    double us = 0.0;
+    return pf_prefers_128(a, split, no_w64, &us);
+}
+
+// us the default choice is estimated to take
+double prefill_estimate(const GemmArgs& a) {
+    int split = 1;
+    double us = 0.0;
+    (void)pf_prefers_128(a, &split, false, &us);
+    return us;
 }
 
 // Kernel choice.  variant 0 (default): prefill_kernel_areg with blocks of 128 rows where prefill_prefers_128_rows says so

@@ -1148,6 +1148,26 @@ void launch_prefill_wreg(const GemmArgs& a, int split_k, hipStream_t stream) {
     }
 }
 
+// K slices of a set launch: N = features of all weights
+static int wr_set_split(const GemmArgs& a, int nblk, int64_t N) {
+    if (!a.ws || nblk >= (a.n_cus * 2) / 3) return 1;
+    int split = a.n_cus / nblk;
+    if (split > wr_longest(a)) split = wr_longest(a);
+    if (split > 8) split = 8;
+    const size_t out = (size_t)a.M * (size_t)N * sizeof(float), fit = out ? a.ws_bytes / out : 0;
+    if ((size_t)split > fit) split = (int)fit;
+    return split < 2 ? 1 : split;
+}
+
+// us a set launch is estimated to take, priced like pf_estimate (gemm_prefill.hip)
+double prefill_set_estimate(const GemmArgs& a, int units, int64_t N) {
+    const int nblk = units * (int)((a.M + kWrBM - 1) / kWrBM), split = wr_set_split(a, nblk, N);
+    const int wgs = nblk * split, rounds = (wgs + a.n_cus - 1) / a.n_cus;
+    const double fill = wgs < a.n_cus ? (double)wgs / a.n_cus : 1.0;
+    const double us = rounds * ((a.Tk + split - 1) / split) * (a.tile / kStepCols) * (0.90 + 0.35 * fill) + 3.0;
+    return split > 1 ? us + 3.0 + (2.0 * split + 1.0) * (double)a.M * (double)N * 4.0 / 5.5e6 : us;
+}
+
 void launch_prefill_wreg_set(const GemmArgs& a, const WeightSet& set, hipStream_t stream) {
     const int tiles_m = (int)((a.M + kWrBM - 1) / kWrBM);
     const int nblk = set.units * tiles_m;
@@ -1155,14 +1175,10 @@ void launch_prefill_wreg_set(const GemmArgs& a, const WeightSet& set, hipStream_
     // tiles): K in slices over the whole set in ONE launch - slice y of weight i writes its partial product to the
     // workspace region of that weight - and one reduction launch over all weights.  (One split launch and one
     // reduction per weight took 126 us on that set.)
-    if (a.ws && nblk < (a.n_cus * 2) / 3) {
-        int64_t out_floats = 0;
-        for (int i = 0; i < set.count; ++i) out_floats += a.M * set.N[i];
-        int split = a.n_cus / nblk;
-        if (split > wr_longest(a)) split = wr_longest(a);
-        if (split > 8) split = 8;
-        const size_t fit = out_floats ? a.ws_bytes / ((size_t)out_floats * sizeof(float)) : 0;
-        if ((size_t)split > fit) split = (int)fit;
+    {
+        int64_t N = 0;
+        for (int i = 0; i < set.count; ++i) N += set.N[i];
+        const int split = wr_set_split(a, nblk, N);
         if (split >= 2) {
             WeightSet part = set;
             WrReduceSet red = {};

@@ -57,6 +57,7 @@ struct WeightOne {
 
 // Up to kDecodeRows rows of X starting at row m0 (decode shape; 16-row blocks, the weights streamed once per launch).
 constexpr int kDecodeRows = 64;
+constexpr int kBatchRows = 128;   // batch_kernel
 //  split_k = K slices (wavefronts) per workgroup,
 // 0 picks a default.  Returns the number used.
 int launch_decode(const GemmArgs& a, int64_t m0, int rows, int split_k, int variant, hipStream_t stream);
@@ -78,7 +79,7 @@ struct WrReduceSet {
     size_t n4[kMaxMany];
 };
 void wr_reduce_set(const WrReduceSet& red, int count, int slices, int ybf16, hipStream_t stream);
-// Up to kDecodeRows rows of X starting at row m0: 128 features per workgroup.  set.units / first[] count groups of 128
+// Up to kBatchRows rows of X starting at row m0: 128 features per workgroup.  set.units / first[] count groups of 128
 // features, each weight rounded up; split > 1 needs a.ws with room for split x rows x N floats of every weight.
 void launch_batch_set(const GemmArgs& a, const WeightSet& set, int64_t m0, int rows, int split, hipStream_t stream);
 
@@ -89,6 +90,8 @@ int prefill_wreg_split(const GemmArgs& a, int requested);       // K slices per 
 int prefill_lds_split(const GemmArgs& a, int requested, int bm = 256);   // the same for the LDS-staged kernel with blocks of bm rows
 // whether the default choice (variant 0, no split requested) is the LDS-staged kernel with blocks of 128 rows, and its split
 bool prefill_prefers_128_rows(const GemmArgs& a, int* split, bool no_w64 = false);
+double prefill_estimate(const GemmArgs& a);                                  // us the default choice is estimated to take
+double prefill_set_estimate(const GemmArgs& a, int units, int64_t N);         // the same for a set: units of 256 features, N features
 // K slices for the last *tail tiles of an unsplit launch with a part-filled last round (needs a.ws); 1 = none
 int prefill_wreg_tail(const GemmArgs& a, int* tail);
 int prefill_wreg_tail_of(int tiles, const GemmArgs& a, int* tail);   // the same for a given tile count (sets of weights)

@@ -603,7 +603,7 @@ struct Q4Wide {
 };
 
 template <int TILE, int RB, bool SPLIT>
-__global__ __launch_bounds__(256 * kBtGroups) void batch4_kernel(const uint16_t* __restrict__ X, int64_t m0, int rows, int64_t K, int Tk, const Q4Wide set) {
+__global__ __launch_bounds__(256 * bt_groups(RB)) void batch4_kernel(const uint16_t* __restrict__ X, int64_t m0, int rows, int64_t K, int Tk, const Q4Wide set) {
     uint64_t payload = reinterpret_cast<uint64_t>(set.payload[0]), scales = reinterpret_cast<uint64_t>(set.scales[0]);
     uint64_t table = reinterpret_cast<uint64_t>(set.table[0]), Y = reinterpret_cast<uint64_t>(set.Y[0]);
     int64_t N = set.N[0];
@@ -627,7 +627,7 @@ __global__ __launch_bounds__(256 * kBtGroups) void batch4_kernel(const uint16_t*
 
 template <int TILE, bool SPLIT>
 static void launch_batch4_t(const uint16_t* X, int64_t m0, int rows, int64_t K, int Tk, const Q4Wide& set, int split, hipStream_t s) {
-    const dim3 grid((unsigned)set.units, (unsigned)split), block(256 * kBtGroups);
+    const dim3 grid((unsigned)set.units, (unsigned)split), block(256 * bt_groups(4));
     if (rows <= 16) hipLaunchKernelGGL((batch4_kernel<TILE, 1, SPLIT>), grid, block, 0, s, X, m0, rows, K, Tk, set);
     else if (rows <= 32) hipLaunchKernelGGL((batch4_kernel<TILE, 2, SPLIT>), grid, block, 0, s, X, m0, rows, K, Tk, set);
     else if (rows <= 48) hipLaunchKernelGGL((batch4_kernel<TILE, 3, SPLIT>), grid, block, 0, s, X, m0, rows, K, Tk, set);

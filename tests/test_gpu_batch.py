@@ -1,4 +1,4 @@
-"""The batched-decoding kernel (128 features x up to 64 rows per workgroup, decode variant 7) where it can go wrong, against the
+"""The batched-decoding kernel (128 features x up to 128 rows per workgroup, decode variant 7) where it can go wrong, against the
 float64 product of the same bf16 values: every count of 16-row blocks and its edges, one to five 128-column units (two wavefront
 groups take them in turn), a last unit of one 64-column step, a last feature group of 64, K in chunks over a workspace that ends in a
 guard region, sets of weights in one launch, bf16 output.  Element bound as in test_gpu_prefill64."""
@@ -31,10 +31,10 @@ def test_batch(tile, N, K, f):
     print(f"batch tile={tile} N={N} K={K} f={f}", flush=True)
     stream = torch.cuda.current_stream().cuda_stream
     (W, P), (W2, P2) = _weight(N, K, tile, f, 1), _weight(tile, K, tile, 1 - f, 2)
-    for M in (1, 8, 16, 17, 32, 33, 48, 49, 64, 70):
+    for M in (1, 8, 16, 17, 32, 33, 48, 49, 64, 65, 80, 81, 96, 97, 128, 130):
         X = torch.randn(M, K, device="cuda", generator=torch.Generator(device="cuda").manual_seed(M)).to(torch.bfloat16)
         for split in (1, 2, 3, 0):
-            rows = min(M, 64)
+            rows = min(M, 128)
             need = max(1, split) * rows * N if split else B.patch_gemm_workspace_bytes(M, P, path=B.PATH_DECODE, variant=7) // 4
             buf = torch.full((need + 1024,), float("nan"), device="cuda")
             buf[need:] = 7.0
@@ -45,10 +45,10 @@ def test_batch(tile, N, K, f):
             B.patch_gemm(X, M, P, Yb, stream, y_bf16=True, **kw)
             assert torch.equal(Yb, Y.to(torch.bfloat16)), "bf16 output is the fp32 sum rounded once"
             assert bool((buf[need:] == 7.0).all()), "wrote behind the workspace"
-        ws = torch.full((8 * min(M, 64) * (2 * N + tile),), float("nan"), device="cuda")
-        for kw in (dict(), dict(workspace=ws), dict(variant=7), dict(variant=7, workspace=ws)):
+        ws = torch.full((8 * M * (2 * N + tile),), float("nan"), device="cuda")
+        for kw in (dict(), dict(workspace=ws), dict(path=B.PATH_DECODE), dict(path=B.PATH_DECODE, variant=7), dict(path=B.PATH_DECODE, variant=7, workspace=ws)):
             Ys = [torch.full((M, n), float("nan"), device="cuda") for n in (N, tile, N)]
-            B.patch_gemm_many(X, M, [P, P2, P], Ys, stream, path=B.PATH_DECODE, **kw)
+            B.patch_gemm_many(X, M, [P, P2, P], Ys, stream, **kw)
             for y, w in zip(Ys, (W, W2, W)):
                 _check(y, X.double(), w, f"set M={M}")
     P.close()
