@@ -783,18 +783,24 @@ size_t patch_gemm_workspace_bytes(int64_t M, const patch_packed* P, const patch_
     DecodePlan wide = {2, 1, 0.0};
     if (any && M > kDecodeRows && M <= kBatchRows && takes_wide_pass(a, decode_shape(P), prefill_estimate(a), &wide) && wide.chunks > 1) least = (size_t)wide.chunks * (size_t)M * (size_t)P->N * sizeof(float);
     if (path == PATCH_PATH_DECODE) {
-        // passes of 12 .. 64 rows may cut K into chunks over the workspace (the largest pass decides)
-        const int rows = (int)(M < kDecodeRows ? M : kDecodeRows);
-        int chunks = 1;
-        if (variant == 4) chunks = mid_split(a, rows, split_k);
-        else if (variant == 7) chunks = batch_plan(a, decode_shape(P), rows, split_k).chunks;
-        else if (variant == 0 && split_k == 0) {
-            // (from 17 rows at least what mid_kernel would take, whichever kernel the plan prefers: a caller that asked before
-            // and one that asks now get no smaller a buffer)
-            chunks = decode_plan(a, decode_shape(P), rows).chunks;
-            if (rows > 16) chunks = std::max(chunks, mid_split(a, rows, 0));
+        // a pass may cut K into chunks over the workspace; the full passes and the last one each have a number of their own
+        const int64_t pass = variant == 7 ? kBatchRows : kDecodeRows;
+        size_t most = 0;
+        for (const int64_t r : {M < pass ? M : pass, M % pass}) {
+            const int rows = (int)r;
+            if (rows == 0) continue;
+            int chunks = 1;
+            if (variant == 4) chunks = mid_split(a, rows, split_k);
+            else if (variant == 7) chunks = batch_plan(a, decode_shape(P), rows, split_k).chunks;
+            else if (variant == 0 && split_k == 0) {
+                // (from 17 rows at least what mid_kernel would take, whichever kernel the plan prefers: a caller that asked before
+                // and one that asks now get no smaller a buffer)
+                chunks = decode_plan(a, decode_shape(P), rows).chunks;
+                if (rows > 16) chunks = std::max(chunks, mid_split(a, rows, 0));
+            }
+            if (chunks > 1) most = std::max(most, (size_t)chunks * (size_t)rows * (size_t)P->N * sizeof(float));
         }
-        return chunks < 2 ? 0 : (size_t)chunks * (size_t)rows * (size_t)P->N * sizeof(float);
+        return most;
     }
     if (variant == 1) return 0;
     if (variant == 0 && split_k == 0) {

@@ -1,0 +1,52 @@
+"""patch_gemm_workspace_bytes against what the launch does: given any amount of workspace a product writes no further than the query
+says (nothing where it says 0), and given exactly that amount it runs the same schedule - the same split of K, hence the same
+bits."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2509_23410_amd import binding as B, synth
+
+pytestmark = pytest.mark.gpu
+PATTERN = 0x7FC0BEEF
+
+
+def _weight(N, K, tile, f):
+    c = synth.make_case("workspace", N, K, 1, tile, f, seed=5)
+    W = torch.from_numpy(c.W.view(np.int16)).cuda().view(torch.bfloat16)
+    stream = torch.cuda.current_stream().cuda_stream
+    B.patch_apply_mask(W, torch.from_numpy(c.mask24).cuda(), c.tile_map, N, K, tile, W, stream)
+    return B.patch_pack(W, N, K, c.tile_map, tile, stream)
+
+
+def _check(P, N, K, M, kw, big):
+    """-> bytes the query asks for; `big`: int32 scratch of more than any schedule wants."""
+    stream = torch.cuda.current_stream().cuda_stream
+    X = torch.randn(M, K, device="cuda", generator=torch.Generator(device="cuda").manual_seed(M)).to(torch.bfloat16)
+    need = B.patch_gemm_workspace_bytes(M, P, **kw)
+    what = f"{N}x{K} M={M} {kw}: {need} bytes asked for"
+    print(what, flush=True)
+    big.fill_(PATTERN)
+    Y, E = torch.full((M, N), float("nan"), device="cuda"), torch.full((M, N), float("nan"), device="cuda")
+    B.patch_gemm(X, M, P, Y, stream, workspace=big.view(torch.float32), **kw)
+    assert bool((big[need // 4:] == PATTERN).all()), what + ", more written"
+    if need:
+        B.patch_gemm(X, M, P, E, stream, workspace=big[:need // 4].view(torch.float32), **kw)
+        assert torch.equal(Y, E), what + ", another schedule with exactly that"
+    return need
+
+
+@pytest.mark.parametrize("tile,N,K,f", [(128, 640, 4096, 0.5), (64, 448, 4160, 0.5)])
+def test_query_of_decode_passes(tile, N, K, f):
+    P = _weight(N, K, tile, f)
+    big = torch.empty(16 * 256 * N, device="cuda", dtype=torch.int32)
+    asked = []
+    for kw in (dict(), dict(path=B.PATH_DECODE), dict(path=B.PATH_DECODE, variant=4), dict(path=B.PATH_DECODE, variant=7),
+               dict(path=B.PATH_DECODE, variant=7, split_k=2), dict(path=B.PATH_DECODE, variant=7, split_k=5)):
+        for M in (1, 8, 12, 16, 17, 33, 64, 65, 100, 128, 130, 200):
+            need = _check(P, N, K, M, kw, big)
+            asked.append(need)
+            if kw.get("split_k"):
+                assert need == kw["split_k"] * min(M, 128) * N * 4, "the requested chunks of the largest pass"
+    assert max(asked) > 0
+    P.close()
