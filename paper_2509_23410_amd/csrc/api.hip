@@ -854,7 +854,11 @@ patch_status patch_gemm_many(const void* X, int64_t M, const patch_packed* const
     }
     a.ybf16 = (opts && opts->y_bf16) ? 1 : 0;
     if (opts && opts->workspace && !aligned16(opts->workspace)) return PATCH_ERR_ARG;
-    if (opts && opts->workspace && split_k == 0) { a.ws = static_cast<float*>(opts->workspace); a.ws_bytes = opts->workspace_bytes; }
+    // (a split asked for is that of one launch per weight, but for the kernel with 128 features, whose chunks cover the set)
+    if (opts && opts->workspace && (split_k == 0 || (path == PATCH_PATH_DECODE && variant == 7))) {
+        a.ws = static_cast<float*>(opts->workspace);
+        a.ws_bytes = opts->workspace_bytes;
+    }
     DecodeSet set = {};
     int strips = 0;
     for (int i = 0; i < count; ++i) {

@@ -53,3 +53,23 @@ def test_batch(tile, N, K, f):
                 _check(y, X.double(), w, f"set M={M}")
     P.close()
     P2.close()
+
+
+@pytest.mark.parametrize("tile,N,K", [(128, 384, 640), (64, 192, 576)])
+def test_set_takes_the_chunks_asked_for(tile, N, K):
+    """split_k of variant 7 counts K chunks over the workspace for a set too: its first split_k x M x (sum of N) floats are written, nothing
+    behind them."""
+    print(f"batch set chunks tile={tile} N={N} K={K}", flush=True)
+    stream = torch.cuda.current_stream().cuda_stream
+    (W, P), (W2, P2) = _weight(N, K, tile, 0.5, 1), _weight(tile, K, tile, 0.5, 2)
+    for M, split in ((5, 2), (64, 3), (100, 5)):
+        X = torch.randn(M, K, device="cuda", generator=torch.Generator(device="cuda").manual_seed(M)).to(torch.bfloat16)
+        Ys = [torch.full((M, n), float("nan"), device="cuda") for n in (N, tile)]
+        need = split * M * (N + tile)
+        ws = torch.full((need + 4096,), float("nan"), device="cuda")
+        B.patch_gemm_many(X, M, [P, P2], Ys, stream, path=B.PATH_DECODE, variant=7, split_k=split, workspace=ws)
+        for y, w in zip(Ys, (W, W2)):
+            _check(y, X.double(), w, f"set M={M} split={split}")
+        assert bool(torch.isfinite(ws[:need]).all()) and bool(ws[need:].isnan().all()), f"M={M} split={split}: not {split} chunks"
+    P.close()
+    P2.close()
