@@ -156,7 +156,8 @@ patch_status patch_gemm_ex(const void* X, int64_t M, const patch_packed* P, void
  * The schedule is the one patch_gemm_ex picks when given a workspace of that size, so results are bit-equal to
  * patch_gemm_ex with such a caller workspace.  Returns PATCH_ERR_SIZE - nothing is launched - when that schedule
  * would want more scratch than the array holds (patch_gemm_workspace_bytes(M, P, NULL) > PATCH_STATIC_SCRATCH_BYTES;
- * e.g. split launches of large M x N); use patch_gemm_ex with a workspace of your own then.  Every partial sum the
+ * e.g. split launches of large M x N; on tile 64 only the slices of whole launches count, and a part-filled last round is
+ * split as far as the array allows); use patch_gemm_ex with a workspace of your own then.  Every partial sum the
  * kernels read from the scratch is written by the same call first, so nothing needs clearing between calls, but
  * all calls on one GPU share the one array: calls that overlap in time on the same GPU (different streams or
  * threads) race on it.  Errors otherwise as patch_gemm_ex.

@@ -764,7 +764,9 @@ patch_status patch_tune_layer(patch_tune_table* t, const void* X_decode, int64_t
     return PATCH_OK;
 }
 
-size_t patch_gemm_workspace_bytes(int64_t M, const patch_packed* P, const patch_gemm_opts* opts) {
+// Bytes of workspace a product uses given any amount.  slices_only: of a prefill launch on mask tile 64 only the split of whole launches,
+// as prefill_kernel_areg would make it - by which patch_gemm_static accepts or refuses; prefill_kernel_w64 runs in what the array holds.
+static size_t workspace_need(int64_t M, const patch_packed* P, const patch_gemm_opts* opts, bool slices_only) {
     if (!P || M <= 0) return 0;
     int path = PATCH_PATH_AUTO, split_k = 0, variant = 0;
     if (opts) { path = opts->path; split_k = opts->split_k; variant = opts->variant; }
@@ -805,12 +807,9 @@ size_t patch_gemm_workspace_bytes(int64_t M, const patch_packed* P, const patch_
     if (variant == 1) return 0;
     if (variant == 0 && split_k == 0) {
         int split128 = 1;
-        // (mask tile 64: what the library asks for here, and with it which calls patch_gemm_static accepts, is the split of
-        // prefill_kernel_areg at either block height; prefill_kernel_w64 takes the slices, and the split of a part-filled
-        // last round, that fit into what it is given)
-        if (prefill_prefers_128_rows(a, &split128, true)) return std::max(least, split128 > 1 ? (size_t)split128 * (size_t)M * (size_t)P->N * sizeof(float) : (size_t)0);
+        if (prefill_prefers_128_rows(a, &split128, slices_only)) return std::max(least, split128 > 1 ? (size_t)split128 * (size_t)M * (size_t)P->N * sizeof(float) : (size_t)0);
     }
-    if (variant == 2 || variant == 4 || variant == 5 || a.tile == 64 || !prefill_wreg_supports(a)) {   // whole-launch K split only (same for both 256-row kernels)
+    if (variant == 2 || variant == 4 || variant == 5 || (a.tile == 64 && (variant == 6 || slices_only)) || !prefill_wreg_supports(a)) {   // whole-launch K split only
         const int sl = prefill_lds_split(a, split_k, variant == 4 || variant == 5 ? 128 : 256);
         return std::max(least, sl > 1 ? (size_t)sl * (size_t)M * (size_t)P->N * sizeof(float) : (size_t)0);
     }
@@ -821,6 +820,8 @@ size_t patch_gemm_workspace_bytes(int64_t M, const patch_packed* P, const patch_
     const int ts = prefill_wreg_tail(a, &tail);   // K slices for the part-filled last round only
     return std::max(least, ts > 1 ? (size_t)ts * (size_t)tail * 256 * 256 * sizeof(float) : (size_t)0);
 }
+
+size_t patch_gemm_workspace_bytes(int64_t M, const patch_packed* P, const patch_gemm_opts* opts) { return workspace_need(M, P, opts, false); }
 
 patch_status patch_gemm_many(const void* X, int64_t M, const patch_packed* const* P, void* const* Y, int count, void* stream,
                              const patch_gemm_opts* opts) {
@@ -949,7 +950,7 @@ patch_status patch_gemm(const void* X, int64_t M, const patch_packed* P, void* Y
 patch_status patch_gemm_static(const void* X, int64_t M, const patch_packed* P, void* Y, void* stream) {
     if (!X || !P || !Y || M < 0) return PATCH_ERR_ARG;
     // what the automatic schedule would use given any amount of workspace: beyond the static array, refuse
-    const size_t need = patch_gemm_workspace_bytes(M, P, nullptr);
+    const size_t need = workspace_need(M, P, nullptr, true);
     if (need > kStaticScratchBytes) return PATCH_ERR_SIZE;
     void* ws = nullptr;
     const patch_status st = static_scratch(&ws);

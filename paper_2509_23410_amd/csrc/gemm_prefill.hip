@@ -700,7 +700,7 @@ int prefill_lds_split(const GemmArgs& a, int requested, int bm) {
 // to unsplit launches of 16 and of 256 workgroups at f = 0.6).  The 256-row side takes the
 // split its launcher would take; the 128-row side its best split of at most 8 slices of at least 512 columns that the
 // workspace holds.  Returns true, and the split, when 128 rows are estimated at least 3 % faster.  no_w64: mask tile 64 as if its
-// 256-row kernel were prefill_kernel_areg (see patch_gemm_workspace_bytes).
+// 256-row kernel were prefill_kernel_areg (what patch_gemm_static goes by).
 static double pf_estimate(const GemmArgs& a, int blocks, int split, double t0, double t1) {
     const int rounds = (blocks * split + a.n_cus - 1) / a.n_cus;
     const int steps = ((a.Tk + split - 1) / split) * (a.tile / kStepCols);

@@ -29,7 +29,8 @@ def _check(P, N, K, M, kw, big):
     big.fill_(PATTERN)
     Y, E = torch.full((M, N), float("nan"), device="cuda"), torch.full((M, N), float("nan"), device="cuda")
     B.patch_gemm(X, M, P, Y, stream, workspace=big.view(torch.float32), **kw)
-    assert bool((big[need // 4:] == PATTERN).all()), what + ", more written"
+    kept = bool((big[need // 4:] == PATTERN).all())
+    assert kept, what + ", more written"
     if need:
         B.patch_gemm(X, M, P, E, stream, workspace=big[:need // 4].view(torch.float32), **kw)
         assert torch.equal(Y, E), what + ", another schedule with exactly that"
@@ -49,4 +50,29 @@ def test_query_of_decode_passes(tile, N, K, f):
             if kw.get("split_k"):
                 assert need == kw["split_k"] * min(M, 128) * N * 4, "the requested chunks of the largest pass"
     assert max(asked) > 0
+    P.close()
+
+
+@pytest.mark.parametrize("N,K,M", [(2112, 2048, 7400), (320, 4160, 300), (4096, 1024, 513), (192, 16448, 300)])
+def test_query_of_prefill_launches_of_mask_tile_64(N, K, M):
+    """A part-filled last round in slices, whole launches in slices in either block height, and a K beyond the register-weight kernel."""
+    P = _weight(N, K, 64, 0.6)
+    big = torch.empty(max(9 * M * N, 64 << 18), device="cuda", dtype=torch.int32)
+    asked = [_check(P, N, K, M, kw, big) for kw in (dict(), dict(path=B.PATH_PREFILL), dict(path=B.PATH_PREFILL, variant=3),
+                                                    dict(path=B.PATH_PREFILL, variant=6), dict(path=B.PATH_PREFILL, split_k=3))]
+    assert max(asked) > 0
+    P.close()
+
+
+def test_static_scratch_takes_a_part_filled_last_round_of_mask_tile_64():
+    """306 blocks of 256 x 256: the 50 of the last round would like 62 MB in slices; patch_gemm_static runs with what its array holds."""
+    N, K, M = 2112, 5120, 8700
+    P = _weight(N, K, 64, 0.5)
+    assert B.patch_gemm_workspace_bytes(M, P) > B.STATIC_SCRATCH_BYTES
+    stream = torch.cuda.current_stream().cuda_stream
+    X = torch.randn(M, K, device="cuda", generator=torch.Generator(device="cuda").manual_seed(M)).to(torch.bfloat16)
+    Y, E = torch.full((M, N), float("nan"), device="cuda"), torch.full((M, N), float("nan"), device="cuda")
+    B.patch_gemm_static(X, M, P, Y, stream)
+    B.patch_gemm(X, M, P, E, stream, workspace=torch.empty(B.STATIC_SCRATCH_BYTES // 4, device="cuda"))
+    assert torch.equal(Y, E)
     P.close()
