@@ -80,9 +80,10 @@ typedef struct {
                  /* default for passes of 8 .. 64 rows where estimated fastest, with a workspace in      */
                  /* chunks; up to 128 rows a pass).  A variant that does not apply falls back to the default.                   */
     void* workspace;        /* DEVICE, 16-byte aligned, caller-owned scratch for launches that split K   */
-                            /* over workgroups (prefill; decode passes of 17 .. 64 rows), or NULL.  The  */
-                            /* library never allocates in a product call.  Launches that may run         */
-                            /* concurrently need distinct workspaces.                                    */
+                            /* over workgroups, or NULL.  Any product call that is given one may write   */
+                            /* it, whatever M, path and number of weights: calls that may overlap in     */
+                            /* time (streams, threads) need a workspace each.  The library never         */
+                            /* allocates in a product call.                                              */
     size_t workspace_bytes; /* its size; patch_gemm_workspace_bytes says what a launch would use         */
     int y_bf16;             /* nonzero: Y (every Y of patch_gemm_many) is M x N bf16 instead of fp32: the fp32  */
                             /* accumulator - after the sum over K slices, where K is split - rounded to nearest, */
@@ -239,19 +240,25 @@ patch_status patch_tune_table_import(patch_tune_table* t, const patch_tune_entry
 patch_status patch_tune_layer(patch_tune_table* t, const void* X_decode, int64_t M_decode, const void* X_prefill, int64_t M_prefill,
                               const patch_packed* P, void* Y, void* workspace, size_t workspace_bytes, void* stream, int reps);
 
-/* Bytes of patch_gemm_opts.workspace the product with these M, P and opts (path, split_k; NULL = defaults) would
- * use if it were given enough: slices x M x N x 4 for a split prefill launch, slices x tiles x 256 KB when only the
- * part-filled last round of a prefill launch is split, chunks x min(M, 64) x N x 4 for decode passes of 17 .. 64
- * rows, else 0. */
+/* Bytes of patch_gemm_opts.workspace that let the product with these M, P and opts (path, split_k, variant; NULL =
+ * defaults) run as if given any amount: slices x M x N x 4 for a split prefill launch, slices x tiles x 256 KB when only
+ * the part-filled last round of a prefill launch is split, chunks x rows x N x 4 for decode passes of `rows` rows (up
+ * to 64; 128 in variant 7 and where AUTO takes 65 .. 128 rows in one pass) whose K is split, and 0 where nothing is split -
+ * then the workspace stays untouched.  For a single weight; a set: see patch_gemm_many. */
 size_t patch_gemm_workspace_bytes(int64_t M, const patch_packed* P, const patch_gemm_opts* opts);
 
 /*
  * The same product for several weights that share one input: Y[i] = X * W_hat[i]^T, i < count (the q / k / v
  * projections of an attention block, the gate / up projections of an MLP; Appendix A times the layer's products
  * for one decode input and one prefill input).  On the decode path all weights run in ONE launch per pass of up
- * to 64 rows of X, which amortises launch and ramp-up over all their bytes; on the prefill path (tile 128) one launch covers the
- * output tiles of all weights - one tail instead of one per weight - unless they are so few that splitting K pays
- * (a workspace is given, split_k = 0), or opts ask for a kernel variant or split: then one launch per weight.
+ * to 64 rows of X (up to 128 where AUTO takes that many in one pass), which amortises launch and ramp-up over all their
+ * bytes; with a workspace and few feature groups a pass may cut K into chunks, summed by a second launch over all weights.  On
+ * the prefill path one launch covers the output tiles of all weights - one tail instead of one per weight; with a workspace and
+ * few tiles (split_k = 0) it cuts K into slices over the whole set, again with one launch that sums them.  Beyond the limits of the
+ * register-weight kernel (K > 16384, M K 2 >= 4 GB), or where opts ask for another prefill variant or a split, the prefill path is one
+ * launch per weight, each as patch_gemm_ex.  Variant 4 runs a set unsplit.
+ * Workspace: at most max(8, split_k) x M x (sum of N) x 4 bytes, or 64 MB for a part-filled last round, are written; with less
+ * there are fewer slices.
  *   P      HOST array of count handles; all with the same K and the same tile, N may differ
  *   Y      HOST array of count DEVICE pointers, Y[i] is M x N[i] fp32 row-major, 16-byte aligned, distinct
  *   count  1 .. PATCH_MAX_MANY

@@ -257,7 +257,8 @@ def _opts(path, split_k, variant, workspace, workspace_bytes, y_bf16=False):
 
 def patch_gemm(X, M: int, P: Packed, Y, stream: int = 0, path: int = PATH_AUTO, split_k: int = 0, variant: int = 0,
                workspace=None, workspace_bytes=None, y_bf16: bool = False) -> None:
-    """workspace: a device tensor (or pointer + workspace_bytes) for split prefill launches; y_bf16: Y is bf16; see patch.h."""
+    """workspace: a device tensor (or pointer + workspace_bytes) that any launch may write when it splits K - calls that may overlap
+    need one each; y_bf16: Y is bf16; see patch.h."""
     if path == PATH_AUTO and split_k == 0 and variant == 0 and workspace is None and not y_bf16:
         st = lib().patch_gemm(_ptr(X), M, P.handle, _ptr(Y), stream)
     else:
@@ -396,7 +397,8 @@ def patch_hard_masks(P_tile, P_24, N: int, K: int, tile: int, mask24, stream: in
 
 def patch_gemm_many(X, M: int, Ps, Ys, stream: int = 0, path: int = PATH_AUTO, split_k: int = 0, variant: int = 0,
                     workspace=None, workspace_bytes=None, y_bf16: bool = False) -> None:
-    """Y[i] = X * W_hat[i]^T for weights that share X (same K, same tile); one decode launch for all of them."""
+    """Y[i] = X * W_hat[i]^T for weights that share X (same K, same tile), one launch for all of them (and one that sums where a
+    workspace lets it split K)."""
     n = len(Ps)
     if n != len(Ys):
         raise PatchError(ERR_ARG, "patch_gemm_many: as many outputs as weights")
@@ -477,7 +479,7 @@ def patch_pack_from4(P4: Packed4, stream: int = 0) -> Packed:
 
 
 def patch_gemm4(X, M: int, P: Packed4, Y, stream: int = 0, workspace=None) -> None:
-    """Y = X . bf16(q s)^T from the 4-bit storage; with a workspace tensor: patch_gemm4_ex (K split for prefill shapes)."""
+    """Y = X . bf16(q s)^T from the 4-bit storage; with a workspace tensor: patch_gemm4_ex (K may be split over it at any M)."""
     if workspace is None:
         _check(lib().patch_gemm4(_ptr(X), M, P.handle, _ptr(Y), stream), "patch_gemm4")
     else:
@@ -486,7 +488,7 @@ def patch_gemm4(X, M: int, P: Packed4, Y, stream: int = 0, workspace=None) -> No
 
 
 def patch_gemm4_many(X, M: int, Ps, Ys, stream: int = 0) -> None:
-    """Several 4-bit weights (same K, same tile) against one X in one launch per 16 rows."""
+    """Several 4-bit weights (same K, same tile) against one X in one launch per 64 rows."""
     n = len(Ps)
     if n != len(Ys):
         raise PatchError(ERR_ARG, "patch_gemm4_many: as many outputs as weights")

@@ -76,3 +76,25 @@ def test_static_scratch_takes_a_part_filled_last_round_of_mask_tile_64():
     B.patch_gemm(X, M, P, E, stream, workspace=torch.empty(B.STATIC_SCRATCH_BYTES // 4, device="cuda"))
     assert torch.equal(Y, E)
     P.close()
+
+
+@pytest.mark.parametrize("tile,N,K,f", [(128, 640, 4096, 0.5), (64, 448, 4160, 0.5)])
+def test_sets_write_what_the_header_says(tile, N, K, f):
+    """patch_gemm_many at any M, few rows included: at most max(8, split_k) x M x (sum of N) floats of the workspace, or 64 MB where the
+    last round of a prefill launch is split."""
+    Ps = [_weight(N, K, tile, f), _weight(tile, K, tile, f)]
+    total, stream = N + tile, torch.cuda.current_stream().cuda_stream
+    big = torch.empty(16 * 300 * total + (16 << 20), device="cuda", dtype=torch.int32)
+    used = []
+    for M in (1, 8, 12, 16, 17, 33, 64, 65, 100, 128, 130, 300):
+        X = torch.randn(M, K, device="cuda", generator=torch.Generator(device="cuda").manual_seed(M)).to(torch.bfloat16)
+        for kw in (dict(), dict(path=B.PATH_DECODE), dict(path=B.PATH_DECODE, variant=4), dict(path=B.PATH_DECODE, variant=7, split_k=12)):
+            big.fill_(PATTERN)
+            Ys = [torch.full((M, n), float("nan"), device="cuda") for n in (N, tile)]
+            B.patch_gemm_many(X, M, Ps, Ys, stream, workspace=big.view(torch.float32), **kw)
+            touched = torch.nonzero(big != PATTERN)
+            used.append(int(touched[-1]) + 1 if len(touched) else 0)
+            assert used[-1] <= max(max(8, kw.get("split_k", 0)) * M * total, 16 << 20 if M > 128 else 0), (M, kw)
+    assert max(used) > 0
+    for P in Ps:
+        P.close()
