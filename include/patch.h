@@ -44,12 +44,12 @@ typedef enum {
 /* Which kernel family patch_gemm_ex uses.  DECODE handles M in passes of up to 64 rows (the weight is streamed
  * once per pass: 16-feature strips per workgroup for few rows, 64 or 128 features per workgroup for more where that
  * fills the chip), PREFILL in blocks of 256 rows (128 where an estimate of both says so: few rows, or a weight of
- * few feature blocks that would otherwise need a deep K split).  AUTO (measured crossovers): decode up to M = 64 (without
- * a workspace, a single weight wider than the chip goes to prefill from M = 33) and, as one pass, up to M = 128
- * where estimated ahead of a prefill launch; beyond, with a
- * workspace for at least two slices (see patch_gemm_opts) prefill, whose K split then fills the chip; without one
- * the cheaper of repeated passes and one unsplit prefill launch by an estimate from the launch geometry (passes up to
- * M = 192 at 4096 x 4096, up to M = 128 from 5120 features, further for long-K weights of few features). */
+ * few feature blocks that would otherwise need a deep K split).  AUTO compares an
+ * estimate of both (fitted to measurements): decode up to M = 64 (a single weight wider than the chip goes to prefill from
+ * M = 33) and, as one pass, up to M = 128 where that is ahead of a prefill launch; beyond, with a workspace for at least two
+ * slices (see patch_gemm_opts) prefill, whose K split then fills the chip; without one the cheaper of repeated passes and one
+ * unsplit prefill launch (passes up to M = 192 at 4096 x 4096, up to M = 128 from 5120 features, further for long-K weights of few
+ * features). */
 typedef enum { PATCH_PATH_AUTO = 0, PATCH_PATH_DECODE = 1, PATCH_PATH_PREFILL = 2 } patch_path;
 
 /* Schedule options (the knobs the paper's Appendix A leaves to an autotuner: tile shape and

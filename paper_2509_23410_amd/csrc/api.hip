@@ -389,69 +389,56 @@ patch_status patch_deserialize(const void* buf, size_t bytes, void* stream, patc
     return PATCH_OK;
 }
 
-// Which kernel a pass of `rows` rows (at most 64) takes, and in how many K chunks.  Three kernels share this range: the strip kernel
-// (gemm_decode.hip: 16 features per workgroup), mid_kernel (64 features) and batch_kernel (128 features).  A launch is bound by
-// what one compute unit draws, so each is estimated as
-//     base + rounds x K-steps per workgroup x step,   rounds = ceil(workgroups / compute units),
-// with step = us per 64 columns, a little more the fuller the chip, fitted to launches of 7 .. 344 workgroups of 8 .. 216 steps at
-// f = 0.5 (mostly within 10 %; us measured):
-//     strip  up to 16 rows  3.0 + (0.027 + 0.0030 rows) (1 + 0.3 fill)     1024 x 8192, 12 / 16 rows 11.1 / 12.4; 4096 x 4096, 16 rows 9.1
-//            up to 64       4.3 + (0.113 + 0.0019 rows) (1 + 0.2 fill)     4096 x 4096, 33 / 64 rows 16.8 / 20.9; 896 x 4864 16.9 / 22.4
-//     mid    up to 16 rows  4.0 + (0.11 + 0.0047 rows) (1 + 0.25 fill)     three 4096 x 4096, 8 / 16 rows 16.1 / 17.1
-//            up to 32       4.0 + (0.10 + 0.0037 rows) (1 + 0.25 fill)     three 4096 x 4096 20.3; 5120 x 13824, 20 rows 44
-//            up to 64       6.5 + (0.165 + 0.0016 rows) (1 + 0.38 fill)    three 4096 x 4096, 33 / 64 rows 24.1 / 28.7; three 5120 x 5120, 64 rows
-//                           35.8; 5120 x 13824, 48 / 64 rows 65 / 73; 13824 x 512, 64 rows 11.6; in chunks 1.5 less: 896 x 4864, 64 rows (8) 13.2
-//     batch                 5.2 + (0.235 + 0.0018 rows) (1 + 0.33 fill)    three 4096 x 4096, 16 / 32 / 33 / 64 rows 24.2 / 26.0 / 26.5 / 29.8, in two
-//                           chunks 20.5 / 20.9 / 22.4 / 25.2; 896 x 896, 64 rows 9.8; gate and up of 4096 / 11008 27.2 / 29.4 / 29.2 / 32.9 (mid: two rounds, 31.1 / 37.1 / 41.4 / 52.6)
-// (every further round: strip 0.7, mid 2 us more; batch has to be 0.7 us ahead) and none takes less than its weights at 6.6 TB/s.  A split costs a second launch (5 us) and its partial sums twice through memory
-// (5 TB/s).  Up to 7 rows (11 for a single weight) the strip kernel's X is small and it is always taken.
+// Which kernel a pass of `rows` rows takes, and in how many K chunks.  Three kernels share up to 64 rows: the strip kernel
+// (gemm_decode.hip: 16 features per workgroup), mid_kernel (64 features) and batch_kernel (128 features, and alone up to 128 rows).  A
+// launch is bound by what one compute unit draws, so each is priced as
+//     base + round (rounds - 1) + rounds x K-steps per workgroup x (step + per_row rows) x (1 + fill min(1, workgroups / compute units)) x (1 + sparse (f - 1/2)),
+// rounds = ceil(workgroups / compute units), f = share of 2:4 tiles, and never less than its weights at 6.6 TB/s.  A split costs a second
+// launch (2.2 us behind mid_kernel, 2.7 behind batch_kernel) and its partial sums twice through memory (5 TB/s).  Fitted to 24 weights from
+// 128 x 4096 to 128256 x 1024 and 12 sets, both mask tiles, f = 0, 1/2 and 1, 22 row counts (860 - 4100 launches per line; rms error
+// 4 - 7 %).  The row ranges are those of the kernels' row blocks: 17 - 32 rows of the strip kernel cost little more than 16 (4096 x 4096, f = 1/2,
+// 17 / 24 / 32 rows 8.8 / 10.6 / 12.1 us, 33 rows 15.2; mid_kernel 14.4 / 15.6 / 17.0).  f tells the kernels apart: at 16 rows three 4096 x 4096 take
+// mid_kernel 19.3 / 17.1 / 12.5 us at f = 0 / 1/2 / 1 and the strip kernel 23.2 / 21.4 / 19.7.
+struct PassPrice { int rows; double base, step, per_row, fill, round, sparse; };
+constexpr PassPrice kStripPrice[] = {{16, 2.5, 0.032, 0.0023, 0.24, 0.35, -0.23}, {32, 2.9, 0.045, 0.0026, 0.06, 0.0, -0.12}, {64, 3.5, 0.082, 0.0024, 0.07, 0.5, -0.03}};
+constexpr PassPrice kMidPrice[] = {{16, 2.6, 0.120, 0.0017, 0.47, 0.0, -0.45}, {32, 3.2, 0.125, 0.0020, 0.40, 2.0, -0.40}, {64, 4.3, 0.143, 0.0024, 0.28, 3.3, -0.31}};
+constexpr PassPrice kBatchPrice[] = {{16, 2.4, 0.257, 0.0005, 0.39, 0.0, -0.30}, {32, 2.7, 0.244, 0.0012, 0.40, 0.8, -0.29}, {64, 3.2, 0.237, 0.0017, 0.31, 3.2, -0.20},
+                                     {80, 3.7, 0.392, 0.0005, 0.14, 4.0, 0.0},   {96, 4.1, 0.452, 0.0004, 0.10, 4.0, 0.03},  {128, 4.7, 0.570, 0.0004, 0.10, 4.0, 0.03}};
+
 struct DecodePlan { int kernel, chunks; double us; };   // kernel: 0 strip, 1 mid, 2 batch
 struct DecodeShape { int64_t N; int strips, groups64, groups128; size_t payload; int count; };   // of a weight or a whole set
 
+static double pass_us(const PassPrice* p, const GemmArgs& a, const DecodeShape& d, int rows, int groups, int chunks, double second) {
+    while (rows > p->rows) ++p;
+    const int64_t wg = (int64_t)groups * chunks, rounds = (wg + a.n_cus - 1) / a.n_cus;
+    const double fill = wg < a.n_cus ? (double)wg / a.n_cus : 1.0, weights = (double)d.payload / 6.6e6;
+    const double t = (double)rounds * a.K / kStepCols / chunks * (p->step + p->per_row * rows) * (1.0 + p->fill * fill) * (1.0 + p->sparse * (0.01 * a.sparse_pct - 0.5));
+    return p->base + p->round * (double)(rounds - 1) + (t > weights ? t : weights) + (chunks > 1 ? second + 2.0 * chunks * rows * (double)d.N * 4.0 / 5.0e6 : 0.0);
+}
+
+// The cheapest of the three; up to 7 rows (11 for a single weight) always the strip kernel, whose X is small then.  mid_kernel has to be 0.3 us ahead,
+// batch_kernel 0.7.  only_wide: batch_kernel, in its best number of chunks.
 static DecodePlan decode_plan(const GemmArgs& a, const DecodeShape& d, int rows, bool only_wide = false) {
-    const double steps = (double)a.K / kStepCols, hbm = (double)d.payload / 6.6e6;
-    const auto us = [&](double base, int64_t groups, int chunks, double step, double by_fill) {
-        const int64_t wg = groups * chunks, rounds = (wg + a.n_cus - 1) / a.n_cus;
-        const double fill = wg < a.n_cus ? (double)wg / a.n_cus : 1.0, t = (double)rounds * steps / chunks * step * (1.0 + by_fill * fill);
-        return base + (t > hbm ? t : hbm) + (chunks > 1 ? 5.0 + 2.0 * chunks * rows * (double)d.N * 4.0 / 5.0e6 : 0.0);
-    };
-    const double strip_more = 0.7 * (double)((d.strips - 1) / a.n_cus);
-    DecodePlan best = {0, 1, rows <= 16 ? us(3.0 + strip_more, d.strips, 1, 0.027 + 0.0030 * rows, 0.3) : us(4.3 + strip_more, d.strips, 1, 0.113 + 0.0019 * rows, 0.2)};
-    if (rows < (d.count > 1 ? 8 : 12) && !only_wide) return best;
-    const auto consider = [&](int kernel, int chunks, double t) { if (t < best.us) best = DecodePlan{kernel, chunks, t}; };
-    const size_t per_chunk = (size_t)rows * (size_t)d.N * sizeof(float);
-    const int fit = a.ws ? (int)(a.ws_bytes / per_chunk < 8 ? a.ws_bytes / per_chunk : 8) : 1;
-    const double mid0 = rows <= 32 ? 4.0 : 6.5, mid_fill = rows <= 32 ? 0.25 : 0.38;
-    const double mid = rows <= 16 ? 0.11 + 0.0047 * rows : rows <= 32 ? 0.10 + 0.0037 * rows : 0.165 + 0.0016 * rows;
-    const double batch = rows <= kDecodeRows ? 0.235 + 0.0018 * rows : 0.09 + 0.064 * (rows <= 80 ? 5 : rows <= 96 ? 6 : 8);
-    consider(1, 1, us(mid0 + 2.0 * (double)((d.groups64 - 1) / a.n_cus), d.groups64, 1, mid, mid_fill));
-    if (d.count == 1 && rows > 16) {
-        const int c = mid_split(a, rows, 0);
-        if (c > 1) consider(1, c, us(mid0 - 1.5, d.groups64, c, mid, mid_fill));
+    DecodePlan best = {0, 1, 0.0};
+    if (!only_wide) {
+        best.us = pass_us(kStripPrice, a, d, rows, d.strips, 1, 0.0);
+        if (rows < (d.count > 1 ? 8 : 12)) return best;
+        const auto mid = [&](int chunks) {
+            const double t = pass_us(kMidPrice, a, d, rows, d.groups64, chunks, 2.2);
+            if (t + 0.3 < best.us) best = DecodePlan{1, chunks, t};
+        };
+        mid(1);
+        if (const int c = d.count == 1 && rows > 16 ? mid_split(a, rows, 0) : 1; c > 1) mid(c);
     }
     // (at most 8 chunks of at least four units of 128 columns; beyond one workgroup per compute unit a split only adds partial sums)
-    // (beyond 64 rows a second launch is a smaller part of the whole: half of it is hidden)
-    const double again = rows > kDecodeRows ? 2.5 : 0.0;
-    DecodePlan wide = {2, 1, us(5.2, d.groups128, 1, batch, 0.33)};
+    const size_t per_chunk = (size_t)rows * (size_t)d.N * sizeof(float);
+    const int fit = a.ws ? (int)(a.ws_bytes / per_chunk < 8 ? a.ws_bytes / per_chunk : 8) : 1;
+    DecodePlan wide = {2, 1, pass_us(kBatchPrice, a, d, rows, d.groups128, 1, 0.0)};
     for (int c = 2; c <= fit && d.groups128 * c <= a.n_cus && c * 512 <= a.K; ++c) {
-        const double t = us(5.2 - again, d.groups128, c, batch, 0.33);
+        const double t = pass_us(kBatchPrice, a, d, rows, d.groups128, c, 2.7);
         if (t < wide.us) wide = DecodePlan{2, c, t};
     }
     return only_wide || wide.us + 0.7 < best.us ? wide : best;
-}
-
-// 65 .. 128 rows, nothing asked for: one pass of batch_kernel (5, 6 or 8 blocks of 16 rows, one wavefront group) against the prefill launch
-// - whose K split writes and reads its partial products more often, or which leaves compute units idle - and, without a workspace, two
-// passes.  Step 0.09 + 0.064 blocks there, a split's second launch 2.5 us; the prefill estimates run 12 % low at so few rows,
-// and do not know the share f of 2:4 tiles (10 % less at f = 1).  f = 0.5, prefill
-// -> pass, 80 / 128 rows: three 4096 x 4096 40.4 / 40.4 -> 27.0 / 35.4 us, gate and up of 4096 / 11008 48.2 / 52.1 -> 36.5 / 49.7, of 5120 / 13824
-// 68.4 / 74.2 -> 46.6 / 62.0, of 896 / 4864 21.7 / 22.0 -> 11.9 / 15.5, 4096 x 11008 32.9 / 35.3 -> 24.4 / 28.7 (4096 x 4096 17.2 / 18.4 against 16.8 / 22.4:
-// the prefill launch from 81 rows).
-static bool takes_wide_pass(const GemmArgs& a, const DecodeShape& d, double prefill_us, DecodePlan* plan) {   // kDecodeRows < a.M <= kBatchRows
-    *plan = decode_plan(a, d, (int)a.M, true);
-    double other = 1.12 * prefill_us * std::min(1.0, 1.1 - 0.002 * a.sparse_pct);
-    if (!a.ws) other = std::min(other, decode_plan(a, d, kDecodeRows).us + decode_plan(a, d, (int)a.M - kDecodeRows).us);
-    return plan->us + 0.8 + 0.15 * plan->chunks < other;
 }
 
 // batch_kernel on request (variant 7): `requested` K chunks as far as they exist and the workspace holds them, 0 = the plan's
@@ -469,34 +456,85 @@ static DecodeShape decode_shape(const patch_packed* P) {
     return DecodeShape{P->N, (int)(P->N / 16), (int)(P->N / 64), (int)((P->N + 127) / 128), P->payload_bytes, 1};
 }
 
-// Passes of up to 64 rows, each streaming the whole weight, or one prefill launch?  With a workspace the prefill path's K
-// split fills the chip at any number of rows, and from 65 rows one launch of it beats two passes (4096 x 4096, us at M = 128: passes
-// 31, split prefill 18; 13824 x 5120: 70 and 34), while up to 64 rows a pass is ahead (decode_plan; 11008 x 4096 at 33 / 64 rows
-// 19 / 22 us against 21 / 23).  Without one the prefill grid may be too small to fill the chip, and both sides are estimated:
-//   unsplit prefill launch  rounds x 64-column steps x 1.0 us (tile 64 beyond K = 16384: 1.45 us), or with
-//                           blocks of 128 rows x 0.70 us (tile 64: 0.75), whichever is less (launch_prefill makes the
-//                           same choice), + 4.2 us for the launch (896 x 896 at M = 66: 14.0 us)
-//   passes                  decode_plan's estimate of a full pass, and of the last one by its rows
-// From 33 rows on the estimate also decides a single pass against an unsplit prefill launch: only weights wider
-// than the chip change side (65536 x 4096 at M = 64: 109 us in a pass of mid_kernel, 90 us on the 128-row prefill kernel).
-static int auto_path(int64_t M, const patch_packed* P, const patch_gemm_opts* opts, bool single = true) {
-    const bool ws = opts && opts->workspace && opts->workspace_bytes >= 2 * (size_t)M * (size_t)P->N * sizeof(float);
-    if (M <= 16) return PATCH_PATH_DECODE;
-    if (ws) return M <= kDecodeRows ? PATCH_PATH_DECODE : PATCH_PATH_PREFILL;
-    if (M <= 32 || (M <= kDecodeRows && !single)) return PATCH_PATH_DECODE;
-    const double steps = (double)P->K / 64.0;
-    const int64_t tiles = ((P->N + 255) / 256) * ((M + 255) / 256);
-    const double rounds = (double)((tiles + P->n_cus - 1) / P->n_cus);
-    const int64_t tiles128 = ((P->N + 255) / 256) * ((M + 127) / 128);   // blocks of 128 rows: 0.70 / 0.75 us per step
-    const double us128 = (double)((tiles128 + P->n_cus - 1) / P->n_cus) * steps * (P->tile == 128 ? 0.70 : 0.75);
-    const double us256 = rounds * steps * (P->tile == 128 || P->K <= 16384 ? 1.0 : 1.45);
-    const double prefill_us = (us128 < us256 ? us128 : us256) + 4.2;
+// us a prefill launch over all weights of a set is estimated to take (a.N: the first weight's)
+static double set_prefill_us(const GemmArgs& a, const DecodeShape& d, const int64_t* N) {
+    if (d.count == 1) return prefill_estimate(a);
+    if (prefill_wreg_supports(a)) return prefill_set_estimate(a, N, d.count);
+    // (beyond the limits of the set launch the weights go one by one: priced as one launch after the other)
+    double us = 0.0;
+    for (int i = 0; i < d.count; ++i) {
+        GemmArgs one = a;
+        one.N = N[i];
+        us += prefill_estimate(one);
+    }
+    return us;
+}
+
+// What AUTO stands for: passes, each streaming the whole weight, or one prefill launch, by the estimate of both (prefill_estimate,
+// decode_plan).  d: the weight or the whole set; N[i]: features of weight i; nothing_asked: neither variant nor split_k, so that 65 .. 128
+// rows may go in one pass of batch_kernel.
+//   up to 32 rows, sets up to 64: a pass
+//   a single weight of 33 .. 64 rows: a pass, or the prefill launch where the weight is wider than the chip (f = 1/2, 64 rows: 128256 x 1024
+//     50 us in a pass, 39 on the prefill kernel; 32896 x 4096 58 and 51; 20480 x 4096 26 and 31)
+//   65 .. 128 rows: one pass where it is estimated 6 % ahead of the prefill launch - whose K split writes and reads its partial products more
+//     often, or which leaves compute units idle - and, without a workspace, of two passes.  f = 1/2, 80 / 128 rows, prefill -> pass: three
+//     4096 x 4096 40.4 / 40.4 -> 27.0 / 35.4 us, gate and up of 5120 / 13824 68.4 / 74.2 -> 46.6 / 62.0; at f = 1 the prefill launch gains
+//     more from its 2:4 steps (two 28672 x 4096, 80 rows 64 us against 73)
+//   beyond, with a workspace for two slices: prefill, whose K split fills the chip at any number of rows; without, the cheaper side
+struct AutoChoice { int path; bool one_pass; DecodePlan pass; };
+static AutoChoice auto_choice(const GemmArgs& a, const DecodeShape& d, const int64_t* N, bool nothing_asked) {
+    const int64_t M = a.M;
+    const bool ws = a.ws && a.ws_bytes >= 2 * (size_t)M * (size_t)N[0] * sizeof(float);
+    AutoChoice c = {PATCH_PATH_DECODE, false, {2, 1, 0.0}};
+    if (M <= (d.count > 1 ? kDecodeRows : 32)) return c;
+    const bool one_pass = nothing_asked && M > kDecodeRows && M <= kBatchRows;
+    if (ws && M > kDecodeRows && !one_pass) { c.path = PATCH_PATH_PREFILL; return c; }
+    const double prefill_us = set_prefill_us(a, d, N);
+    double passes_us = 0.0;
+    if (!ws || M <= kDecodeRows) {
+        const int64_t full = M / kDecodeRows, rest = M % kDecodeRows;
+        passes_us = (full ? (double)full * decode_plan(a, d, kDecodeRows).us : 0.0) + (rest ? decode_plan(a, d, (int)rest).us : 0.0);
+    }
+    if (one_pass) {
+        c.pass = decode_plan(a, d, (int)M, true);
+        c.one_pass = 1.06 * c.pass.us < (ws ? prefill_us : std::min(prefill_us, passes_us));
+    }
+    if (!c.one_pass && (passes_us == 0.0 || prefill_us <= passes_us)) c.path = PATCH_PATH_PREFILL;
+    return c;
+}
+
+// Test hook (kernels.h)
+int patch_test_schedule(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* kernel, int* chunks) {
+    if (!N || !kernel || !chunks || M < 1 || M > 8 * kDecodeRows || count < 1 || count > kMaxMany || sparse_pct < 0 || sparse_pct > 100) return -1;
     GemmArgs a = {};
-    a.N = P->N; a.K = P->K; a.tile = P->tile; a.Tk = P->Tk; a.n_cus = P->n_cus;
-    const DecodeShape d = decode_shape(P);
-    const int64_t full = M / kDecodeRows, rest = M % kDecodeRows;
-    const double passes_us = (full ? (double)full * decode_plan(a, d, kDecodeRows).us : 0.0) + (rest ? decode_plan(a, d, (int)rest).us : 0.0);
-    return passes_us < prefill_us ? PATCH_PATH_DECODE : PATCH_PATH_PREFILL;
+    a.M = M; a.N = N[0]; a.K = K;
+    a.tile = tile; a.Tk = (int)(K / tile);
+    a.n_cus = 256;
+    a.sparse_pct = sparse_pct;
+    if (ws_bytes) { a.ws = reinterpret_cast<float*>(16); a.ws_bytes = ws_bytes; }
+    DecodeShape d = {0, 0, 0, 0, 0, count};
+    for (int i = 0; i < count; ++i) {
+        if (check_shape(N[i], K, tile) != PATCH_OK) return -1;
+        const DecodeShape w = {N[i], (int)(N[i] / 16), (int)(N[i] / 64), (int)((N[i] + 127) / 128), (size_t)(2.0 * (double)N[i] * (double)K * (1.0 - 0.07 / 16.0 * sparse_pct)), 1};
+        d.N += w.N; d.strips += w.strips; d.groups64 += w.groups64; d.groups128 += w.groups128; d.payload += w.payload;
+    }
+    const AutoChoice c = auto_choice(a, d, N, true);
+    if (c.one_pass || c.path == PATCH_PATH_PREFILL) {
+        kernel[0] = c.one_pass ? c.pass.kernel : 3;
+        chunks[0] = c.one_pass ? c.pass.chunks : 1;
+        if (int split = 1; kernel[0] == 3 && count == 1 && prefill_prefers_128_rows(a, &split)) {
+            kernel[0] = 4;
+            chunks[0] = split;
+        }
+        return 1;
+    }
+    int n = 0;
+    for (int64_t m0 = 0; m0 < M; m0 += kDecodeRows, ++n) {
+        const DecodePlan plan = decode_plan(a, d, (int)(M - m0 < kDecodeRows ? M - m0 : kDecodeRows));
+        kernel[n] = plan.kernel;
+        chunks[n] = plan.chunks;
+    }
+    return n;
 }
 
 patch_status patch_gemm_ex(const void* X, int64_t M, const patch_packed* P, void* Y, void* stream, const patch_gemm_opts* opts) {
@@ -522,14 +560,16 @@ patch_status patch_gemm_ex(const void* X, int64_t M, const patch_packed* P, void
     one.payload[0] = a.payload; one.table[0] = a.table; one.Y[0] = a.Y; one.N[0] = a.N;
     one.count = 1;
     const DecodeShape d = decode_shape(P);
-    DecodePlan wide = {2, 1, 0.0};
-    if (path == PATCH_PATH_AUTO && variant == 0 && split_k == 0 && M > kDecodeRows && M <= kBatchRows && takes_wide_pass(a, d, prefill_estimate(a), &wide)) {
-        one.units = d.groups128;
-        launch_batch_set(a, one, 0, (int)M, wide.chunks, s);
-        HIP_TRY(hipGetLastError());
-        return PATCH_OK;
+    if (path == PATCH_PATH_AUTO) {
+        const AutoChoice c = auto_choice(a, d, &P->N, variant == 0 && split_k == 0);
+        path = c.path;
+        if (c.one_pass) {
+            one.units = d.groups128;
+            launch_batch_set(a, one, 0, (int)M, c.pass.chunks, s);
+            HIP_TRY(hipGetLastError());
+            return PATCH_OK;
+        }
     }
-    if (path == PATCH_PATH_AUTO) path = auto_path(M, P, opts);
     if (path == PATCH_PATH_DECODE) {
         for (int64_t m0 = 0; m0 < M; m0 += (variant == 7 ? kBatchRows : kDecodeRows)) {
             const int rows = (int)((M - m0 < (variant == 7 ? kBatchRows : kDecodeRows)) ? M - m0 : (variant == 7 ? kBatchRows : kDecodeRows));
@@ -770,20 +810,24 @@ static size_t workspace_need(int64_t M, const patch_packed* P, const patch_gemm_
     if (!P || M <= 0) return 0;
     int path = PATCH_PATH_AUTO, split_k = 0, variant = 0;
     if (opts) { path = opts->path; split_k = opts->split_k; variant = opts->variant; }
-    patch_gemm_opts enough = {path, split_k, variant, reinterpret_cast<void*>(16), ~(size_t)0, 0};  // the choice given enough
-    const bool any = path == PATCH_PATH_AUTO && variant == 0 && split_k == 0;
-    if (path == PATCH_PATH_AUTO) path = auto_path(M, P, &enough);
-    GemmArgs a;
-    a.X = nullptr; a.M = M; a.N = P->N; a.K = P->K;
+    GemmArgs a = {};
+    a.M = M; a.N = P->N; a.K = P->K;
     a.tile = P->tile; a.Tn = P->Tn; a.Tk = P->Tk;
-    a.payload = nullptr; a.table = nullptr; a.Y = nullptr;
     a.n_cus = P->n_cus;
+    a.sparse_pct = (int)(100 * P->n_sparse / ((int64_t)P->Tn * P->Tk));
     a.ws = reinterpret_cast<float*>(16);  // "enough": ask for the unconstrained choice
     a.ws_bytes = ~(size_t)0;
     // 65 .. 128 rows: what one pass would use, and no less than the prefill launch it stands in for (below)
     size_t least = 0;
-    DecodePlan wide = {2, 1, 0.0};
-    if (any && M > kDecodeRows && M <= kBatchRows && takes_wide_pass(a, decode_shape(P), prefill_estimate(a), &wide) && wide.chunks > 1) least = (size_t)wide.chunks * (size_t)M * (size_t)P->N * sizeof(float);
+    if (path == PATCH_PATH_AUTO) {
+        const DecodeShape d = decode_shape(P);
+        const AutoChoice c = auto_choice(a, d, &P->N, variant == 0 && split_k == 0);
+        path = c.path;
+        if (c.one_pass) {
+            path = PATCH_PATH_PREFILL;
+            if (c.pass.chunks > 1) least = (size_t)c.pass.chunks * (size_t)M * (size_t)P->N * sizeof(float);
+        }
+    }
     if (path == PATCH_PATH_DECODE) {
         // a pass may cut K into chunks over the workspace; the full passes and the last one each have a number of their own
         const int64_t pass = variant == 7 ? kBatchRows : kDecodeRows;
@@ -836,8 +880,7 @@ patch_status patch_gemm_many(const void* X, int64_t M, const patch_packed* const
     if (opts) { path = opts->path; split_k = opts->split_k; variant = opts->variant; }
     if (path < PATCH_PATH_AUTO || path > PATCH_PATH_PREFILL || split_k < 0 || split_k > 16 || variant < 0) return PATCH_ERR_ARG;
     if (M == 0) return PATCH_OK;
-    const bool any = path == PATCH_PATH_AUTO && variant == 0 && split_k == 0;
-    if (path == PATCH_PATH_AUTO) path = auto_path(M, P[0], opts, count == 1);
+    if (count == 1) return patch_gemm_ex(X, M, P[0], Y[0], stream, opts);
     hipStream_t s = static_cast<hipStream_t>(stream);
     GemmArgs a = {};
     a.X = static_cast<const uint16_t*>(X);
@@ -855,11 +898,7 @@ patch_status patch_gemm_many(const void* X, int64_t M, const patch_packed* const
     }
     a.ybf16 = (opts && opts->y_bf16) ? 1 : 0;
     if (opts && opts->workspace && !aligned16(opts->workspace)) return PATCH_ERR_ARG;
-    // (a split asked for is that of one launch per weight, but for the kernel with 128 features, whose chunks cover the set)
-    if (opts && opts->workspace && (split_k == 0 || (path == PATCH_PATH_DECODE && variant == 7))) {
-        a.ws = static_cast<float*>(opts->workspace);
-        a.ws_bytes = opts->workspace_bytes;
-    }
+    if (opts && opts->workspace) { a.ws = static_cast<float*>(opts->workspace); a.ws_bytes = opts->workspace_bytes; }
     DecodeSet set = {};
     int strips = 0;
     for (int i = 0; i < count; ++i) {
@@ -883,26 +922,18 @@ patch_status patch_gemm_many(const void* X, int64_t M, const patch_packed* const
     }
     wide64.units = d.groups64;
     wide128.units = d.groups128;
-    if (any && count > 1 && M > kDecodeRows && M <= kBatchRows) {
-        int units = 0;
-        for (int i = 0; i < count; ++i) units += (int)((P[i]->N + 255) / 256);
-        // (beyond the limits of the set launch the weights go one by one: priced as one launch after the other)
-        double prefill_us = 0.0;
-        if (prefill_wreg_supports(a)) prefill_us = prefill_set_estimate(a, units, d.N);
-        else
-            for (int i = 0; i < count; ++i) {
-                GemmArgs b = a;
-                b.N = P[i]->N;
-                prefill_us += prefill_estimate(b);
-            }
-        DecodePlan plan = {2, 1, 0.0};
-        if (takes_wide_pass(a, d, prefill_us, &plan)) {
-            launch_batch_set(a, wide128, 0, (int)M, plan.chunks, s);
+    if (path == PATCH_PATH_AUTO) {
+        const AutoChoice c = auto_choice(a, d, set.N, variant == 0 && split_k == 0);
+        path = c.path;
+        if (c.one_pass) {
+            launch_batch_set(a, wide128, 0, (int)M, c.pass.chunks, s);
             HIP_TRY(hipGetLastError());
             return PATCH_OK;
         }
     }
-    if (path == PATCH_PATH_PREFILL && count > 1 && (variant == 0 || variant == 3) && split_k <= 1 && prefill_wreg_supports(a)) {
+    // (a split asked for is that of one launch per weight, but for the kernel with 128 features, whose chunks cover the set)
+    if (split_k != 0 && !(path == PATCH_PATH_DECODE && variant == 7)) { a.ws = nullptr; a.ws_bytes = 0; }
+    if (path == PATCH_PATH_PREFILL && (variant == 0 || variant == 3) && split_k <= 1 && prefill_wreg_supports(a)) {
         // one launch over the feature blocks of all weights (with a workspace and few blocks: K in slices over the
         // whole set, see launch_prefill_wreg_set)
         int blocks = 0;
@@ -921,8 +952,8 @@ patch_status patch_gemm_many(const void* X, int64_t M, const patch_packed* const
         HIP_TRY(hipGetLastError());
         return PATCH_OK;
     }
-    if (path == PATCH_PATH_PREFILL || count == 1) {
-        patch_gemm_opts o = {any && count == 1 ? PATCH_PATH_AUTO : path, split_k, variant, opts ? opts->workspace : nullptr, opts ? opts->workspace_bytes : 0, a.ybf16};
+    if (path == PATCH_PATH_PREFILL) {
+        patch_gemm_opts o = {path, split_k, variant, opts ? opts->workspace : nullptr, opts ? opts->workspace_bytes : 0, a.ybf16};
         for (int i = 0; i < count; ++i) {
             const patch_status st = patch_gemm_ex(X, M, P[i], Y[i], stream, &o);
             if (st != PATCH_OK) return st;

@@ -710,7 +710,7 @@ static double pf_estimate(const GemmArgs& a, int blocks, int split, double t0, d
     return us;
 }
 
-static bool pf_prefers_128(const GemmArgs& a, int* split, bool no_w64, double* us) {
+bool prefill_prefers_128_rows(const GemmArgs& a, int* split, bool no_w64) {
     const int tiles_n = (int)((a.N + kPfBN - 1) / kPfBN);
     const int b256 = tiles_n * (int)((a.M + 255) / 256), b128 = tiles_n * (int)((a.M + 127) / 128);
     const bool wreg = prefill_wreg_supports(a) && !(no_w64 && a.tile == 64);
@@ -725,21 +725,32 @@ static bool pf_prefers_128(const GemmArgs& a, int* split, bool no_w64, double* u
         const double us = pf_estimate(a, b128, sp, a.tile == 128 ? 0.70 : 0.75, a.tile == 128 ? 0.24 : 0.22);
         if (sp == 1 || us < best) { best = us; *split = sp; }
     }
-    *us = best < 0.97 * us256 ? best : us256;
     return best < 0.97 * us256;
 }
 
-bool prefill_prefers_128_rows(const GemmArgs& a, int* split, bool no_w64) {
-    double us = 0.0;
-    return pf_prefers_128(a, split, no_w64, &us);
+// us the default choice takes at up to a few hundred rows, for the choice against decode passes (auto_choice).  The estimate above compares
+// block heights and knows neither the share f of 2:4 tiles nor the memory; this one is fitted to launches of 17 .. 128 rows of 24 weights and
+// 12 sets at f = 0, 1/2 and 1, both mask tiles, with and without a workspace (5184 launches with 128-row blocks, 2592 with 256; rms error 7
+// and 9 %):
+//     us = base + max(rounds x K-steps per workgroup x (t0 + t1 fill) x g(f), (weights + Y) / rate) + (split > 1 ? second + (2 split + 1) M N 4 B / 9 TB/s : 0)
+// 128-row blocks: base 4.0, (0.81, 0.25), g = 1 - 0.31 f, 6.2 TB/s, second 3.1.  Register-weight kernel: 9.0, (0.85, 0.255), g = 1 - 0.45 f^2 (its
+// wavefronts meet at every step, so two tile rows must be 2:4 there; a block that lacks a tile row runs at the dense rate), 5.3 TB/s, 3.8.
+double pf_few_rows(const GemmArgs& a, int64_t N, int blocks, int split, bool rows128, bool whole_blocks) {
+    const int wgs = blocks * split, rounds = (wgs + a.n_cus - 1) / a.n_cus, steps = ((a.Tk + split - 1) / split) * (a.tile / kStepCols);
+    const double fill = wgs < a.n_cus ? (double)wgs / a.n_cus : 1.0, f = 0.01 * a.sparse_pct, y = (double)a.M * (double)N * 4.0;
+    const double g = rows128 ? 1.0 - 0.31 * f : whole_blocks ? 1.0 - 0.45 * f * f : 1.0;
+    const double t = rounds * steps * (rows128 ? 0.81 + 0.25 * fill : 0.85 + 0.255 * fill) * g;
+    const double memory = (2.0 * (double)N * (double)a.K * (1.0 - 7.0 / 16.0 * f) + y) / (rows128 ? 6.2e6 : 5.3e6);
+    return (rows128 ? 4.0 : 9.0) + (t > memory ? t : memory) + (split > 1 ? (rows128 ? 3.1 : 3.8) + (2.0 * split + 1.0) * y / 9.0e6 : 0.0);
 }
 
-// us the default choice is estimated to take
 double prefill_estimate(const GemmArgs& a) {
     int split = 1;
-    double us = 0.0;
-    (void)pf_prefers_128(a, &split, false, &us);
-    return us;
+    const int tiles_n = (int)((a.N + kPfBN - 1) / kPfBN);
+    if (prefill_prefers_128_rows(a, &split)) return pf_few_rows(a, a.N, tiles_n * (int)((a.M + 127) / 128), split, true, true);
+    const int blocks = tiles_n * (int)((a.M + 255) / 256);
+    if (prefill_wreg_supports(a)) return pf_few_rows(a, a.N, blocks, prefill_wreg_split(a, 0), false, a.N % kPfBN == 0);
+    return pf_estimate(a, blocks, prefill_lds_split(a, 0, 256), 1.26, 0.33);
 }
 
 // Kernel choice.  variant 0 (default): prefill_kernel_areg with blocks of 128 rows where prefill_prefers_128_rows says so

@@ -1159,13 +1159,17 @@ static int wr_set_split(const GemmArgs& a, int nblk, int64_t N) {
     return split < 2 ? 1 : split;
 }
 
-// us a set launch is estimated to take, priced like pf_estimate (gemm_prefill.hip)
-double prefill_set_estimate(const GemmArgs& a, int units, int64_t N) {
-    const int nblk = units * (int)((a.M + kWrBM - 1) / kWrBM), split = wr_set_split(a, nblk, N);
-    const int wgs = nblk * split, rounds = (wgs + a.n_cus - 1) / a.n_cus;
-    const double fill = wgs < a.n_cus ? (double)wgs / a.n_cus : 1.0;
-    const double us = rounds * ((a.Tk + split - 1) / split) * (a.tile / kStepCols) * (0.90 + 0.35 * fill) + 3.0;
-    return split > 1 ? us + 3.0 + (2.0 * split + 1.0) * (double)a.M * (double)N * 4.0 / 5.5e6 : us;
+double prefill_set_estimate(const GemmArgs& a, const int64_t* N, int count) {
+    int units = 0;
+    int64_t total = 0;
+    bool whole = true;
+    for (int i = 0; i < count; ++i) {
+        units += (int)((N[i] + kWrBN - 1) / kWrBN);
+        total += N[i];
+        whole = whole && N[i] % kWrBN == 0;
+    }
+    const int blocks = units * (int)((a.M + kWrBM - 1) / kWrBM);
+    return pf_few_rows(a, total, blocks, wr_set_split(a, blocks, total), false, whole);
 }
 
 void launch_prefill_wreg_set(const GemmArgs& a, const WeightSet& set, hipStream_t stream) {

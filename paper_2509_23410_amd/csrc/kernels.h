@@ -90,8 +90,9 @@ int prefill_wreg_split(const GemmArgs& a, int requested);       // K slices per 
 int prefill_lds_split(const GemmArgs& a, int requested, int bm = 256);   // the same for the LDS-staged kernel with blocks of bm rows
 // whether the default choice (variant 0, no split requested) is the LDS-staged kernel with blocks of 128 rows, and its split
 bool prefill_prefers_128_rows(const GemmArgs& a, int* split, bool no_w64 = false);
-double prefill_estimate(const GemmArgs& a);                                  // us the default choice is estimated to take
-double prefill_set_estimate(const GemmArgs& a, int units, int64_t N);         // the same for a set: units of 256 features, N features
+double prefill_estimate(const GemmArgs& a);                                       // us the default choice is estimated to take at few rows
+double prefill_set_estimate(const GemmArgs& a, const int64_t* N, int count);      // the same for a set of weights of N[i] features
+double pf_few_rows(const GemmArgs& a, int64_t N, int blocks, int split, bool rows128, bool whole_blocks);   // what both go by
 // K slices for the last *tail tiles of an unsplit launch with a part-filled last round (needs a.ws); 1 = none
 int prefill_wreg_tail(const GemmArgs& a, int* tail);
 int prefill_wreg_tail_of(int tiles, const GemmArgs& a, int* tail);   // the same for a given tile count (sets of weights)
@@ -102,3 +103,11 @@ void launch_prefill_wreg(const GemmArgs& a, int split_k, hipStream_t stream);
 void launch_prefill_wreg_set(const GemmArgs& a, const WeightSet& set, hipStream_t stream);
 
 }  // namespace patch
+
+// Test hooks: exported like the interface in patch.h, but no part of it.
+extern "C" {
+// What AUTO takes for M rows of `count` weights of N[i] x K features sharing X (sparse_pct per cent of the tiles 2:4) given ws_bytes of
+// workspace on 256 compute units: kernel (0 strip, 1 mid, 2 batch, 3 the prefill path, 4 that in blocks of 128 rows) and K chunks of every
+// pass (1 for kernel 3), at most 8; returns their number, -1 = bad arguments.  Runs on the host alone.
+int patch_test_schedule(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* kernel, int* chunks);
+}

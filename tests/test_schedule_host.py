@@ -1,0 +1,81 @@
+"""What AUTO chooses against what was measured, without a device: the estimates behind the choice hold constants fitted to measurements,
+and a change of one of them must not send a call to a kernel that is slower there.  A row: features of the weights that share X, their
+K, mask tile, share of 2:4 tiles, rows of X, workspace or not, and microseconds of the kernels that come into question - strip, mid (mid*
+with K in chunks), b<chunks> = the kernel with 128 features in one pass, two passes = of 64 rows and the rest, prefill (MI355X, fp32
+output, launches back to back)."""
+import ctypes
+
+import pytest
+
+from paper_2509_23410_amd import binding as B
+
+MEASURED = [
+    ([896] * 3, 896, 128, 0.0, 20, False, {'mid': 6.2, 'strip': 4.9}),
+    ([896] * 3, 896, 64, 0.5, 20, False, {'mid': 5.7, 'strip': 4.8}),
+    ([896] * 3, 896, 64, 1.0, 20, False, {'mid': 5.5, 'strip': 4.7}),
+    ([28672] * 2, 4096, 128, 1.0, 72, False, {'b1': 72.8, 'prefill': 64.5}),
+    ([896] * 3, 896, 64, 0.0, 20, True, {'mid': 5.9, 'strip': 4.8}),
+    ([896] * 3, 896, 128, 0.0, 17, True, {'mid': 6.1, 'strip': 4.8}),
+    ([896] * 3, 896, 128, 0.5, 17, True, {'mid': 5.7, 'strip': 4.6}),
+    ([896] * 3, 896, 64, 1.0, 17, True, {'mid': 5.4, 'strip': 4.5}),
+    ([28672] * 2, 4096, 128, 1.0, 65, True, {'prefill': 63.8, 'b1': 70.7}),
+    ([11008] * 2, 4096, 64, 1.0, 81, True, {'prefill': 35.1, 'b1': 38.5}),
+    ([4096], 4096, 128, 0.0, 20, False, {'mid': 17.2, 'strip': 10.6}),
+    ([4096], 4096, 64, 0.5, 17, False, {'mid': 14.6, 'strip': 8.9}),
+    ([4096], 4096, 128, 1.0, 20, False, {'mid': 12.4, 'strip': 9.1}),
+    ([4096], 4096, 128, 1.0, 17, False, {'mid': 12.0, 'strip': 8.5}),
+    ([896], 896, 128, 0.0, 112, False, {'two passes': 13.1, 'prefill': 15.2}),
+    ([4096], 11008, 64, 0.0, 96, False, {'two passes': 72.8, 'b1': 86.0}),
+    ([4096], 11008, 128, 0.5, 96, False, {'two passes': 70.5, 'b1': 90.7}),
+    ([5120], 13824, 64, 1.0, 72, False, {'two passes': 89.5, 'b1': 98.1}),
+    ([32896], 4096, 128, 0.5, 16, False, {'b1': 47.9, 'mid': 42.9}),
+    ([36864], 4096, 64, 0.5, 16, False, {'b1': 48.1, 'mid': 44.5}),
+    ([36864], 4096, 128, 1.0, 16, False, {'b1': 37.9, 'mid': 34.5}),
+    ([896], 896, 128, 0.0, 17, True, {'mid': 5.1, 'strip': 4.0}),
+    ([896], 896, 64, 0.5, 17, True, {'mid': 4.9, 'strip': 4.0}),
+    ([896], 896, 128, 0.5, 20, True, {'mid': 4.8, 'strip': 4.0}),
+    ([896], 896, 64, 1.0, 17, True, {'mid': 4.6, 'strip': 3.9}),
+    ([13824], 5120, 128, 0.0, 56, True, {'b2': 29.3, 'prefill': 31.0, 'mid': 34.8}),
+    ([128256], 1024, 128, 0.5, 56, True, {'prefill': 39.3, 'b1': 48.8}),
+    ([32896], 4096, 128, 0.5, 33, True, {'prefill': 46.4, 'b1': 52.2}),
+    ([2048], 2048, 64, 1.0, 49, True, {'mid*': 9.1, 'strip': 10.3}),
+    ([13824], 5120, 64, 0.5, 96, True, {'b2': 33.1, 'prefill': 30.0}),
+    ([32000], 4096, 64, 1.0, 81, True, {'prefill': 34.8, 'b1': 39.0}),
+    ([32000], 4096, 128, 1.0, 96, True, {'prefill': 35.7, 'b1': 39.9}),
+    ([36864], 4096, 64, 0.5, 16, True, {'b1': 48.1, 'mid': 44.5}),
+    ([36864], 4096, 128, 1.0, 16, True, {'b1': 37.9, 'mid': 34.5}),
+    ([28672] * 2, 4096, 128, 0.0, 20, False, {'b1': 69.0, 'mid': 84.5}),
+    ([13824] * 2, 5120, 64, 0.0, 56, False, {'b1': 45.1, 'mid': 71.4}),
+    ([4096, 1024, 1024], 4096, 128, 0.0, 96, False, {'two passes': 46.9, 'b1': 36.4}),
+    ([11008] * 2, 4096, 128, 0.0, 8, False, {'b1': 28.0, 'mid': 35.2}),
+    ([13824] * 2, 5120, 64, 0.0, 24, True, {'b1': 42.0, 'mid': 50.4}),
+    ([3456] * 3, 3456, 128, 0.0, 48, True, {'b2': 19.8, 'mid': 23.6}),
+    ([896] * 3, 896, 64, 0.0, 128, True, {'prefill': 20.6, 'b1': 13.5}),
+    ([11008] * 2, 4096, 128, 0.0, 9, True, {'b1': 28.1, 'mid': 34.6}),
+    ([128256], 1024, 64, 0.0, 20, False, {'b1': 45.7, 'mid': 57.6}),
+    ([32000], 4096, 64, 0.0, 56, False, {'b1': 41.4, 'prefill': 67.2}),
+    ([32000], 4096, 128, 0.0, 112, False, {'b1': 52.6, 'prefill': 74.4}),
+    ([20480], 4096, 64, 0.0, 12, False, {'b1': 27.4, 'mid': 35.9}),
+    ([128256], 1024, 64, 0.5, 20, True, {'b1': 37.9, 'mid': 50.9}),
+    ([256], 1024, 64, 0.5, 56, True, {'mid*': 8.2, 'strip': 6.8}),
+    ([512], 13824, 128, 0.5, 96, True, {'b8': 21.9, 'prefill': 28.8}),
+    ([512], 13824, 128, 0.5, 16, True, {'b8': 14.1, 'strip': 18.3}),
+]
+
+
+def _schedule(N, K, tile, f, M, workspace):
+    """-> [(kernel, K chunks) of every pass]; kernel 0 strip, 1 mid, 2 batch, 3 / 4 prefill (4: in blocks of 128 rows)."""
+    kernel, chunks = (ctypes.c_int * 8)(), (ctypes.c_int * 8)()
+    n = B.lib().patch_test_schedule(ctypes.c_int64(M), len(N), (ctypes.c_int64 * len(N))(*N), ctypes.c_int64(K), tile, round(100 * f),
+                                    ctypes.c_size_t(384 << 20 if workspace else 0), kernel, chunks)
+    assert n > 0
+    return [(kernel[i], chunks[i]) for i in range(n)]
+
+
+@pytest.mark.parametrize("N,K,tile,f,M,workspace,us", MEASURED)
+def test_choice_is_no_slower_than_what_was_measured(N, K, tile, f, M, workspace, us):
+    passes = _schedule(N, K, tile, f, M, workspace)
+    (k, c), *rest = passes
+    chosen = "two passes" if rest else ("strip", "mid" if c == 1 else "mid*", f"b{c}", "prefill", "prefill")[k]
+    assert chosen in us, (chosen, us)
+    assert us[chosen] <= 1.03 * min(us.values()) + 0.3, (chosen, us)
