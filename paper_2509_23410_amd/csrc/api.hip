@@ -505,7 +505,7 @@ static AutoChoice auto_choice(const GemmArgs& a, const DecodeShape& d, const int
 
 // Test hook (kernels.h)
 int patch_test_schedule(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* kernel, int* chunks) {
-    if (!N || !kernel || !chunks || M < 1 || M > 8 * kDecodeRows || count < 1 || count > kMaxMany || sparse_pct < 0 || sparse_pct > 100) return -1;
+    if (!N || !kernel || !chunks || M < 1 || count < 1 || count > kMaxMany || sparse_pct < 0 || sparse_pct > 100) return -1;
     GemmArgs a = {};
     a.M = M; a.N = N[0]; a.K = K;
     a.tile = tile; a.Tk = (int)(K / tile);
@@ -528,6 +528,7 @@ int patch_test_schedule(int64_t M, int count, const int64_t* N, int64_t K, int t
         }
         return 1;
     }
+    if (M > 8 * kDecodeRows) return -1;
     int n = 0;
     for (int64_t m0 = 0; m0 < M; m0 += kDecodeRows, ++n) {
         const DecodePlan plan = decode_plan(a, d, (int)(M - m0 < kDecodeRows ? M - m0 : kDecodeRows));

@@ -697,7 +697,9 @@ int prefill_lds_split(const GemmArgs& a, int requested, int bm) {
 // A step is slower the fuller the chip (shared L2 bandwidth, power): t_step = t0 + t1 x min(1, workgroups / compute
 // units), with (t0, t1) = (0.90, 0.35) us for prefill_kernel_wreg and prefill_kernel_w64, (1.26, 0.33) for the 256-row
 // kernels beyond their limits, and for prefill_kernel_areg with 128 rows (0.70, 0.24) on mask tile 128, (0.75, 0.22) on mask tile 64 (fitted
-// to unsplit launches of 16 and of 256 workgroups at f = 0.6).  The 256-row side takes the
+// to unsplit launches of 16 and of 256 workgroups at f = 0.6).  prefill_kernel_w64 in slices: (0.90, 0.30) and 5 us more - its start-up
+// (entry lists, three X stages, weights two steps ahead) is paid per slice (5120 x 5120, 6 slices, 160 rows 27.7 us, 128-row blocks
+// 23.2; fitted to 16 weights at 129 - 2048 rows).  The 256-row side takes the
 // split its launcher would take; the 128-row side its best split of at most 8 slices of at least 512 columns that the
 // workspace holds.  Returns true, and the split, when 128 rows are estimated at least 3 % faster.  no_w64: mask tile 64 as if its
 // 256-row kernel were prefill_kernel_areg (what patch_gemm_static goes by).
@@ -714,8 +716,9 @@ bool prefill_prefers_128_rows(const GemmArgs& a, int* split, bool no_w64) {
     const int tiles_n = (int)((a.N + kPfBN - 1) / kPfBN);
     const int b256 = tiles_n * (int)((a.M + 255) / 256), b128 = tiles_n * (int)((a.M + 127) / 128);
     const bool wreg = prefill_wreg_supports(a) && !(no_w64 && a.tile == 64);
-    const double us256 = pf_estimate(a, b256, wreg ? prefill_wreg_split(a, 0) : prefill_lds_split(a, 0, 256), wreg ? 0.90 : 1.26,
-                                     wreg ? 0.35 : 0.33);
+    const int split256 = wreg ? prefill_wreg_split(a, 0) : prefill_lds_split(a, 0, 256);
+    const bool slices64 = wreg && a.tile == 64 && split256 > 1;
+    const double us256 = pf_estimate(a, b256, split256, wreg ? 0.90 : 1.26, slices64 ? 0.30 : wreg ? 0.35 : 0.33) + (slices64 ? 5.0 : 0.0);
     const size_t per_slice = (size_t)a.M * (size_t)a.N * sizeof(float);
     const int fit = a.ws ? (int)(a.ws_bytes / per_slice < 8 ? a.ws_bytes / per_slice : 8) : 1;
     const int longest = a.Tk * a.tile / 512;

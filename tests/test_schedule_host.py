@@ -79,3 +79,14 @@ def test_choice_is_no_slower_than_what_was_measured(N, K, tile, f, M, workspace,
     chosen = "two passes" if rest else ("strip", "mid" if c == 1 else "mid*", f"b{c}", "prefill", "prefill")[k]
     assert chosen in us, (chosen, us)
     assert us[chosen] <= 1.03 * min(us.values()) + 0.3, (chosen, us)
+
+
+@pytest.mark.parametrize("N,K,M,us", [
+    (5120, 5120, 129, {128: 22.6, 256: 27.0}), (5120, 5120, 160, {128: 23.2, 256: 27.7}), (6912, 3456, 192, {128: 23.3, 256: 27.3}),
+    (4096, 4096, 1003, {128: 43.0, 256: 46.2}), (11008, 4096, 300, {128: 52.8, 256: 48.1}), (13824, 5120, 300, {128: 65.6, 256: 60.6}),
+    (11008, 4096, 1003, {128: 106.7, 256: 67.9}),
+])
+def test_block_height_of_mask_tile_64(N, K, M, us):
+    """A prefill launch on mask tile 64, f = 1/2, with a workspace: blocks of 128 rows or the 256-row register-weight kernel."""
+    (k, _), = _schedule([N], K, 64, 0.5, M, True)
+    assert us[{4: 128, 3: 256}[k]] == min(us.values())
