@@ -400,8 +400,8 @@ patch_status patch_deserialize(const void* buf, size_t bytes, void* stream, patc
 // 17 / 24 / 32 rows 8.8 / 10.6 / 12.1 us, 33 rows 15.2; mid_kernel 14.4 / 15.6 / 17.0).  f tells the kernels apart: at 16 rows three 4096 x 4096 take
 // mid_kernel 19.3 / 17.1 / 12.5 us at f = 0 / 1/2 / 1 and the strip kernel 23.2 / 21.4 / 19.7.
 struct PassPrice { int rows; double base, step, per_row, fill, round, sparse; };
-constexpr PassPrice kStripPrice[] = {{16, 2.5, 0.032, 0.0023, 0.24, 0.35, -0.23}, {32, 2.9, 0.045, 0.0026, 0.06, 0.0, -0.12}, {64, 3.5, 0.082, 0.0024, 0.07, 0.5, -0.03}};
-constexpr PassPrice kMidPrice[] = {{16, 2.6, 0.120, 0.0017, 0.47, 0.0, -0.45}, {32, 3.2, 0.125, 0.0020, 0.40, 2.0, -0.40}, {64, 4.3, 0.143, 0.0024, 0.28, 3.3, -0.31}};
+constexpr PassPrice kStripPrice[] = {{16, 2.5, 0.032, 0.0023, 0.24, 0.35, -0.23}, {32, 2.9, 0.045, 0.0026, 0.06, 0.4, -0.12}, {64, 3.5, 0.082, 0.0024, 0.07, 0.5, -0.03}};
+constexpr PassPrice kMidPrice[] = {{16, 2.6, 0.120, 0.0017, 0.47, 1.5, -0.45}, {32, 3.2, 0.125, 0.0020, 0.40, 2.0, -0.40}, {64, 4.3, 0.143, 0.0024, 0.28, 3.3, -0.31}};
 constexpr PassPrice kBatchPrice[] = {{16, 2.4, 0.257, 0.0005, 0.39, 0.0, -0.30}, {32, 2.7, 0.244, 0.0012, 0.40, 0.8, -0.29}, {64, 3.2, 0.237, 0.0017, 0.31, 3.2, -0.20},
                                      {80, 3.7, 0.392, 0.0005, 0.14, 4.0, 0.0},   {96, 4.1, 0.452, 0.0004, 0.10, 4.0, 0.03},  {128, 4.7, 0.570, 0.0004, 0.10, 4.0, 0.03}};
 
@@ -476,7 +476,7 @@ static double set_prefill_us(const GemmArgs& a, const DecodeShape& d, const int6
 //   up to 32 rows, sets up to 64: a pass
 //   a single weight of 33 .. 64 rows: a pass, or the prefill launch where the weight is wider than the chip (f = 1/2, 64 rows: 128256 x 1024
 //     50 us in a pass, 39 on the prefill kernel; 32896 x 4096 58 and 51; 20480 x 4096 26 and 31)
-//   65 .. 128 rows: one pass where it is estimated 6 % ahead of the prefill launch - whose K split writes and reads its partial products more
+//   65 .. 128 rows: one pass where it is estimated 2 % ahead of the prefill launch - whose K split writes and reads its partial products more
 //     often, or which leaves compute units idle - and, without a workspace, of two passes.  f = 1/2, 80 / 128 rows, prefill -> pass: three
 //     4096 x 4096 40.4 / 40.4 -> 27.0 / 35.4 us, gate and up of 5120 / 13824 68.4 / 74.2 -> 46.6 / 62.0; at f = 1 the prefill launch gains
 //     more from its 2:4 steps (two 28672 x 4096, 80 rows 64 us against 73)
@@ -497,7 +497,7 @@ static AutoChoice auto_choice(const GemmArgs& a, const DecodeShape& d, const int
     }
     if (one_pass) {
         c.pass = decode_plan(a, d, (int)M, true);
-        c.one_pass = 1.06 * c.pass.us < (ws ? prefill_us : std::min(prefill_us, passes_us));
+        c.one_pass = 1.02 * c.pass.us < (ws ? prefill_us : std::min(prefill_us, passes_us));
     }
     if (!c.one_pass && (passes_us == 0.0 || prefill_us <= passes_us)) c.path = PATCH_PATH_PREFILL;
     return c;

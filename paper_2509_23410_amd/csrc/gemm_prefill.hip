@@ -736,14 +736,16 @@ bool prefill_prefers_128_rows(const GemmArgs& a, int* split, bool no_w64) {
 // 12 sets at f = 0, 1/2 and 1, both mask tiles, with and without a workspace (5184 launches with 128-row blocks, 2592 with 256; rms error 7
 // and 9 %):
 //     us = base + max(rounds x K-steps per workgroup x (t0 + t1 fill) x g(f), (weights + Y) / rate) + (split > 1 ? second + (2 split + 1) M N 4 B / 9 TB/s : 0)
-// 128-row blocks: base 4.0, (0.81, 0.25), g = 1 - 0.31 f, 6.2 TB/s, second 3.1.  Register-weight kernel: 9.0, (0.85, 0.255), g = 1 - 0.45 f^2 (its
+// 128-row blocks: base 4.0, (0.81, 0.25), g = 1 - 0.31 f, 8 TB/s, second 3.1.  Register-weight kernel: 9.0, (0.85, 0.255), g = 1 - 0.45 f^2 (its
 // wavefronts meet at every step, so two tile rows must be 2:4 there; a block that lacks a tile row runs at the dense rate), 5.3 TB/s, 3.8.
+// Weights that the 256 MB last-level cache cannot keep: 4.5 TB/s (36864 x 4096, f = 0, 49 - 64 rows 83 us; 65536 x 4096, f = 1/2, 128 rows 97).
 double pf_few_rows(const GemmArgs& a, int64_t N, int blocks, int split, bool rows128, bool whole_blocks) {
     const int wgs = blocks * split, rounds = (wgs + a.n_cus - 1) / a.n_cus, steps = ((a.Tk + split - 1) / split) * (a.tile / kStepCols);
     const double fill = wgs < a.n_cus ? (double)wgs / a.n_cus : 1.0, f = 0.01 * a.sparse_pct, y = (double)a.M * (double)N * 4.0;
     const double g = rows128 ? 1.0 - 0.31 * f : whole_blocks ? 1.0 - 0.45 * f * f : 1.0;
     const double t = rounds * steps * (rows128 ? 0.81 + 0.25 * fill : 0.85 + 0.255 * fill) * g;
-    const double memory = (2.0 * (double)N * (double)a.K * (1.0 - 7.0 / 16.0 * f) + y) / (rows128 ? 6.2e6 : 5.3e6);
+    const double weights = 2.0 * (double)N * (double)a.K * (1.0 - 7.0 / 16.0 * f);
+    const double memory = (weights + y) / (weights > 256.0e6 ? 4.5e6 : rows128 ? 8.0e6 : 5.3e6);
     return (rows128 ? 4.0 : 9.0) + (t > memory ? t : memory) + (split > 1 ? (rows128 ? 3.1 : 3.8) + (2.0 * split + 1.0) * y / 9.0e6 : 0.0);
 }
 

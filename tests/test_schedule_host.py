@@ -60,6 +60,11 @@ MEASURED = [
     ([256], 1024, 64, 0.5, 56, True, {'mid*': 8.2, 'strip': 6.8}),
     ([512], 13824, 128, 0.5, 96, True, {'b8': 21.9, 'prefill': 28.8}),
     ([512], 13824, 128, 0.5, 16, True, {'b8': 14.1, 'strip': 18.3}),
+    # launches of many rounds over a short K, and weights beyond the last-level cache
+    ([128256], 1024, 64, 1.0, 12, False, {'b1': 24.6, 'mid': 34.7, 'strip': 38.9}),
+    ([128256], 1024, 128, 0.5, 16, True, {'b1': 35.8, 'mid': 43.4, 'strip': 43.7}),
+    ([36864], 4096, 128, 0.0, 56, True, {'b1': 66.0, 'prefill': 82.7}),
+    ([32000], 4096, 128, 0.5, 112, True, {'b1': 50.9, 'prefill': 43.3}),
 ]
 
 
