@@ -1113,7 +1113,7 @@ static Q4Plan q4_pass_plan(int strips, int groups128, int64_t N, int64_t K, int 
 }
 
 static patch_status q4_passes(const void* X, int64_t M, const patch_packed4* const* P, void* const* Y, int count, float* ws, size_t ws_bytes,
-                              hipStream_t s);
+                              hipStream_t s, const Q4Plan* asked = nullptr);
 
 patch_status patch_gemm4_many(const void* X, int64_t M, const patch_packed4* const* P, void* const* Y, int count, void* stream) {
     if (!X || !P || !Y || M < 0 || count < 1 || count > PATCH_MAX_MANY) return PATCH_ERR_ARG;
@@ -1128,9 +1128,9 @@ patch_status patch_gemm4_many(const void* X, int64_t M, const patch_packed4* con
 }
 
 // Passes of up to 64 rows over all weights, which share X (checked by the callers): the strip kernel or batch4_kernel, whichever is
-// estimated faster.  A single weight may split K over a workspace.
+// estimated faster, or the one `asked` for.  A single weight may split K over a workspace.
 static patch_status q4_passes(const void* X, int64_t M, const patch_packed4* const* P, void* const* Y, int count, float* ws, size_t ws_bytes,
-                              hipStream_t s) {
+                              hipStream_t s, const Q4Plan* asked) {
     const patch_packed4* P0 = P[0];
     const int total = P0->Tk * (P0->tile / kStepCols);
     int first[kMaxMany], total_strips = 0;
@@ -1159,7 +1159,7 @@ static patch_status q4_passes(const void* X, int64_t M, const patch_packed4* con
     auto run = [&](const auto& set) {
         for (int64_t m0 = 0; m0 < M; m0 += kQ4Rows) {
             const int rows = (int)(M - m0 < kQ4Rows ? M - m0 : kQ4Rows);
-            const Q4Plan plan = q4_pass_plan(total_strips, wide.units, P0->N, P0->K, P0->tile, rows, P0->n_cus, kept, count == 1 ? ws_bytes : 0);
+            const Q4Plan plan = asked ? *asked : q4_pass_plan(total_strips, wide.units, P0->N, P0->K, P0->tile, rows, P0->n_cus, kept, count == 1 ? ws_bytes : 0);
             if (plan.wide) {
                 launch_batch4(static_cast<const uint16_t*>(X), m0, rows, P0->K, P0->tile, wide, plan.chunks, ws, s);
                 continue;
@@ -1252,6 +1252,30 @@ static int q4_prefill_split(int64_t M, const patch_packed4* P, const GemmArgs& a
     return best < passes_us ? best_split : 0;
 }
 
+// One prefill-shaped launch in blocks of bm rows; split > 1: K slices, partial sums in ws (split x M x N floats).
+static patch_status q4_prefill(const uint16_t* X, int64_t M, const patch_packed4* P, float* Y, int split, int bm, float* ws, hipStream_t s) {
+    const int tiles_n = (int)((P->N + kP4BN - 1) / kP4BN), tiles_m = (int)((M + bm - 1) / bm);
+    const int grid = ((tiles_n * tiles_m + 7) / 8) * 8;
+    const int lds_bytes = 2 * bm * 128;
+    auto launch = [&](auto whole, auto sliced) {
+        if (split == 1) {
+            hipLaunchKernelGGL(whole, dim3(grid), dim3(512), lds_bytes, s, X, M, P->N, P->K, P->d_payload, P->d_scales, P->d_table, P->Tk, tiles_n,
+                               tiles_m, Y);
+        } else {
+            hipLaunchKernelGGL(sliced, dim3(grid, split), dim3(512), lds_bytes, s, X, M, P->N, P->K, P->d_payload, P->d_scales, P->d_table, P->Tk,
+                               tiles_n, tiles_m, ws);
+            wr_reduce(ws, (size_t)M * (size_t)P->N / 4, split, Y, 0, s);
+        }
+    };
+    if (P->tile == 128 && bm == 128) launch(prefill4_kernel<128, 128, false>, prefill4_kernel<128, 128, true>);
+    else if (P->tile == 128) launch(prefill4_kernel<128, 256, false>, prefill4_kernel<128, 256, true>);
+    else if (bm == 128) launch(prefill4_kernel<64, 128, false>, prefill4_kernel<64, 128, true>);
+    else launch(prefill4_kernel<64, 256, false>, prefill4_kernel<64, 256, true>);
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) { patch_note_hip_error((int)err); return PATCH_ERR_HIP; }
+    return PATCH_OK;
+}
+
 patch_status patch_gemm4_ex(const void* X, int64_t M, const patch_packed4* P, void* Y, void* workspace, size_t workspace_bytes,
                             void* stream) {
     if (!X || !P || !Y || M < 0) return PATCH_ERR_ARG;
@@ -1267,27 +1291,27 @@ patch_status patch_gemm4_ex(const void* X, int64_t M, const patch_packed4* P, vo
     const int split = q4_prefill_split(M, P, a, &bm);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (split == 0) return q4_passes(X, M, &P, &Y, 1, a.ws, a.ws_bytes, s);
-    const int tiles_n = (int)((P->N + kP4BN - 1) / kP4BN), tiles_m = (int)((M + bm - 1) / bm);
-    const int grid = ((tiles_n * tiles_m + 7) / 8) * 8;
-    const int lds_bytes = 2 * bm * 128;
-    const uint16_t* Xp = static_cast<const uint16_t*>(X);
-    auto launch = [&](auto whole, auto sliced) {
-        if (split == 1) {
-            hipLaunchKernelGGL(whole, dim3(grid), dim3(512), lds_bytes, s, Xp, M, P->N, P->K, P->d_payload, P->d_scales, P->d_table, P->Tk, tiles_n,
-                               tiles_m, static_cast<float*>(Y));
-        } else {
-            hipLaunchKernelGGL(sliced, dim3(grid, split), dim3(512), lds_bytes, s, Xp, M, P->N, P->K, P->d_payload, P->d_scales, P->d_table, P->Tk,
-                               tiles_n, tiles_m, a.ws);
-            wr_reduce(a.ws, (size_t)M * (size_t)P->N / 4, split, static_cast<float*>(Y), 0, s);
-        }
-    };
-    if (P->tile == 128 && bm == 128) launch(prefill4_kernel<128, 128, false>, prefill4_kernel<128, 128, true>);
-    else if (P->tile == 128) launch(prefill4_kernel<128, 256, false>, prefill4_kernel<128, 256, true>);
-    else if (bm == 128) launch(prefill4_kernel<64, 128, false>, prefill4_kernel<64, 128, true>);
-    else launch(prefill4_kernel<64, 256, false>, prefill4_kernel<64, 256, true>);
-    const hipError_t err = hipGetLastError();
-    if (err != hipSuccess) { patch_note_hip_error((int)err); return PATCH_ERR_HIP; }
-    return PATCH_OK;
+    return q4_prefill(static_cast<const uint16_t*>(X), M, P, static_cast<float*>(Y), split, bm, a.ws, s);
+}
+
+// Test hook (kernels.h)
+int patch_test_gemm4(const void* X, int64_t M, const patch_packed4* const* P, void* const* Y, int count, int kernel, int chunks,
+                              void* workspace, size_t workspace_bytes, void* stream) {
+    if (!X || !P || !Y || M < 1 || count < 1 || count > kMaxMany || kernel < 0 || kernel > 3 || !q4_aligned16(X)) return PATCH_ERR_ARG;
+    for (int i = 0; i < count; ++i) {
+        if (!P[i] || !Y[i] || !q4_aligned16(Y[i])) return PATCH_ERR_ARG;
+        if (P[i]->K != P[0]->K || P[i]->tile != P[0]->tile) return PATCH_ERR_SHAPE;
+    }
+    const int longest = kernel == 1 ? (int)((P[0]->K + kBtUnit - 1) / kBtUnit) : kernel == 0 ? 1 : P[0]->Tk;
+    const int64_t rows = kernel == 1 && M > kQ4Rows ? kQ4Rows : M;
+    if (chunks < 1 || chunks > longest || (count > 1 && (chunks > 1 || kernel > 1))) return PATCH_ERR_ARG;
+    if (chunks > 1 && (!workspace || !q4_aligned16(workspace) || workspace_bytes < (size_t)chunks * (size_t)rows * (size_t)P[0]->N * sizeof(float)))
+        return PATCH_ERR_SIZE;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    if (kernel > 1)
+        return q4_prefill(static_cast<const uint16_t*>(X), M, P[0], static_cast<float*>(Y[0]), chunks, kernel == 2 ? 128 : 256, static_cast<float*>(workspace), s);
+    const Q4Plan plan = {kernel == 1, chunks, 0.0};
+    return q4_passes(X, M, P, Y, count, static_cast<float*>(workspace), workspace_bytes, s, &plan);
 }
 
 patch_status patch_pack_from4(const patch_packed4* P4, void* stream, patch_packed** out) {

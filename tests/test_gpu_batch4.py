@@ -1,7 +1,10 @@
-"""Batched decoding from the 4-bit storage at sizes whose passes take the kernel with 128 features per workgroup, against the
-float64 product of the dequantized weight: counts of 16-row blocks and their edges, a last unit of one 64-column step, a last
-feature group of 64, K in chunks over a workspace that ends in a guard region, sets in one launch.  Element bound as in
-test_gpu_prefill64 (the dequantized weight is a bf16 matrix, so products are exact in fp32)."""
+"""The 4-bit batched-decoding kernel (batch4_kernel, 128 features x up to 64 rows per workgroup) called for by name - the dispatch takes
+it at larger sizes only - against the float64 product of the dequantized weight: every count of 16-row blocks and its edges, one to five
+128-column units (two wavefront groups take them in turn), a last unit of one 64-column step, a last feature group of 64, K in chunks
+over a workspace that ends in a guard region, sets in one launch.  Then the interface itself, whichever kernel it takes.  Element bound as in test_gpu_prefill64 (the dequantized weight is a bf16 matrix, so products are exact
+in fp32)."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -27,13 +30,49 @@ def _check(Y, X, W, what):
     assert worst <= 1.0, (what, worst)       # (NaN, an output never written, fails too)
 
 
-@pytest.mark.parametrize("tile,N,K,f", [(128, 384, 4096, 0.5), (64, 320, 4160, 0.6), (64, 64, 2112, 1.0), (128, 128, 6144, 0.0)])
-def test_batch4_split(tile, N, K, f):
+def _x(M, K):
+    return torch.randn(M, K, device="cuda", generator=torch.Generator(device="cuda").manual_seed(M)).to(torch.bfloat16)
+
+
+def _batch4(X, M, Ps, Ys, chunks=1, workspace=None):
+    """batch4_kernel in passes of 64 rows (kernel 1 of the test hook)."""
+    vp, n = ctypes.c_void_p, len(Ps)
+    st = B.lib().patch_test_gemm4(vp(X.data_ptr()), ctypes.c_int64(M), (vp * n)(*[p.handle for p in Ps]), (vp * n)(*[y.data_ptr() for y in Ys]), n, 1, chunks,
+                                  vp(workspace.data_ptr() if workspace is not None else 0), ctypes.c_size_t(4 * workspace.numel() if workspace is not None else 0),
+                                  vp(torch.cuda.current_stream().cuda_stream))
+    assert st == B.OK, st
+
+
+@pytest.mark.parametrize("tile,N,K,f", [(64, 64, 64, 1.0), (64, 192, 192, 0.5), (64, 320, 576, 0.6), (128, 128, 128, 0.0), (128, 384, 640, 0.5), (128, 256, 2048, 1.0)])
+def test_batch4(tile, N, K, f):
     print(f"batch4 tile={tile} N={N} K={K} f={f}", flush=True)
+    (W, P), (W2, P2) = _weight(N, K, tile, f, 1), _weight(tile, K, tile, 1 - f, 2)
+    for M in (1, 8, 16, 17, 32, 33, 48, 49, 64, 70):
+        X, rows = _x(M, K), min(M, 64)
+        for chunks in sorted({1, min(2, (K + 127) // 128), min(5, (K + 127) // 128)}):
+            need = chunks * rows * N
+            buf = torch.full((need + 1024,), float("nan"), device="cuda")
+            buf[need:] = 7.0
+            Y = torch.full((M, N), float("nan"), device="cuda")
+            _batch4(X, M, [P], [Y], chunks, buf[:need])
+            _check(Y, X.double(), W, f"M={M} chunks={chunks}")
+            assert bool((buf[need:] == 7.0).all()), "wrote behind the workspace"
+        Ys = [torch.full((M, n), float("nan"), device="cuda") for n in (N, tile, N)]
+        _batch4(X, M, [P, P2, P], Ys)
+        for y, w in zip(Ys, (W, W2, W)):
+            _check(y, X.double(), w, f"set M={M}")
+    P.close()
+    P2.close()
+
+
+@pytest.mark.parametrize("tile,N,K,f", [(128, 384, 4096, 0.5), (64, 320, 4160, 0.6), (64, 64, 2112, 1.0), (128, 128, 6144, 0.0)])
+def test_workspaces_of_gemm4(tile, N, K, f):
+    """patch_gemm4_ex at any size of workspace, whatever kernel it takes: nothing is written behind it."""
+    print(f"gemm4 workspace tile={tile} N={N} K={K} f={f}", flush=True)
     stream = torch.cuda.current_stream().cuda_stream
     W, P = _weight(N, K, tile, f, 1)
     for M in (16, 17, 33, 48, 49, 64):
-        X = torch.randn(M, K, device="cuda", generator=torch.Generator(device="cuda").manual_seed(M)).to(torch.bfloat16)
+        X = _x(M, K)
         for slices in (2, 3, 8):
             need = slices * M * N
             buf = torch.full((need + 1024,), float("nan"), device="cuda")
@@ -46,12 +85,12 @@ def test_batch4_split(tile, N, K, f):
 
 
 @pytest.mark.parametrize("tile,K", [(128, 4096), (64, 4160)])
-def test_batch4_set(tile, K):
-    print(f"batch4 set tile={tile} K={K}", flush=True)
+def test_set_of_gemm4(tile, K):
+    print(f"gemm4 set tile={tile} K={K}", flush=True)
     stream = torch.cuda.current_stream().cuda_stream
     (W, P), (W2, P2) = _weight(8192 + tile, K, tile, 0.5, 1), _weight(8192, K, tile, 0.7, 2)
     for M in (17, 33, 64, 70):
-        X = torch.randn(M, K, device="cuda", generator=torch.Generator(device="cuda").manual_seed(M)).to(torch.bfloat16)
+        X = _x(M, K)
         Ys = [torch.full((M, n), float("nan"), device="cuda") for n in (8192 + tile, 8192)]
         B.patch_gemm4_many(X, M, [P, P2], Ys, stream)
         for y, w in zip(Ys, (W, W2)):
