@@ -116,4 +116,6 @@ int patch_test_schedule(int64_t M, int count, const int64_t* N, int64_t K, int t
 // kernels 1 - 3): K in that many chunks over the workspace.
 int patch_test_gemm4(const void* X, int64_t M, const patch_packed4* const* P, void* const* Y, int count, int kernel, int chunks,
                      void* workspace, size_t workspace_bytes, void* stream);
+// patch_test_schedule for patch_gemm4_ex (count 1) and patch_gemm4_many: kernels as in patch_test_gemm4.
+int patch_test_schedule4(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* kernel, int* chunks);
 }

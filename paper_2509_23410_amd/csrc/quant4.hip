@@ -1081,35 +1081,62 @@ patch_status patch_unpack4(const patch_packed4* P, void* W_deq, void* codes, voi
     return PATCH_OK;
 }
 
-// A pass of `rows` rows (at most 64) over all weights of a set (N features of a single weight, whose K may be split over ws_bytes of
-// workspace; 0 = none): the strip kernel or batch4_kernel, and in how many K chunks.  Both are estimated, in us with steps = 64-column steps
-// (fitted to launches of 16 .. 1728 strips at f = 0.5, mostly within 12 %; measured in brackets, strip / batch):
-//   strip   3 + share x (0.6 R + 0.2 + 0.04 rows) x 0.05 x steps up to 16 rows, beyond with 1.09 + 0.076 (rows - 17), from 33 rows
-//           2.23 + 0.068 (rows - 32) in place of the last two terms; R = strips per workgroup, share = workgroups / compute units where more
-//           than one (then 15 % more: they share a compute unit), else 1; x (0.55 + 0.6 kept share of the weights), 1 at f = 0.5.  (Finer
-//           than the estimate R is chosen by.)
-//   batch   5 + rounds x steps / chunks x (0.17 + 0.041 blocks of 16 rows) (1 + 0.12 fill), mask tile 64 8 % more (two scales and
-//           position loads per unit), and 1.2 (up to 8 rows 3) to be worth it; a split 2.7 for the second launch, and its partial sums twice at 5 TB/s
-// gate and up of 4096 / 11008 at 1 / 16 / 32 / 64 rows (17.4 / 19.6, 19.6 / 19.5, 25.8 / 22.5, 41.9 / 28.2), of 5120 / 13824 (26.1 / 23.8, 31.3 / 23.6,
-// 41.8 / 27.7, 78.0 / 35.0); three 4096 x 4096 (9.8 / 19.5, 11.1 / 19.3, 15.9 / 22.0, 22.7 / 27.5); 4096 x 11008 in 8 chunks at 8 / 16 / 40 rows (12.1 / 13.3,
-// 16.4 / 13.9, 29.9 / 17.2).
-struct Q4Plan { bool wide; int chunks; double us; };
-static Q4Plan q4_pass_plan(int strips, int groups128, int64_t N, int64_t K, int tile, int rows, int n_cus, double kept, size_t ws_bytes) {
-    const double steps = (double)K / kStepCols;
-    const int R = q4_strips_per_group(strips, n_cus, rows);
-    const double x = rows <= 16 ? 0.2 + 0.04 * rows : rows <= 32 ? 1.09 + 0.076 * (rows - 17) : 2.23 + 0.068 * (rows - 32);
-    const double share = (double)((strips + R - 1) / R) / n_cus;
-    Q4Plan best = {false, 1, 3.0 + (share > 1.0 ? 1.15 * share : 1.0) * (0.6 * R + x) * (0.55 + 0.6 * kept) * 0.05 * steps};
-    const double margin = rows <= 8 ? 3.0 : 1.2;
-    const double step = (0.17 + 0.041 * ((rows + 15) / 16)) * (tile == 64 ? 1.08 : 1.0);
-    const size_t fit = ws_bytes / ((size_t)rows * (size_t)N * sizeof(float));
-    for (int c = 1; c == 1 || (c <= 8 && (size_t)c <= fit && groups128 * c <= n_cus && c * 512 <= K); ++c) {
-        const int wg = groups128 * c, rounds = (wg + n_cus - 1) / n_cus;
-        const double fill = wg < n_cus ? (double)wg / n_cus : 1.0;
-        const double us = (best.wide ? 5.0 : 5.0 + margin) + rounds * steps / c * step * (1.0 + 0.12 * fill) + (c > 1 ? 2.7 + 2.0 * c * rows * (double)N * 4.0 / 5.0e6 : 0.0);
-        if (us < best.us) best = Q4Plan{true, c, best.wide ? us : us - margin};
+// What the choices below go by: `count` weights of N features and K columns together (a single weight's K may be split over ws_bytes of
+// workspace, 0 = none), f = share of 2:4 tiles.
+struct Q4Shape { int count, strips, groups128; int64_t N, K; int tile, n_cus; double f; size_t ws_bytes; };
+
+static Q4Shape q4_shape(const patch_packed4* const* P, int count, size_t ws_bytes) {
+    Q4Shape d = {count, 0, 0, 0, P[0]->K, P[0]->tile, P[0]->n_cus, 0.0, count == 1 ? ws_bytes : 0};
+    double sparse = 0.0, tiles = 0.0;
+    for (int i = 0; i < count; ++i) {
+        d.strips += (int)(P[i]->N / kStripRows);
+        d.groups128 += (int)((P[i]->N + kBtFeatures - 1) / kBtFeatures);
+        d.N += P[i]->N;
+        sparse += (double)P[i]->n_sparse;
+        tiles += (double)P[i]->Tn * P[i]->Tk;
     }
-    return best;
+    d.f = sparse / tiles;
+    return d;
+}
+
+// A pass of `rows` rows (at most 64) over all weights: the strip kernel or batch4_kernel, and in how many K chunks.  Both are priced, in us with
+// steps = 64-column steps, fitted by row range to launches of 24 weights and 12 sets, both mask tiles, f = 0, 1/2 and 1, 14 row counts (rms
+// error 5 - 8 %; 650 - 4100 launches per line):
+//   strip   base + share x (per_strip R + constant + per_row rows) x 0.05 x steps x (1 + sparse (f - 1/2)); R = strips per workgroup, share = workgroups /
+//           compute units where more than one (then x over: they share a compute unit; beyond two 0.2 more), else 1.  (Finer than the estimate R is
+//           chosen by.)
+//   batch   base + (1 + round (rounds - 1)) x steps / chunks x (step + per_row rows) x (1 + fill min(1, workgroups / compute units)) x (tile64 on mask
+//           tile 64: two scales and position loads per unit) x (1 + sparse (f - 1/2)); a split 2.7 for the second launch and its partial sums twice at
+//           5 TB/s; to be worth it 0.8 ahead (up to 8 rows 1)
+// Measured, strip / batch, f = 1/2: gate and up of 4096 / 11008 at 1 / 16 / 32 / 64 rows (17.4 / 19.6, 19.6 / 19.5, 25.8 / 22.5, 41.9 / 28.2), of 5120 / 13824 (26.1 / 23.8,
+// 31.3 / 23.6, 41.8 / 27.7, 78.0 / 35.0); three 4096 x 4096 (9.8 / 19.5, 11.1 / 19.3, 15.9 / 22.0, 22.7 / 27.5); 4096 x 11008 in 8 chunks at 8 / 16 / 40 rows
+// (12.1 / 13.3, 16.4 / 13.9, 29.9 / 17.2).
+struct Q4StripPrice { int rows; double base, per_strip, constant, per_row, over, sparse; };
+constexpr Q4StripPrice kQ4StripPrice[] = {{8, 3.0, 0.54, 0.02, 0.031, 1.12, -0.21}, {16, 2.9, 0.48, 0.0, 0.0505, 1.06, -0.15}, {32, 3.4, 0.70, 0.0, 0.0453, 1.12, -0.13}, {64, 3.8, 0.62, 0.0, 0.0557, 1.20, -0.02}};
+struct Q4BatchPrice { int rows; double base, step, per_row, fill, tile64, sparse, round; };
+constexpr Q4BatchPrice kQ4BatchPrice[] = {{16, 2.7, 0.2204, 0.0001, 0.17, 1.12, -0.24, 0.53}, {32, 3.0, 0.2487, 0.0003, 0.15, 1.11, -0.21, 0.57}, {64, 3.6, 0.217, 0.0019, 0.15, 1.10, -0.20, 1.05}};
+
+struct Q4Plan { bool wide; int chunks; double us; };
+static Q4Plan q4_pass_plan(const Q4Shape& d, int rows) {
+    const double steps = (double)d.K / kStepCols;
+    const Q4StripPrice* p = kQ4StripPrice;
+    while (rows > p->rows) ++p;
+    const int R = q4_strips_per_group(d.strips, d.n_cus, rows);
+    const double share = (double)((d.strips + R - 1) / R) / d.n_cus;
+    const Q4Plan strip = {false, 1, p->base + (share > 1.0 ? p->over * (share + (share > 2.0 ? 0.2 : 0.0)) : 1.0) * (p->per_strip * R + p->constant + p->per_row * rows) * 0.05 * steps * (1.0 + p->sparse * (d.f - 0.5))};
+    const Q4BatchPrice* b = kQ4BatchPrice;
+    while (rows > b->rows) ++b;
+    const size_t fit = d.ws_bytes / ((size_t)rows * (size_t)d.N * sizeof(float));
+    Q4Plan wide = {true, 1, 0.0};
+    for (int c = 1; c == 1 || (c <= 8 && (size_t)c <= fit && d.groups128 * c <= d.n_cus && c * 512 <= d.K); ++c) {
+        const int wg = d.groups128 * c, rounds = (wg + d.n_cus - 1) / d.n_cus;
+        const double fill = wg < d.n_cus ? (double)wg / d.n_cus : 1.0;
+        const double us = b->base + (1.0 + b->round * (rounds - 1)) * steps / c * (b->step + b->per_row * rows) * (1.0 + b->fill * fill) * (d.tile == 64 ? b->tile64 : 1.0) *
+                              (1.0 + b->sparse * (d.f - 0.5)) +
+                          (c > 1 ? 2.7 + 2.0 * c * rows * (double)d.N * 4.0 / 5.0e6 : 0.0);
+        if (c == 1 || us < wide.us) wide = Q4Plan{true, c, us};
+    }
+    return wide.us + (rows <= 8 ? 1.0 : 0.8) < strip.us ? wide : strip;
 }
 
 static patch_status q4_passes(const void* X, int64_t M, const patch_packed4* const* P, void* const* Y, int count, float* ws, size_t ws_bytes,
@@ -1149,17 +1176,12 @@ static patch_status q4_passes(const void* X, int64_t M, const patch_packed4* con
         wide.units += (int)((P[i]->N + kBtFeatures - 1) / kBtFeatures);
     }
     wide.count = count;
-    double sparse_tiles = 0.0, tiles = 0.0;
-    for (int i = 0; i < count; ++i) {
-        sparse_tiles += (double)P[i]->n_sparse;
-        tiles += (double)P[i]->Tn * P[i]->Tk;
-    }
-    const double kept = 1.0 - 0.5 * sparse_tiles / tiles;
+    const Q4Shape shape = q4_shape(P, count, ws_bytes);
     // One launch per pass of up to 64 rows (1, 2 or 4 blocks of 16), R strips per workgroup (q4_strips_per_group).
     auto run = [&](const auto& set) {
         for (int64_t m0 = 0; m0 < M; m0 += kQ4Rows) {
             const int rows = (int)(M - m0 < kQ4Rows ? M - m0 : kQ4Rows);
-            const Q4Plan plan = asked ? *asked : q4_pass_plan(total_strips, wide.units, P0->N, P0->K, P0->tile, rows, P0->n_cus, kept, count == 1 ? ws_bytes : 0);
+            const Q4Plan plan = asked ? *asked : q4_pass_plan(shape, rows);
             if (plan.wide) {
                 launch_batch4(static_cast<const uint16_t*>(X), m0, rows, P0->K, P0->tile, wide, plan.chunks, ws, s);
                 continue;
@@ -1213,43 +1235,63 @@ patch_status patch_gemm4(const void* X, int64_t M, const patch_packed4* P, void*
 
 // Passes of up to 64 rows or the prefill-shaped kernel?  Both sides are estimated from measured rates, as for the bf16 kernels:
 //   passes           q4_pass_plan's estimate of a full pass, and of the last one by its rows
-//   prefill kernel   rounds x steps per workgroup x (t0 + t1 fill) us + 3, fill = min(1, workgroups / compute units),
-//                    for blocks of 128 and of 256 rows (the dequantization makes a step 0.2 - 0.4 us longer than the
-//                    bf16 kernel's), + for a split 3 + (2 split + 1) M N 4 B / 5.5 TB/s; splits of at most 8 slices of at
-//                    least 512 columns
+//   prefill kernel   base + rounds x steps per workgroup x (t0 + t1 fill) x (tile64 on mask tile 64) x (1 + sparse (f - 1/2)), fill = min(1, workgroups /
+//                    compute units), for blocks of 128 and of 256 rows, + for a split 3 + (2 split + 1) M N 4 B / 8.3 TB/s; splits of at most 8
+//                    slices of at least 512 columns.  Fitted to 9072 and 9630 launches of 24 weights at 17 - 400 rows, both mask tiles, f = 0, 1/2 and 1
+//                    (rms error 4 %); a step of 256 rows dequantizes the same codes for twice the rows.
 // Returns the split to launch the prefill kernel with (and the block height), or 0 for passes.
-static int q4_prefill_split(int64_t M, const patch_packed4* P, const GemmArgs& a, int* bm_out) {
+struct Q4PrefillPrice { int bm; double base, t0, t1, tile64, sparse; };
+constexpr Q4PrefillPrice kQ4PrefillPrice[] = {{128, 4.6, 0.766, 0.076, 1.065, -0.30}, {256, 6.1, 1.22, 0.142, 1.054, -0.387}};
+
+static int q4_prefill_split(int64_t M, const Q4Shape& d, int* bm_out) {
     *bm_out = 128;
     if (M <= 16) return 0;
-    const int kpt = P->tile / 64, strips = (int)(P->N / 16);
+    const int kpt = d.tile / kStepCols, Tk = (int)(d.K / d.tile);
     const int64_t full = M / kQ4Rows;
     const int rest = (int)(M % kQ4Rows);
-    const auto pass_us = [&](int rows) {
-        return q4_pass_plan(strips, (int)((P->N + kBtFeatures - 1) / kBtFeatures), P->N, P->K, P->tile, rows, P->n_cus,
-                            1.0 - 0.5 * (double)P->n_sparse / ((double)P->Tn * P->Tk), a.ws ? a.ws_bytes : 0).us;
-    };
-    const double passes_us = (full ? (double)full * pass_us(kQ4Rows) : 0.0) + (rest ? pass_us(rest) : 0.0);
-    const size_t per_slice = (size_t)M * (size_t)P->N * sizeof(float);
-    const int fit = a.ws ? (int)(a.ws_bytes / per_slice < 8 ? a.ws_bytes / per_slice : 8) : 1;
-    const int longest = P->Tk * P->tile / 512;
+    const double passes_us = (full ? (double)full * q4_pass_plan(d, kQ4Rows).us : 0.0) + (rest ? q4_pass_plan(d, rest).us : 0.0);
+    const size_t per_slice = (size_t)M * (size_t)d.N * sizeof(float);
+    const size_t fit = d.ws_bytes / per_slice;
     int best_split = 1;
     double best = 0.0;
-    bool first = true;
-    for (int bm : {128, 256}) {
-        const int blocks = (int)((P->N + kP4BN - 1) / kP4BN) * (int)((M + bm - 1) / bm);
-        // a step of 256 rows dequantizes the same codes for twice the rows: 1.2 + 0.47 fill us against 0.88 + 0.2 fill
-        // (fitted to unsplit launches of 16 .. 256 workgroups); it pays once 128-row blocks would need a second round
-        const double t0 = bm == 128 ? 0.88 : 1.2, t1 = bm == 128 ? 0.2 : 0.47;
-        for (int sp = 1; sp <= 8 && (sp == 1 || (sp <= fit && sp <= longest)); ++sp) {
-            const int wgs = blocks * sp;
-            const int rounds = (wgs + P->n_cus - 1) / P->n_cus;
-            const double fill = wgs < P->n_cus ? (double)wgs / P->n_cus : 1.0;
-            double us = rounds * ((P->Tk + sp - 1) / sp) * kpt * (t0 + t1 * fill) + 3.0;
-            if (sp > 1) us += 3.0 + (2.0 * sp + 1.0) * (double)per_slice / 5.5e6;
-            if (first || us < best) { best = us; best_split = sp; *bm_out = bm; first = false; }
+    for (const Q4PrefillPrice& p : kQ4PrefillPrice) {
+        const int64_t blocks = ((d.N + kP4BN - 1) / kP4BN) * ((M + p.bm - 1) / p.bm);
+        for (int sp = 1; sp == 1 || (sp <= 8 && (size_t)sp <= fit && sp * 512 <= d.K); ++sp) {
+            const int64_t wgs = blocks * sp, rounds = (wgs + d.n_cus - 1) / d.n_cus;
+            const double fill = wgs < d.n_cus ? (double)wgs / d.n_cus : 1.0;
+            double us = p.base + (double)(rounds * ((Tk + sp - 1) / sp) * kpt) * (p.t0 + p.t1 * fill) * (d.tile == 64 ? p.tile64 : 1.0) * (1.0 + p.sparse * (d.f - 0.5));
+            if (sp > 1) us += 3.0 + (2.0 * sp + 1.0) * (double)per_slice / 8.3e6;
+            if (best == 0.0 || us < best) { best = us; best_split = sp; *bm_out = p.bm; }
         }
     }
     return best < passes_us ? best_split : 0;
+}
+
+// Test hook (kernels.h)
+int patch_test_schedule4(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* kernel, int* chunks) {
+    if (!N || !kernel || !chunks || M < 1 || count < 1 || count > kMaxMany || (tile != 64 && tile != 128) || K < tile || K % tile || sparse_pct < 0 || sparse_pct > 100) return -1;
+    Q4Shape d = {count, 0, 0, 0, K, tile, 256, 0.01 * sparse_pct, 0};
+    for (int i = 0; i < count; ++i) {
+        if (N[i] < tile || N[i] % tile) return -1;
+        d.strips += (int)(N[i] / kStripRows);
+        d.groups128 += (int)((N[i] + kBtFeatures - 1) / kBtFeatures);
+        d.N += N[i];
+    }
+    if (count == 1 && ws_bytes >= 2 * (size_t)M * (size_t)d.N * sizeof(float)) d.ws_bytes = ws_bytes;
+    int bm = 128;
+    if (const int split = count == 1 ? q4_prefill_split(M, d, &bm) : 0) {
+        kernel[0] = bm == 128 ? 2 : 3;
+        chunks[0] = split;
+        return 1;
+    }
+    if (M > 8 * kQ4Rows) return -1;
+    int n = 0;
+    for (int64_t m0 = 0; m0 < M; m0 += kQ4Rows, ++n) {
+        const Q4Plan plan = q4_pass_plan(d, (int)(M - m0 < kQ4Rows ? M - m0 : kQ4Rows));
+        kernel[n] = plan.wide ? 1 : 0;
+        chunks[n] = plan.chunks;
+    }
+    return n;
 }
 
 // One prefill-shaped launch in blocks of bm rows; split > 1: K slices, partial sums in ws (split x M x N floats).
@@ -1282,16 +1324,13 @@ patch_status patch_gemm4_ex(const void* X, int64_t M, const patch_packed4* P, vo
     if (!q4_aligned16(X) || !q4_aligned16(Y) || (workspace && !q4_aligned16(workspace))) return PATCH_ERR_ARG;
     if (M == 0) return PATCH_OK;
     const bool ws = workspace && workspace_bytes >= 2 * (size_t)M * (size_t)P->N * sizeof(float);
-    GemmArgs a = {};
-    a.M = M; a.N = P->N; a.K = P->K;
-    a.tile = P->tile; a.Tn = P->Tn; a.Tk = P->Tk;
-    a.n_cus = P->n_cus;
-    if (ws) { a.ws = static_cast<float*>(workspace); a.ws_bytes = workspace_bytes; }
+    float* const part = ws ? static_cast<float*>(workspace) : nullptr;
+    const size_t part_bytes = ws ? workspace_bytes : 0;
     int bm = 128;
-    const int split = q4_prefill_split(M, P, a, &bm);
+    const int split = q4_prefill_split(M, q4_shape(&P, 1, part_bytes), &bm);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (split == 0) return q4_passes(X, M, &P, &Y, 1, a.ws, a.ws_bytes, s);
-    return q4_prefill(static_cast<const uint16_t*>(X), M, P, static_cast<float*>(Y), split, bm, a.ws, s);
+    if (split == 0) return q4_passes(X, M, &P, &Y, 1, part, part_bytes, s);
+    return q4_prefill(static_cast<const uint16_t*>(X), M, P, static_cast<float*>(Y), split, bm, part, s);
 }
 
 // Test hook (kernels.h)

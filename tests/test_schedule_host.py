@@ -95,3 +95,47 @@ def test_block_height_of_mask_tile_64(N, K, M, us):
     """A prefill launch on mask tile 64, f = 1/2, with a workspace: blocks of 128 rows or the 256-row register-weight kernel."""
     (k, _), = _schedule([N], K, 64, 0.5, M, True)
     assert us[{4: 128, 3: 256}[k]] == min(us.values())
+
+
+# the 4-bit storage: patch_gemm4_ex (one weight), patch_gemm4_many; the passes of a call joined by "+"
+MEASURED4 = [
+    ([49152], 2048, 64, 0.0, 12, False, {'strip': 16.8, 'b1': 18.4}),
+    ([36864], 4096, 128, 0.0, 16, False, {'strip': 24.1, 'b1': 29.6}),
+    ([1024], 8192, 128, 0.0, 193, False, {'strip+strip+strip+strip': 102.7, 'prefill': 120.5}),
+    ([128256], 1024, 64, 1.0, 64, False, {'prefill': 31.7, 'b1': 36.4}),
+    ([36864], 4096, 128, 0.0, 32, False, {'strip': 46.4, 'b1': 34.5}),
+    ([5120], 13824, 128, 1.0, 193, False, {'prefill': 144.7, 'strip+strip+strip+strip': 185.8}),
+    ([512], 13824, 64, 0.0, 9, True, {'strip': 12.5, 'b8': 14.1}),
+    ([32000], 4096, 64, 0.0, 2, True, {'strip': 19.4, 'b1': 21.4}),
+    ([256], 1024, 128, 0.0, 96, True, {'strip+strip': 12.3, 'prefill': 13.3}),
+    ([512], 13824, 64, 0.5, 9, True, {'strip': 12.0, 'b8': 13.4}),
+    ([32000], 4096, 128, 1.0, 80, True, {'prefill': 34.9, 'b1+b1': 43.5}),
+    ([11008] * 2, 4096, 128, 0.0, 12, False, {'strip': 17.5, 'b1': 20.0}),
+    ([11008] * 2, 4096, 64, 0.0, 16, False, {'strip': 18.6, 'b1': 21.9}),
+    ([49152], 2048, 128, 0.0, 17, False, {'strip': 24.3, 'b1': 18.8}),
+    ([896], 896, 64, 0.0, 256, False, {'strip+strip+strip+strip': 26.5, 'prefill': 17.4}),
+    ([32000], 4096, 128, 0.5, 64, False, {'prefill': 56.6, 'b1': 29.1}),
+    ([32000], 4096, 64, 0.5, 65, False, {'prefill': 61.4, 'b1+strip': 49.1}),
+    ([128256], 1024, 64, 1.0, 16, False, {'strip': 20.8, 'b1': 16.9}),
+    ([13824], 5120, 64, 1.0, 80, False, {'strip+strip': 59.3, 'b1+strip': 46.9}),
+    ([5120], 13824, 128, 0.0, 16, True, {'strip': 23.0, 'b6': 16.3}),
+    ([896], 896, 64, 0.0, 256, True, {'strip+strip+strip+strip': 26.5, 'prefill': 17.4}),
+    ([896], 4864, 128, 0.5, 33, True, {'strip': 13.0, 'b8': 10.3}),
+    ([256], 1024, 64, 0.5, 160, True, {'strip+strip+strip': 18.6, 'prefill': 13.4}),
+    ([896], 4864, 128, 1.0, 33, True, {'strip': 13.1, 'b8': 9.9}),
+    ([4864], 896, 64, 1.0, 129, True, {'strip+strip+strip': 18.5, 'prefill': 14.3}),
+    ([13824] * 2, 5120, 128, 0.0, 48, False, {'strip': 58.3, 'b1': 32.1}),
+    ([13824] * 2, 5120, 128, 0.5, 16, False, {'strip': 28.7, 'b1': 23.1}),
+    ([28672] * 2, 4096, 64, 1.0, 64, False, {'strip': 92.7, 'b1': 53.6}),
+]
+
+
+@pytest.mark.parametrize("N,K,tile,f,M,workspace,us", MEASURED4)
+def test_choice_from_the_4_bit_storage(N, K, tile, f, M, workspace, us):
+    kernel, chunks = (ctypes.c_int * 8)(), (ctypes.c_int * 8)()
+    n = B.lib().patch_test_schedule4(ctypes.c_int64(M), len(N), (ctypes.c_int64 * len(N))(*N), ctypes.c_int64(K), tile, round(100 * f),
+                                     ctypes.c_size_t(384 << 20 if workspace else 0), kernel, chunks)
+    assert n > 0
+    chosen = "prefill" if kernel[0] > 1 else "+".join("strip" if kernel[i] == 0 else f"b{chunks[i]}" for i in range(n))
+    assert chosen in us, (chosen, us)
+    assert us[chosen] <= 1.03 * min(us.values()) + 0.3, (chosen, us)
