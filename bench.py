@@ -6,7 +6,8 @@ Headline workload (the line's `value`): the LLaMA-2-7B MLP prefill set -- gate a
 rows of X.  One step = one pass of patch_gemm over the three projections (inputs resident in HBM).
 `value` = dense-equivalent TFLOP/s = 3 * 2 M N K / step time.
 
-Also reported on the same JSON line:
+stdout: ONE JSON line with the headline, roofline, cpu_baseline and speedup_vs_all_dense (about 2 KB).  The other sections below go to stderr,
+one JSON object {"section": name, "data": ...} per line (some 40 KB together), and with --details FILE into that file as one object:
   roofline      dominant (prefill) kernel: issued matrix-instruction flops M N K (2 - f) per launch over
                 its average launch duration, against the published dense bf16 MFMA peak (2.5 PFLOP/s)
   decode        7B attention projection 4096 x 4096, M in {1, 4, 16}, five 2:4 fractions: GB/s on the
@@ -47,6 +48,18 @@ import numpy as np
 PEAK_HBM_GBS = 8000.0       # MI355X published HBM3E bandwidth
 PEAK_MFMA_BF16_TF = 2500.0  # MI355X published dense bf16 matrix peak
 PAPER_CONTEXT = "paper: 1.18x-1.38x end-to-end LLaMA-2 7B speedup on an A6000 at 25-45% sparsity (context, not a target)"
+
+
+def report(line, sections, details=""):
+    """The result: `line` on stdout as the one JSON line, every section on a line of its own on stderr, all sections in the
+    file `details` if given."""
+    for name, data in sections.items():
+        print(json.dumps(dict(section=name, data=data)), file=sys.stderr)
+    if details:
+        with open(details, "w") as fh:
+            json.dump(sections, fh)
+    sys.stderr.flush()
+    print(json.dumps(line), flush=True)
 
 
 def _keep_top2(torch, W):
@@ -189,6 +202,7 @@ def main():
     ap.add_argument("--skip", default="", help="comma list of sections to skip: decode,dense,half,bf16out,cpu,pack,mid,sweep,layer,ceilings,stack,alloc,qwen,q4,tile64")
     ap.add_argument("--variant", type=int, default=0)
     ap.add_argument("--decode-launches", type=int, default=200)
+    ap.add_argument("--details", default="", help="file that receives every section as one JSON object")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also run one 1 GiB device-to-device copy (known traffic, for scaling profiler byte counters)")
     args = ap.parse_args()
@@ -894,8 +908,9 @@ def main():
         "roofline": roof, "cpu_baseline": cpu, "speedup_vs_all_dense": speedup, "context": PAPER_CONTEXT,
         "input_prep_s": round(prep_s, 1),
     }
-    line.update(out)
-    print(json.dumps(line))
+    if "relF_vs_oracle_on_sample" in out:
+        line["relF_vs_oracle_on_sample"] = out.pop("relF_vs_oracle_on_sample")
+    report(line, out, args.details)
 
 
 if __name__ == "__main__":
