@@ -78,7 +78,8 @@ typedef struct {
                  /* default picks 6 where at least a quarter of the tiles are 2:4); 7 = the kernel with  */
                  /* 128 features per workgroup (its split_k = K chunks over `workspace`, 0 = auto; the   */
                  /* default for passes of 8 .. 64 rows where estimated fastest, with a workspace in      */
-                 /* chunks; up to 128 rows a pass).  A variant that does not apply falls back to the default.                   */
+                 /* chunks; up to 128 rows a pass).  A variant that does not apply falls back to the     */
+                 /* default.                                                                             */
     void* workspace;        /* DEVICE, 16-byte aligned, caller-owned scratch for launches that split K   */
                             /* over workgroups, or NULL.  Any product call that is given one may write   */
                             /* it, whatever M, path and number of weights: calls that may overlap in     */
@@ -172,7 +173,8 @@ patch_status patch_gemm_static(const void* X, int64_t M, const patch_packed* P, 
  * patch_gemm_ex for this M and P on the device, on real operands; patch_tune returns the fastest.  Candidates:
  *   decode path (M <= 256): 16-feature-strip kernel with 8 or 4 K-steps per wavefront (variants 2 / 3) and 2 .. 16
  *     wavefronts per workgroup (split_k: the wavefronts-per-compute-unit dimension), up to 8 rows both ways of loading
- *     X (variants 5 / 6), the 64-features-per-wavefront kernel (variant 4) unsplit and with K chunks over the workspace;
+ *     X (variants 5 / 6), from 12 rows the 64-features-per-wavefront kernel (variant 4) unsplit and with K chunks over the
+ *     workspace and the kernel with 128 features per workgroup (variant 7) unsplit and in the planned number of chunks;
  *   prefill path, tile 128: the execution tiles 256 x 256 with one wavefront per SIMD (default), 256 x 256 with two
  *     (variant 2) and the small 128 x 128 tile (variant 1; Appendix O reports that small execution tiles under-use
  *     the matrix units - it is timed so that the report shows it), and the K-split counts the workspace allows;
@@ -336,10 +338,10 @@ patch_status patch_deserialize(const void* buf, size_t bytes, void* stream, patc
  *                  once per 64 rows of X; for prefill shapes dequantize once (patch_unpack4) and patch_pack the result
  *   patch_gemm4_ex  the same product with an optional caller workspace (DEVICE, 16-byte aligned, or NULL; used when it
  *                  holds at least two slices of M x N fp32).  A prefill-shaped kernel reads the 4-bit weight once per
- *                  128 rows of X and dequantizes in registers (no bf16 copy of the weight); with a workspace it splits K
+ *                  128 or 256 rows of X and dequantizes in registers (no bf16 copy of the weight); with a workspace it splits K
  *                  over workgroups (partial sums in the workspace, summed in slice order).  It is taken where an
  *                  estimate of both sides puts it ahead of passes of up to 64 rows (with a workspace from about 65
- *                  rows; without one from a few hundred rows, from 129 on wide weights);
+ *                  rows; without one from about two hundred rows, earlier on wide weights and where most tiles are 2:4);
  *                  otherwise passes as patch_gemm4 (= patch_gemm4_ex without a workspace), which may split K over the
  *                  workspace too.  Launches that may run concurrently need distinct workspaces
  *   patch_gemm4_many  up to PATCH_MAX_MANY weights with the same K and tile against one X in one launch per 64 rows

@@ -397,8 +397,8 @@ patch_status patch_deserialize(const void* buf, size_t bytes, void* stream, patc
 // launch (2.2 us behind mid_kernel, 2.7 behind batch_kernel) and its partial sums twice through memory (5 TB/s).  Fitted to 24 weights from
 // 128 x 4096 to 128256 x 1024 and 12 sets, both mask tiles, f = 0, 1/2 and 1, 22 row counts (860 - 4100 launches per line; rms error
 // 4 - 7 %).  The row ranges are those of the kernels' row blocks: 17 - 32 rows of the strip kernel cost little more than 16 (4096 x 4096, f = 1/2,
-// 17 / 24 / 32 rows 8.8 / 10.6 / 12.1 us, 33 rows 15.2; mid_kernel 14.4 / 15.6 / 17.0).  f tells the kernels apart: at 16 rows three 4096 x 4096 take
-// mid_kernel 19.3 / 17.1 / 12.5 us at f = 0 / 1/2 / 1 and the strip kernel 23.2 / 21.4 / 19.7.
+// 16 / 17 / 24 / 32 rows 8.0 / 8.9 / 10.6 / 12.1 us, 33 rows 15.2; mid_kernel 13.5 / 14.4 / 15.6 / 16.8 and 19.9).  f tells the kernels apart: at 16 rows three
+// 4096 x 4096 take mid_kernel 19.8 / 16.1 / 12.3 us at f = 0 / 1/2 / 1 and the strip kernel 22.9 / 19.4 / 17.5.
 struct PassPrice { int rows; double base, step, per_row, fill, round, sparse; };
 constexpr PassPrice kStripPrice[] = {{16, 2.5, 0.032, 0.0023, 0.24, 0.35, -0.23}, {32, 2.9, 0.045, 0.0026, 0.06, 0.4, -0.12}, {64, 3.5, 0.082, 0.0024, 0.07, 0.5, -0.03}};
 constexpr PassPrice kMidPrice[] = {{16, 2.6, 0.120, 0.0017, 0.47, 1.5, -0.45}, {32, 3.2, 0.125, 0.0020, 0.40, 2.0, -0.40}, {64, 4.3, 0.143, 0.0024, 0.28, 3.3, -0.31}};
@@ -475,10 +475,10 @@ static double set_prefill_us(const GemmArgs& a, const DecodeShape& d, const int6
 // rows may go in one pass of batch_kernel.
 //   up to 32 rows, sets up to 64: a pass
 //   a single weight of 33 .. 64 rows: a pass, or the prefill launch where the weight is wider than the chip (f = 1/2, 64 rows: 128256 x 1024
-//     50 us in a pass, 39 on the prefill kernel; 32896 x 4096 58 and 51; 20480 x 4096 26 and 31)
+//     51 us in a pass, 39 on the prefill kernel; 32896 x 4096 59 and 52; 20480 x 4096 31 and 50, split over a workspace 30)
 //   65 .. 128 rows: one pass where it is estimated 2 % ahead of the prefill launch - whose K split writes and reads its partial products more
 //     often, or which leaves compute units idle - and, without a workspace, of two passes.  f = 1/2, 80 / 128 rows, prefill -> pass: three
-//     4096 x 4096 40.4 / 40.4 -> 27.0 / 35.4 us, gate and up of 5120 / 13824 68.4 / 74.2 -> 46.6 / 62.0; at f = 1 the prefill launch gains
+//     4096 x 4096 32.7 / 34.7 -> 26.0 / 34.8 us, gate and up of 5120 / 13824 59.6 / 64.0 -> 46.6 / 61.6; at f = 1 the prefill launch gains
 //     more from its 2:4 steps (two 28672 x 4096, 80 rows 64 us against 73)
 //   beyond, with a workspace for two slices: prefill, whose K split fills the chip at any number of rows; without, the cheaper side
 struct AutoChoice { int path; bool one_pass; DecodePlan pass; };

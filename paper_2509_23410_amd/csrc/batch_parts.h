@@ -1,5 +1,5 @@
-// The batched-decoding product (up to 64 rows of X per launch) shared by the bf16 weights (gemm_batch.hip, which says what bounds
-// it) and the 4-bit storage (quant4.hip).
+// The batched-decoding product shared by the bf16 weights (gemm_batch.hip, up to 128 rows of X per launch; it says what bounds the
+// kernel) and the 4-bit storage (quant4.hip, up to 64).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -7,9 +7,9 @@
 // features - the weights of a 128-column unit are 20 - 32 KB, its 64 rows of X 16 KB - and X goes through LDS, read there by the
 // four wavefronts (two strips each) that multiply the unit.  Two such wavefront groups take the units in turn and add
 // their sums in LDS.  Where the groups of 128 features leave compute units idle, gridDim.y workgroups share a group's
-// columns and wr_reduce_set_kernel adds their partial sums in order; that second launch costs about 4 us, which is why
-// decode_plan (api.hip) weighs it.  f = 0.5, 47 rows, before -> now: gate and up of 4096 / 11008 (172 workgroups, no split) 46.7 -> 31.4 us
-// (4.5 TB/s of weights), of 5120 / 13824 59.0 -> 41.4; 4096 x 11008 (8 chunks) 23.9 -> 21.8; 5120 x 13824 at 16 rows (6 chunks) 37.3 -> 23.5.
+// columns and wr_reduce_set_kernel adds their partial sums in order; that second launch costs about 3 us, which is why
+// decode_plan (api.hip) weighs it.  f = 0.5, 48 rows, mid_kernel -> this kernel: gate and up of 4096 / 11008 (172 workgroups, no split) 45.4 -> 29.4 us
+// (4.8 TB/s of weights), of 5120 / 13824 58.5 -> 40.4; 4096 x 11008 (7 chunks) 22.6 -> 19.9; 5120 x 13824 at 16 rows (strip kernel 36.9; 5 chunks) 22.6.
 //
 // Beyond 64 rows, up to 128, one wavefront group per workgroup (80 - 128 accumulators and operands of up to eight row blocks per
 // lane: 272 - 384 registers): X then costs as much as the weights, still once per 128 features.

@@ -55,11 +55,11 @@ struct WeightOne {
     int64_t N;
 };
 
+constexpr int kDecodeRows = 64;    // rows of X per decode launch
+constexpr int kBatchRows = 128;    // batch_kernel
+
 // Up to kDecodeRows rows of X starting at row m0 (decode shape; 16-row blocks, the weights streamed once per launch).
-constexpr int kDecodeRows = 64;
-constexpr int kBatchRows = 128;   // batch_kernel
-//  split_k = K slices (wavefronts) per workgroup,
-// 0 picks a default.  Returns the number used.
+// split_k = K slices (wavefronts) per workgroup, 0 picks a default.  Returns the number used.
 int launch_decode(const GemmArgs& a, int64_t m0, int rows, int split_k, int variant, hipStream_t stream);
 // The same for a set of weights; a supplies X, K, tile, Tk, n_cus (its payload / table / Y / N are ignored).
 int launch_decode_set(const GemmArgs& a, const DecodeSet& set, int64_t m0, int rows, int split_k, int variant, hipStream_t stream);
@@ -88,7 +88,7 @@ void launch_prefill(const GemmArgs& a, int variant, int split_k, hipStream_t str
 bool prefill_wreg_supports(const GemmArgs& a);                  // K <= 16384, M * K * 2 < 4 GB
 int prefill_wreg_split(const GemmArgs& a, int requested);       // K slices per output tile the launch will use
 int prefill_lds_split(const GemmArgs& a, int requested, int bm = 256);   // the same for the LDS-staged kernel with blocks of bm rows
-// whether the default choice (variant 0, no split requested) is the LDS-staged kernel with blocks of 128 rows, and its split
+// whether the default choice (variant 0, no split requested) is prefill_kernel_areg with blocks of 128 rows, and its split; no_w64: see there
 bool prefill_prefers_128_rows(const GemmArgs& a, int* split, bool no_w64 = false);
 double prefill_estimate(const GemmArgs& a);                                       // us the default choice is estimated to take at few rows
 double prefill_set_estimate(const GemmArgs& a, const int64_t* N, int count);      // the same for a set of weights of N[i] features
