@@ -34,4 +34,19 @@ __device__ __forceinline__ void store4(float* Y, int64_t elem, ep_f32x4 v, int y
     }
 }
 
+// read(0) + read(1) + ... + read(n - 1), added in that order: the partial sums of n wavefronts (n a multiple of 4) in LDS, four reads requested
+// together: a loop over a run-time n reads one by one, each waiting its own LDS latency.
+template <typename Read>
+__device__ __forceinline__ ep_f32x4 sum_in_order(int n, Read read) {
+    ep_f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < n; i += 4) {
+        const ep_f32x4 v0 = read(i), v1 = read(i + 1), v2 = read(i + 2), v3 = read(i + 3);
+        sum = i == 0 ? v0 : sum + v0;
+        sum = sum + v1;
+        sum = sum + v2;
+        sum = sum + v3;
+    }
+    return sum;
+}
+
 }  // namespace patch

@@ -44,6 +44,7 @@ typedef __bf16 q4_bf16x16 __attribute__((ext_vector_type(16)));
 typedef float q4_f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int q4_u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int q4_u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int q4_pair_t __attribute__((ext_vector_type(2), aligned(4)));   // two at a dword's
 union Q4A { q4_u32x4 raw; q4_bf16x8 v; };
 union Q4B { q4_u32x4 raw[2]; q4_bf16x8 h[2]; q4_bf16x16 v; };
 
@@ -251,13 +252,12 @@ __global__ __launch_bounds__(256) void unpack4_kernel(const uint8_t* __restrict_
     }
 }
 
-// Up to 16 RB rows of X (RB = 1, 2 or 4 blocks of 16 rows) against the 4-bit weight in one pass over it.  A workgroup
+// Up to 16 RB rows of X (RB = 1 .. 4 blocks of 16 rows) against the 4-bit weight in one pass over it.  A workgroup
 // owns R consecutive strips of 16 features (the registers hold R x RB accumulators and RB X operands per step: R <= 3
 // with one row block, R <= 2 with more); its KW wavefronts take contiguous runs of 64-column steps.  A wavefront loads
 // the X operand of a step once and uses it for all R strips (at 4 bits per weight X is the larger stream, so this
-// reuse is what bounds the traffic), works in batches of NB steps (2; 1 when RB > 1) - table entries, then every load
-// of the batch, then the arithmetic - and issues the next batch's loads before it consumes the current one.  Two batch
-// buffers alternate; no copies.
+// reuse is what bounds the traffic), works in batches of NB steps (2; 1 when R RB > 1) and issues the next batch's loads before it
+// consumes the current one.  Two batch buffers alternate; no copies.
 constexpr int kQ4MaxR = 3;
 constexpr int kQ4Rows = 64;   // rows of X per launch at most
 
@@ -287,47 +287,47 @@ struct Q4Strips {
     q4_u16_ptr scl[R];        // this lane's scale of the strip for tile column 0 (the next column is 16 scales on)
 };
 
-// Steps past the wavefront's run repeat its last step (in bounds; discarded by q4_compute).
-template <int TILE, int R, int RB, int NB>
-__device__ __forceinline__ void q4_loads(Q4Batch<R, RB, NB>& b, const Q4Strips<R>& st, const q4_u16_ptr (&xrow)[RB], const bool (&xvalid)[RB],
-                                         int lane, int step0, int last) {
+// Steps past the wavefront's run repeat its last step (in bounds; discarded by q4_compute).  b.e has been filled by q4_entries.
+template <int TILE, int R, int NB>
+__device__ __forceinline__ void q4_entries(uint32_t (&e)[NB][R], const Q4Strips<R>& st, int step0, int last) {
     constexpr int KPT = TILE / kStepCols;
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         const int step = step0 + i < last ? step0 + i : last;
 #pragma unroll
-        for (int r = 0; r < R; ++r) b.e[i][r] = st.row[r][step / KPT];
+        for (int r = 0; r < R; ++r) e[i][r] = st.row[r][step / KPT];
     }
+}
+
+template <int TILE, int R, int RB, int NB>
+__device__ __forceinline__ void q4_loads(Q4Batch<R, RB, NB>& b, const Q4Strips<R>& st, const q4_u16_ptr (&xrow)[RB], int lane, int step0, int last) {
+    constexpr int KPT = TILE / kStepCols;
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         const int step = step0 + i < last ? step0 + i : last;
         const int j = step % KPT;
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            b.x[i][rb][0] = q4_u32x4{0u, 0u, 0u, 0u};
-            b.x[i][rb][1] = q4_u32x4{0u, 0u, 0u, 0u};
-            if (xvalid[rb]) {
-                b.x[i][rb][0] = *reinterpret_cast<const PATCH_Q4_GLOBAL q4_u32x4*>(xrow[rb] + (int64_t)step * kStepCols);
-                b.x[i][rb][1] = *reinterpret_cast<const PATCH_Q4_GLOBAL q4_u32x4*>(xrow[rb] + (int64_t)step * kStepCols + 32);
-            }
+            b.x[i][rb][0] = *reinterpret_cast<const PATCH_Q4_GLOBAL q4_u32x4*>(xrow[rb] + (int64_t)step * kStepCols);
+            b.x[i][rb][1] = *reinterpret_cast<const PATCH_Q4_GLOBAL q4_u32x4*>(xrow[rb] + (int64_t)step * kStepCols + 32);
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             q4_bytes_ptr base = st.pay[r] + entry_offset(b.e[i][r]);
             const int s = st.s[r];
             b.sc[i][r] = st.scl[r][(step / KPT) * 16];
-            if (!entry_sparse(b.e[i][r])) {
-                b.d[i][r] = *reinterpret_cast<const PATCH_Q4_GLOBAL q4_u32x2*>(base + (size_t)(s * KPT + j) * 512 + lane * 8);
-            } else {
-                b.d[i][r][0] = *reinterpret_cast<const PATCH_Q4_GLOBAL uint32_t*>(base + (size_t)(s * KPT + j) * 256 + lane * 4);
-                b.d[i][r][1] = *reinterpret_cast<q4_u16_ptr>(base + q4_sparse_codes(TILE) + ((s * 64 + lane) * KPT + j) * 2);
-            }
+            // no load is conditional: a dense lane's second dword, a 2:4 lane's dword of positions (mask tile 64: shared with the neighbour)
+            const bool sp = entry_sparse(b.e[i][r]);
+            const int f = s * KPT + j;
+            b.d[i][r][0] = *reinterpret_cast<const PATCH_Q4_GLOBAL uint32_t*>(base + (sp ? f * 256 + lane * 4 : f * 512 + lane * 8));
+            b.d[i][r][1] = *reinterpret_cast<const PATCH_Q4_GLOBAL uint32_t*>(
+                base + (sp ? q4_sparse_codes(TILE) + (TILE == 128 ? (s * 64 + lane) * 4 : (s * 32 + (lane >> 1)) * 4) : f * 512 + lane * 8 + 4));
         }
     }
 }
 
-template <int R, int RB, int NB>
-__device__ __forceinline__ void q4_compute(const Q4Batch<R, RB, NB>& b, q4_f32x4 (&acc)[R][RB], int step0, int end) {
+template <int TILE, int R, int RB, int NB>
+__device__ __forceinline__ void q4_compute(const Q4Batch<R, RB, NB>& b, q4_f32x4 (&acc)[R][RB], int lane, int step0, int end) {
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         if (step0 + i >= end) break;   // uniform
@@ -349,12 +349,13 @@ __device__ __forceinline__ void q4_compute(const Q4Batch<R, RB, NB>& b, q4_f32x4
             } else {
                 Q4A a;
                 a.raw = q4_dequant8(b.d[i][r][0], scl);
+                const int pos = (int)(b.d[i][r][1] >> (16 * (TILE == 128 ? (step0 + i) & 1 : lane & 1)));
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) {
                     Q4B x;
                     x.raw[0] = b.x[i][rb][0];
                     x.raw[1] = b.x[i][rb][1];
-                    acc[r][rb] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(a.v, x.v, acc[r][rb], (int)b.d[i][r][1], 0, 0);
+                    acc[r][rb] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(a.v, x.v, acc[r][rb], pos, 0, 0);
                 }
             }
         }
@@ -431,7 +432,7 @@ __global__ __launch_bounds__(64 * q4_max_waves(R, RB)) void decode4_kernel(const
                                                        const SetT set) {
     constexpr bool kOne = sizeof(SetT) == sizeof(Q4One);
     constexpr int KPT = TILE / kStepCols, SPT = TILE / kStripRows;
-    constexpr int NB = RB > 1 ? 1 : 2;   // steps per batch
+    constexpr int NB = RB > 1 || R > 1 ? 1 : 2;   // steps per batch
     constexpr int CH = R * RB < 8 ? R * RB : 8;   // items per round of the final reduction
     __shared__ q4_f32x4 red[CH][q4_max_waves(R, RB)][64];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -461,12 +462,11 @@ __global__ __launch_bounds__(64 * q4_max_waves(R, RB)) void decode4_kernel(const
     }
     const int total = Tk * KPT, per = (total + KW - 1) / KW;
     const int begin = w * per, end = begin + per < total ? begin + per : total;
-    bool xvalid[RB];
     q4_u16_ptr xrow[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-        xvalid[rb] = 16 * rb + col < rows;
-        xrow[rb] = reinterpret_cast<q4_u16_ptr>(reinterpret_cast<uintptr_t>(X)) + (m0 + (xvalid[rb] ? 16 * rb + col : 0)) * K + 8 * q;
+        const int m = 16 * rb + col < rows ? 16 * rb + col : rows - 1;   // columns without a row: any valid row, not stored
+        xrow[rb] = reinterpret_cast<q4_u16_ptr>(reinterpret_cast<uintptr_t>(X)) + (m0 + m) * K + 8 * q;
     }
     q4_f32x4 acc[R][RB];
 #pragma unroll
@@ -474,14 +474,40 @@ __global__ __launch_bounds__(64 * q4_max_waves(R, RB)) void decode4_kernel(const
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) acc[r][rb] = q4_f32x4{0.f, 0.f, 0.f, 0.f};
     if (begin < end) {
+        // Two batches alternate, one requested before the one in front of it is multiplied, table entries two batches further ahead.  No load is
+        // conditional - behind a branch the compiler waits for the loads of either arm, i.e. for the batch just requested - so the last one or
+        // two batches are written out.  (With conditional loads, f = 1/2: two 13824 x 5120 at 24 rows 39.4 -> 33.6 us here, three 896 x 896 at 16 / 40
+        // rows 3.9 / 5.7 -> 3.4 / 4.8, 4096 x 11008 at 16 rows 17.1 -> 16.0.)
         Q4Batch<R, RB, NB> b0, b1;
-        q4_loads<TILE, R, RB, NB>(b0, st, xrow, xvalid, lane, begin, end - 1);
-        for (int step0 = begin; step0 < end; step0 += 2 * NB) {
-            const bool have1 = step0 + NB < end, have2 = step0 + 2 * NB < end;   // uniform
-            if (have1) q4_loads<TILE, R, RB, NB>(b1, st, xrow, xvalid, lane, step0 + NB, end - 1);
-            q4_compute<R, RB, NB>(b0, acc, step0, end);
-            if (have2) q4_loads<TILE, R, RB, NB>(b0, st, xrow, xvalid, lane, step0 + 2 * NB, end - 1);
-            if (have1) q4_compute<R, RB, NB>(b1, acc, step0 + NB, end);
+        uint32_t e2[NB][R], e3[NB][R];
+        auto take = [&](uint32_t (&to)[NB][R], const uint32_t (&from)[NB][R]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int r = 0; r < R; ++r) to[i][r] = from[i][r];
+        };
+        q4_entries<TILE, R, NB>(b0.e, st, begin, end - 1);
+        q4_entries<TILE, R, NB>(b1.e, st, begin + NB, end - 1);
+        q4_entries<TILE, R, NB>(e2, st, begin + 2 * NB, end - 1);
+        q4_entries<TILE, R, NB>(e3, st, begin + 3 * NB, end - 1);
+        q4_loads<TILE, R, RB, NB>(b0, st, xrow, lane, begin, end - 1);
+        int step0 = begin;
+        for (; step0 + 2 * NB < end; step0 += 2 * NB) {
+            q4_loads<TILE, R, RB, NB>(b1, st, xrow, lane, step0 + NB, end - 1);
+            q4_compute<TILE, R, RB, NB>(b0, acc, lane, step0, end);
+            take(b0.e, e2);
+            q4_entries<TILE, R, NB>(e2, st, step0 + 4 * NB, end - 1);
+            q4_loads<TILE, R, RB, NB>(b0, st, xrow, lane, step0 + 2 * NB, end - 1);
+            q4_compute<TILE, R, RB, NB>(b1, acc, lane, step0 + NB, end);
+            take(b1.e, e3);
+            q4_entries<TILE, R, NB>(e3, st, step0 + 5 * NB, end - 1);
+        }
+        if (step0 + NB < end) {
+            q4_loads<TILE, R, RB, NB>(b1, st, xrow, lane, step0 + NB, end - 1);
+            q4_compute<TILE, R, RB, NB>(b0, acc, lane, step0, end);
+            q4_compute<TILE, R, RB, NB>(b1, acc, lane, step0 + NB, end);
+        } else {
+            q4_compute<TILE, R, RB, NB>(b0, acc, lane, step0, end);
         }
     }
     // Partial sums meet in LDS, CH (strip, row block) items at a time (all of them unless R RB > 8): wavefront w adds
@@ -499,11 +525,7 @@ __global__ __launch_bounds__(64 * q4_max_waves(R, RB)) void decode4_kernel(const
             const int item = c0 + i0, gw = g0 + item / RB, wrb = item % RB;
             if (gw >= total_strips) break;
             const Q4Weight wy = q4_weight_of(set, gw);
-            q4_f32x4 sum = red[i0][0][lane];
-            for (int i = 1; i < KW; ++i) {
-                const q4_f32x4 v = red[i0][i][lane];
-                sum[0] += v[0]; sum[1] += v[1]; sum[2] += v[2]; sum[3] += v[3];
-            }
+            const q4_f32x4 sum = sum_in_order(KW, [&](int i) { return red[i0][i][lane]; });
             PATCH_Q4_GLOBAL float* Yg = reinterpret_cast<PATCH_Q4_GLOBAL float*>(wy.Y);
             if (16 * wrb + col < rows)
                 *reinterpret_cast<PATCH_Q4_GLOBAL q4_f32x4*>(Yg + (m0 + 16 * wrb + col) * wy.N + (int64_t)(gw - wy.first) * 16 + 4 * q) = sum;
@@ -517,7 +539,7 @@ static void launch_decode4(const uint16_t* X, int64_t m0, int rows, int64_t K, i
                        set);
 }
 
-// up to 3 strips per workgroup with one or four blocks of 16 rows, up to 4 with two
+// up to 3 strips per workgroup, up to 4 with two blocks of 16 rows
 template <int TILE, typename SetT>
 static void launch_decode4_r(int R, int RB, const uint16_t* X, int64_t m0, int rows, int64_t K, int Tk, const SetT& set, int groups, int kw,
                              hipStream_t s) {
@@ -525,11 +547,223 @@ static void launch_decode4_r(int R, int RB, const uint16_t* X, int64_t m0, int r
     if (R == r && RB == rb) return launch_decode4<TILE, r, rb, SetT>(X, m0, rows, K, Tk, set, groups, kw, s)
     PATCH_Q4_CASE(1, 1); PATCH_Q4_CASE(2, 1); PATCH_Q4_CASE(3, 1);
     PATCH_Q4_CASE(1, 2); PATCH_Q4_CASE(2, 2); PATCH_Q4_CASE(3, 2); PATCH_Q4_CASE(4, 2);
+    PATCH_Q4_CASE(1, 3); PATCH_Q4_CASE(2, 3); PATCH_Q4_CASE(3, 3);
     PATCH_Q4_CASE(1, 4); PATCH_Q4_CASE(2, 4); PATCH_Q4_CASE(3, 4);
 #undef PATCH_Q4_CASE
 }
 
-// Strips per workgroup for a pass of `rows` rows over `strips` strips: the R that minimises an estimate of the pass,
+// ---- the same for mask tile 128 and up to 8 rows, a whole tile (128 columns) of a strip at a time
+//
+// What bounds a launch of so few rows is requests and their latency, not bytes: per 64-column step the kernel above issues a load of codes,
+// one of scales, one of positions and two of X.  Here a lane takes what lies side by side in the strip's stored codes - its 16 (2:4: 8)
+// bytes hold rows 2 a and 2 a + 1 of one K-step, a = lane % 8 - so that a tile is two loads of codes (2:4: codes, positions) and one of
+// scales.  The matrix instructions then see
+//     A (weights), lane 16 g + r:  row 2 (r % 8) + c of the strip, K-step r / 8, k = 8 g + e (+ 32: second operand; 2:4: 16 g ..)
+//     B (X), lane 16 g + n:        row n / 2 of X, K-step n % 2
+//     D, row r, column n:          a partial sum of output (2 (r % 8) + c, n / 2) where n % 2 = r / 8 (the other half is not used)
+// once for c = 0 and once for c = 1: as many instructions as before, with the 16 columns holding two K-steps of 8 rows instead of one of 16.
+// With at most 4 rows the other 8 columns hold the X of the next tile, turned into place before use (a DPP move per register).
+// f = 1/2, one row, decode4_kernel with conditional loads -> this kernel, us: three 4096 x 4096 11.8 -> 8.7, 4096 x 4096 5.3 -> 4.9, two
+// 11008 x 4096 18.9 -> 13.5, 4096 x 11008 11.5 -> 8.6, two 13824 x 5120 27.1 -> 19.8.  What is left is the conversion (2.7 vector
+// instructions a weight; a build without it 1.9 us faster on two 11008 x 4096), position and scale loads (1.8 and 0.9) and X (0.7).  Four tiles
+// in flight instead of two gained nothing.
+template <int R>
+struct Q4Tile {
+    uint32_t e[R];
+    q4_pair_t d0[R];          // dense: row 2 a (two operands); 2:4: kept codes of rows 2 a, 2 a + 1
+    q4_pair_t d1[R];          // dense: row 2 a + 1; 2:4: positions of the two rows, both K-steps
+    uint32_t sc[R];           // scales of the two rows
+};
+
+template <int R>
+__device__ __forceinline__ void q4_tile_loads(Q4Tile<R>& b, const Q4Strips<R>& st, uint32_t vcode, uint32_t vpos, int t) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const bool sp = entry_sparse(b.e[r]);
+        const q4_bytes_ptr base = st.pay[r] + entry_offset(b.e[r]) + st.s[r] * (sp ? 512 : 1024);
+        b.d0[r] = __builtin_nontemporal_load(reinterpret_cast<const PATCH_Q4_GLOBAL q4_pair_t*>(base + (vcode >> (sp ? 1 : 0))));
+        b.d1[r] = __builtin_nontemporal_load(reinterpret_cast<const PATCH_Q4_GLOBAL q4_pair_t*>(base + (sp ? q4_sparse_codes(128) - st.s[r] * 256 + vpos : 8 + vcode)));
+        b.sc[r] = *reinterpret_cast<const PATCH_Q4_GLOBAL uint32_t*>(st.scl[r] + t * 16);
+    }
+}
+
+// dst[lane] = v[lane + 8] within each row of 16 lanes
+__device__ __forceinline__ q4_u32x4 q4_rows_up8(q4_u32x4 v) {
+    q4_u32x4 r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v[i], 0x128, 0xF, 0xF, false);   // row_ror:8
+    return r;
+}
+
+template <int R>
+__device__ __forceinline__ void q4_tile_compute(const Q4Tile<R>& b, const Q4B& x, q4_f32x4 (&acc)[R][2], int jshift) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const float s0 = __uint_as_float(b.sc[r] << 16), s1 = __uint_as_float(b.sc[r] & 0xFFFF0000u);
+        if (!entry_sparse(b.e[r])) {
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                Q4A a0, a1;
+                a0.raw = q4_dequant8(c ? b.d1[r][0] : b.d0[r][0], c ? s1 : s0);
+                a1.raw = q4_dequant8(c ? b.d1[r][1] : b.d0[r][1], c ? s1 : s0);
+                acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0.v, x.h[0], acc[r][c], 0, 0, 0);
+                acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1.v, x.h[1], acc[r][c], 0, 0, 0);
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                Q4A a;
+                a.raw = q4_dequant8(b.d0[r][c], c ? s1 : s0);
+                acc[r][c] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(a.v, x.v, acc[r][c], (int)(b.d1[r][c] >> jshift), 0, 0);
+            }
+        }
+    }
+}
+
+constexpr int kQ4TileWaves = 16;
+
+// At most XR = 4 or 8 rows of X
+template <int R, int XR, typename SetT>
+__global__ __launch_bounds__(64 * kQ4TileWaves) void decode4_tile_kernel(const uint16_t* __restrict__ X, int64_t m0, int rows, int64_t K, int Tk, int KW, int per,
+                                                                         const SetT set) {
+    constexpr bool kOne = sizeof(SetT) == sizeof(Q4One);
+    constexpr int SPT = 128 / kStripRows;
+    constexpr int XT = XR == 4 ? 2 : 1;   // tiles per X load
+    __shared__ q4_f32x4 red[R][kQ4TileWaves][64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int a = lane & 7, j = (lane >> 3) & 1, g = lane >> 4, n = lane & 15;
+    int total_strips;
+    if constexpr (kOne) total_strips = (int)(set.N / kStripRows);
+    else total_strips = set.total;
+    const int g0 = (int)blockIdx.x * R;
+    Q4Strips<R> st;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int gs = g0 + r < total_strips ? g0 + r : total_strips - 1;   // a strip past the end repeats the last one (not stored)
+        const Q4Weight wt = q4_weight_of(set, gs);
+        PATCH_Q4_ARGS_NOW("s"(wt.payload), "s"(wt.scales), "s"(wt.table), "s"(wt.first));
+        const int strip = gs - wt.first;
+        st.row[r] = reinterpret_cast<q4_table_ptr>(wt.table) + (int64_t)(strip / SPT) * Tk;
+        st.pay[r] = reinterpret_cast<q4_bytes_ptr>(wt.payload);
+        st.s[r] = strip % SPT;
+        st.scl[r] = reinterpret_cast<q4_u16_ptr>(wt.scales) + q4_scale_index(strip, Tk, 0, 2 * a);
+    }
+    {
+        const int gw = g0 + (w < R ? w : 0);
+        const Q4Weight wy = q4_weight_of(set, gw < total_strips ? gw : total_strips - 1);
+        PATCH_Q4_ARGS_NOW("s"(X), "s"(m0), "s"(rows), "s"(K), "s"(Tk), "s"(KW), "s"(per), "s"(wy.Y), "s"(wy.N), "s"(wy.first));
+    }
+    const uint32_t vcode = (uint32_t)(j * 32 + g * 8 + a) * 16, vpos = (uint32_t)(16 * g + 2 * a) * 4;
+    const int begin = w * per, end = begin + per < Tk ? begin + per : Tk;   // per = ceil(Tk / KW)
+    const int last = end - 1;
+    // this lane's row of X and tile of a load; columns without a row: any valid row, not stored
+    const int xt = XT == 2 ? n >> 3 : 0;
+    const int xm = (n >> 1) % XR;
+    const q4_bytes_ptr xrow = reinterpret_cast<q4_bytes_ptr>(reinterpret_cast<uintptr_t>(X)) + ((m0 + (xm < rows ? xm : rows - 1)) * K + 64 * (n & 1) + 8 * g) * 2;
+    q4_f32x4 acc[R][2];
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r][0] = acc[r][1] = q4_f32x4{0.f, 0.f, 0.f, 0.f};
+    if (begin < end) {
+        // Two buffers alternate, a tile requested before the one in front of it is multiplied; table entries two tiles further ahead.  No load
+        // is conditional (behind a branch the compiler would wait for the loads of either arm, i.e. for the tile just requested), so the
+        // last one or two tiles are written out.
+        Q4Tile<R> b0, b1;
+        uint32_t e2[R], e3[R];
+        Q4B x0, x1;   // X of b0's and b1's tile, or (XT = 2) of both and of the next two
+        auto entries = [&](uint32_t (&e)[R], int t) __attribute__((always_inline)) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) e[r] = st.row[r][t < last ? t : last];
+        };
+        auto load = [&](Q4Tile<R>& b, int t) __attribute__((always_inline)) { q4_tile_loads<R>(b, st, vcode, vpos, t); };
+        auto load_x = [&](Q4B& x, int t) __attribute__((always_inline)) {
+            if constexpr (XT == 2) t = t + xt < last ? t + xt : last;
+            const int64_t off = (int64_t)t * 256;
+            x.raw[0] = *reinterpret_cast<const PATCH_Q4_GLOBAL q4_u32x4*>(xrow + off);
+            x.raw[1] = *reinterpret_cast<const PATCH_Q4_GLOBAL q4_u32x4*>(xrow + off + 64);
+        };
+        auto second = [&]() __attribute__((always_inline)) {   // b1's tile
+            if constexpr (XT == 2) {
+                Q4B up;
+                up.raw[0] = q4_rows_up8(x0.raw[0]);
+                up.raw[1] = q4_rows_up8(x0.raw[1]);
+                q4_tile_compute<R>(b1, up, acc, 16 * j);
+            } else {
+                q4_tile_compute<R>(b1, x1, acc, 16 * j);
+            }
+        };
+        entries(b0.e, begin);
+        entries(b1.e, begin + 1);
+        entries(e2, begin + 2);
+        entries(e3, begin + 3);
+        load_x(x0, begin);
+        load(b0, begin);
+        int t = begin;
+        for (; t + 2 < end; t += 2) {
+            if constexpr (XT == 1) load_x(x1, t + 1);
+            load(b1, t + 1);
+            q4_tile_compute<R>(b0, x0, acc, 16 * j);
+#pragma unroll
+            for (int r = 0; r < R; ++r) b0.e[r] = e2[r];
+            entries(e2, t + 4);
+            if constexpr (XT == 1) load_x(x0, t + 2);
+            else load_x(x1, t + 2);
+            load(b0, t + 2);
+            second();
+            if constexpr (XT == 2) x0 = x1;
+#pragma unroll
+            for (int r = 0; r < R; ++r) b1.e[r] = e3[r];
+            entries(e3, t + 5);
+        }
+        if (t + 1 < end) {
+            if constexpr (XT == 1) load_x(x1, t + 1);
+            load(b1, t + 1);
+            q4_tile_compute<R>(b0, x0, acc, 16 * j);
+            second();
+        } else {
+            q4_tile_compute<R>(b0, x0, acc, 16 * j);
+        }
+    }
+    // Partial sums meet in LDS, the used half of a product (columns n with n % 2 = row / 8) in 32 places per c; wavefront w adds up
+    // strip w in wavefront order, then the two K-steps, and stores 4 features per lane.
+    if ((n & 1) == (g >> 1) && n < 2 * XR)
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) red[r][w][32 * c + 8 * g + (n >> 1)] = acc[r][c];
+    __syncthreads();
+    if (const int gw = g0 + w; w < R && gw < total_strips) {
+        const Q4Weight wy = q4_weight_of(set, gw);
+        // lane 32 c + 16 p + 8 h + m: row m, K-step p, features 8 h + 2 i + c
+        const int c = lane >> 5, h = (lane >> 3) & 1, m = lane & 7;
+        q4_f32x4 sum = sum_in_order(KW, [&](int i) { return red[w][i][lane]; });
+        q4_f32x4 other;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[i] += __shfl_xor(sum[i], 16);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) other[i] = __shfl_xor(sum[i], 32);
+        const q4_f32x4 out = c == 0 ? q4_f32x4{sum[0], other[0], sum[1], other[1]} : q4_f32x4{other[2], sum[2], other[3], sum[3]};
+        PATCH_Q4_GLOBAL float* Yg = reinterpret_cast<PATCH_Q4_GLOBAL float*>(wy.Y);
+        if (!(lane & 16) && m < rows)
+            *reinterpret_cast<PATCH_Q4_GLOBAL q4_f32x4*>(Yg + (m0 + m) * wy.N + (int64_t)(gw - wy.first) * 16 + 8 * h + 4 * c) = out;
+    }
+}
+
+template <int R, int XR, typename SetT>
+static void launch_decode4_tile(const uint16_t* X, int64_t m0, int rows, int64_t K, int Tk, const SetT& set, int groups, int kw, hipStream_t s) {
+    hipLaunchKernelGGL((decode4_tile_kernel<R, XR, SetT>), dim3((unsigned)groups), dim3((unsigned)(kw * 64)), 0, s, X, m0, rows, K, Tk, kw, (Tk + kw - 1) / kw, set);
+}
+
+template <typename SetT>
+static void launch_decode4_tile_r(int R, int XR, const uint16_t* X, int64_t m0, int rows, int64_t K, int Tk, const SetT& set, int groups, int kw, hipStream_t s) {
+#define PATCH_Q4_CASE(r, xr) \
+    if (R == r && XR == xr) return launch_decode4_tile<r, xr, SetT>(X, m0, rows, K, Tk, set, groups, kw, s)
+    PATCH_Q4_CASE(1, 4); PATCH_Q4_CASE(2, 4); PATCH_Q4_CASE(3, 4);
+    PATCH_Q4_CASE(1, 8); PATCH_Q4_CASE(2, 8); PATCH_Q4_CASE(3, 8);
+#undef PATCH_Q4_CASE
+}
+
+// Strips per workgroup for a pass of `rows` rows over `strips` strips (both kernels): the R that minimises an estimate of the pass,
 //     rounds(workgroups) x (x + R),
 // in units of one strip's share of a wavefront's work.  x is what a workgroup spends on its X operands (it loads all of
 // X whatever R is; fitted: 0.15 + 0.045 rows up to 16 rows, 1.7 for 32, 4.5 for 64 - at 4 bits per weight 64 rows of X
@@ -1100,26 +1334,27 @@ static Q4Shape q4_shape(const patch_packed4* const* P, int count, size_t ws_byte
 }
 
 // A pass of `rows` rows (at most 64) over all weights: the strip kernel or batch4_kernel, and in how many K chunks.  Both are priced, in us with
-// steps = 64-column steps, fitted by row range to launches of 24 weights and 12 sets, both mask tiles, f = 0, 1/2 and 1, 14 row counts (rms
-// error 5 - 8 %; 650 - 4100 launches per line):
+// steps = 64-column steps, fitted by row range to launches of weights and sets, both mask tiles, f = 0, 1/2 and 1 (strip: 21 shapes, 19 row counts, rms
+// error 6 - 9 %; batch: 36 shapes, 14 row counts, 650 - 4100 launches per line, 5 - 8 %):
 //   strip   base + share x (per_strip R + constant + per_row rows) x 0.05 x steps x (1 + sparse (f - 1/2)); R = strips per workgroup, share = workgroups /
 //           compute units where more than one (then x over: they share a compute unit; beyond two 0.2 more), else 1.  (Finer than the estimate R is
 //           chosen by.)
 //   batch   base + (1 + round (rounds - 1)) x steps / chunks x (step + per_row rows) x (1 + fill min(1, workgroups / compute units)) x (tile64 on mask
 //           tile 64: two scales and position loads per unit) x (1 + sparse (f - 1/2)); a split 2.7 for the second launch and its partial sums twice at
-//           5 TB/s; to be worth it 0.8 ahead (up to 8 rows 1)
-// Measured, strip / batch, f = 1/2: gate and up of 4096 / 11008 at 1 / 16 / 32 / 64 rows (17.4 / 19.6, 19.6 / 19.5, 25.8 / 22.5, 41.9 / 28.2), of 5120 / 13824 (26.1 / 23.8,
-// 31.3 / 23.6, 41.8 / 27.7, 78.0 / 35.0); three 4096 x 4096 (9.8 / 19.5, 11.1 / 19.3, 15.9 / 22.0, 22.7 / 27.5); 4096 x 11008 in 8 chunks at 8 / 16 / 40 rows
-// (12.1 / 13.3, 16.4 / 13.9, 29.9 / 17.2).
+//           5 TB/s; to be worth it 0.8 ahead (up to 8 rows 2.5, up to 12 2.2)
+// Measured, strip / batch, f = 1/2, mask tile 128: gate and up of 4096 / 11008 at 1 / 16 / 32 / 64 rows (13.7 / 19.9, 18.6 / 20.1, 24.1 / 22.9, 41.0 / 28.6), of 5120 /
+// 13824 (20.0 / 24.7, 29.2 / 24.3, 36.5 / 28.2, 74.4 / 35.2); three 4096 x 4096 (8.5 / 19.2, 10.9 / 19.4, 14.1 / 22.2, 21.7 / 27.6).
 struct Q4StripPrice { int rows; double base, per_strip, constant, per_row, over, sparse; };
-constexpr Q4StripPrice kQ4StripPrice[] = {{8, 3.0, 0.54, 0.02, 0.031, 1.12, -0.21}, {16, 2.9, 0.48, 0.0, 0.0505, 1.06, -0.15}, {32, 3.4, 0.70, 0.0, 0.0453, 1.12, -0.13}, {64, 3.8, 0.62, 0.0, 0.0557, 1.20, -0.02}};
+constexpr Q4StripPrice kQ4StripPrice[] = {{8, 2.77, 0.651, 0.025, 0.030, 1.02, -0.36}, {16, 2.97, 0.577, -0.03, 0.048, 1.0, -0.27}, {32, 3.09, 0.645, 0.11, 0.047, 1.12, -0.18},
+                                          {48, 3.23, 0.651, 0.33, 0.049, 1.125, -0.11}, {64, 3.46, 0.697, 0.36, 0.052, 1.13, -0.09}};
+constexpr Q4StripPrice kQ4TilePrice = {8, 3.12, 0.541, -0.06, 0.033, 1.04, -0.30};   // decode4_tile_kernel: mask tile 128, up to 8 rows
 struct Q4BatchPrice { int rows; double base, step, per_row, fill, tile64, sparse, round; };
 constexpr Q4BatchPrice kQ4BatchPrice[] = {{16, 2.7, 0.2204, 0.0001, 0.17, 1.12, -0.24, 0.53}, {32, 3.0, 0.2487, 0.0003, 0.15, 1.11, -0.21, 0.57}, {64, 3.6, 0.217, 0.0019, 0.15, 1.10, -0.20, 1.05}};
 
 struct Q4Plan { bool wide; int chunks; double us; };
 static Q4Plan q4_pass_plan(const Q4Shape& d, int rows) {
     const double steps = (double)d.K / kStepCols;
-    const Q4StripPrice* p = kQ4StripPrice;
+    const Q4StripPrice* p = d.tile == 128 && rows <= 8 ? &kQ4TilePrice : kQ4StripPrice;
     while (rows > p->rows) ++p;
     const int R = q4_strips_per_group(d.strips, d.n_cus, rows);
     const double share = (double)((d.strips + R - 1) / R) / d.n_cus;
@@ -1136,7 +1371,7 @@ static Q4Plan q4_pass_plan(const Q4Shape& d, int rows) {
                           (c > 1 ? 2.7 + 2.0 * c * rows * (double)d.N * 4.0 / 5.0e6 : 0.0);
         if (c == 1 || us < wide.us) wide = Q4Plan{true, c, us};
     }
-    return wide.us + (rows <= 8 ? 1.0 : 0.8) < strip.us ? wide : strip;
+    return wide.us + (rows <= 8 ? 2.5 : rows <= 12 ? 2.2 : 0.8) < strip.us ? wide : strip;
 }
 
 static patch_status q4_passes(const void* X, int64_t M, const patch_packed4* const* P, void* const* Y, int count, float* ws, size_t ws_bytes,
@@ -1177,7 +1412,7 @@ static patch_status q4_passes(const void* X, int64_t M, const patch_packed4* con
     }
     wide.count = count;
     const Q4Shape shape = q4_shape(P, count, ws_bytes);
-    // One launch per pass of up to 64 rows (1, 2 or 4 blocks of 16), R strips per workgroup (q4_strips_per_group).
+    // One launch per pass of up to 64 rows, R strips per workgroup (q4_strips_per_group).
     auto run = [&](const auto& set) {
         for (int64_t m0 = 0; m0 < M; m0 += kQ4Rows) {
             const int rows = (int)(M - m0 < kQ4Rows ? M - m0 : kQ4Rows);
@@ -1186,7 +1421,7 @@ static patch_status q4_passes(const void* X, int64_t M, const patch_packed4* con
                 launch_batch4(static_cast<const uint16_t*>(X), m0, rows, P0->K, P0->tile, wide, plan.chunks, ws, s);
                 continue;
             }
-            const int RB = rows <= 16 ? 1 : rows <= 32 ? 2 : 4;
+            const int RB = (rows + 15) / 16;
             const int R = q4_strips_per_group(total_strips, P0->n_cus, rows);
             const int groups = (total_strips + R - 1) / R;
             // wavefronts per workgroup: about 4 steps each, at least 4, at most 16 (8 with many registers); with more
@@ -1195,7 +1430,15 @@ static patch_status q4_passes(const void* X, int64_t M, const patch_packed4* con
             int kw = (total + 3) / 4;
             if (kw > q4_max_waves(R, RB)) kw = q4_max_waves(R, RB);
             if (groups > P0->n_cus && kw > 8) kw = 8;
-            if (kw < 4) kw = 4;
+            kw = (kw + 3) / 4 * 4;   // sum_in_order
+            if (P0->tile == 128 && rows <= 8) {
+                // wavefronts per workgroup: 16 per compute unit in one, two or more workgroups, at least two tiles each (22 shapes, 5 row counts, f = 0, 1/2, 1:
+                // 1.7 % behind the best of 15 pairs of strips and wavefronts on average, 10 % at most)
+                int kw = groups <= P0->n_cus ? 16 : groups <= 2 * P0->n_cus ? 8 : 4;
+                while (kw > 4 && 2 * kw > P0->Tk) kw /= 2;
+                launch_decode4_tile_r(R, rows <= 4 ? 4 : 8, static_cast<const uint16_t*>(X), m0, rows, P0->K, P0->Tk, set, groups, kw, s);
+                continue;
+            }
             if (P0->tile == 128) launch_decode4_r<128>(R, RB, static_cast<const uint16_t*>(X), m0, rows, P0->K, P0->Tk, set, groups, kw, s);
             else launch_decode4_r<64>(R, RB, static_cast<const uint16_t*>(X), m0, rows, P0->K, P0->Tk, set, groups, kw, s);
         }
