@@ -405,37 +405,50 @@ constexpr PassPrice kMidPrice[] = {{16, 2.6, 0.120, 0.0017, 0.47, 1.5, -0.45}, {
 constexpr PassPrice kBatchPrice[] = {{16, 2.4, 0.257, 0.0005, 0.39, 0.0, -0.30}, {32, 2.7, 0.244, 0.0012, 0.40, 0.8, -0.29}, {64, 3.2, 0.237, 0.0017, 0.31, 3.2, -0.20},
                                      {80, 3.7, 0.392, 0.0005, 0.14, 4.0, 0.0},   {96, 4.1, 0.452, 0.0004, 0.10, 4.0, 0.03},  {128, 4.7, 0.570, 0.0004, 0.10, 4.0, 0.03}};
 
-struct DecodePlan { int kernel, chunks; double us; };   // kernel: 0 strip, 1 mid, 2 batch
+struct DecodePlan { int kernel, chunks; double us; int deal = 1; };   // kernel: 0 strip, 1 mid, 2 batch; rows dealt over up to `deal` workgroups (rows_each)
 struct DecodeShape { int64_t N; int strips, groups64, groups128; size_t payload; int count; };   // of a weight or a whole set
 
-static double pass_us(const PassPrice* p, const GemmArgs& a, const DecodeShape& d, int rows, int groups, int chunks, double second) {
+static double pass_us(const PassPrice* p, const GemmArgs& a, const DecodeShape& d, int all_rows, int deal, int groups, int chunks, double second) {
+    const int rows = rows_each(all_rows, deal);
     while (rows > p->rows) ++p;
-    const int64_t wg = (int64_t)groups * chunks, rounds = (wg + a.n_cus - 1) / a.n_cus;
+    const int64_t wg = (int64_t)groups * chunks * rows_deals(all_rows, rows), rounds = (wg + a.n_cus - 1) / a.n_cus;
     const double fill = wg < a.n_cus ? (double)wg / a.n_cus : 1.0, weights = (double)d.payload / 6.6e6;
     const double t = (double)rounds * a.K / kStepCols / chunks * (p->step + p->per_row * rows) * (1.0 + p->fill * fill) * (1.0 + p->sparse * (0.01 * a.sparse_pct - 0.5));
-    return p->base + p->round * (double)(rounds - 1) + (t > weights ? t : weights) + (chunks > 1 ? second + 2.0 * chunks * rows * (double)d.N * 4.0 / 5.0e6 : 0.0);
+    return p->base + p->round * (double)(rounds - 1) + (t > weights ? t : weights) + (chunks > 1 ? second + 2.0 * chunks * all_rows * (double)d.N * 4.0 / 5.0e6 : 0.0);
 }
 
-// The cheapest of the three; up to 7 rows (11 for a single weight) always the strip kernel, whose X is small then.  mid_kernel has to be 0.3 us ahead,
-// batch_kernel 0.7.  only_wide: batch_kernel, in its best number of chunks.
+// The cheapest of the three; up to 7 rows (11 for a single weight) always the strip kernel, whose X is small then.  mid_kernel has to be 0.3 us ahead
+// of it, batch_kernel 0.7 of both; of the strip kernel with its rows dealt (below) mid_kernel may be 0.15 behind.  only_wide: batch_kernel, in its best number of chunks.
+// In a call of 17 .. 64 rows the strip kernel and mid_kernel may deal the blocks of 16 rows over 2 or 4 workgroups per feature group: a weight of few groups leaves compute units idle
+// while each of its workgroups draws all of X.  What is read twice is the weight, from the L2s.  The same prices hold (540 combinations of 15 weights
+// and sets, both mask tiles, f = 0, 1/2 and 1, 17 - 64 rows: 12 % faster on average than undealt, 3 % behind the best of all kernels,
+// deals and chunks, 4 cells 4 - 8 % behind the undealt choice; batch_kernel dealt as well gained another 0.4 %).  f = 1/2, mask tile 128, 64 rows, undealt -> dealt: three 896 x 896 6.5 -> 5.3, 896 x 4864
+// (8 chunks) 12.3 -> 8.2 in one launch, 4096 x 4096 14.7 -> 11.2, three 2048 x 2048 13.3 -> 10.0 us.
 static DecodePlan decode_plan(const GemmArgs& a, const DecodeShape& d, int rows, bool only_wide = false) {
     DecodePlan best = {0, 1, 0.0};
     if (!only_wide) {
-        best.us = pass_us(kStripPrice, a, d, rows, d.strips, 1, 0.0);
+        best.us = pass_us(kStripPrice, a, d, rows, 1, d.strips, 1, 0.0);
         if (rows < (d.count > 1 ? 8 : 12)) return best;
-        const auto mid = [&](int chunks) {
-            const double t = pass_us(kMidPrice, a, d, rows, d.groups64, chunks, 2.2);
-            if (t + 0.3 < best.us) best = DecodePlan{1, chunks, t};
-        };
-        mid(1);
-        if (const int c = d.count == 1 && rows > 16 ? mid_split(a, rows, 0) : 1; c > 1) mid(c);
+        for (int deal = 1, last = 0; deal <= 4; deal *= 2) {
+            const int each = rows_each(rows, deal);
+            if (deal > 1 && (rows <= 16 || a.M > kDecodeRows || each == last)) break;
+            last = each;
+            const auto take = [&](int kernel, int chunks, double us, double ahead) {
+                if (us + ahead < best.us) { best = DecodePlan{kernel, chunks, us}; best.deal = deal; }
+            };
+            if (deal > 1) take(0, 1, pass_us(kStripPrice, a, d, rows, deal, d.strips, 1, 0.0), 0.0);
+            const auto ahead = [&]() { return best.kernel != 0 ? 0.0 : best.deal == 1 ? 0.3 : -0.15; };
+            take(1, 1, pass_us(kMidPrice, a, d, rows, deal, d.groups64, 1, 2.2), ahead());
+            if (const int c = d.count == 1 && rows > 16 ? mid_split(a, rows, 0, (int)rows_deals(rows, each)) : 1; c > 1)
+                take(1, c, pass_us(kMidPrice, a, d, rows, deal, d.groups64, c, 2.2), ahead());
+        }
     }
     // (at most 8 chunks of at least four units of 128 columns; beyond one workgroup per compute unit a split only adds partial sums)
     const size_t per_chunk = (size_t)rows * (size_t)d.N * sizeof(float);
     const int fit = a.ws ? (int)(a.ws_bytes / per_chunk < 8 ? a.ws_bytes / per_chunk : 8) : 1;
-    DecodePlan wide = {2, 1, pass_us(kBatchPrice, a, d, rows, d.groups128, 1, 0.0)};
+    DecodePlan wide = {2, 1, pass_us(kBatchPrice, a, d, rows, 1, d.groups128, 1, 0.0)};
     for (int c = 2; c <= fit && d.groups128 * c <= a.n_cus && c * 512 <= a.K; ++c) {
-        const double t = pass_us(kBatchPrice, a, d, rows, d.groups128, c, 2.7);
+        const double t = pass_us(kBatchPrice, a, d, rows, 1, d.groups128, c, 2.7);
         if (t < wide.us) wide = DecodePlan{2, c, t};
     }
     return only_wide || wide.us + 0.7 < best.us ? wide : best;
@@ -531,9 +544,10 @@ int patch_test_schedule(int64_t M, int count, const int64_t* N, int64_t K, int t
     if (M > 8 * kDecodeRows) return -1;
     int n = 0;
     for (int64_t m0 = 0; m0 < M; m0 += kDecodeRows, ++n) {
-        const DecodePlan plan = decode_plan(a, d, (int)(M - m0 < kDecodeRows ? M - m0 : kDecodeRows));
+        const int rows = (int)(M - m0 < kDecodeRows ? M - m0 : kDecodeRows);
+        const DecodePlan plan = decode_plan(a, d, rows);
         kernel[n] = plan.kernel;
-        chunks[n] = plan.chunks;
+        chunks[n] = plan.chunks * (int)rows_deals(rows, rows_each(rows, plan.deal));
     }
     return n;
 }
@@ -580,8 +594,8 @@ patch_status patch_gemm_ex(const void* X, int64_t M, const patch_packed* P, void
             else if (variant == 0 && split_k == 0) plan = decode_plan(a, d, rows);
             one.units = plan.kernel == 2 ? d.groups128 : d.groups64;
             if (plan.kernel == 2) launch_batch_set(a, one, m0, rows, plan.chunks, s);
-            else if (plan.kernel == 1) launch_mid_set(a, one, m0, rows, plan.chunks, s);
-            else launch_decode(a, m0, rows, split_k, variant, s);
+            else if (plan.kernel == 1) launch_mid_set(a, one, m0, rows, plan.chunks, s, plan.deal);
+            else launch_decode(a, m0, rows, split_k, variant, s, plan.deal);
         }
     } else {
         launch_prefill(a, variant, split_k, s);
@@ -968,8 +982,8 @@ patch_status patch_gemm_many(const void* X, int64_t M, const patch_packed* const
         else if (variant == 7) plan = batch_plan(a, d, rows, split_k);
         else if (variant == 0 && split_k == 0) plan = decode_plan(a, d, rows);
         if (plan.kernel == 2) launch_batch_set(a, wide128, m0, rows, plan.chunks, s);
-        else if (plan.kernel == 1) launch_mid_set(a, wide64, m0, rows, 1, s);
-        else launch_decode_set(a, set, m0, rows, split_k, variant, s);
+        else if (plan.kernel == 1) launch_mid_set(a, wide64, m0, rows, 1, s, plan.deal);
+        else launch_decode_set(a, set, m0, rows, split_k, variant, s, plan.deal);
     }
     HIP_TRY(hipGetLastError());
     return PATCH_OK;

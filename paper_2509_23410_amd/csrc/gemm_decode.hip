@@ -86,6 +86,9 @@ __global__ __launch_bounds__(MAXW * 64) void decode_kernel(const uint16_t* __res
     constexpr int SPL = kWide ? 8 / XR : 1;               // steps served by one X load
     constexpr int NL = kWide ? (NK + SPL - 1) / SPL : 1;   // X loads per pass
     __shared__ f32x4 red[MAXW][RB][64];
+    // rows dealt over gridDim.z workgroups (launch_decode_set)
+    m0 += 16 * RB * (int64_t)blockIdx.z;
+    rows -= 16 * RB * (int)blockIdx.z;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -342,24 +345,25 @@ __global__ __launch_bounds__(MAXW * 64) void decode_kernel(const uint16_t* __res
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) red[w][rb][lane] = acc[rb];
     __syncthreads();
-    if (w == 0) {
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            f32x4 sum = red[0][rb][lane];
-            for (int i = 1; i < KW; ++i) {
-                const f32x4 v = red[i][rb][lane];
-                sum[0] += v[0]; sum[1] += v[1]; sum[2] += v[2]; sum[3] += v[3];
-            }
-            if (16 * rb + col < rows) store4(Y, (m0 + 16 * rb + col) * N + (int64_t)strip * 16 + 4 * q, sum, ybf16);
+    // row block rb: wavefront rb (the first one where there are fewer)
+    for (int rb = w; rb < RB; rb += KW) {
+        f32x4 sum;
+        if ((KW & 3) == 0) {
+            sum = sum_in_order(KW, [&](int i) { return red[i][rb][lane]; });
+        } else {
+            sum = red[0][rb][lane];
+            for (int i = 1; i < KW; ++i) sum = sum + red[i][rb][lane];
         }
+        if (16 * rb + col < rows) store4(Y, (m0 + 16 * rb + col) * N + (int64_t)strip * 16 + 4 * q, sum, ybf16);
     }
 }
 
 template <int TILE, typename SetT>
-static void launch_decode_s(const GemmArgs& a, const SetT& set, int units, int64_t m0, int rows, int nk, int kw, int xr, hipStream_t stream) {
-    dim3 grid((unsigned)units), block((unsigned)(kw * 64));
-    if (rows > 32) hipLaunchKernelGGL((decode_kernel<TILE, 4, 8, 4, SetT>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
-    else if (rows > 16) hipLaunchKernelGGL((decode_kernel<TILE, 4, 8, 2, SetT>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
+static void launch_decode_s(const GemmArgs& a, const SetT& set, int units, int64_t m0, int rows, int deal, int nk, int kw, int xr, hipStream_t stream) {
+    const int each = rows_each(rows, deal);
+    dim3 grid((unsigned)units, 1, rows_deals(rows, each)), block((unsigned)(kw * 64));
+    if (each > 32) hipLaunchKernelGGL((decode_kernel<TILE, 4, 8, 4, SetT>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
+    else if (each > 16) hipLaunchKernelGGL((decode_kernel<TILE, 4, 8, 2, SetT>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
     else if (xr == 16 && nk == 8) hipLaunchKernelGGL((decode_kernel<TILE, 8, 8, 1, SetT>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
     else if (xr == 16) hipLaunchKernelGGL((decode_kernel<TILE, 4, 16, 1, SetT>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
 #define PATCH_DECODE_WIDE(XR_)                                                                                                               \
@@ -374,12 +378,12 @@ static void launch_decode_s(const GemmArgs& a, const SetT& set, int units, int64
 }
 
 template <int TILE>
-static void launch_decode_t(const GemmArgs& a, const DecodeSet& set, int64_t m0, int rows, int nk, int kw, int xr, hipStream_t stream) {
+static void launch_decode_t(const GemmArgs& a, const DecodeSet& set, int64_t m0, int rows, int deal, int nk, int kw, int xr, hipStream_t stream) {
     if (set.count == 1) {
         const WeightOne one = {set.payload[0], set.table[0], set.Y[0], set.N[0]};
-        launch_decode_s<TILE>(a, one, set.units, m0, rows, nk, kw, xr, stream);
+        launch_decode_s<TILE>(a, one, set.units, m0, rows, deal, nk, kw, xr, stream);
     } else {
-        launch_decode_s<TILE>(a, set, set.units, m0, rows, nk, kw, xr, stream);
+        launch_decode_s<TILE>(a, set, set.units, m0, rows, deal, nk, kw, xr, stream);
     }
 }
 
@@ -392,7 +396,7 @@ static void launch_decode_t(const GemmArgs& a, const DecodeSet& set, int64_t m0,
 //   about one workgroup per compute unit and a long K (>= 128 steps): NK = 4, KW = 16 - more, shorter passes per
 //     wavefront (4096 x 11008: 16.3 vs 17.7 us);
 //   else NK = 8 if that still leaves about four wavefronts per compute unit, else 4.
-int launch_decode(const GemmArgs& a, int64_t m0, int rows, int split_k, int variant, hipStream_t stream) {
+int launch_decode(const GemmArgs& a, int64_t m0, int rows, int split_k, int variant, hipStream_t stream, int deal) {
     DecodeSet set = {};
     set.payload[0] = a.payload;
     set.table[0] = a.table;
@@ -400,18 +404,19 @@ int launch_decode(const GemmArgs& a, int64_t m0, int rows, int split_k, int vari
     set.N[0] = a.N;
     set.count = 1;
     set.units = (int)(a.N / 16);
-    return launch_decode_set(a, set, m0, rows, split_k, variant, stream);
+    return launch_decode_set(a, set, m0, rows, split_k, variant, stream, deal);
 }
 
-int launch_decode_set(const GemmArgs& a, const DecodeSet& set, int64_t m0, int rows, int split_k, int variant, hipStream_t stream) {
-    const int64_t strips = set.units;
+int launch_decode_set(const GemmArgs& a, const DecodeSet& set, int64_t m0, int rows, int split_k, int variant, hipStream_t stream, int deal) {
+    const int each = rows_each(rows, deal);
+    const int64_t strips = (int64_t)set.units * rows_deals(rows, each);
     const int total = a.Tk * (a.tile / kStepCols);
     int nk = 0;
     if (variant == 2) nk = 8;
     else if (variant == 3) nk = 4;
     if (nk == 0 && split_k > 0) nk = ((total + split_k - 1) / split_k > 4) ? 8 : 4;
     int kw_default = 0;
-    if (nk == 0 && rows <= 16) {
+    if (nk == 0 && each <= 16) {
         if (strips >= 2 * (int64_t)a.n_cus) { nk = 8; kw_default = 4; }
         else if (total >= 128) nk = 4;
     }
@@ -420,8 +425,8 @@ int launch_decode_set(const GemmArgs& a, const DecodeSet& set, int64_t m0, int r
         if (kw8 > 8) kw8 = 8;
         nk = (strips * kw8 >= (int64_t)a.n_cus * 4) ? 8 : 4;
     }
-    if (rows > 16) nk = 4;   // 17 .. 64 rows: 4 steps and 8 wavefronts (registers hold X for up to four row blocks)
-    const int maxw = (nk == 4 && rows <= 16) ? 16 : 8;
+    if (each > 16) nk = 4;   // 17 .. 64 rows: 4 steps and 8 wavefronts (registers hold X for up to four row blocks)
+    const int maxw = (nk == 4 && each <= 16) ? 16 : 8;
     int kw = split_k > 0 ? split_k : kw_default > 0 ? kw_default : (total + nk - 1) / nk;
     if (kw > maxw) kw = maxw;
     if (kw < 1) kw = 1;
@@ -431,8 +436,8 @@ int launch_decode_set(const GemmArgs& a, const DecodeSet& set, int64_t m0, int r
     // keeps the two loads per step, variant 6 asks for the new schedule whatever the map.
     const bool wide = rows <= 8 && variant != 5 && (variant == 6 || a.sparse_pct >= 25);
     const int xr = !wide ? 16 : rows == 1 ? 1 : rows <= 4 ? 4 : 8;
-    if (a.tile == 128) launch_decode_t<128>(a, set, m0, rows, nk, kw, xr, stream);
-    else launch_decode_t<64>(a, set, m0, rows, nk, kw, xr, stream);
+    if (a.tile == 128) launch_decode_t<128>(a, set, m0, rows, deal, nk, kw, xr, stream);
+    else launch_decode_t<64>(a, set, m0, rows, deal, nk, kw, xr, stream);
     return kw;
 }
 

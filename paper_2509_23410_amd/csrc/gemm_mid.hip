@@ -50,6 +50,10 @@ __global__ __launch_bounds__(kMidKW * 64) __attribute__((amdgpu_waves_per_eu(2, 
     constexpr int SB = kMidSB, NK = kMidNK, KW = kMidKW;
     constexpr int KH = KW / 2;
     __shared__ mid_f32x4 red[KH][SB * RB][64];  // 64 KB at RB = 4: half of the wavefronts at a time
+    // rows dealt over gridDim.z workgroups
+    const int all_rows = rows, row0 = 16 * RB * (int)blockIdx.z;
+    m0 += row0;
+    rows -= row0;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -240,7 +244,7 @@ __global__ __launch_bounds__(kMidKW * 64) __attribute__((amdgpu_waves_per_eu(2, 
     }
     __syncthreads();
     // SPLIT: Y is the workspace, slices of rows x N fp32; else row m0 of Y (fp32 or bf16 elements)
-    float* dst = SPLIT ? Y + (int64_t)blockIdx.y * rows * N : ybf16 ? reinterpret_cast<float*>(reinterpret_cast<uint16_t*>(Y) + m0 * N) : Y + m0 * N;
+    float* dst = SPLIT ? Y + ((int64_t)blockIdx.y * all_rows + row0) * N : ybf16 ? reinterpret_cast<float*>(reinterpret_cast<uint16_t*>(Y) + m0 * N) : Y + m0 * N;
     for (int t = w; t < SB * RB; t += KW) {
         const int sb = t / RB, rb = t % RB;
         mid_f32x4 sum = red[0][t][lane];
@@ -254,11 +258,11 @@ __global__ __launch_bounds__(kMidKW * 64) __attribute__((amdgpu_waves_per_eu(2, 
     }
 }
 
-// K-chunks per 64-feature group: as many as bring the workgroup count closest to one per compute unit, each at
+// K-chunks per 64-feature group (whose rows are dealt over `deals` workgroups): as many as bring the workgroup count closest to one per compute unit, each at
 // least two tiles long, at most 8, and no more than the workspace a.ws holds partial sums for (rows x N fp32 each).
 // 1 = no split (no workspace needed).
-int mid_split(const GemmArgs& a, int rows, int requested) {
-    const int64_t groups = a.N / 64;
+int mid_split(const GemmArgs& a, int rows, int requested, int deals) {
+    const int64_t groups = a.N / 64 * deals;
     int s = requested;
     if (s <= 0) {
         s = (int)((a.n_cus + groups / 2) / groups);
@@ -276,31 +280,32 @@ int mid_split(const GemmArgs& a, int rows, int requested) {
 }
 
 template <int TILE>
-static void launch_mid_t(const GemmArgs& a, const WeightSet& set, int64_t m0, int rows, int split, hipStream_t stream) {
+static void launch_mid_t(const GemmArgs& a, const WeightSet& set, int64_t m0, int rows, int split, int deal, hipStream_t stream) {
     const dim3 block(kMidKW * 64);
+    const int each = rows_each(rows, deal);
     if (split > 1) {
         WeightSet part = set;
         part.Y[0] = a.ws;
-        const dim3 grid((unsigned)set.units, (unsigned)split);
-        if (rows <= 16) hipLaunchKernelGGL((mid_kernel<TILE, 1, true>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, part, 0);
-        else if (rows <= 32) hipLaunchKernelGGL((mid_kernel<TILE, 2, true>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, part, 0);
+        const dim3 grid((unsigned)set.units, (unsigned)split, rows_deals(rows, each));
+        if (each <= 16) hipLaunchKernelGGL((mid_kernel<TILE, 1, true>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, part, 0);
+        else if (each <= 32) hipLaunchKernelGGL((mid_kernel<TILE, 2, true>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, part, 0);
         else hipLaunchKernelGGL((mid_kernel<TILE, 4, true>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, part, 0);
         float* y0 = a.ybf16 ? reinterpret_cast<float*>(reinterpret_cast<uint16_t*>(set.Y[0]) + m0 * set.N[0]) : set.Y[0] + m0 * set.N[0];
         wr_reduce(a.ws, (size_t)rows * (size_t)set.N[0] / 4, split, y0, a.ybf16, stream);
     } else {
-        const dim3 grid((unsigned)set.units);
-        if (rows <= 16) hipLaunchKernelGGL((mid_kernel<TILE, 1, false>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
-        else if (rows <= 32) hipLaunchKernelGGL((mid_kernel<TILE, 2, false>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
+        const dim3 grid((unsigned)set.units, 1, rows_deals(rows, each));
+        if (each <= 16) hipLaunchKernelGGL((mid_kernel<TILE, 1, false>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
+        else if (each <= 32) hipLaunchKernelGGL((mid_kernel<TILE, 2, false>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
         else hipLaunchKernelGGL((mid_kernel<TILE, 4, false>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
     }
 }
 
 // Up to 64 rows of X starting at row m0.  set.units / first[] count 64-feature groups.  A K split (split > 1) needs
 // a single weight and a.ws with room for split x rows x N floats.
-void launch_mid_set(const GemmArgs& a, const WeightSet& set, int64_t m0, int rows, int split, hipStream_t stream) {
+void launch_mid_set(const GemmArgs& a, const WeightSet& set, int64_t m0, int rows, int split, hipStream_t stream, int deal) {
     if (set.count != 1) split = 1;
-    if (a.tile == 128) launch_mid_t<128>(a, set, m0, rows, split, stream);
-    else launch_mid_t<64>(a, set, m0, rows, split, stream);
+    if (a.tile == 128) launch_mid_t<128>(a, set, m0, rows, split, deal, stream);
+    else launch_mid_t<64>(a, set, m0, rows, split, deal, stream);
 }
 
 }  // namespace patch

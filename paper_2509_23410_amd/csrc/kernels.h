@@ -57,18 +57,22 @@ struct WeightOne {
 
 constexpr int kDecodeRows = 64;    // rows of X per decode launch
 constexpr int kBatchRows = 128;    // batch_kernel
+// The rows of a strip-kernel or mid_kernel pass may be dealt over up to `deal` workgroups per feature group (gridDim.z; 1, 2 or 4), whole blocks of 16 each: the rows of one,
+// and how many workgroups that makes
+inline int rows_each(int rows, int deal) { return deal > 1 ? 16 * (((rows + 15) / 16 + deal - 1) / deal) : rows; }
+inline unsigned rows_deals(int rows, int each) { return (unsigned)((rows + each - 1) / each); }
 
 // Up to kDecodeRows rows of X starting at row m0 (decode shape; 16-row blocks, the weights streamed once per launch).
 // split_k = K slices (wavefronts) per workgroup, 0 picks a default.  Returns the number used.
-int launch_decode(const GemmArgs& a, int64_t m0, int rows, int split_k, int variant, hipStream_t stream);
+int launch_decode(const GemmArgs& a, int64_t m0, int rows, int split_k, int variant, hipStream_t stream, int deal = 1);
 // The same for a set of weights; a supplies X, K, tile, Tk, n_cus (its payload / table / Y / N are ignored).
-int launch_decode_set(const GemmArgs& a, const DecodeSet& set, int64_t m0, int rows, int split_k, int variant, hipStream_t stream);
+int launch_decode_set(const GemmArgs& a, const DecodeSet& set, int64_t m0, int rows, int split_k, int variant, hipStream_t stream, int deal = 1);
 
 // Up to kDecodeRows rows of X starting at row m0 (batched decode): 64 features per wavefront, so X is read once per
 // four strips.  set.units / first[] count 64-feature groups.  split > 1 (single weight only, a.ws must hold
 // split x rows x N floats) cuts K into chunks over more workgroups; mid_split picks the count (1 without a.ws).
-int mid_split(const GemmArgs& a, int rows, int requested);
-void launch_mid_set(const GemmArgs& a, const WeightSet& set, int64_t m0, int rows, int split, hipStream_t stream);
+int mid_split(const GemmArgs& a, int rows, int requested, int deals = 1);
+void launch_mid_set(const GemmArgs& a, const WeightSet& set, int64_t m0, int rows, int split, hipStream_t stream, int deal = 1);
 // Y[i] = sum over the slices of ws[slice * n4 + i] (float4 units), slice 0 first
 void wr_reduce(const float* ws, size_t n4, int slices, float* Y, int ybf16, hipStream_t stream);
 
@@ -108,8 +112,8 @@ void launch_prefill_wreg_set(const GemmArgs& a, const WeightSet& set, hipStream_
 struct patch_packed4;
 extern "C" {
 // What AUTO takes for M rows of `count` weights of N[i] x K features sharing X (sparse_pct per cent of the tiles 2:4) given ws_bytes of
-// workspace on 256 compute units: kernel (0 strip, 1 mid, 2 batch, 3 the prefill path, 4 that in blocks of 128 rows) and K chunks of every
-// pass (1 for kernel 3), at most 8; returns their number, -1 = bad arguments.  Runs on the host alone.
+// workspace on 256 compute units: kernel (0 strip, 1 mid, 2 batch, 3 the prefill path, 4 that in blocks of 128 rows) and workgroups per
+// feature group - K chunks x deals of the rows - of every pass (1 for kernel 3), at most 8 passes; returns their number, -1 = bad arguments.  Runs on the host alone.
 int patch_test_schedule(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* kernel, int* chunks);
 // The 4-bit product of `count` weights sharing X by one kernel, whatever the dispatch would take: 0 the strip kernel, 1 batch4_kernel, both in
 // passes of up to 64 rows, 2 / 3 the prefill-shaped kernel in blocks of 128 / 256 rows (a single weight).  chunks > 1 (a single weight,
