@@ -495,19 +495,34 @@ typedef __attribute__((address_space(3))) void* wr_lptr_t;
 
 
 // Y = sum over the slices of the partial products, slice 0 first: a fixed order, so the result is reproducible.
-// (Adding the partials to Y with fp32 atomics instead was 2-3x slower than this second launch.)
-__global__ __launch_bounds__(256) void wr_reduce_kernel(const wr_f32x4* __restrict__ ws, size_t n4, int slices, float* __restrict__ Y, int ybf16) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += (size_t)gridDim.x * blockDim.x) {
-        wr_f32x4 acc = ws[i];
-        for (int s = 1; s < slices; ++s) {
-            const wr_f32x4 v = ws[(size_t)s * n4 + i];
-            acc[0] += v[0]; acc[1] += v[1]; acc[2] += v[2]; acc[3] += v[3];
-        }
-        store4(Y, (int64_t)(4 * i), acc, ybf16);
+// (Adding the partials to Y with fp32 atomics instead was 2-3x slower than this second launch.)  S = number of slices, so that those of an
+// element are requested together; 0 = a run-time number, requested one by one (more than 8, which only a caller asks for).  Small sums are bound by that
+// latency: 64 x 896 in 8 slices, whole call 12.6 -> 11.3 us; large ones by memory: 512 x 15360 in 2 slices 87.0 -> 84.4.
+template <int S>
+__device__ __forceinline__ wr_f32x4 wr_sum(const wr_f32x4* __restrict__ ws, size_t n4, int slices) {
+    if constexpr (S == 0) {
+        wr_f32x4 acc = ws[0];
+        for (int s = 1; s < slices; ++s) acc = acc + ws[(size_t)s * n4];
+        return acc;
+    } else {
+        wr_f32x4 v[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) v[s] = ws[(size_t)s * n4];
+        wr_f32x4 acc = v[0];
+#pragma unroll
+        for (int s = 1; s < S; ++s) acc = acc + v[s];
+        return acc;
     }
 }
 
+template <int S>
+__global__ __launch_bounds__(256) void wr_reduce_kernel(const wr_f32x4* __restrict__ ws, size_t n4, int slices, float* __restrict__ Y, int ybf16) {
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += (size_t)gridDim.x * blockDim.x)
+        store4(Y, (int64_t)(4 * i), wr_sum<S>(ws + i, n4, slices), ybf16);
+}
+
 // The same for a set of weights in one launch: blockIdx.y = weight; its slices lie one behind the other at ws[y].
+template <int S>
 __global__ __launch_bounds__(256) void wr_reduce_set_kernel(const WrReduceSet set, int slices, int ybf16) {
     const int y = blockIdx.y;
     const wr_f32x4* ws = reinterpret_cast<const wr_f32x4*>(set.ws[0]);
@@ -516,14 +531,8 @@ __global__ __launch_bounds__(256) void wr_reduce_set_kernel(const WrReduceSet se
 #pragma unroll
     for (int i = 1; i < kMaxMany; ++i)
         if (y == i) { ws = reinterpret_cast<const wr_f32x4*>(set.ws[i]); Y = set.Y[i]; n4 = set.n4[i]; }
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += (size_t)gridDim.x * blockDim.x) {
-        wr_f32x4 acc = ws[i];
-        for (int s = 1; s < slices; ++s) {
-            const wr_f32x4 v = ws[(size_t)s * n4 + i];
-            acc[0] += v[0]; acc[1] += v[1]; acc[2] += v[2]; acc[3] += v[3];
-        }
-        store4(Y, (int64_t)(4 * i), acc, ybf16);
-    }
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += (size_t)gridDim.x * blockDim.x)
+        store4(Y, (int64_t)(4 * i), wr_sum<S>(ws + i, n4, slices), ybf16);
 }
 
 __device__ __forceinline__ uint64_t wr_uniform64(uint64_t v) {
@@ -1097,16 +1106,21 @@ static void wr_launch(const GemmArgs& a, const WeightSet& set, int tiles_m, int 
 }
 
 void wr_reduce(const float* ws, size_t n4, int slices, float* Y, int ybf16, hipStream_t stream) {
+    constexpr decltype(&wr_reduce_kernel<0>) kernels[] = {wr_reduce_kernel<0>, wr_reduce_kernel<0>, wr_reduce_kernel<2>, wr_reduce_kernel<3>, wr_reduce_kernel<4>,
+                                                          wr_reduce_kernel<5>, wr_reduce_kernel<6>, wr_reduce_kernel<7>, wr_reduce_kernel<8>};
     const size_t blocks = (n4 + 255) / 256;
-    hipLaunchKernelGGL(wr_reduce_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, stream,
+    hipLaunchKernelGGL(kernels[slices <= 8 ? slices : 0], dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, stream,
                        reinterpret_cast<const wr_f32x4*>(ws), n4, slices, Y, ybf16);
 }
 
 void wr_reduce_set(const WrReduceSet& red, int count, int slices, int ybf16, hipStream_t stream) {
+    constexpr decltype(&wr_reduce_set_kernel<0>) kernels[] = {wr_reduce_set_kernel<0>, wr_reduce_set_kernel<0>, wr_reduce_set_kernel<2>, wr_reduce_set_kernel<3>,
+                                                              wr_reduce_set_kernel<4>, wr_reduce_set_kernel<5>, wr_reduce_set_kernel<6>, wr_reduce_set_kernel<7>,
+                                                              wr_reduce_set_kernel<8>};
     size_t n4 = 0;
     for (int i = 0; i < count; ++i) n4 = red.n4[i] > n4 ? red.n4[i] : n4;
     const size_t blocks = (n4 + 255) / 256;
-    hipLaunchKernelGGL(wr_reduce_set_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048), (unsigned)count), dim3(256), 0, stream, red, slices,
+    hipLaunchKernelGGL(kernels[slices <= 8 ? slices : 0], dim3((unsigned)(blocks < 2048 ? blocks : 2048), (unsigned)count), dim3(256), 0, stream, red, slices,
                        ybf16);
 }
 
