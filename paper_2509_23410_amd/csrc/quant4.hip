@@ -235,7 +235,7 @@ __global__ __launch_bounds__(256) void unpack4_kernel(const uint8_t* __restrict_
         if (W_deq) {
             q4_u32x4 w;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) w[k] = bf16_rne_bits((float)qv[2 * k] * scl) | (bf16_rne_bits((float)qv[2 * k + 1] * scl) << 16);
+            for (int k = 0; k < 4; ++k) w[k] = bf16_pair((float)qv[2 * k] * scl, (float)qv[2 * k + 1] * scl);
             *reinterpret_cast<q4_u32x4*>(W_deq + at) = w;
         }
         if (codes_out) {
