@@ -1009,23 +1009,21 @@ __global__ __launch_bounds__(512) void prefill4_kernel(const uint16_t* __restric
         for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
 
     auto step_begin = [&](int ks, int pf_ks) {
-        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), where the compiler sees it: it waits for none of these loads again
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         load_x(pf_ks, (ks & 1) ^ 1);
     };
-    struct Operands { A8 h0a, h0b, h1a, h1b; };
-    auto dequant = [&](Operands& h, const P4Codes& c, uint32_t sbits, int sp) {
+    auto step_mma = [&](int ks, const P4Codes& c, uint32_t p0, uint32_t p1, uint32_t sbits, int sp, int j) {
         const float scl = q4_bf16_to_float(sbits);
-        h.h0a.raw = q4_dequant8(c.a0, scl);
-        h.h1a.raw = q4_dequant8(c.a1, scl);
-        h.h0b.raw = h.h0a.raw;                             // a 2:4 step does not use the second operands
-        h.h1b.raw = h.h1a.raw;
+        A8 h0a, h0b, h1a, h1b;
+        h0a.raw = q4_dequant8(c.a0, scl);
+        h1a.raw = q4_dequant8(c.a1, scl);
+        h0b.raw = h0a.raw;                                 // a 2:4 step does not use the second operands
+        h1b.raw = h1a.raw;
         if (!sp) {
-            h.h0b.raw = q4_dequant8(c.b0, scl);
-            h.h1b.raw = q4_dequant8(c.b1, scl);
+            h0b.raw = q4_dequant8(c.b0, scl);
+            h1b.raw = q4_dequant8(c.b1, scl);
         }
-    };
-    auto multiply = [&](int ks, const Operands& h, uint32_t p0, uint32_t p1, int sp, int j) {
         const uint8_t* bs = lds + (ks & 1) * kP4Stage;
         B16 xa[3], xb[3];
         auto fetch = [&](int p, int buf) {
@@ -1042,160 +1040,67 @@ __global__ __launch_bounds__(512) void prefill4_kernel(const uint16_t* __restric
         for (int p = 0; p < NB; ++p) {
             if (p + 2 < NB) fetch(p + 2, (p + 2) % 3);
             const int u = p / (NB / 2), b0 = 2 * (p % (NB / 2)), buf = p % 3;
-            mma_step(acc[b0], acc[b0 + 1], u ? h.h1a.v : h.h0a.v, u ? h.h1b.v : h.h0b.v, xa[buf], xb[buf], (int)((u ? p1 : p0) >> (16 * j)), sp);
+            mma_step(acc[b0], acc[b0 + 1], u ? h1a.v : h0a.v, u ? h1b.v : h0b.v, xa[buf], xb[buf], (int)((u ? p1 : p0) >> (16 * j)), sp);
         }
     };
-    // A step between its barriers: the first four wavefronts multiply the operands they have and then convert those of the next step (whose codes
-    // were requested a step ago), the other four convert this step's and then multiply: the two wavefronts of a SIMD (w and w + 4) are at the
-    // matrix unit and at the vector unit in turn.  Before, all eight converted and then multiplied; f = 1/2, us: 4096 x 11008 at 500 rows unsplit 143.6 -> 138.7,
-    // 11008 x 4096 59.3 -> 57.4 (f = 0: 66.1 -> 63.3), 4096 x 4096 at 2048 rows 66.1 -> 63.4, mask tile 64 68.7 -> 65.2.  Codes requested only in the step that
-    // converts them gained three times as much on weights in the caches and lost 3 % on a set of weights read from memory.
-    auto steps_ahead = [&]() __attribute__((always_inline)) {
-        Operands h;
-        P4Codes c0, c1;              // codes of the even / odd step
+
+    if constexpr (KPT == 2) {
+        P4Codes c0, c1;              // codes of the even / odd step of a tile
         c0.b0 = c0.b1 = c1.b0 = c1.b1 = 0u;
-        uint32_t p0 = 0u, p1 = 0u, pn0 = 0u, pn1 = 0u, s0 = 0u, s1 = 0u;
-        // an opaque copy, so that it does not become a copy on the loop's back edge right behind the loads
-        auto take = [&](uint32_t& to, uint32_t from) __attribute__((always_inline)) { asm volatile("v_mov_b32 %0, %1" : "=v"(to) : "v"(from)); };
-        if constexpr (KPT == 2) {
-            uint32_t e = trow[0];
-            load_x(0, 0);
-            load_codes(c0, e, 0);
-            load_tile(pn0, pn1, s1, e, 0);
+        uint32_t p0 = 0u, p1 = 0u, sb = 0u, pn0 = 0u, pn1 = 0u, sbn = 0u;
+        uint32_t e = trow[0];
+        load_x(0, 0);
+        load_codes(c0, e, 0);
+        load_tile(pn0, pn1, sbn, e, 0);
+        __builtin_assume(Tk > 0);
+        for (int tk = 0; tk < Tk; ++tk) {
+            const int more = tk + 1 < Tk ? 1 : 0;
+            const uint32_t en = trow[tk + more];
+            const int sp = (int)(e & 1u);
+            step_begin(2 * tk, 2 * tk + 1);
+            // this tile's position dwords and scale were loaded a step ago and have landed; an opaque copy, so that it does
+            // not become a copy on the loop's back edge right behind the loads
+            asm volatile("v_mov_b32 %0, %3\n\tv_mov_b32 %1, %4\n\tv_mov_b32 %2, %5" : "=&v"(p0), "=&v"(p1), "=&v"(sb) : "v"(pn0), "v"(pn1), "v"(sbn));
             load_codes(c1, e, 1);
-            dequant(h, c0, s1, (int)(e & 1u));
-            __builtin_assume(Tk > 0);
-            for (int tk = 0; tk < Tk; ++tk) {
-                const int more = tk + 1 < Tk ? 1 : 0;
-                const uint32_t en = trow[tk + more];
-                const int sp = (int)(e & 1u);
-                step_begin(2 * tk, 2 * tk + 1);
-                take(p0, pn0);
-                take(p1, pn1);
-                take(s0, s1);
-                load_codes(c0, en, 0);
-                load_tile(pn0, pn1, s1, en, tk + more);
-                multiply(2 * tk, h, p0, p1, sp, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                dequant(h, c1, s0, sp);
-                step_begin(2 * tk + 1, 2 * tk + 1 + more);
-                load_codes(c1, en, 1);
-                multiply(2 * tk + 1, h, p0, p1, sp, 1);
-                __builtin_amdgcn_sched_barrier(0);
-                dequant(h, c0, s1, (int)(en & 1u));
-                e = en;
-            }
-        } else {
-            const int S = Tk;
-            uint32_t q0 = 0u, q1 = 0u;   // position words: p the step's, pn / q of the next even / odd step
-            uint32_t e0 = trow[0], e1 = trow[S > 1 ? 1 : 0];
-            load_x(0, 0);
-            load_codes(c0, e0, 0);
-            load_tile(pn0, pn1, s0, e0, 0);
+            step_mma(2 * tk, c0, p0, p1, sb, sp, 0);
+            step_begin(2 * tk + 1, 2 * tk + 1 + more);
+            load_codes(c0, en, 0);
+            load_tile(pn0, pn1, sbn, en, tk + more);
+            step_mma(2 * tk + 1, c1, p0, p1, sb, sp, 1);
+            e = en;
+        }
+    } else {
+        // Mask tile 64: every step is a tile of its own, with its own scale and position words.  Steps go in pairs (the
+        // buffers alternate without a copy), table entries are read two steps ahead; past the end the last step is
+        // fetched again, and the second step of the last pair is skipped when the count is odd.
+        const int S = Tk;
+        P4Codes c0, c1;
+        c0.b0 = c0.b1 = c1.b0 = c1.b1 = 0u;
+        uint32_t a0 = 0u, a1 = 0u, as_ = 0u, b0_ = 0u, b1_ = 0u, bs_ = 0u;   // position words and scale of c0 / c1
+        uint32_t e0 = trow[0], e1 = trow[S > 1 ? 1 : 0];
+        load_x(0, 0);
+        load_codes(c0, e0, 0);
+        load_tile(a0, a1, as_, e0, 0);
+        __builtin_assume(S > 0);
+        for (int s_ = 0; s_ < S; s_ += 2) {
+            const int s1 = s_ + 1 < S ? s_ + 1 : S - 1, s2 = s_ + 2 < S ? s_ + 2 : S - 1, s3 = s_ + 3 < S ? s_ + 3 : S - 1;
+            const uint32_t e2 = trow[s2], e3 = trow[s3];
+            step_begin(s_, s1);
             load_codes(c1, e1, 0);
-            load_tile(q0, q1, s1, e1, S > 1 ? 1 : 0);
-            dequant(h, c0, s0, (int)(e0 & 1u));
-            __builtin_assume(S > 0);
-            for (int s_ = 0; s_ < S; s_ += 2) {
-                const int n1 = s_ + 1 < S ? s_ + 1 : S - 1, n2 = s_ + 2 < S ? s_ + 2 : S - 1, n3 = s_ + 3 < S ? s_ + 3 : S - 1;
-                const uint32_t e2 = trow[n2], e3 = trow[n3];
-                step_begin(s_, n1);
-                take(p0, pn0);
-                take(p1, pn1);
+            load_tile(b0_, b1_, bs_, e1, s1);
+            step_mma(s_, c0, a0, a1, as_, (int)(e0 & 1u), 0);
+            if (s_ + 1 < S) {
+                step_begin(s_ + 1, s2);
                 load_codes(c0, e2, 0);
-                load_tile(pn0, pn1, s0, e2, n2);
-                multiply(s_, h, p0, p1, (int)(e0 & 1u), 0);
-                __builtin_amdgcn_sched_barrier(0);
-                dequant(h, c1, s1, (int)(e1 & 1u));
-                if (s_ + 1 < S) {
-                    step_begin(s_ + 1, n2);
-                    take(p0, q0);
-                    take(p1, q1);
-                    load_codes(c1, e3, 0);
-                    load_tile(q0, q1, s1, e3, n3);
-                    multiply(s_ + 1, h, p0, p1, (int)(e1 & 1u), 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    dequant(h, c0, s0, (int)(e2 & 1u));
-                }
-                e0 = e2;
-                e1 = e3;
+                load_tile(a0, a1, as_, e2, s2);
+                step_mma(s_ + 1, c1, b0_, b1_, bs_, (int)(e1 & 1u), 0);
             }
+            e0 = e2;
+            e1 = e3;
         }
-    };
-    auto steps = [&]() __attribute__((always_inline)) {
-        auto step = [&](int ks, const P4Codes& c, uint32_t p0, uint32_t p1, uint32_t sbits, int sp, int j) __attribute__((always_inline)) {
-            Operands h;
-            dequant(h, c, sbits, sp);
-            multiply(ks, h, p0, p1, sp, j);
-        };
-        if constexpr (KPT == 2) {
-            P4Codes c0, c1;              // codes of the even / odd step of a tile
-            c0.b0 = c0.b1 = c1.b0 = c1.b1 = 0u;
-            uint32_t p0 = 0u, p1 = 0u, sb = 0u, pn0 = 0u, pn1 = 0u, sbn = 0u;
-            uint32_t e = trow[0];
-            load_x(0, 0);
-            load_codes(c0, e, 0);
-            load_tile(pn0, pn1, sbn, e, 0);
-            __builtin_assume(Tk > 0);
-            for (int tk = 0; tk < Tk; ++tk) {
-                const int more = tk + 1 < Tk ? 1 : 0;
-                const uint32_t en = trow[tk + more];
-                const int sp = (int)(e & 1u);
-                step_begin(2 * tk, 2 * tk + 1);
-                // this tile's position dwords and scale were loaded a step ago and have landed; an opaque copy, so that it does
-                // not become a copy on the loop's back edge right behind the loads
-                asm volatile("v_mov_b32 %0, %3\n\tv_mov_b32 %1, %4\n\tv_mov_b32 %2, %5" : "=&v"(p0), "=&v"(p1), "=&v"(sb) : "v"(pn0), "v"(pn1), "v"(sbn));
-                load_codes(c1, e, 1);
-                step(2 * tk, c0, p0, p1, sb, sp, 0);
-                step_begin(2 * tk + 1, 2 * tk + 1 + more);
-                load_codes(c0, en, 0);
-                load_tile(pn0, pn1, sbn, en, tk + more);
-                step(2 * tk + 1, c1, p0, p1, sb, sp, 1);
-                e = en;
-            }
-        } else {
-            // Mask tile 64: every step is a tile of its own, with its own scale and position words.  Steps go in pairs (the
-            // buffers alternate without a copy), table entries are read two steps ahead; past the end the last step is
-            // fetched again, and the second step of the last pair is skipped when the count is odd.
-            const int S = Tk;
-            P4Codes c0, c1;
-            c0.b0 = c0.b1 = c1.b0 = c1.b1 = 0u;
-            uint32_t a0 = 0u, a1 = 0u, as_ = 0u, b0_ = 0u, b1_ = 0u, bs_ = 0u;   // position words and scale of c0 / c1
-            uint32_t e0 = trow[0], e1 = trow[S > 1 ? 1 : 0];
-            load_x(0, 0);
-            load_codes(c0, e0, 0);
-            load_tile(a0, a1, as_, e0, 0);
-            __builtin_assume(S > 0);
-            for (int s_ = 0; s_ < S; s_ += 2) {
-                const int s1 = s_ + 1 < S ? s_ + 1 : S - 1, s2 = s_ + 2 < S ? s_ + 2 : S - 1, s3 = s_ + 3 < S ? s_ + 3 : S - 1;
-                const uint32_t e2 = trow[s2], e3 = trow[s3];
-                step_begin(s_, s1);
-                load_codes(c1, e1, 0);
-                load_tile(b0_, b1_, bs_, e1, s1);
-                step(s_, c0, a0, a1, as_, (int)(e0 & 1u), 0);
-                if (s_ + 1 < S) {
-                    step_begin(s_ + 1, s2);
-                    load_codes(c0, e2, 0);
-                    load_tile(a0, a1, as_, e2, s2);
-                    step(s_ + 1, c1, b0_, b1_, bs_, (int)(e1 & 1u), 0);
-                }
-                e0 = e2;
-                e1 = e3;
-            }
-        }
-    };
-    auto through = [&]() __attribute__((always_inline)) {
-        // (the matrix instructions are asm: nothing of the compiler's may touch the accumulators before they are through)
-        asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            f32x16& c = acc[b];
-            asm volatile("" : "+v"(c));
-        }
-    };
-    if (w < 4) { steps_ahead(); through(); }
-    else { steps(); through(); }
+    }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
     // acc[b][i]: feature n0 + fo + 8 (i/4) + 4 q + i%4, row m0 + 32 b + i32.  The X stages are free once every wavefront
     // has left the loop: each block of 32 rows is turned through 4 KB of them and stored in whole rows
     // (store_block_rows).
