@@ -492,7 +492,7 @@ __global__ __launch_bounds__(64 * q4_max_waves(R, RB)) void decode4_kernel(const
         q4_entries<TILE, R, NB>(e3, st, begin + 3 * NB, end - 1);
         q4_loads<TILE, R, RB, NB>(b0, st, xrow, lane, begin, end - 1);
         int step0 = begin;
-        for (; step0 + 2 * NB < end; step0 += 2 * NB) {
+        auto two_batches = [&]() __attribute__((always_inline)) {
             q4_loads<TILE, R, RB, NB>(b1, st, xrow, lane, step0 + NB, end - 1);
             q4_compute<TILE, R, RB, NB>(b0, acc, lane, step0, end);
             take(b0.e, e2);
@@ -501,6 +501,18 @@ __global__ __launch_bounds__(64 * q4_max_waves(R, RB)) void decode4_kernel(const
             q4_compute<TILE, R, RB, NB>(b1, acc, lane, step0 + NB, end);
             take(b1.e, e3);
             q4_entries<TILE, R, NB>(e3, st, step0 + 5 * NB, end - 1);
+        };
+        // With the test at the top the compiler copies the batch just requested at every turn - waits for it and holds it twice - in some kernels for
+        // mask tile 128 (R = 3, RB = 4 in a set of more than three: 256 vector registers and 236 bytes of scratch per lane, 194 as do .. while; R = 3,
+        // RB = 1 in a set 119, 78).  f = 1/2: four 2560 x 2560 at 16 / 32 / 64 rows 9.9 / 11.9 / 36.4 -> 9.4 / 10.9 / 16.9 us, 4864 / 4864 / 896 / 896 x 896 at
+        // 64 17.2 -> 9.2, three 896 x 896 at 16 4.0 -> 3.7.  On mask tile 64 it never did, and do .. while is 0.5 % slower (10 % of the calls 2 - 7 %).
+        if constexpr (TILE == 128) {
+            if (step0 + 2 * NB < end) do {
+                two_batches();
+                step0 += 2 * NB;
+            } while (step0 + 2 * NB < end);
+        } else {
+            for (; step0 + 2 * NB < end; step0 += 2 * NB) two_batches();
         }
         if (step0 + NB < end) {
             q4_loads<TILE, R, RB, NB>(b1, st, xrow, lane, step0 + NB, end - 1);

@@ -315,6 +315,31 @@ def test_kernels_with_untracked_loads_do_not_spill(source, kernel, at_least):
     assert seen >= at_least, f"expected several instantiations of {kernel}, saw {seen}"
 
 
+def test_4_bit_decoding_kernels_keep_their_batches_in_registers():
+    """No instantiation of the 4-bit decoding kernels may spill vector registers, and one for a set of weights may need only a few more than the
+    same kernel for one weight (a batch of loads held twice, e.g. copied at the head of a loop, is 40 to 90 more): a set of four ran twice as long."""
+    import subprocess
+    from paper_2509_23410_amd import build
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    cmd = [hipcc, *[f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")], "-c", "--cuda-device-only",
+           "-Rpass-analysis=kernel-resource-usage", "-I", os.path.join(ROOT, "include"), "-I", build.CSRC,
+           "-o", os.devnull, os.path.join(build.CSRC, "quant4.hip")]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout[-2000:]
+    used = {}   # (kernel, template numbers) -> {set type: vector registers}
+    for b in re.split(r"remark: Function Name: ", r.stdout)[1:]:
+        m = re.match(r"_ZN5patch\d+(decode4_kernel|decode4_tile_kernel|batch4_kernel)I((?:L[ib]\d+E)+)(NS_5Q4(?:One|SetILi\dE))?", b.split()[0])
+        if not m:
+            continue
+        get = lambda key: int(re.search(re.escape(key) + r":\s*(\d+)", b).group(1))
+        assert get("VGPRs Spill") == 0 and get("ScratchSize [bytes/lane]") == 0, b.split()[0]
+        used.setdefault(m.group(1, 2), {})[m.group(3)] = get("VGPRs")
+    strip = {k: v for k, v in used.items() if k[0] != "batch4_kernel"}
+    assert len(strip) == 2 * 13 + 6 and len(used) > len(strip), sorted(used)
+    for k, v in strip.items():
+        assert len(v) == 3 and max(v.values()) <= v["NS_5Q4One"] + 16, (k, v)
+
+
 def test_no_flat_memory_instructions(tmp_path):
     """Every pointer the kernels dereference is device memory.  A pointer that reached a kernel inside a by-value struct
     or through scalar selects loses its address space unless the code restores it; the compiler then emits flat

@@ -56,3 +56,16 @@ def test_strip4(tile, N, K, f):
         again = torch.empty_like(Ys[0])
         _strip4(X, M, [P, P2, P], [again, Ys[1], Ys[2]])
         assert torch.equal(again, Ys[0]), "not reproducible"
+
+
+@pytest.mark.parametrize("tile,N,K,f", [(128, [256, 128, 128, 384], 384, 0.5), (128, [2560] * 4, 640, 0.5), (128, [128] * 8, 1152, 1.0), (64, [64, 192, 64, 64, 128], 320, 0.4)])
+def test_strip4_set_of_more_than_three(tile, N, K, f):
+    """2560: three strips per workgroup, which then hold strips of two weights (2560 / 16 = 160 strips each)"""
+    print(f"strip4 set tile={tile} N={N} K={K} f={f}", flush=True)
+    weights = [_weight(n, K, tile, f, 1 + i) for i, n in enumerate(N)]
+    for M in (1, 8, 9, 16, 17, 32, 33, 48, 49, 64):
+        X = torch.randn(M, K, device="cuda", generator=torch.Generator(device="cuda").manual_seed(M)).to(torch.bfloat16)
+        Ys = [torch.full((M, n), float("nan"), device="cuda") for n in N]
+        _strip4(X, M, [p for _, p in weights], Ys)
+        for i, (y, (w, _)) in enumerate(zip(Ys, weights)):
+            _check(y, X.double(), w, f"M={M} weight {i}")
