@@ -264,7 +264,8 @@ constexpr int kQ4Rows = 64;   // rows of X per launch at most
 template <int R, int RB, int NB>
 struct Q4Batch {
     uint32_t e[NB][R];
-    q4_u32x2 d[NB][R];         // dense: both dwords; 2:4: [0] = codes, [1] = positions
+    q4_pair_t d[NB][R];        // codes (the second dword: q4_loads with ARMS, dense)
+    uint32_t p[NB][R];         // 2:4: positions; dense without ARMS: the second dword of codes
     uint32_t sc[NB][R];        // scale bits
     q4_u32x4 x[NB][RB][2];
 };
@@ -287,7 +288,7 @@ struct Q4Strips {
     q4_u16_ptr scl[R];        // this lane's scale of the strip for tile column 0 (the next column is 16 scales on)
 };
 
-// Steps past the wavefront's run repeat its last step (in bounds; discarded by q4_compute).  b.e has been filled by q4_entries.
+// Steps past the wavefront's run repeat its last step (in bounds; discarded by q4_compute).
 template <int TILE, int R, int NB>
 __device__ __forceinline__ void q4_entries(uint32_t (&e)[NB][R], const Q4Strips<R>& st, int step0, int last) {
     constexpr int KPT = TILE / kStepCols;
@@ -299,7 +300,12 @@ __device__ __forceinline__ void q4_entries(uint32_t (&e)[NB][R], const Q4Strips<
     }
 }
 
-template <int TILE, int R, int RB, int NB>
+// The loads of a batch whose entries q4_entries has filled in.  Either no load is conditional, a dense lane's two dwords one load each, or (ARMS) a
+// dense lane's come by one load behind a branch.  Both arms then issue two loads: the compiler knows how many are in flight only if they are as many,
+// and would otherwise wait for all of them.  The branches cost a wavefront more issue time than the wider load saves unless it runs for a while
+// (27 x 2 x 3 single weights, 11 row counts, ARMS against none, mean ratio at f = 0 / 1/2 / 1: 2 steps a wavefront 1.025 / 1.027 / 1.028, 4 steps
+// 0.99 / 1.00 / 1.01, 5 and more 0.967 / 0.981 / 1.001; f = 0, 9 rows, mask tile 64: 512 x 13824 13.7 -> 12.9 us).
+template <int TILE, int R, int RB, int NB, bool ARMS>
 __device__ __forceinline__ void q4_loads(Q4Batch<R, RB, NB>& b, const Q4Strips<R>& st, const q4_u16_ptr (&xrow)[RB], int lane, int step0, int last) {
     constexpr int KPT = TILE / kStepCols;
 #pragma unroll
@@ -316,17 +322,27 @@ __device__ __forceinline__ void q4_loads(Q4Batch<R, RB, NB>& b, const Q4Strips<R
             q4_bytes_ptr base = st.pay[r] + entry_offset(b.e[i][r]);
             const int s = st.s[r];
             b.sc[i][r] = st.scl[r][(step / KPT) * 16];
-            // no load is conditional: a dense lane's second dword, a 2:4 lane's dword of positions (mask tile 64: shared with the neighbour)
+            // positions on mask tile 64: a dword is shared with the neighbour
             const bool sp = entry_sparse(b.e[i][r]);
             const int f = s * KPT + j;
-            b.d[i][r][0] = *reinterpret_cast<const PATCH_Q4_GLOBAL uint32_t*>(base + (sp ? f * 256 + lane * 4 : f * 512 + lane * 8));
-            b.d[i][r][1] = *reinterpret_cast<const PATCH_Q4_GLOBAL uint32_t*>(
-                base + (sp ? q4_sparse_codes(TILE) + (TILE == 128 ? (s * 64 + lane) * 4 : (s * 32 + (lane >> 1)) * 4) : f * 512 + lane * 8 + 4));
+            if constexpr (ARMS) {
+                if (sp) {
+                    b.d[i][r][0] = *reinterpret_cast<const PATCH_Q4_GLOBAL uint32_t*>(base + f * 256 + lane * 4);
+                    b.p[i][r] = *reinterpret_cast<const PATCH_Q4_GLOBAL uint32_t*>(base + q4_sparse_codes(TILE) + (TILE == 128 ? (s * 64 + lane) * 4 : (s * 32 + (lane >> 1)) * 4));
+                } else {
+                    b.d[i][r] = *reinterpret_cast<const PATCH_Q4_GLOBAL q4_pair_t*>(base + f * 512 + lane * 8);
+                    b.p[i][r] = *reinterpret_cast<const PATCH_Q4_GLOBAL uint32_t*>(base);   // not used
+                }
+            } else {
+                b.d[i][r][0] = *reinterpret_cast<const PATCH_Q4_GLOBAL uint32_t*>(base + (sp ? f * 256 + lane * 4 : f * 512 + lane * 8));
+                b.p[i][r] = *reinterpret_cast<const PATCH_Q4_GLOBAL uint32_t*>(
+                    base + (sp ? q4_sparse_codes(TILE) + (TILE == 128 ? (s * 64 + lane) * 4 : (s * 32 + (lane >> 1)) * 4) : f * 512 + lane * 8 + 4));
+            }
         }
     }
 }
 
-template <int TILE, int R, int RB, int NB>
+template <int TILE, int R, int RB, int NB, bool ARMS>
 __device__ __forceinline__ void q4_compute(const Q4Batch<R, RB, NB>& b, q4_f32x4 (&acc)[R][RB], int lane, int step0, int end) {
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
@@ -337,7 +353,7 @@ __device__ __forceinline__ void q4_compute(const Q4Batch<R, RB, NB>& b, q4_f32x4
             if (!entry_sparse(b.e[i][r])) {
                 Q4A a0, a1;
                 a0.raw = q4_dequant8(b.d[i][r][0], scl);
-                a1.raw = q4_dequant8(b.d[i][r][1], scl);
+                a1.raw = q4_dequant8(ARMS ? b.d[i][r][1] : b.p[i][r], scl);
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) {
                     Q4B x;
@@ -349,7 +365,7 @@ __device__ __forceinline__ void q4_compute(const Q4Batch<R, RB, NB>& b, q4_f32x4
             } else {
                 Q4A a;
                 a.raw = q4_dequant8(b.d[i][r][0], scl);
-                const int pos = (int)(b.d[i][r][1] >> (16 * (TILE == 128 ? (step0 + i) & 1 : lane & 1)));
+                const int pos = (int)(b.p[i][r] >> (16 * (TILE == 128 ? (step0 + i) & 1 : lane & 1)));
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) {
                     Q4B x;
@@ -427,7 +443,7 @@ __device__ __forceinline__ Q4Weight q4_weight_of(const SetT& set, int g) {
 // (whose registers do not fit 16 times into a compute unit)
 constexpr int q4_max_waves(int R, int RB) { return RB == 4 || R * RB > 4 || (RB == 2 && R > 1) ? 8 : 16; }
 
-template <int TILE, int R, int RB, typename SetT>
+template <int TILE, int R, int RB, typename SetT, bool ARMS>
 __global__ __launch_bounds__(64 * q4_max_waves(R, RB)) void decode4_kernel(const uint16_t* __restrict__ X, int64_t m0, int rows, int64_t K, int Tk, int KW,
                                                        const SetT set) {
     constexpr bool kOne = sizeof(SetT) == sizeof(Q4One);
@@ -490,23 +506,24 @@ __global__ __launch_bounds__(64 * q4_max_waves(R, RB)) void decode4_kernel(const
         q4_entries<TILE, R, NB>(b1.e, st, begin + NB, end - 1);
         q4_entries<TILE, R, NB>(e2, st, begin + 2 * NB, end - 1);
         q4_entries<TILE, R, NB>(e3, st, begin + 3 * NB, end - 1);
-        q4_loads<TILE, R, RB, NB>(b0, st, xrow, lane, begin, end - 1);
+        q4_loads<TILE, R, RB, NB, ARMS>(b0, st, xrow, lane, begin, end - 1);
         int step0 = begin;
         auto two_batches = [&]() __attribute__((always_inline)) {
-            q4_loads<TILE, R, RB, NB>(b1, st, xrow, lane, step0 + NB, end - 1);
-            q4_compute<TILE, R, RB, NB>(b0, acc, lane, step0, end);
+            q4_loads<TILE, R, RB, NB, ARMS>(b1, st, xrow, lane, step0 + NB, end - 1);
+            q4_compute<TILE, R, RB, NB, ARMS>(b0, acc, lane, step0, end);
             take(b0.e, e2);
             q4_entries<TILE, R, NB>(e2, st, step0 + 4 * NB, end - 1);
-            q4_loads<TILE, R, RB, NB>(b0, st, xrow, lane, step0 + 2 * NB, end - 1);
-            q4_compute<TILE, R, RB, NB>(b1, acc, lane, step0 + NB, end);
+            q4_loads<TILE, R, RB, NB, ARMS>(b0, st, xrow, lane, step0 + 2 * NB, end - 1);
+            q4_compute<TILE, R, RB, NB, ARMS>(b1, acc, lane, step0 + NB, end);
             take(b1.e, e3);
             q4_entries<TILE, R, NB>(e3, st, step0 + 5 * NB, end - 1);
         };
         // With the test at the top the compiler copies the batch just requested at every turn - waits for it and holds it twice - in some kernels for
         // mask tile 128 (R = 3, RB = 4 in a set of more than three: 256 vector registers and 236 bytes of scratch per lane, 194 as do .. while; R = 3,
         // RB = 1 in a set 119, 78).  f = 1/2: four 2560 x 2560 at 16 / 32 / 64 rows 9.9 / 11.9 / 36.4 -> 9.4 / 10.9 / 16.9 us, 4864 / 4864 / 896 / 896 x 896 at
-        // 64 17.2 -> 9.2, three 896 x 896 at 16 4.0 -> 3.7.  On mask tile 64 it never did, and do .. while is 0.5 % slower (10 % of the calls 2 - 7 %).
-        if constexpr (TILE == 128) {
+        // 64 17.2 -> 9.2, three 896 x 896 at 16 4.0 -> 3.7.  On mask tile 64 it never did: there do .. while saves registers from R RB = 6 on
+        // (R = 3, RB = 2: 127, 115) and is 0.5 % slower below (10 % of the calls 2 - 7 %).
+        if constexpr (TILE == 128 || R * RB > 4) {
             if (step0 + 2 * NB < end) do {
                 two_batches();
                 step0 += 2 * NB;
@@ -515,11 +532,11 @@ __global__ __launch_bounds__(64 * q4_max_waves(R, RB)) void decode4_kernel(const
             for (; step0 + 2 * NB < end; step0 += 2 * NB) two_batches();
         }
         if (step0 + NB < end) {
-            q4_loads<TILE, R, RB, NB>(b1, st, xrow, lane, step0 + NB, end - 1);
-            q4_compute<TILE, R, RB, NB>(b0, acc, lane, step0, end);
-            q4_compute<TILE, R, RB, NB>(b1, acc, lane, step0 + NB, end);
+            q4_loads<TILE, R, RB, NB, ARMS>(b1, st, xrow, lane, step0 + NB, end - 1);
+            q4_compute<TILE, R, RB, NB, ARMS>(b0, acc, lane, step0, end);
+            q4_compute<TILE, R, RB, NB, ARMS>(b1, acc, lane, step0 + NB, end);
         } else {
-            q4_compute<TILE, R, RB, NB>(b0, acc, lane, step0, end);
+            q4_compute<TILE, R, RB, NB, ARMS>(b0, acc, lane, step0, end);
         }
     }
     // Partial sums meet in LDS, CH (strip, row block) items at a time (all of them unless R RB > 8): wavefront w adds
@@ -547,8 +564,10 @@ __global__ __launch_bounds__(64 * q4_max_waves(R, RB)) void decode4_kernel(const
 
 template <int TILE, int R, int RB, typename SetT>
 static void launch_decode4(const uint16_t* X, int64_t m0, int rows, int64_t K, int Tk, const SetT& set, int groups, int kw, hipStream_t s) {
-    hipLaunchKernelGGL((decode4_kernel<TILE, R, RB, SetT>), dim3((unsigned)groups), dim3((unsigned)(kw * 64)), 0, s, X, m0, rows, K, Tk, kw,
-                       set);
+    // the wider loads of dense tiles: a single weight and more than four steps per wavefront (q4_loads)
+    constexpr bool kOne = sizeof(SetT) == sizeof(Q4One);
+    auto* kernel = kOne && Tk * (TILE / kStepCols) > 4 * kw ? decode4_kernel<TILE, R, RB, SetT, kOne> : decode4_kernel<TILE, R, RB, SetT, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3((unsigned)(kw * 64)), 0, s, X, m0, rows, K, Tk, kw, set);
 }
 
 // up to 3 strips per workgroup, up to 4 with two blocks of 16 rows

@@ -329,7 +329,7 @@ def test_4_bit_decoding_kernels_keep_their_batches_in_registers():
     used = {}   # (kernel, template numbers) -> {set type: vector registers}
     for b in re.split(r"remark: Function Name: ", r.stdout)[1:]:
         m = re.match(r"_ZN5patch\d+(decode4_kernel|decode4_tile_kernel|batch4_kernel)I((?:L[ib]\d+E)+)(NS_5Q4(?:One|SetILi\dE))?", b.split()[0])
-        if not m:
+        if not m or re.search(r"Q4OneELb1E", b.split()[0]):   # (long runs of one weight: below)
             continue
         get = lambda key: int(re.search(re.escape(key) + r":\s*(\d+)", b).group(1))
         assert get("VGPRs Spill") == 0 and get("ScratchSize [bytes/lane]") == 0, b.split()[0]
@@ -338,6 +338,23 @@ def test_4_bit_decoding_kernels_keep_their_batches_in_registers():
     assert len(strip) == 2 * 13 + 6 and len(used) > len(strip), sorted(used)
     for k, v in strip.items():
         assert len(v) == 3 and max(v.values()) <= v["NS_5Q4One"] + 16, (k, v)
+
+
+def test_long_runs_of_the_4_bit_strip_kernel_read_dense_codes_by_one_load(tmp_path):
+    """decode4_kernel with ARMS (a single weight, more than four steps per wavefront): a lane's two dwords of a dense tile come by one load, and the
+    branch it stands behind does not make the loop wait for every load in flight (the compiler does that when the arms issue different numbers of
+    them, or when one writes a register that the other loads)."""
+    from paper_2509_23410_amd import build
+    text = open(build.device_asm("quant4.hip", str(tmp_path / "q4.s"))).read()
+    bodies = re.findall(r"^(_ZN5patch14decode4_kernelILi\d+ELi(\d)ELi\dENS_5Q4OneELb1E\w+):[^\n]*\n(.*?)^\.Lfunc_end", text, re.S | re.M)
+    assert len(bodies) == 26
+    for name, strips, body in bodies:
+        blocks = re.split(r"(?m)^(?=\.LBB)", body)
+        header = next(b.split(":")[0][2:] for b in blocks if "Loop Header: Depth=1" in b.split("\n")[0] and "mfma" in "".join(blocks))
+        loop = "".join(b for b in blocks if b.startswith(".L" + header + ":") or f"Header={header} " in b.split("\n")[0])
+        assert "v_mfma" in loop and "v_smfmac" in loop, name
+        assert len(re.findall(r"global_load_dwordx2\b", loop)) >= 2 * int(strips), name   # two batches a turn
+        assert not re.search(r"s_waitcnt[^\n]*vmcnt\(0\)", loop), name
 
 
 def test_no_flat_memory_instructions(tmp_path):

@@ -69,3 +69,15 @@ def test_strip4_set_of_more_than_three(tile, N, K, f):
         _strip4(X, M, [p for _, p in weights], Ys)
         for i, (y, (w, _)) in enumerate(zip(Ys, weights)):
             _check(y, X.double(), w, f"M={M} weight {i}")
+
+
+@pytest.mark.parametrize("tile,N,K,f", [(64, 64, 4160, 0.0), (64, 192, 4672, 0.5), (64, 12352, 2176, 0.5), (128, 128, 4480, 1.0), (128, 256, 4736, 0.4)])
+def test_strip4_long_runs(tile, N, K, f):
+    """one weight, more than four 64-column steps per wavefront: dense codes by one load behind a branch"""
+    print(f"strip4 long tile={tile} N={N} K={K} f={f}", flush=True)
+    W, P = _weight(N, K, tile, f, 1)
+    for M in (1, 9, 16, 17, 33, 49, 64):
+        X = torch.randn(M, K, device="cuda", generator=torch.Generator(device="cuda").manual_seed(M)).to(torch.bfloat16)
+        Y = torch.full((M, N), float("nan"), device="cuda")
+        _strip4(X, M, [P], [Y])
+        _check(Y, X.double(), W, f"M={M}")
