@@ -1365,20 +1365,25 @@ static Q4Shape q4_shape(const patch_packed4* const* P, int count, size_t ws_byte
 }
 
 // A pass of `rows` rows (at most 64) over all weights: the strip kernel or batch4_kernel, and in how many K chunks.  Both are priced, in us with
-// steps = 64-column steps, fitted by row range to launches of weights and sets, both mask tiles, f = 0, 1/2 and 1 (strip: 21 shapes, 19 row counts, rms
-// error 6 - 9 %; batch: 36 shapes, 14 row counts, 650 - 4100 launches per line, 5 - 8 %):
-//   strip   base + share x (per_strip R + constant + per_row rows) x 0.05 x steps x (1 + sparse (f - 1/2)); R = strips per workgroup, share = workgroups /
-//           compute units where more than one (then x over: they share a compute unit; beyond two 0.2 more), else 1.  (Finer than the estimate R is
-//           chosen by.)
+// steps = 64-column steps, fitted by row range to launches of weights and sets, both mask tiles, f = 0, 1/2 and 1 (strip: 42 shapes, 25 row counts, 630 - 1764
+// launches per line, rms error 7 - 8 %; batch: 36 shapes, 14 row counts, 650 - 4100 launches per line, 5 - 8 %):
+//   strip   base + turns x (per_strip R + constant + per_row rows) x 0.05 x steps x (1 + sparse (f - 1/2)); R = strips per workgroup, turns = 1 up to one
+//           workgroup per compute unit, beyond over x ((1 - whole) share + whole ceil(share) + late where share > 2), share = workgroups / compute units:
+//           the unit with the most workgroups decides most of it, and two are resident.  (By share alone, launches just past a whole number were
+//           estimated up to 29 % short and those just below it up to 30 % long.)
 //   batch   base + (1 + round (rounds - 1)) x steps / chunks x (step + per_row rows) x (1 + fill min(1, workgroups / compute units)) x (tile64 on mask
 //           tile 64: two scales and position loads per unit) x (1 + sparse (f - 1/2)); a split 2.7 for the second launch and its partial sums twice at
-//           5 TB/s; to be worth it 0.8 ahead (up to 8 rows 2.5, up to 12 2.2)
-// Measured, strip / batch, f = 1/2, mask tile 128: gate and up of 4096 / 11008 at 1 / 16 / 32 / 64 rows (13.7 / 19.9, 18.6 / 20.1, 24.1 / 22.9, 41.0 / 28.6), of 5120 /
-// 13824 (20.0 / 24.7, 29.2 / 24.3, 36.5 / 28.2, 74.4 / 35.2); three 4096 x 4096 (8.5 / 19.2, 10.9 / 19.4, 14.1 / 22.2, 21.7 / 27.6).
-struct Q4StripPrice { int rows; double base, per_strip, constant, per_row, over, sparse; };
-constexpr Q4StripPrice kQ4StripPrice[] = {{8, 2.77, 0.651, 0.025, 0.030, 1.02, -0.36}, {16, 2.97, 0.577, -0.03, 0.048, 1.0, -0.27}, {32, 3.09, 0.645, 0.11, 0.047, 1.12, -0.18},
-                                          {48, 3.23, 0.651, 0.33, 0.049, 1.125, -0.11}, {64, 3.46, 0.697, 0.36, 0.052, 1.13, -0.09}};
-constexpr Q4StripPrice kQ4TilePrice = {8, 3.12, 0.541, -0.06, 0.033, 1.04, -0.30};   // decode4_tile_kernel: mask tile 128, up to 8 rows
+//           5 TB/s
+// The cheaper one is taken, the batch kernel up to 8 rows if it is 0.4 ahead, up to 16 also 0.2 behind (its K chunks are estimated that much long there:
+// 4096 x 11008, f = 1, 12 rows 10.9, measured 10.8, the strip kernel 10.9 and 13.0).  Over those 42 shapes that is 0.02 - 0.27 % slower, by row range and mask tile,
+// than the faster of the two always (by share alone, and the batch kernel to be 0.8 ahead, up to 8 rows 2.5, up to 12 2.2: 0.1 - 0.9 %).
+// Measured, strip / batch, f = 1/2, mask tile 128: gate and up of 4096 / 11008 at 1 / 16 / 32 / 64 rows (13.7 / 19.0, 16.6 / 19.5, 23.2 / 22.2, 40.1 / 28.3), of 5120 /
+// 13824 (20.0 / 23.8, 26.6 / 23.6, 34.2 / 27.5, 70.4 / 35.1); three 4096 x 4096 (8.6 / 19.2, 10.3 / 19.2, 13.8 / 21.6, 21.6 / 27.0).
+struct Q4StripPrice { int rows; double base, per_strip, constant, per_row, over, whole, sparse, late; };
+constexpr Q4StripPrice kQ4StripPrice[] = {{8, 3.119, 0.522, 0.041, 0.029, 0.966, 0.777, -0.314, -0.172}, {16, 2.971, 0.452, 0.076, 0.045, 0.95, 0.888, -0.284, -0.131},
+                                          {32, 3.087, 0.528, 0.238, 0.046, 1.029, 0.485, -0.178, 0.395}, {48, 3.244, 0.508, 0.341, 0.052, 1.023, 0.867, -0.108, 0.116},
+                                          {64, 3.43, 0.546, 0.517, 0.052, 1.039, 0.871, -0.083, 0.088}};
+constexpr Q4StripPrice kQ4TilePrice = {8, 3.108, 0.531, -0.059, 0.028, 1.016, 0.579, -0.306, 0.043};   // decode4_tile_kernel: mask tile 128, up to 8 rows
 struct Q4BatchPrice { int rows; double base, step, per_row, fill, tile64, sparse, round; };
 constexpr Q4BatchPrice kQ4BatchPrice[] = {{16, 2.7, 0.2204, 0.0001, 0.17, 1.12, -0.24, 0.53}, {32, 3.0, 0.2487, 0.0003, 0.15, 1.11, -0.21, 0.57}, {64, 3.6, 0.217, 0.0019, 0.15, 1.10, -0.20, 1.05}};
 
@@ -1388,8 +1393,9 @@ static Q4Plan q4_pass_plan(const Q4Shape& d, int rows) {
     const Q4StripPrice* p = d.tile == 128 && rows <= 8 ? &kQ4TilePrice : kQ4StripPrice;
     while (rows > p->rows) ++p;
     const int R = q4_strips_per_group(d.strips, d.n_cus, rows);
-    const double share = (double)((d.strips + R - 1) / R) / d.n_cus;
-    const Q4Plan strip = {false, 1, p->base + (share > 1.0 ? p->over * (share + (share > 2.0 ? 0.2 : 0.0)) : 1.0) * (p->per_strip * R + p->constant + p->per_row * rows) * 0.05 * steps * (1.0 + p->sparse * (d.f - 0.5))};
+    const int groups = (d.strips + R - 1) / R;
+    const double turns = groups <= d.n_cus ? 1.0 : p->over * ((1.0 - p->whole) * groups / d.n_cus + p->whole * ((groups + d.n_cus - 1) / d.n_cus) + (groups > 2 * d.n_cus ? p->late : 0.0));
+    const Q4Plan strip = {false, 1, p->base + turns * (p->per_strip * R + p->constant + p->per_row * rows) * 0.05 * steps * (1.0 + p->sparse * (d.f - 0.5))};
     const Q4BatchPrice* b = kQ4BatchPrice;
     while (rows > b->rows) ++b;
     const size_t fit = d.ws_bytes / ((size_t)rows * (size_t)d.N * sizeof(float));
@@ -1402,7 +1408,7 @@ static Q4Plan q4_pass_plan(const Q4Shape& d, int rows) {
                           (c > 1 ? 2.7 + 2.0 * c * rows * (double)d.N * 4.0 / 5.0e6 : 0.0);
         if (c == 1 || us < wide.us) wide = Q4Plan{true, c, us};
     }
-    return wide.us + (rows <= 8 ? 2.5 : rows <= 12 ? 2.2 : 0.8) < strip.us ? wide : strip;
+    return wide.us + (rows <= 8 ? 0.4 : rows <= 16 ? -0.2 : 0.0) < strip.us ? wide : strip;
 }
 
 static patch_status q4_passes(const void* X, int64_t M, const patch_packed4* const* P, void* const* Y, int count, float* ws, size_t ws_bytes,

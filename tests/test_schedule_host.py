@@ -99,34 +99,44 @@ def test_block_height_of_mask_tile_64(N, K, M, us):
 
 # the 4-bit storage: patch_gemm4_ex (one weight), patch_gemm4_many; the passes of a call joined by "+"
 MEASURED4 = [
-    ([49152], 2048, 64, 0.0, 12, False, {'strip': 16.8, 'b1': 18.4}),
-    ([36864], 4096, 128, 0.0, 16, False, {'strip': 24.1, 'b1': 29.6}),
-    ([1024], 8192, 128, 0.0, 193, False, {'strip+strip+strip+strip': 102.7, 'prefill': 120.5}),
-    ([128256], 1024, 64, 1.0, 64, False, {'prefill': 31.7, 'b1': 36.4}),
-    ([36864], 4096, 128, 0.0, 32, False, {'strip': 46.4, 'b1': 34.5}),
-    ([5120], 13824, 128, 1.0, 193, False, {'prefill': 144.7, 'strip+strip+strip+strip': 185.8}),
-    ([512], 13824, 64, 0.0, 9, True, {'strip': 12.5, 'b8': 14.1}),
-    ([32000], 4096, 64, 0.0, 2, True, {'strip': 19.4, 'b1': 21.4}),
-    ([256], 1024, 128, 0.0, 96, True, {'strip+strip': 12.3, 'prefill': 13.3}),
-    ([512], 13824, 64, 0.5, 9, True, {'strip': 12.0, 'b8': 13.4}),
-    ([32000], 4096, 128, 1.0, 80, True, {'prefill': 34.9, 'b1+b1': 43.5}),
-    ([11008] * 2, 4096, 128, 0.0, 12, False, {'strip': 17.5, 'b1': 20.0}),
-    ([11008] * 2, 4096, 64, 0.0, 16, False, {'strip': 18.6, 'b1': 21.9}),
-    ([49152], 2048, 128, 0.0, 17, False, {'strip': 24.3, 'b1': 18.8}),
-    ([896], 896, 64, 0.0, 256, False, {'strip+strip+strip+strip': 26.5, 'prefill': 17.4}),
-    ([32000], 4096, 128, 0.5, 64, False, {'prefill': 56.6, 'b1': 29.1}),
-    ([32000], 4096, 64, 0.5, 65, False, {'prefill': 61.4, 'b1+strip': 49.1}),
-    ([128256], 1024, 64, 1.0, 16, False, {'strip': 20.8, 'b1': 16.9}),
-    ([13824], 5120, 64, 1.0, 80, False, {'strip+strip': 59.3, 'b1+strip': 46.9}),
-    ([5120], 13824, 128, 0.0, 16, True, {'strip': 23.0, 'b6': 16.3}),
-    ([896], 896, 64, 0.0, 256, True, {'strip+strip+strip+strip': 26.5, 'prefill': 17.4}),
-    ([896], 4864, 128, 0.5, 33, True, {'strip': 13.0, 'b8': 10.3}),
-    ([256], 1024, 64, 0.5, 160, True, {'strip+strip+strip': 18.6, 'prefill': 13.4}),
-    ([896], 4864, 128, 1.0, 33, True, {'strip': 13.1, 'b8': 9.9}),
-    ([4864], 896, 64, 1.0, 129, True, {'strip+strip+strip': 18.5, 'prefill': 14.3}),
-    ([13824] * 2, 5120, 128, 0.0, 48, False, {'strip': 58.3, 'b1': 32.1}),
-    ([13824] * 2, 5120, 128, 0.5, 16, False, {'strip': 28.7, 'b1': 23.1}),
-    ([28672] * 2, 4096, 64, 1.0, 64, False, {'strip': 92.7, 'b1': 53.6}),
+    ([49152], 2048, 64, 0.0, 12, False, {'strip': 17.1, 'b1': 19.3}),
+    ([36864], 4096, 128, 0.0, 16, False, {'strip': 22.3, 'b1': 29.9}),
+    ([1024], 8192, 128, 0.0, 193, False, {'strip+strip+strip+strip': 100.8, 'prefill': 120.5}),
+    ([128256], 1024, 64, 1.0, 64, False, {'prefill': 33.3, 'b1': 36.8}),
+    ([36864], 4096, 128, 0.0, 32, False, {'strip': 40.3, 'b1': 34.5}),
+    ([5120], 13824, 128, 1.0, 193, False, {'prefill': 148.3, 'strip+strip+strip+strip': 169.6}),
+    ([512], 13824, 64, 0.0, 9, True, {'strip': 12.6, 'b8': 12.7}),
+    ([32000], 4096, 64, 0.0, 2, True, {'strip': 18.0, 'b1': 22.6}),
+    ([256], 1024, 128, 0.0, 96, True, {'strip+strip': 10.3, 'prefill': 13.4}),
+    ([512], 13824, 64, 0.5, 9, True, {'strip': 11.9, 'b8': 12.3}),
+    ([32000], 4096, 128, 1.0, 80, True, {'prefill': 34.8, 'b1+b1': 42.7}),
+    ([11008] * 2, 4096, 128, 0.0, 12, False, {'strip': 16.6, 'b1': 20.0}),
+    ([11008] * 2, 4096, 64, 0.0, 16, False, {'strip': 17.4, 'b1': 21.8}),
+    ([49152], 2048, 128, 0.0, 17, False, {'strip': 23.5, 'b1': 18.6}),
+    ([896], 896, 64, 0.0, 256, False, {'strip+strip+strip+strip': 22.6, 'prefill': 17.3}),
+    ([32000], 4096, 128, 0.5, 64, False, {'prefill': 58.1, 'b1': 29.3}),
+    ([32000], 4096, 64, 0.5, 65, False, {'prefill': 62.2, 'b1+strip': 48.4}),
+    ([128256], 1024, 64, 1.0, 16, False, {'strip': 18.1, 'b1': 17.1}),
+    ([13824], 5120, 64, 1.0, 80, False, {'strip+strip': 54.7, 'b1+strip': 46.3}),
+    ([5120], 13824, 128, 0.0, 16, True, {'strip': 21.0, 'b6': 15.6}),
+    ([896], 896, 64, 0.0, 256, True, {'strip+strip+strip+strip': 22.7, 'prefill': 17.5}),
+    ([896], 4864, 128, 0.5, 33, True, {'strip': 12.5, 'b8': 9.3}),
+    ([256], 1024, 64, 0.5, 160, True, {'strip+strip+strip': 16.1, 'prefill': 13.5}),
+    ([896], 4864, 128, 1.0, 33, True, {'strip': 12.2, 'b8': 8.8}),
+    ([4864], 896, 64, 1.0, 129, True, {'strip+strip+strip': 15.7, 'prefill': 14.5}),
+    ([13824] * 2, 5120, 128, 0.0, 48, False, {'strip': 59.6, 'b1': 32.4}),
+    ([13824] * 2, 5120, 128, 0.5, 16, False, {'strip': 26.3, 'b1': 23.2}),
+    ([28672] * 2, 4096, 64, 1.0, 64, False, {'strip': 90.0, 'b1': 53.9}),
+    # launches just past or just below a whole number of workgroups per compute unit, and K chunks at 11 - 36 rows
+    ([32896], 4096, 128, 0.5, 24, False, {'strip': 34.6, 'b1': 30.0}),
+    ([24576], 4096, 64, 1.0, 20, False, {'strip': 16.7, 'b1': 21.4}),
+    ([49152], 2048, 64, 0.0, 14, False, {'strip': 16.9, 'b1': 19.0}),
+    ([49152], 2048, 64, 0.0, 20, False, {'strip': 24.2, 'b1': 20.8}),
+    ([28672] * 2, 4096, 64, 0.5, 1, False, {'strip': 25.5, 'b1': 33.8}),
+    ([16384], 4096, 64, 0.0, 33, False, {'strip': 24.0, 'b1': 27.2}),
+    ([512], 13824, 128, 1.0, 11, True, {'strip': 13.1, 'b8': 10.4}),
+    ([4096], 11008, 128, 1.0, 12, True, {'strip': 13.0, 'b8': 10.8}),
+    ([4096], 4096, 64, 1.0, 36, True, {'strip': 12.1, 'b8': 10.1}),
 ]
 
 
