@@ -516,9 +516,14 @@ static AutoChoice auto_choice(const GemmArgs& a, const DecodeShape& d, const int
     return c;
 }
 
-// Test hook (kernels.h)
+// Test hooks (kernels.h)
 int patch_test_schedule(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* kernel, int* chunks) {
-    if (!N || !kernel || !chunks || M < 1 || count < 1 || count > kMaxMany || sparse_pct < 0 || sparse_pct > 100) return -1;
+    int deals[8];
+    return patch_test_schedule_deals(M, count, N, K, tile, sparse_pct, ws_bytes, kernel, chunks, deals);
+}
+
+int patch_test_schedule_deals(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* kernel, int* chunks, int* deals) {
+    if (!N || !kernel || !chunks || !deals || M < 1 || count < 1 || count > kMaxMany || sparse_pct < 0 || sparse_pct > 100) return -1;
     GemmArgs a = {};
     a.M = M; a.N = N[0]; a.K = K;
     a.tile = tile; a.Tk = (int)(K / tile);
@@ -535,6 +540,7 @@ int patch_test_schedule(int64_t M, int count, const int64_t* N, int64_t K, int t
     if (c.one_pass || c.path == PATCH_PATH_PREFILL) {
         kernel[0] = c.one_pass ? c.pass.kernel : 3;
         chunks[0] = c.one_pass ? c.pass.chunks : 1;
+        deals[0] = 1;
         if (int split = 1; kernel[0] == 3 && count == 1 && prefill_prefers_128_rows(a, &split)) {
             kernel[0] = 4;
             chunks[0] = split;
@@ -547,7 +553,8 @@ int patch_test_schedule(int64_t M, int count, const int64_t* N, int64_t K, int t
         const int rows = (int)(M - m0 < kDecodeRows ? M - m0 : kDecodeRows);
         const DecodePlan plan = decode_plan(a, d, rows);
         kernel[n] = plan.kernel;
-        chunks[n] = plan.chunks * (int)rows_deals(rows, rows_each(rows, plan.deal));
+        chunks[n] = plan.chunks;
+        deals[n] = (int)rows_deals(rows, rows_each(rows, plan.deal));
     }
     return n;
 }

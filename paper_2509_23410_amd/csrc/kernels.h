@@ -112,9 +112,11 @@ void launch_prefill_wreg_set(const GemmArgs& a, const WeightSet& set, hipStream_
 struct patch_packed4;
 extern "C" {
 // What AUTO takes for M rows of `count` weights of N[i] x K features sharing X (sparse_pct per cent of the tiles 2:4) given ws_bytes of
-// workspace on 256 compute units: kernel (0 strip, 1 mid, 2 batch, 3 the prefill path, 4 that in blocks of 128 rows) and workgroups per
-// feature group - K chunks x deals of the rows - of every pass (1 for kernel 3), at most 8 passes; returns their number, -1 = bad arguments.  Runs on the host alone.
+// workspace on 256 compute units: kernel (0 strip, 1 mid, 2 batch, 3 the prefill path, 4 that in blocks of 128 rows) and K chunks of every
+// pass (1 for kernel 3), at most 8; returns their number, -1 = bad arguments.  Runs on the host alone.
 int patch_test_schedule(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* kernel, int* chunks);
+// The same and, per pass, over how many workgroups per feature group its rows are dealt (rows_deals; 1 = not).
+int patch_test_schedule_deals(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* kernel, int* chunks, int* deals);
 // The 4-bit product of `count` weights sharing X by one kernel, whatever the dispatch would take: 0 the strip kernel, 1 batch4_kernel, both in
 // passes of up to 64 rows, 2 / 3 the prefill-shaped kernel in blocks of 128 / 256 rows (a single weight).  chunks > 1 (a single weight,
 // kernels 1 - 3): K in that many chunks over the workspace.

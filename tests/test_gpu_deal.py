@@ -20,22 +20,26 @@ def _weight(N, K, tile, f, seed):
     return W.double(), B.patch_pack(W, N, K, c.tile_map, tile, stream)
 
 
-def _groups(M, N, K, tile, f, ws_bytes):
-    """workgroups per feature group of the pass the dispatch takes"""
-    kernel, chunks = (ctypes.c_int * 8)(), (ctypes.c_int * 8)()
-    assert B.lib().patch_test_schedule(ctypes.c_int64(M), len(N), (ctypes.c_int64 * len(N))(*N), ctypes.c_int64(K), tile, round(100 * f), ctypes.c_size_t(ws_bytes), kernel, chunks) == 1
-    return kernel[0], chunks[0]
+def _plan(M, N, K, tile, f, ws_bytes):
+    """kernel (0 strip, 1 mid), K chunks and deals of the rows of the pass the dispatch takes"""
+    kernel, chunks, deals = (ctypes.c_int * 8)(), (ctypes.c_int * 8)(), (ctypes.c_int * 8)()
+    assert B.lib().patch_test_schedule_deals(ctypes.c_int64(M), len(N), (ctypes.c_int64 * len(N))(*N), ctypes.c_int64(K), tile, round(100 * f), ctypes.c_size_t(ws_bytes), kernel, chunks, deals) == 1
+    return kernel[0], chunks[0], deals[0]
 
 
-@pytest.mark.parametrize("tile,N,K,f,ws", [(128, [896] * 3, 896, 0.5, 0), (128, [896], 4864, 0.5, 0), (64, [896], 4864, 1.0, 32 << 20), (128, [2048], 2048, 0.0, 0), (64, [2048] * 3, 2048, 0.5, 0),
-                                           (128, [4096], 4096, 0.5, 32 << 20), (64, [512], 13824, 0.5, 32 << 20), (64, [1088, 64, 320], 1088, 0.4, 32 << 20)])
-def test_rows_dealt_over_workgroups(tile, N, K, f, ws):
+# takes: (kernel, K in chunks or not, deals) that have to be among the passes; 1472 and 1088 + 64 + 320 features are 92 strips, 5504 are 86 groups of 64
+@pytest.mark.parametrize("tile,N,K,f,ws,takes", [
+    (128, [896] * 3, 896, 0.5, 0, {(1, False, 3), (1, False, 4)}), (128, [896], 4864, 0.5, 0, {(0, False, 2), (0, False, 3), (0, False, 4)}),
+    (64, [896], 4864, 1.0, 32 << 20, {(1, True, 2), (1, True, 3)}), (128, [2048], 2048, 0.0, 0, {(0, False, 2)}), (64, [2048] * 3, 2048, 0.5, 0, {(1, False, 2)}),
+    (128, [4096], 4096, 0.5, 0, {(1, False, 3), (1, False, 4)}), (64, [512], 13824, 0.5, 32 << 20, {(1, True, 2), (1, True, 3), (1, True, 4)}),
+    (64, [1088, 64, 320], 1088, 0.4, 32 << 20, {(0, False, 2)}), (64, [1472], 1472, 0.5, 32 << 20, {(0, False, 2)}), (128, [5504], 2048, 0.5, 0, {(1, False, 2)})])
+def test_rows_dealt_over_workgroups(tile, N, K, f, ws, takes):
     weights = [_weight(n, K, tile, f, 1 + i) for i, n in enumerate(N)]
-    dealt = 0
+    taken = set()
     for M in (17, 31, 32, 33, 47, 48, 49, 63, 64):
-        kernel, groups = _groups(M, N, K, tile, f, ws)
-        dealt += groups > 1
-        print(f"deal tile={tile} N={N} K={K} M={M} kernel={kernel} workgroups per group={groups}", flush=True)
+        kernel, chunks, deals = _plan(M, N, K, tile, f, ws)
+        taken.add((kernel, chunks > 1, deals))
+        print(f"deal tile={tile} N={N} K={K} M={M} kernel={kernel} chunks={chunks} deals={deals}", flush=True)
         X = torch.randn(M, K, device="cuda", generator=torch.Generator(device="cuda").manual_seed(M)).to(torch.bfloat16)
         for dtype in (torch.float32, torch.bfloat16):
             bufs = [torch.full((M * n + 2048,), 7.0, device="cuda", dtype=dtype) for n in N]
@@ -58,4 +62,4 @@ def test_rows_dealt_over_workgroups(tile, N, K, f, ws):
                 assert bool((b[:1024] == 7.0).all()) and bool((b[1024 + M * n:] == 7.0).all()), "wrote outside Y"
             if ws:
                 assert bool((work[ws // 4:] == 7.0).all()), "wrote behind the workspace"
-    assert dealt, "no pass with several workgroups per feature group"
+    assert takes <= taken, (takes, taken)

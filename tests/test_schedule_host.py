@@ -1,8 +1,8 @@
 """What AUTO chooses against what was measured, without a device: the estimates behind the choice hold constants fitted to measurements,
 and a change of one of them must not send a call to a kernel that is slower there.  A row: features of the weights that share X, their
 K, mask tile, share of 2:4 tiles, rows of X, workspace or not, and microseconds of the kernels that come into question - strip, mid (mid*
-with K in chunks), b<chunks> = the kernel with 128 features in one pass, two passes = of 64 rows and the rest, prefill (MI355X, fp32
-output, launches back to back)."""
+with K in chunks), both with /<deals> where the rows are dealt over several workgroups per feature group, b<chunks> = the kernel with 128 features in
+one pass, two passes = of 64 rows and the rest, prefill (MI355X, fp32 output, launches back to back)."""
 import ctypes
 
 import pytest
@@ -31,14 +31,14 @@ MEASURED = [
     ([32896], 4096, 128, 0.5, 16, False, {'b1': 47.9, 'mid': 42.9}),
     ([36864], 4096, 64, 0.5, 16, False, {'b1': 48.1, 'mid': 44.5}),
     ([36864], 4096, 128, 1.0, 16, False, {'b1': 37.9, 'mid': 34.5}),
-    ([896], 896, 128, 0.0, 17, True, {'mid': 5.1, 'strip': 4.0}),
-    ([896], 896, 64, 0.5, 17, True, {'mid': 4.9, 'strip': 4.0}),
-    ([896], 896, 128, 0.5, 20, True, {'mid': 4.8, 'strip': 4.0}),
-    ([896], 896, 64, 1.0, 17, True, {'mid': 4.6, 'strip': 3.9}),
+    ([896], 896, 128, 0.0, 17, True, {'mid': 5.0, 'strip': 4.0, 'strip/2': 3.5}),
+    ([896], 896, 64, 0.5, 17, True, {'mid': 5.0, 'strip': 3.9, 'strip/2': 3.5}),
+    ([896], 896, 128, 0.5, 20, True, {'mid': 5.1, 'strip': 4.1, 'strip/2': 3.5}),
+    ([896], 896, 64, 1.0, 17, True, {'mid': 4.8, 'strip': 3.9, 'strip/2': 3.4}),
     ([13824], 5120, 128, 0.0, 56, True, {'b2': 29.3, 'prefill': 31.0, 'mid': 34.8}),
     ([128256], 1024, 128, 0.5, 56, True, {'prefill': 39.3, 'b1': 48.8}),
     ([32896], 4096, 128, 0.5, 33, True, {'prefill': 46.4, 'b1': 52.2}),
-    ([2048], 2048, 64, 1.0, 49, True, {'mid*': 9.1, 'strip': 10.3}),
+    ([2048], 2048, 64, 1.0, 49, True, {'mid*': 9.0, 'strip': 9.6, 'b4': 8.3, 'mid/4': 6.2}),
     ([13824], 5120, 64, 0.5, 96, True, {'b2': 33.1, 'prefill': 30.0}),
     ([32000], 4096, 64, 1.0, 81, True, {'prefill': 34.8, 'b1': 39.0}),
     ([32000], 4096, 128, 1.0, 96, True, {'prefill': 35.7, 'b1': 39.9}),
@@ -57,7 +57,7 @@ MEASURED = [
     ([32000], 4096, 128, 0.0, 112, False, {'b1': 52.6, 'prefill': 74.4}),
     ([20480], 4096, 64, 0.0, 12, False, {'b1': 27.4, 'mid': 35.9}),
     ([128256], 1024, 64, 0.5, 20, True, {'b1': 37.9, 'mid': 50.9}),
-    ([256], 1024, 64, 0.5, 56, True, {'mid*': 8.2, 'strip': 6.8}),
+    ([256], 1024, 64, 0.5, 56, True, {'mid*': 8.8, 'strip': 6.5, 'strip/4': 3.6}),
     ([512], 13824, 128, 0.5, 96, True, {'b8': 21.9, 'prefill': 28.8}),
     ([512], 13824, 128, 0.5, 16, True, {'b8': 14.1, 'strip': 18.3}),
     # launches of many rounds over a short K, and weights beyond the last-level cache
@@ -65,23 +65,34 @@ MEASURED = [
     ([128256], 1024, 128, 0.5, 16, True, {'b1': 35.8, 'mid': 43.4, 'strip': 43.7}),
     ([36864], 4096, 128, 0.0, 56, True, {'b1': 66.0, 'prefill': 82.7}),
     ([32000], 4096, 128, 0.5, 112, True, {'b1': 50.9, 'prefill': 43.3}),
+    # rows dealt over workgroups: few feature groups, K whole and in chunks
+    ([896] * 3, 896, 128, 0.5, 40, False, {'strip': 6.3, 'mid': 7.8, 'b1': 8.2, 'mid/3': 4.9}),
+    ([896] * 3, 896, 128, 0.5, 64, False, {'strip': 7.2, 'mid': 8.7, 'b1': 8.8, 'mid/4': 4.8}),
+    ([896], 4864, 128, 0.5, 64, False, {'strip': 21.3, 'mid': 28.5, 'strip/4': 8.6}),
+    ([896], 4864, 128, 0.5, 24, True, {'strip': 11.5, 'mid*': 7.8, 'b8': 8.6, 'mid*/2': 6.8}),
+    ([896], 4864, 128, 0.5, 40, True, {'strip': 16.8, 'mid*': 9.7, 'b8': 9.5, 'mid*/3': 7.7}),
+    ([512], 13824, 64, 0.5, 64, True, {'mid*': 17.6, 'b8': 15.5, 'mid*/4': 9.7}),
+    ([4096], 4096, 128, 0.5, 64, False, {'strip': 20.1, 'mid': 25.8, 'b1': 27.1, 'mid/4': 13.1}),
+    ([2048] * 3, 2048, 64, 0.5, 48, True, {'strip': 18.9, 'mid': 14.2, 'b1': 14.1, 'mid/2': 10.4}),
+    ([4864], 13824, 128, 0.5, 40, False, {'strip': 80.4, 'mid': 59.6, 'b1': 74.9, 'mid/3': 39.9}),
+    ([1472], 1472, 64, 0.5, 33, False, {'strip': 6.8, 'mid': 8.6, 'b1': 8.8, 'strip/2': 5.8}),
 ]
 
 
 def _schedule(N, K, tile, f, M, workspace):
-    """-> [(kernel, K chunks) of every pass]; kernel 0 strip, 1 mid, 2 batch, 3 / 4 prefill (4: in blocks of 128 rows)."""
-    kernel, chunks = (ctypes.c_int * 8)(), (ctypes.c_int * 8)()
-    n = B.lib().patch_test_schedule(ctypes.c_int64(M), len(N), (ctypes.c_int64 * len(N))(*N), ctypes.c_int64(K), tile, round(100 * f),
-                                    ctypes.c_size_t(384 << 20 if workspace else 0), kernel, chunks)
+    """-> [(kernel, K chunks, deals of the rows) of every pass]; kernel 0 strip, 1 mid, 2 batch, 3 / 4 prefill (4: in blocks of 128 rows)."""
+    kernel, chunks, deals = (ctypes.c_int * 8)(), (ctypes.c_int * 8)(), (ctypes.c_int * 8)()
+    n = B.lib().patch_test_schedule_deals(ctypes.c_int64(M), len(N), (ctypes.c_int64 * len(N))(*N), ctypes.c_int64(K), tile, round(100 * f),
+                                    ctypes.c_size_t(384 << 20 if workspace else 0), kernel, chunks, deals)
     assert n > 0
-    return [(kernel[i], chunks[i]) for i in range(n)]
+    return [(kernel[i], chunks[i], deals[i]) for i in range(n)]
 
 
 @pytest.mark.parametrize("N,K,tile,f,M,workspace,us", MEASURED)
 def test_choice_is_no_slower_than_what_was_measured(N, K, tile, f, M, workspace, us):
     passes = _schedule(N, K, tile, f, M, workspace)
-    (k, c), *rest = passes
-    chosen = "two passes" if rest else ("strip", "mid" if c == 1 else "mid*", f"b{c}", "prefill", "prefill")[k]
+    (k, c, deals), *rest = passes
+    chosen = "two passes" if rest else ("strip", "mid" if c == 1 else "mid*", f"b{c}", "prefill", "prefill")[k] + (f"/{deals}" if deals > 1 else "")
     assert chosen in us, (chosen, us)
     assert us[chosen] <= 1.03 * min(us.values()) + 0.3, (chosen, us)
 
@@ -93,7 +104,7 @@ def test_choice_is_no_slower_than_what_was_measured(N, K, tile, f, M, workspace,
 ])
 def test_block_height_of_mask_tile_64(N, K, M, us):
     """A prefill launch on mask tile 64, f = 1/2, with a workspace: blocks of 128 rows or the 256-row register-weight kernel."""
-    (k, _), = _schedule([N], K, 64, 0.5, M, True)
+    (k, _, _), = _schedule([N], K, 64, 0.5, M, True)
     assert us[{4: 128, 3: 256}[k]] == min(us.values())
 
 
