@@ -420,10 +420,11 @@ static double pass_us(const PassPrice* p, const GemmArgs& a, const DecodeShape& 
 // The cheapest of the three; up to 7 rows (11 for a single weight) always the strip kernel, whose X is small then.  mid_kernel has to be 0.3 us ahead
 // of it, batch_kernel 0.7 of both; of the strip kernel with its rows dealt (below) mid_kernel may be 0.15 behind.  only_wide: batch_kernel, in its best number of chunks.
 // In a call of 17 .. 64 rows the strip kernel and mid_kernel may deal the blocks of 16 rows over 2 or 4 workgroups per feature group: a weight of few groups leaves compute units idle
-// while each of its workgroups draws all of X.  What is read twice is the weight, from the L2s.  The same prices hold (540 combinations of 15 weights
-// and sets, both mask tiles, f = 0, 1/2 and 1, 17 - 64 rows: 12 % faster on average than undealt, 3 % behind the best of all kernels,
-// deals and chunks, 4 cells 4 - 8 % behind the undealt choice; batch_kernel dealt as well gained another 0.4 %).  f = 1/2, mask tile 128, 64 rows, undealt -> dealt: three 896 x 896 6.5 -> 5.3, 896 x 4864
-// (8 chunks) 12.3 -> 8.2 in one launch, 4096 x 4096 14.7 -> 11.2, three 2048 x 2048 13.3 -> 10.0 us.
+// while each of its workgroups draws all of X.  The weights are read by every deal, from one L2 (deal_units).  The same prices hold: 5128 dealt calls over 48 weights and
+// sets, both mask tiles, f = 0, 1/2 and 1, 17 - 64 rows, hot and cold weights, took 0.70 of the time of the best undealt choice, one of them 6 % more (8192 x 2048, f = 0,
+// 44 rows with a workspace: 13.1 us, batch_kernel in 4 chunks 12.1).  f = 1/2, mask tile 128, 64 rows, undealt -> dealt: three 896 x 896 7.2 -> 4.8, 896 x 4864
+// 21.3 -> 8.6, 4096 x 4096 20.1 -> 13.1, 4864 x 13824 at 40 rows 59.6 -> 39.9 us.  (A call of more rows is passes of 64 and the rest, and takes the prefill path
+// where that is cheaper; dealing its passes was not measured.)
 static DecodePlan decode_plan(const GemmArgs& a, const DecodeShape& d, int rows, bool only_wide = false) {
     DecodePlan best = {0, 1, 0.0};
     if (!only_wide) {
@@ -558,6 +559,8 @@ int patch_test_schedule_deals(int64_t M, int count, const int64_t* N, int64_t K,
     }
     return n;
 }
+
+int patch_test_deal_units(int units, int deals, int n_cus) { return units < 1 || deals < 1 || n_cus < 8 ? -1 : (int)deal_units(units, (unsigned)deals, n_cus); }
 
 patch_status patch_gemm_ex(const void* X, int64_t M, const patch_packed* P, void* Y, void* stream, const patch_gemm_opts* opts) {
     if (!X || !P || !Y || M < 0) return PATCH_ERR_ARG;

@@ -76,7 +76,8 @@ __device__ __forceinline__ u32x4 rows_up(u32x4 v, int s) {   // s is a constant 
 //      each - column c = operand c / XR (K-step (c / XR) / 2 of the load, half (c / XR) % 2), row c % XR - so one
 //      instruction fetches X for 8 / XR steps, and each step rotates its two operands down to columns 0 .. XR - 1
 //      (four DPP moves each).  Columns XR .. 15 of the product are then other steps' leftovers; they are never stored.
-template <int TILE, int NK, int MAXW, int RB, typename SetT, int XR = 16>
+// DEAL: rows dealt over gridDim.z workgroups, gridDim.x rounded up (deal_units).
+template <int TILE, int NK, int MAXW, int RB, typename SetT, int XR = 16, bool DEAL = false>
 __global__ __launch_bounds__(MAXW * 64) void decode_kernel(const uint16_t* __restrict__ X, int64_t m0, int rows, int64_t K, int Tk,
                                                            const SetT set, int ybf16) {
     constexpr bool kOne = sizeof(SetT) == sizeof(WeightOne);
@@ -86,9 +87,10 @@ __global__ __launch_bounds__(MAXW * 64) void decode_kernel(const uint16_t* __res
     constexpr int SPL = kWide ? 8 / XR : 1;               // steps served by one X load
     constexpr int NL = kWide ? (NK + SPL - 1) / SPL : 1;   // X loads per pass
     __shared__ f32x4 red[MAXW][RB][64];
-    // rows dealt over gridDim.z workgroups (launch_decode_set)
-    m0 += 16 * RB * (int64_t)blockIdx.z;
-    rows -= 16 * RB * (int)blockIdx.z;
+    if constexpr (DEAL) {
+        m0 += 16 * RB * (int64_t)blockIdx.z;
+        rows -= 16 * RB * (int)blockIdx.z;
+    }
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -127,6 +129,8 @@ __global__ __launch_bounds__(MAXW * 64) void decode_kernel(const uint16_t* __res
         N = (int64_t)uniform64((uint64_t)N);
     }
     const int strip = (int)blockIdx.x - __builtin_amdgcn_readfirstlane(first);
+    if constexpr (DEAL)
+        if ((int64_t)strip * kStripRows >= N) return;
     const int tn = strip / SPT, s = strip % SPT;
     const int col = lane & 15, q = lane >> 4;
     const bool xvalid = col < rows;   // row block 0; block rb holds rows 16 rb + col
@@ -361,8 +365,12 @@ __global__ __launch_bounds__(MAXW * 64) void decode_kernel(const uint16_t* __res
 template <int TILE, typename SetT>
 static void launch_decode_s(const GemmArgs& a, const SetT& set, int units, int64_t m0, int rows, int deal, int nk, int kw, int xr, hipStream_t stream) {
     const int each = rows_each(rows, deal);
-    dim3 grid((unsigned)units, 1, rows_deals(rows, each)), block((unsigned)(kw * 64));
-    if (each > 32) hipLaunchKernelGGL((decode_kernel<TILE, 4, 8, 4, SetT>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
+    const unsigned deals = rows_deals(rows, each);
+    const dim3 grid(deal_units(units, deals, a.n_cus), 1, deals), block((unsigned)(kw * 64));
+    if (deals > 1) {
+        auto* kernel = each > 16 ? decode_kernel<TILE, 4, 8, 2, SetT, 16, true> : nk == 8 ? decode_kernel<TILE, 8, 8, 1, SetT, 16, true> : decode_kernel<TILE, 4, 16, 1, SetT, 16, true>;
+        hipLaunchKernelGGL(kernel, grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
+    } else if (each > 32) hipLaunchKernelGGL((decode_kernel<TILE, 4, 8, 4, SetT>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
     else if (each > 16) hipLaunchKernelGGL((decode_kernel<TILE, 4, 8, 2, SetT>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
     else if (xr == 16 && nk == 8) hipLaunchKernelGGL((decode_kernel<TILE, 8, 8, 1, SetT>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
     else if (xr == 16) hipLaunchKernelGGL((decode_kernel<TILE, 4, 16, 1, SetT>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);

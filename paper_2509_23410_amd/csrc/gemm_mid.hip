@@ -41,17 +41,17 @@ __device__ __forceinline__ uint64_t mid_uniform64(uint64_t v) {
 }
 
 // RB = 16-row blocks of X (1: up to 16 rows, 2: up to 32, 4: up to 64).  SPLIT: gridDim.y K-chunks, partial sums to a workspace.
+// DEAL: rows dealt over gridDim.z workgroups, K whole: gridDim.x rounded up (deal_units).  Instantiations of their own: the check costs a launch that has no deals 3 %.
 // Two 64-column steps per pass, all their loads in flight together; the register budget is held to two wavefronts
 // per SIMD (243 registers at RB = 4), so a second workgroup's loads overlap this one's matrix instructions.
-template <int TILE, int RB, bool SPLIT>
+template <int TILE, int RB, bool SPLIT, bool DEAL>
 __global__ __launch_bounds__(kMidKW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void mid_kernel(const uint16_t* __restrict__ X, int64_t m0, int rows, int64_t K, int Tk,
                                                           const WeightSet set, int ybf16) {
     constexpr int KPT = TILE / kStepCols, SPT = TILE / kStripRows, GPT = SPT / kMidSB;  // groups per tile row
     constexpr int SB = kMidSB, NK = kMidNK, KW = kMidKW;
     constexpr int KH = KW / 2;
     __shared__ mid_f32x4 red[KH][SB * RB][64];  // 64 KB at RB = 4: half of the wavefronts at a time
-    // rows dealt over gridDim.z workgroups
-    const int all_rows = rows, row0 = 16 * RB * (int)blockIdx.z;
+    const int all_rows = rows, row0 = DEAL ? 16 * RB * (int)blockIdx.z : 0;
     m0 += row0;
     rows -= row0;
 
@@ -78,6 +78,8 @@ __global__ __launch_bounds__(kMidKW * 64) __attribute__((amdgpu_waves_per_eu(2, 
     Y = reinterpret_cast<float*>(mid_uniform64(reinterpret_cast<uint64_t>(Y)));
     N = (int64_t)mid_uniform64((uint64_t)N);
     const int grp = (int)blockIdx.x - __builtin_amdgcn_readfirstlane(first);
+    if constexpr (DEAL && !SPLIT)
+        if ((int64_t)grp * (SB * kStripRows) >= N) return;
     const int tn = grp / GPT, s0 = (grp % GPT) * SB;  // tile row, first strip inside the tile
     const int col = lane & 15, q = lane >> 4;
     const uint32_t* trow = table + (int64_t)tn * Tk;
@@ -279,24 +281,25 @@ int mid_split(const GemmArgs& a, int rows, int requested, int deals) {
     return s < 2 ? 1 : s;
 }
 
+template <int TILE, bool SPLIT>
+static void launch_mid_k(const GemmArgs& a, const WeightSet& set, int64_t m0, int rows, int split, int deal, int ybf16, hipStream_t stream) {
+    const int each = rows_each(rows, deal);
+    const unsigned deals = rows_deals(rows, each);
+    auto* kernel = each <= 16 ? (deals > 1 ? mid_kernel<TILE, 1, SPLIT, true> : mid_kernel<TILE, 1, SPLIT, false>)
+                 : each <= 32 ? (deals > 1 ? mid_kernel<TILE, 2, SPLIT, true> : mid_kernel<TILE, 2, SPLIT, false>) : mid_kernel<TILE, 4, SPLIT, false>;
+    hipLaunchKernelGGL(kernel, dim3(SPLIT ? (unsigned)set.units : deal_units(set.units, deals, a.n_cus), (unsigned)split, deals), dim3(kMidKW * 64), 0, stream, a.X, m0, rows, a.K, a.Tk, set, ybf16);
+}
+
 template <int TILE>
 static void launch_mid_t(const GemmArgs& a, const WeightSet& set, int64_t m0, int rows, int split, int deal, hipStream_t stream) {
-    const dim3 block(kMidKW * 64);
-    const int each = rows_each(rows, deal);
     if (split > 1) {
         WeightSet part = set;
         part.Y[0] = a.ws;
-        const dim3 grid((unsigned)set.units, (unsigned)split, rows_deals(rows, each));
-        if (each <= 16) hipLaunchKernelGGL((mid_kernel<TILE, 1, true>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, part, 0);
-        else if (each <= 32) hipLaunchKernelGGL((mid_kernel<TILE, 2, true>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, part, 0);
-        else hipLaunchKernelGGL((mid_kernel<TILE, 4, true>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, part, 0);
+        launch_mid_k<TILE, true>(a, part, m0, rows, split, deal, 0, stream);
         float* y0 = a.ybf16 ? reinterpret_cast<float*>(reinterpret_cast<uint16_t*>(set.Y[0]) + m0 * set.N[0]) : set.Y[0] + m0 * set.N[0];
         wr_reduce(a.ws, (size_t)rows * (size_t)set.N[0] / 4, split, y0, a.ybf16, stream);
     } else {
-        const dim3 grid((unsigned)set.units, 1, rows_deals(rows, each));
-        if (each <= 16) hipLaunchKernelGGL((mid_kernel<TILE, 1, false>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
-        else if (each <= 32) hipLaunchKernelGGL((mid_kernel<TILE, 2, false>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
-        else hipLaunchKernelGGL((mid_kernel<TILE, 4, false>), grid, block, 0, stream, a.X, m0, rows, a.K, a.Tk, set, a.ybf16);
+        launch_mid_k<TILE, false>(a, set, m0, rows, 1, deal, a.ybf16, stream);
     }
 }
 

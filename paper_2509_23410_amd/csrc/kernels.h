@@ -61,6 +61,15 @@ constexpr int kBatchRows = 128;    // batch_kernel
 // and how many workgroups that makes
 inline int rows_each(int rows, int deal) { return deal > 1 ? 16 * (((rows + 15) / 16 + deal - 1) / deal) : rows; }
 inline unsigned rows_deals(int rows, int each) { return (unsigned)((rows + each - 1) / each); }
+// gridDim.x of a launch over `units` feature groups (K whole) whose rows are dealt: a multiple of 8, workgroups beyond `units` end at once.  Workgroups go to the eight dies in
+// turn by their linear index, each die with an L2 of its own: those that share a feature group's weights then meet in one L2, and memory sends the weights
+// once.  64 rows, units as they are -> rounded up: three 896 x 896 (42 groups) 5.3 -> 5.1 us, weights cold 7.1 -> 5.9; 40 rows of 4864 x 13824, f = 1/2 (76) 47.5 -> 39.7;
+// 24 rows of 5504 x 2048, f = 0 (86) 12.0 -> 9.4.  Not where the fullest die would need one more round of its compute units than all of them together, nor for
+// K in chunks (896 x 4864 in 6 chunks, 3 deals: 36 workgroups on the 32 units of a die, 7.4 -> 10.1; in 8 and 2, no round more, 2 % slower: few bytes a group).
+inline unsigned deal_units(int units, unsigned deals, int n_cus) {
+    const int each = (int)deals, die = n_cus / 8, up = (units + 7) / 8;
+    return (unsigned)(deals > 1 && (up * each + die - 1) / die <= (units * each + n_cus - 1) / n_cus ? 8 * up : units);
+}
 
 // Up to kDecodeRows rows of X starting at row m0 (decode shape; 16-row blocks, the weights streamed once per launch).
 // split_k = K slices (wavefronts) per workgroup, 0 picks a default.  Returns the number used.
@@ -117,6 +126,8 @@ extern "C" {
 int patch_test_schedule(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* kernel, int* chunks);
 // The same and, per pass, over how many workgroups per feature group its rows are dealt (rows_deals; 1 = not).
 int patch_test_schedule_deals(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* kernel, int* chunks, int* deals);
+// deal_units: gridDim.x of a launch over `units` feature groups whose rows go over `deals` workgroups
+int patch_test_deal_units(int units, int deals, int n_cus);
 // The 4-bit product of `count` weights sharing X by one kernel, whatever the dispatch would take: 0 the strip kernel, 1 batch4_kernel, both in
 // passes of up to 64 rows, 2 / 3 the prefill-shaped kernel in blocks of 128 / 256 rows (a single weight).  chunks > 1 (a single weight,
 // kernels 1 - 3): K in that many chunks over the workspace.

@@ -97,6 +97,17 @@ def test_choice_is_no_slower_than_what_was_measured(N, K, tile, f, M, workspace,
     assert us[chosen] <= 1.03 * min(us.values()) + 0.3, (chosen, us)
 
 
+@pytest.mark.parametrize("deals", [1, 2, 3, 4])
+def test_deals_of_a_feature_group_meet_in_one_die(deals):
+    """256 compute units on eight dies that take workgroups in turn: a dealt launch over `units` feature groups is made a multiple of 8 wide, so that
+    a group's workgroups are multiples of 8 apart, unless the fullest die would then need more rounds than the launch as it is."""
+    for units in range(1, 300):
+        width = B.lib().patch_test_deal_units(units, deals, 256)
+        fullest = max(deals * len(range(die, units, 8)) for die in range(8))
+        rounds, fits = -(-units * deals // 256), -(-fullest // 32)
+        assert width == (units if deals == 1 or fits > rounds else -(-units // 8) * 8), (units, deals)
+
+
 @pytest.mark.parametrize("N,K,M,us", [
     (5120, 5120, 129, {128: 22.6, 256: 27.0}), (5120, 5120, 160, {128: 23.2, 256: 27.7}), (6912, 3456, 192, {128: 23.3, 256: 27.3}),
     (4096, 4096, 1003, {128: 43.0, 256: 46.2}), (11008, 4096, 300, {128: 52.8, 256: 48.1}), (13824, 5120, 300, {128: 65.6, 256: 60.6}),
