@@ -174,7 +174,8 @@ patch_status patch_gemm_static(const void* X, int64_t M, const patch_packed* P, 
  *   decode path (M <= 256): 16-feature-strip kernel with 8 or 4 K-steps per wavefront (variants 2 / 3) and 2 .. 16
  *     wavefronts per workgroup (split_k: the wavefronts-per-compute-unit dimension), up to 8 rows both ways of loading
  *     X (variants 5 / 6), from 12 rows the 64-features-per-wavefront kernel (variant 4) unsplit and with K chunks over the
- *     workspace and the kernel with 128 features per workgroup (variant 7) unsplit and in the planned number of chunks;
+ *     workspace, the kernel with 128 features per workgroup (variant 7) unsplit and in the planned number of chunks, and with a
+ *     workspace what AUTO would run of this path (variant 0, split_k 0);
  *   prefill path, tile 128: the execution tiles 256 x 256 with one wavefront per SIMD (default), 256 x 256 with two
  *     (variant 2) and the small 128 x 128 tile (variant 1; Appendix O reports that small execution tiles under-use
  *     the matrix units - it is timed so that the report shows it), and the K-split counts the workspace allows;

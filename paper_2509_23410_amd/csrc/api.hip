@@ -635,6 +635,7 @@ patch_status patch_tune_all(const void* X, int64_t M, const patch_packed* P, voi
         for (int kw : {2, 4, 8, 16})           // wavefronts per workgroup
             for (int v : {2, 3})
                 if (kw * (v == 2 ? 8 : 4) <= 2 * steps && (kw <= 8 || v == 3)) add(PATCH_PATH_DECODE, kw, v, false);
+        if (M >= 12 && workspace) add(PATCH_PATH_DECODE, 0, 0, true);   // what AUTO takes of the decode path: K chunks and dealt rows together are no other candidate's
         if (M >= 12) {  // the 64-features-per-wavefront kernel, unsplit and with K-chunks over the workspace
             add(PATCH_PATH_DECODE, 0, 4, false);
             const size_t per_slice = (size_t)(M < kDecodeRows ? M : kDecodeRows) * (size_t)P->N * sizeof(float);

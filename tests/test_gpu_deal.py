@@ -63,3 +63,21 @@ def test_rows_dealt_over_workgroups(tile, N, K, f, ws, takes):
             if ws:
                 assert bool((work[ws // 4:] == 7.0).all()), "wrote behind the workspace"
     assert takes <= taken, (takes, taken)
+
+
+@pytest.mark.parametrize("M", [12, 17, 40, 64])
+def test_tuner_times_what_an_untuned_call_runs(M):
+    """512 x 13824 with a workspace: from 17 rows on mid_kernel in chunks with its rows dealt, which no single variant stands for"""
+    tile, N, K, f = 64, 512, 13824, 0.5
+    _, P = _weight(N, K, tile, f, 1)
+    X = torch.randn(M, K, device="cuda", generator=torch.Generator(device="cuda").manual_seed(M)).to(torch.bfloat16)
+    Y, work, stream = torch.empty(M, N, device="cuda"), torch.empty(8 << 20, device="cuda"), torch.cuda.current_stream().cuda_stream
+    print(f"tune M={M}", flush=True)
+    timed = B.patch_tune_all(X, M, P, Y, work, stream=stream, reps=2)
+    assert len(timed) < 64 and dict(path=B.PATH_DECODE, split_k=0, variant=0, uses_workspace=True) in [sched for sched, _ in timed]
+    _, chunks, deals = _plan(M, [N], K, tile, f, 4 * work.numel())
+    assert (chunks > 1 and deals > 1) or M < 17
+    B.patch_gemm(X, M, P, Y, stream, path=B.PATH_DECODE, workspace=work)
+    auto = torch.empty_like(Y)
+    B.patch_gemm(X, M, P, auto, stream, workspace=work)
+    assert torch.equal(Y, auto)
