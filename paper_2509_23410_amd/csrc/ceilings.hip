@@ -10,6 +10,8 @@
 #include <stdint.h>
 
 #include "../../include/patch.h"
+#include "epilogue.h"
+#include "kernels.h"
 
 namespace patch {
 
@@ -249,6 +251,17 @@ __global__ __launch_bounds__(256) void lds_read_kernel(int iters, float* __restr
     out[(size_t)blockIdx.x * 256 + tid] = acc;
 }
 
+// Test hook (kernels.h): every bit pattern through bf16_pair, twice at once and in either half, against bf16_rne_bits
+__global__ __launch_bounds__(256) void bf16_compare_kernel(uint32_t* __restrict__ mismatches) {
+    uint32_t bad = 0;
+    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < 0x80000000u; i += gridDim.x * 256u) {
+        const float lo = __uint_as_float(2u * i), hi = __uint_as_float(2u * i + 1u);
+        bad += bf16_pair(lo, hi) != (bf16_rne_bits(lo) | (bf16_rne_bits(hi) << 16));
+        bad += bf16_pair(hi, lo) != (bf16_rne_bits(hi) | (bf16_rne_bits(lo) << 16));
+    }
+    if (bad) atomicAdd(mismatches, bad);
+}
+
 }  // namespace patch
 
 extern "C" {
@@ -324,3 +337,9 @@ patch_status patch_probe_lds_read(int workgroups, int iters, void* out, size_t o
 }
 
 }  // extern "C"
+
+int patch_test_bf16_mismatches(void* mismatches, void* stream) {
+    if (!mismatches) return PATCH_ERR_ARG;
+    hipLaunchKernelGGL(patch::bf16_compare_kernel, dim3(4096), dim3(256), 0, static_cast<hipStream_t>(stream), static_cast<uint32_t*>(mismatches));
+    return hipGetLastError() == hipSuccess ? PATCH_OK : PATCH_ERR_HIP;
+}

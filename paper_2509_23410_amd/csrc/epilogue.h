@@ -1,5 +1,5 @@
 // Output stage shared by the product kernels: four consecutive features of one row, either as fp32 (the accumulator
-// itself) or rounded to bf16 (round to nearest, ties to even, on the bit pattern: no floating-point instruction).
+// itself) or rounded to bf16 (round to nearest, ties to even: v_cvt_pk_bf16_f32).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -17,8 +17,8 @@ __device__ __forceinline__ uint32_t bf16_rne_bits(float f) {
 
 typedef unsigned int ep_u32x2 __attribute__((ext_vector_type(2)));
 
-// The same for two values at once, lo in the low half: v_cvt_pk_bf16_f32, which agrees with bf16_rne_bits on all 2^32 patterns (compared on the
-// device) in one instruction for about fourteen; a bf16 output stage of 256 x 256 spent 4 us on those (512 x 15360, K = 128: 17.9 -> 14.0 us; 65536 x 5120 at 1024 rows 454 -> 429).
+// The same for two values at once, lo in the low half: v_cvt_pk_bf16_f32, which agrees with bf16_rne_bits on all 2^32 patterns
+// (patch_test_bf16_mismatches compares them) in one instruction for about fourteen; a bf16 output stage of 256 x 256 spent 4 us on those (512 x 15360, K = 128: 17.9 -> 14.0 us; 65536 x 5120 at 1024 rows 454 -> 429).
 typedef float ep_f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 ep_bf16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {

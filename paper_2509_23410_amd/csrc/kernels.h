@@ -135,4 +135,6 @@ int patch_test_gemm4(const void* X, int64_t M, const patch_packed4* const* P, vo
                      void* workspace, size_t workspace_bytes, void* stream);
 // patch_test_schedule for patch_gemm4_ex (count 1) and patch_gemm4_many: kernels as in patch_test_gemm4.
 int patch_test_schedule4(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* kernel, int* chunks);
+// Adds to the uint32 at `mismatches` (device) how often the conversion of bf16 outputs differs from rounding on the bit pattern, over all 2^32 patterns.
+int patch_test_bf16_mismatches(void* mismatches, void* stream);
 }

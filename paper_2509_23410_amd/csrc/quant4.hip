@@ -253,8 +253,8 @@ __global__ __launch_bounds__(256) void unpack4_kernel(const uint8_t* __restrict_
 }
 
 // Up to 16 RB rows of X (RB = 1 .. 4 blocks of 16 rows) against the 4-bit weight in one pass over it.  A workgroup
-// owns R consecutive strips of 16 features (the registers hold R x RB accumulators and RB X operands per step: R <= 3
-// with one row block, R <= 2 with more); its KW wavefronts take contiguous runs of 64-column steps.  A wavefront loads
+// owns R consecutive strips of 16 features (the registers hold R x RB accumulators and RB X operands per step: R <= 3,
+// with two row blocks R <= 4); its KW wavefronts take contiguous runs of 64-column steps.  A wavefront loads
 // the X operand of a step once and uses it for all R strips (at 4 bits per weight X is the larger stream, so this
 // reuse is what bounds the traffic), works in batches of NB steps (2; 1 when R RB > 1) and issues the next batch's loads before it
 // consumes the current one.  Two batch buffers alternate; no copies.
@@ -797,11 +797,11 @@ static void launch_decode4_tile_r(int R, int XR, const uint16_t* X, int64_t m0, 
 // Strips per workgroup for a pass of `rows` rows over `strips` strips (both kernels): the R that minimises an estimate of the pass,
 //     rounds(workgroups) x (x + R),
 // in units of one strip's share of a wavefront's work.  x is what a workgroup spends on its X operands (it loads all of
-// X whatever R is; fitted: 0.15 + 0.045 rows up to 16 rows, 1.7 for 32, 4.5 for 64 - at 4 bits per weight 64 rows of X
+// X whatever R is; fitted: 0.15 + 0.045 rows up to 16 rows, 1.7 for 32, 4.5 for 64 and taken from 33 on - at 4 bits per weight 64 rows of X
 // are 16 times a strip's codes); rounds = workgroups / compute units, rounded up while at most two rounds are resident at
 // once (then the busiest compute unit decides), with half a round for the tail beyond.  More strips per workgroup
 // share X further but must not leave compute units idle: 688 strips on 256 units run as 230 workgroups of 3 (one
-// round) rather than 344 of 2.  R <= 3 (one or four row blocks) or 4 (two): what the registers hold.
+// round) rather than 344 of 2.  R <= 4 with two row blocks, else 3: what the registers hold.
 static int q4_strips_per_group(int strips, int n_cus, int rows) {
     const int max_r = rows > 16 && rows <= 32 ? 4 : kQ4MaxR;
     const double x = rows <= 16 ? 0.15 + 0.045 * rows : rows <= 32 ? 1.7 : 4.5;
@@ -1471,7 +1471,7 @@ static patch_status q4_passes(const void* X, int64_t M, const patch_packed4* con
             if (P0->tile == 128 && rows <= 8) {
                 // wavefronts per workgroup: 16 per compute unit in one, two or more workgroups, at least two tiles each (22 shapes, 5 row counts, f = 0, 1/2, 1:
                 // 1.7 % behind the best of 15 pairs of strips and wavefronts on average, 10 % at most)
-                int kw = groups <= P0->n_cus ? 16 : groups <= 2 * P0->n_cus ? 8 : 4;
+                kw = groups <= P0->n_cus ? 16 : groups <= 2 * P0->n_cus ? 8 : 4;
                 while (kw > 4 && 2 * kw > P0->Tk) kw /= 2;
                 launch_decode4_tile_r(R, rows <= 4 ? 4 : 8, static_cast<const uint16_t*>(X), m0, rows, P0->K, P0->Tk, set, groups, kw, s);
                 continue;

@@ -1,5 +1,7 @@
 """The last steps of a product: the sum over K slices at every number of slices (2 - 8 by name, more by a loop), for one weight and for a set, and
 the rounding of a bf16 output at ties, range ends, denormals, infinities and NaN, against the float64 product and torch's rounding on the CPU."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -70,3 +72,9 @@ def test_bf16_rounding_at_the_edges(path, variant):
     ref = (X[:, 0].cpu().float() + X[:, 1].cpu().float()).to(torch.bfloat16)[:, None].expand(M, N)
     assert torch.equal(ref[exact], got[exact])
     P.close()
+
+
+def test_bf16_conversion_of_every_pattern():
+    bad = torch.zeros(1, device="cuda", dtype=torch.int32)
+    st = B.lib().patch_test_bf16_mismatches(ctypes.c_void_p(bad.data_ptr()), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert st == B.OK and bad.item() == 0
