@@ -20,13 +20,14 @@
 // instructions as the bf16 decode kernel: a workgroup owns one to three strips of 16 features, its wavefronts split K,
 // partial sums meet in LDS in wavefront order (bit-reproducible); several weights sharing X run as one launch
 // (patch_gemm4_many).  That kernel takes up to 64 rows of X (one, two or four blocks of 16) per pass over the weight;
-// for more rows mask tile 128 has a prefill-shaped kernel that keeps the weight in 4 bits (prefill4_kernel below,
-// patch_gemm4_ex), and any weight can be dequantized once and packed as bf16 (patch_pack_from4).
+// for more rows there are prefill-shaped kernels that keep the weight in 4 bits (prefill4_kernel below, prefill4_kgroups_kernel in
+// quant4_kgroups.h; patch_gemm4_ex), and any weight can be dequantized once and packed as bf16 (patch_pack_from4).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <string.h>
 
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/patch.h"
@@ -1146,6 +1147,8 @@ __global__ __launch_bounds__(512) void prefill4_kernel(const uint16_t* __restric
 
 }  // namespace patch
 
+#include "quant4_kgroups.h"
+
 using namespace patch;
 
 struct patch_packed4 {
@@ -1515,16 +1518,27 @@ patch_status patch_gemm4(const void* X, int64_t M, const patch_packed4* P, void*
 
 // Passes of up to 64 rows or the prefill-shaped kernel?  Both sides are estimated from measured rates, as for the bf16 kernels:
 //   passes           q4_pass_plan's estimate of a full pass, and of the last one by its rows
-//   prefill kernel   base + rounds x steps per workgroup x (t0 + t1 fill) x (tile64 on mask tile 64) x (1 + sparse (f - 1/2)), fill = min(1, workgroups /
-//                    compute units), for blocks of 128 and of 256 rows, + for a split 3 + (2 split + 1) M N 4 B / 8.3 TB/s; splits of at most 8
-//                    slices of at least 512 columns.  Fitted to 9072 and 9630 launches of 24 weights at 17 - 400 rows, both mask tiles, f = 0, 1/2 and 1
-//                    (rms error 4 %); a step of 256 rows dequantizes the same codes for twice the rows.
-// Returns the split to launch the prefill kernel with (and the block height), or 0 for passes.
-struct Q4PrefillPrice { int bm; double base, t0, t1, tile64, sparse; };
-constexpr Q4PrefillPrice kQ4PrefillPrice[] = {{128, 4.6, 0.766, 0.076, 1.065, -0.30}, {256, 6.1, 1.22, 0.142, 1.054, -0.387}};
+//   prefill kernels  base + start fill + round (rounds - 1) + rounds x steps per workgroup x (t0 + t1 fill) x (tile64 on mask tile 64) x (1 + sparse (f - 1/2)),
+//                    fill = min(1, workgroups / compute units), + for a split second x (3 + (2 split + 1) M N 4 B / 8.3 TB/s); splits of at most 8
+//                    slices of at least 512 columns.  prefill4_kernel in blocks of 128 and of 256 rows (which converts the same codes for twice the
+//                    rows): fitted to 9072 and 9630 launches of 24 weights at 17 - 400 rows, both mask tiles, f = 0, 1/2 and 1 (rms error 4 %).
+//                    prefill4_kgroups_kernel (128 rows; its workgroup starts later and adds two halves at the end, and its steps are a third
+//                    shorter): 3012 launches of 13 weights from 896 x 896 to 13824 x 5120 at 40 - 4096 rows (4.7 %), and has to be 2 % ahead.
+// Held against all 8249 launches, with a workspace: 0.94 of the time that prefill4_kernel alone chose, one of 772 calls 1.4 % more; without: 0.79 and
+// none.  (Passes are given up by prefill4_kernel's price alone, as before: 1024 x 8192 at 193 rows without a workspace, four passes 101 us, would take
+// about 85.)  prefill4_kernel stays ahead on few steps per workgroup (1024 x 1024 at 200 rows, f = 1: 12.2 us against 14.9; 4864 x 896 at 2048 rows 24.5 and 30.8).
+// Returns the split to launch the prefill kernel with (and which), or 0 for passes.
+enum Q4PrefillKernel { kQ4Rows128, kQ4Rows256, kQ4Groups };
+struct Q4PrefillPrice { int bm; double base, start, round, t0, t1, tile64, sparse, second; };
+constexpr Q4PrefillPrice kQ4PrefillPrice[] = {{128, 4.6, 0.0, 0.0, 0.766, 0.076, 1.065, -0.30, 1.0}, {256, 6.1, 0.0, 0.0, 1.22, 0.142, 1.054, -0.387, 1.0},
+                                              {128, 8.1, 1.5, 4.1, 0.489, 0.142, 1.023, -0.255, 0.91}};
 
-static int q4_prefill_split(int64_t M, const Q4Shape& d, int* bm_out) {
-    *bm_out = 128;
+static hipError_t q4_grant(decltype(&prefill4_kgroups_kernel<128, false>) kernel) {   // more LDS than a launch gets without asking
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kKgLds);
+}
+
+static int q4_prefill_split(int64_t M, const Q4Shape& d, Q4PrefillKernel* kernel) {
+    *kernel = kQ4Rows128;
     if (M <= 16) return 0;
     const int kpt = d.tile / kStepCols, Tk = (int)(d.K / d.tile);
     const int64_t full = M / kQ4Rows;
@@ -1534,17 +1548,25 @@ static int q4_prefill_split(int64_t M, const Q4Shape& d, int* bm_out) {
     const size_t fit = d.ws_bytes / per_slice;
     int best_split = 1;
     double best = 0.0;
-    for (const Q4PrefillPrice& p : kQ4PrefillPrice) {
+    const auto take = [&](Q4PrefillKernel k) {
+        const Q4PrefillPrice& p = kQ4PrefillPrice[k];
         const int64_t blocks = ((d.N + kP4BN - 1) / kP4BN) * ((M + p.bm - 1) / p.bm);
         for (int sp = 1; sp == 1 || (sp <= 8 && (size_t)sp <= fit && sp * 512 <= d.K); ++sp) {
             const int64_t wgs = blocks * sp, rounds = (wgs + d.n_cus - 1) / d.n_cus;
             const double fill = wgs < d.n_cus ? (double)wgs / d.n_cus : 1.0;
-            double us = p.base + (double)(rounds * ((Tk + sp - 1) / sp) * kpt) * (p.t0 + p.t1 * fill) * (d.tile == 64 ? p.tile64 : 1.0) * (1.0 + p.sparse * (d.f - 0.5));
-            if (sp > 1) us += 3.0 + (2.0 * sp + 1.0) * (double)per_slice / 8.3e6;
-            if (best == 0.0 || us < best) { best = us; best_split = sp; *bm_out = p.bm; }
+            int steps = ((Tk + sp - 1) / sp) * kpt;
+            if (k == kQ4Groups) steps = (steps + 1) / 2 * 2;   // units of two
+            double us = p.base + p.start * fill + p.round * (double)(rounds - 1) + (double)(rounds * steps) * (p.t0 + p.t1 * fill) * (d.tile == 64 ? p.tile64 : 1.0) * (1.0 + p.sparse * (d.f - 0.5));
+            if (sp > 1) us += p.second * (3.0 + (2.0 * sp + 1.0) * (double)per_slice / 8.3e6);
+            if (k == kQ4Groups) us *= 1.02;
+            if (best == 0.0 || us < best) { best = us; best_split = sp; *kernel = k; }
         }
-    }
-    return best < passes_us ? best_split : 0;
+    };
+    take(kQ4Rows128);
+    take(kQ4Rows256);
+    if (best >= passes_us) return 0;
+    if (d.K <= kKgMaxK) take(kQ4Groups);
+    return best_split;
 }
 
 // Test hook (kernels.h)
@@ -1558,9 +1580,9 @@ int patch_test_schedule4(int64_t M, int count, const int64_t* N, int64_t K, int 
         d.N += N[i];
     }
     if (count == 1 && ws_bytes >= 2 * (size_t)M * (size_t)d.N * sizeof(float)) d.ws_bytes = ws_bytes;
-    int bm = 128;
-    if (const int split = count == 1 ? q4_prefill_split(M, d, &bm) : 0) {
-        kernel[0] = bm == 128 ? 2 : 3;
+    Q4PrefillKernel which;
+    if (const int split = count == 1 ? q4_prefill_split(M, d, &which) : 0) {
+        kernel[0] = 2 + which;
         chunks[0] = split;
         return 1;
     }
@@ -1574,11 +1596,12 @@ int patch_test_schedule4(int64_t M, int count, const int64_t* N, int64_t K, int 
     return n;
 }
 
-// One prefill-shaped launch in blocks of bm rows; split > 1: K slices, partial sums in ws (split x M x N floats).
-static patch_status q4_prefill(const uint16_t* X, int64_t M, const patch_packed4* P, float* Y, int split, int bm, float* ws, hipStream_t s) {
+// One prefill-shaped launch; split > 1: K slices, partial sums in ws (split x M x N floats).
+static patch_status q4_prefill(const uint16_t* X, int64_t M, const patch_packed4* P, float* Y, int split, Q4PrefillKernel kernel, float* ws, hipStream_t s) {
+    const int bm = kernel == kQ4Rows256 ? 256 : 128;
     const int tiles_n = (int)((P->N + kP4BN - 1) / kP4BN), tiles_m = (int)((M + bm - 1) / bm);
     const int grid = ((tiles_n * tiles_m + 7) / 8) * 8;
-    const int lds_bytes = 2 * bm * 128;
+    const int lds_bytes = kernel == kQ4Groups ? kKgLds : 2 * bm * 128;
     auto launch = [&](auto whole, auto sliced) {
         if (split == 1) {
             hipLaunchKernelGGL(whole, dim3(grid), dim3(512), lds_bytes, s, X, M, P->N, P->K, P->d_payload, P->d_scales, P->d_table, P->Tk, tiles_n,
@@ -1589,7 +1612,13 @@ static patch_status q4_prefill(const uint16_t* X, int64_t M, const patch_packed4
             wr_reduce(ws, (size_t)M * (size_t)P->N / 4, split, Y, 0, s);
         }
     };
-    if (P->tile == 128 && bm == 128) launch(prefill4_kernel<128, 128, false>, prefill4_kernel<128, 128, true>);
+    if (kernel == kQ4Groups) {
+        static const hipError_t granted[] = {q4_grant(prefill4_kgroups_kernel<128, false>), q4_grant(prefill4_kgroups_kernel<128, true>),
+                                             q4_grant(prefill4_kgroups_kernel<64, false>), q4_grant(prefill4_kgroups_kernel<64, true>)};
+        (void)granted;
+        if (P->tile == 128) launch(prefill4_kgroups_kernel<128, false>, prefill4_kgroups_kernel<128, true>);
+        else launch(prefill4_kgroups_kernel<64, false>, prefill4_kgroups_kernel<64, true>);
+    } else if (P->tile == 128 && bm == 128) launch(prefill4_kernel<128, 128, false>, prefill4_kernel<128, 128, true>);
     else if (P->tile == 128) launch(prefill4_kernel<128, 256, false>, prefill4_kernel<128, 256, true>);
     else if (bm == 128) launch(prefill4_kernel<64, 128, false>, prefill4_kernel<64, 128, true>);
     else launch(prefill4_kernel<64, 256, false>, prefill4_kernel<64, 256, true>);
@@ -1606,17 +1635,17 @@ patch_status patch_gemm4_ex(const void* X, int64_t M, const patch_packed4* P, vo
     const bool ws = workspace && workspace_bytes >= 2 * (size_t)M * (size_t)P->N * sizeof(float);
     float* const part = ws ? static_cast<float*>(workspace) : nullptr;
     const size_t part_bytes = ws ? workspace_bytes : 0;
-    int bm = 128;
-    const int split = q4_prefill_split(M, q4_shape(&P, 1, part_bytes), &bm);
+    Q4PrefillKernel kernel;
+    const int split = q4_prefill_split(M, q4_shape(&P, 1, part_bytes), &kernel);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (split == 0) return q4_passes(X, M, &P, &Y, 1, part, part_bytes, s);
-    return q4_prefill(static_cast<const uint16_t*>(X), M, P, static_cast<float*>(Y), split, bm, part, s);
+    return q4_prefill(static_cast<const uint16_t*>(X), M, P, static_cast<float*>(Y), split, kernel, part, s);
 }
 
 // Test hook (kernels.h)
 int patch_test_gemm4(const void* X, int64_t M, const patch_packed4* const* P, void* const* Y, int count, int kernel, int chunks,
                               void* workspace, size_t workspace_bytes, void* stream) {
-    if (!X || !P || !Y || M < 1 || count < 1 || count > kMaxMany || kernel < 0 || kernel > 3 || !q4_aligned16(X)) return PATCH_ERR_ARG;
+    if (!X || !P || !Y || M < 1 || count < 1 || count > kMaxMany || kernel < 0 || kernel > 4 || !q4_aligned16(X)) return PATCH_ERR_ARG;
     for (int i = 0; i < count; ++i) {
         if (!P[i] || !Y[i] || !q4_aligned16(Y[i])) return PATCH_ERR_ARG;
         if (P[i]->K != P[0]->K || P[i]->tile != P[0]->tile) return PATCH_ERR_SHAPE;
@@ -1627,8 +1656,9 @@ int patch_test_gemm4(const void* X, int64_t M, const patch_packed4* const* P, vo
     if (chunks > 1 && (!workspace || !q4_aligned16(workspace) || workspace_bytes < (size_t)chunks * (size_t)rows * (size_t)P[0]->N * sizeof(float)))
         return PATCH_ERR_SIZE;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (kernel == 4 && P[0]->K > kKgMaxK) return PATCH_ERR_SHAPE;
     if (kernel > 1)
-        return q4_prefill(static_cast<const uint16_t*>(X), M, P[0], static_cast<float*>(Y[0]), chunks, kernel == 2 ? 128 : 256, static_cast<float*>(workspace), s);
+        return q4_prefill(static_cast<const uint16_t*>(X), M, P[0], static_cast<float*>(Y[0]), chunks, (Q4PrefillKernel)(kernel - 2), static_cast<float*>(workspace), s);
     const Q4Plan plan = {kernel == 1, chunks, 0.0};
     return q4_passes(X, M, P, Y, count, static_cast<float*>(workspace), workspace_bytes, s, &plan);
 }

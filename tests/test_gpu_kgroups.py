@@ -1,0 +1,47 @@
+"""The 4-bit prefill-shaped kernel with two K groups per workgroup, called for by name: one to fourteen K-steps (fewer than its three units in
+flight, odd counts, every place in its rotation of three buffers), all-dense, mixed and all-2:4 maps, missing tile rows, part-filled row blocks, more
+than 64 tiles along K, K in slices over a workspace with a guard region behind it, against the float64 product of the dequantized weight.
+Element bound as in test_gpu_strip4; repeated launches bit-equal."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2509_23410_amd import binding as B, synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("f", [0.0, 0.5, 1.0])
+@pytest.mark.parametrize("tile,N,K", [(128, 128, 128), (128, 384, 384), (128, 640, 896), (128, 256, 8448), (64, 64, 64), (64, 192, 192), (64, 320, 832), (64, 256, 4224)])
+def test_two_k_groups(tile, N, K, f):
+    vp = ctypes.c_void_p
+    c = synth.make_case("kgroups", N, K, 1, tile, f, seed=3)
+    Wd = torch.from_numpy(c.W.view(np.int16)).cuda().view(torch.bfloat16)
+    stream = torch.cuda.current_stream().cuda_stream
+    B.patch_apply_mask(Wd, torch.from_numpy(c.mask24).cuda(), c.tile_map, N, K, tile, Wd, stream)
+    P = B.patch_pack4(Wd, N, K, c.tile_map, tile, stream)
+    B.patch_unpack4(P, W_deq=Wd, stream=stream)
+    W = Wd.double()
+    for M in (1, 32, 33, 127, 128, 129, 300):
+        X = torch.randn(M, K, device="cuda", generator=torch.Generator(device="cuda").manual_seed(M)).to(torch.bfloat16)
+        ref, bound = X.double() @ W.T, 2 * K ** 0.5 * 2.0 ** -24 * X.double().norm(dim=1)[:, None] * W.norm(dim=1)[None, :]
+        for chunks in sorted({1, 2, 3, K // tile} & set(range(1, min(8, K // tile) + 1))):
+            print(f"kgroups tile={tile} N={N} K={K} f={f} M={M} chunks={chunks}", flush=True)
+            buf = torch.full((M * N + 2048,), 7.0, device="cuda")
+            Y = buf[1024:1024 + M * N].view(M, N)
+            first = None
+            for _ in range(2):
+                Y.fill_(float("nan"))
+                ws = torch.full((chunks * M * N + 1024,), 7.0, device="cuda")
+                st = B.lib().patch_test_gemm4(vp(X.data_ptr()), ctypes.c_int64(M), (vp * 1)(P.handle), (vp * 1)(Y.data_ptr()), 1, 4, chunks, vp(ws.data_ptr()),
+                                              ctypes.c_size_t(4 * chunks * M * N), vp(stream))
+                assert st == B.OK, st
+                worst = ((Y.double() - ref).abs() / bound).max().item()
+                assert worst <= 1.0, (M, chunks, worst)       # (NaN, an output never written, fails too)
+                assert bool((buf[:1024] == 7.0).all()) and bool((buf[1024 + M * N:] == 7.0).all()), "wrote outside Y"
+                assert bool((ws[chunks * M * N:] == 7.0).all()), "wrote behind the workspace"
+                assert first is None or torch.equal(Y, first), "launches of one configuration must be bit-equal"
+                first = Y.clone()
+    P.close()
