@@ -69,8 +69,9 @@ typedef struct {
                  /* LDS-staged kernel with blocks of 256 features x 128 rows, 5 = blocks of 128 rows with  */
                  /* the weights loaded straight into registers, 6 = the same with 256 rows (tile 64 only:  */
                  /* its 256-row default beyond the limits of 3).                                           */
-                 /* Blocks of 128 rows (5) are the default, with no split requested, where estimated       */
-                 /* faster (up to a few hundred rows).  Decode: 2 / 3 = 8 / 4                              */
+                 /* Blocks of 128 rows (5, or a kernel of their own where those fill the chip at most      */
+                 /* once) are the default, with no split requested, where estimated faster (up to a few    */
+                 /* hundred rows).  Decode: 2 / 3 = 8 / 4                                                  */
                  /* K-steps per wavefront of the 16-feature-strip kernel; 4 = the kernel with 64         */
                  /* features per wavefront (its split_k = K chunks over `workspace`, 0 = auto; the       */
                  /* default for passes of 8 .. 64 rows where estimated fastest); 5 / 6 = the strip kernel */

@@ -560,6 +560,43 @@ int patch_test_schedule_deals(int64_t M, int count, const int64_t* N, int64_t K,
     return n;
 }
 
+int patch_test_prefill128_split(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes) {
+    if (!N || M < 1 || count < 1 || count > kMaxMany || sparse_pct < 0 || sparse_pct > 100) return -1;
+    for (int i = 0; i < count; ++i)
+        if (check_shape(N[i], K, tile) != PATCH_OK) return -1;
+    GemmArgs a = {};
+    a.M = M; a.N = N[0]; a.K = K;
+    a.tile = tile; a.Tk = (int)(K / tile);
+    a.n_cus = 256;
+    a.sparse_pct = sparse_pct;
+    if (ws_bytes) { a.ws = reinterpret_cast<float*>(16); a.ws_bytes = ws_bytes; }
+    return prefill_r128_split(a, N, count);
+}
+
+int patch_test_prefill128(const void* X, int64_t M, const patch_packed* const* P, void* const* Y, int count, int split, int y_bf16, void* workspace,
+                          size_t workspace_bytes, void* stream) {
+    if (!X || !P || !Y || M < 1 || count < 1 || count > kMaxMany || split < 1 || split > 16 || split > P[0]->Tk) return -1;
+    GemmArgs a = {};
+    a.X = static_cast<const uint16_t*>(X);
+    a.M = M; a.K = P[0]->K; a.tile = P[0]->tile; a.Tk = P[0]->Tk; a.n_cus = P[0]->n_cus;
+    a.ybf16 = y_bf16 ? 1 : 0;
+    a.ws = static_cast<float*>(workspace);
+    a.ws_bytes = workspace_bytes;
+    WeightSet set = {};
+    size_t need = 0;
+    for (int i = 0; i < count; ++i) {
+        if (!P[i] || !Y[i] || P[i]->K != a.K || P[i]->tile != a.tile) return -1;
+        set.payload[i] = P[i]->d_payload; set.table[i] = P[i]->d_table; set.Y[i] = static_cast<float*>(Y[i]); set.N[i] = P[i]->N;
+        set.first[i] = set.units;
+        set.units += (int)((P[i]->N + 255) / 256);
+        need += (size_t)split * (size_t)M * (size_t)P[i]->N * sizeof(float);
+    }
+    set.count = count;
+    if (split > 1 && (!workspace || workspace_bytes < need)) return -1;
+    launch_prefill_r128(a, set, split, static_cast<hipStream_t>(stream));
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
 int patch_test_deal_units(int units, int deals, int n_cus) { return units < 1 || deals < 1 || n_cus < 8 ? -1 : (int)deal_units(units, (unsigned)deals, n_cus); }
 
 patch_status patch_gemm_ex(const void* X, int64_t M, const patch_packed* P, void* Y, void* stream, const patch_gemm_opts* opts) {
@@ -875,6 +912,10 @@ static size_t workspace_need(int64_t M, const patch_packed* P, const patch_gemm_
         return most;
     }
     if (variant == 1) return 0;
+    if (variant == 0 && split_k == 0 && !slices_only) {
+        const int split = prefill_r128_split(a, &P->N, 1);   // (and no less than the launch would take without that kernel)
+        if (split > 1) least = std::max(least, (size_t)split * (size_t)M * (size_t)P->N * sizeof(float));
+    }
     if (variant == 0 && split_k == 0) {
         int split128 = 1;
         if (prefill_prefers_128_rows(a, &split128, slices_only)) return std::max(least, split128 > 1 ? (size_t)split128 * (size_t)M * (size_t)P->N * sizeof(float) : (size_t)0);
@@ -974,7 +1015,9 @@ patch_status patch_gemm_many(const void* X, int64_t M, const patch_packed* const
         }
         set.count = count;
         set.units = blocks;
-        launch_prefill_wreg_set(a, set, s);
+        const int split128 = variant == 0 && split_k == 0 ? prefill_r128_split(a, set.N, count) : 0;
+        if (split128) launch_prefill_r128(a, set, split128, s);
+        else launch_prefill_wreg_set(a, set, s);
         HIP_TRY(hipGetLastError());
         return PATCH_OK;
     }

@@ -758,8 +758,53 @@ double prefill_estimate(const GemmArgs& a) {
     return pf_estimate(a, blocks, prefill_lds_split(a, 0, 256), 1.26, 0.33);
 }
 
-// Kernel choice.  variant 0 (default): prefill_kernel_areg with blocks of 128 rows where prefill_prefers_128_rows says so
-// (no split requested); else 256 rows: prefill_kernel_wreg (tile 128) or prefill_kernel_w64 (tile 64) where their limits
+// One round of prefill_kernel_r128, or what the launch took without it?  Priced by launches of 100 .. 4096 rows of 13 weights at f = 0, 1/2 and 1, both
+// mask tiles, with and without a workspace (4718 timings):
+//     us = base + begin fill + rounds x K-steps per workgroup x (t0 + t1 fill) x g(f) + (split > 1 ? second + (2 split + 1) M N 4 B / rate : 0)
+// (prices below; rms error 6 % for blocks of 128 rows, 7 % for 256).  A second workgroup on a compute unit gains little - the matrix cores and the
+// path from the L2 are shared: 11008 x 4096, f = 1/2, 172 / 344 workgroups 55 / 95 us, where 256-row blocks take 73 - so that the blocks, times the
+// slices, must not be more than the compute units.  Split: at most 8 slices of at least 512 columns that the workspace holds.  Taken where the price is
+// at least 3 % below: with a workspace 279 of 618 launches, 0.96 of the earlier time over all of them and 0.95 over those of 20 us and more
+// (4096 x 4096, f = 1/2, 2048 rows 57.7 -> 53.7 us; 15360 x 5120, 200 rows 58.1 -> 45.7; 5120 x 5120, 512 rows 43.6 -> 38.0), without one 381, 0.90 and
+// 0.87 (4096 x 4096, 512 rows 49.9 -> 45.9; 11008 x 4096, 512 rows 65.2 -> 54.9); at worst 4.5 % behind (4096 x 4096, f = 0, 512 rows 31.8 -> 33.2).
+// The best choice of each would be 0.95 and 0.90.  Whether the decode path's passes run instead is decided by the prices above, as if this kernel
+// did not exist.
+struct PrefillPrice { double base, begin, t0, t1, g1, g2, second, rate; };
+constexpr PrefillPrice kPriceR128 = {6.7, 2.3, 0.682, 0.171, 0.365, 0.0, 2.2, 10.3e6}, kPriceAreg128 = {4.6, 3.2, 0.864, 0.199, 0.347, 0.0, 3.3, 13.0e6},
+                       kPriceWreg = {10.6, 0.5, 0.841, 0.411, 0.017, 0.364, 1.6, 8.4e6};
+static double pf_price(const PrefillPrice& p, const GemmArgs& a, int64_t N, int64_t blocks, int split) {
+    const int64_t wgs = blocks * split, rounds = (wgs + a.n_cus - 1) / a.n_cus, steps = (int64_t)((a.Tk + split - 1) / split) * (a.tile / kStepCols);
+    const double fill = wgs < a.n_cus ? (double)wgs / a.n_cus : 1.0, f = 0.01 * a.sparse_pct, y = (double)a.M * (double)N * 4.0;
+    return p.base + p.begin * fill + (double)rounds * (double)steps * (p.t0 + p.t1 * fill) * (1.0 - p.g1 * f - p.g2 * f * f) +
+           (split > 1 ? p.second + (2.0 * split + 1.0) * y / p.rate : 0.0);
+}
+
+int prefill_r128_split(const GemmArgs& a, const int64_t* N, int count) {
+    int64_t units = 0, total = 0;
+    for (int i = 0; i < count; ++i) {
+        units += (N[i] + kPfBN - 1) / kPfBN;
+        total += N[i];
+    }
+    const int64_t b128 = units * ((a.M + 127) / 128);
+    if (b128 > a.n_cus) return 0;
+    const int b256 = (int)(units * ((a.M + 255) / 256));
+    const size_t per_slice = (size_t)a.M * (size_t)total * sizeof(float);
+    double best = 0.0;
+    int split = 1;
+    for (int s = 1; s <= 8 && (s == 1 || (b128 * s <= a.n_cus && (int64_t)s * 512 <= a.K && a.ws && a.ws_bytes / per_slice >= (size_t)s)); ++s) {
+        const double us = pf_price(kPriceR128, a, total, b128, s);
+        if (s == 1 || us < best) { best = us; split = s; }
+    }
+    int split128 = 1;
+    double other;
+    if (count == 1 && prefill_prefers_128_rows(a, &split128)) other = pf_price(kPriceAreg128, a, total, b128, split128);
+    else if (prefill_wreg_supports(a)) other = pf_price(kPriceWreg, a, total, b256, count == 1 ? prefill_wreg_split(a, 0) : prefill_wreg_set_split(a, b256, total));
+    else other = pf_estimate(a, b256, prefill_lds_split(a, 0, 256), 1.26, 0.33);
+    return 1.03 * best < other ? split : 0;
+}
+
+// Kernel choice.  variant 0 (default): prefill_kernel_r128 where prefill_r128_split says so, prefill_kernel_areg with blocks of 128 rows where
+// prefill_prefers_128_rows does (both: no split requested); else 256 rows: prefill_kernel_wreg (tile 128) or prefill_kernel_w64 (tile 64) where their limits
 // hold, else tile 128 -> prefill_kernel_lds, tile 64 -> prefill_kernel_areg.  variant 1 forces prefill_kernel_v0, 2
 // prefill_kernel_lds (256 rows), 3 prefill_kernel_wreg / prefill_kernel_w64, 4 prefill_kernel_lds with 128 rows, 5 prefill_kernel_areg with 128 rows, 6 prefill_kernel_areg
 // with 256 rows (mask tile 64 only); each falls back to the default choice where it does not apply.
@@ -788,6 +833,17 @@ static void launch_prefill_lds(const GemmArgs& a, int split_k, hipStream_t strea
 
 void launch_prefill(const GemmArgs& a, int variant, int split_k, hipStream_t stream) {
     if (variant == 0 && split_k == 0) {
+        if (const int split = prefill_r128_split(a, &a.N, 1)) {
+            WeightSet set = {};
+            set.payload[0] = a.payload;
+            set.table[0] = a.table;
+            set.Y[0] = a.Y;
+            set.N[0] = a.N;
+            set.count = 1;
+            set.units = (int)((a.N + kPfBN - 1) / kPfBN);
+            launch_prefill_r128(a, set, split, stream);
+            return;
+        }
         int split128 = 1;
         if (prefill_prefers_128_rows(a, &split128)) {
             if (a.tile == 128) launch_prefill_areg<128, 128>(a, split128, stream);

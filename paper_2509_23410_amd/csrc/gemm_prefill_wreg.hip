@@ -1163,7 +1163,7 @@ void launch_prefill_wreg(const GemmArgs& a, int split_k, hipStream_t stream) {
 }
 
 // K slices of a set launch: N = features of all weights
-static int wr_set_split(const GemmArgs& a, int nblk, int64_t N) {
+int prefill_wreg_set_split(const GemmArgs& a, int nblk, int64_t N) {
     if (!a.ws || nblk >= (a.n_cus * 2) / 3) return 1;
     int split = a.n_cus / nblk;
     if (split > wr_longest(a)) split = wr_longest(a);
@@ -1183,7 +1183,7 @@ double prefill_set_estimate(const GemmArgs& a, const int64_t* N, int count) {
         whole = whole && N[i] % kWrBN == 0;
     }
     const int blocks = units * (int)((a.M + kWrBM - 1) / kWrBM);
-    return pf_few_rows(a, total, blocks, wr_set_split(a, blocks, total), false, whole);
+    return pf_few_rows(a, total, blocks, prefill_wreg_set_split(a, blocks, total), false, whole);
 }
 
 void launch_prefill_wreg_set(const GemmArgs& a, const WeightSet& set, hipStream_t stream) {
@@ -1196,7 +1196,7 @@ void launch_prefill_wreg_set(const GemmArgs& a, const WeightSet& set, hipStream_
     {
         int64_t N = 0;
         for (int i = 0; i < set.count; ++i) N += set.N[i];
-        const int split = wr_set_split(a, nblk, N);
+        const int split = prefill_wreg_set_split(a, nblk, N);
         if (split >= 2) {
             WeightSet part = set;
             WrReduceSet red = {};

@@ -101,7 +101,8 @@ void launch_prefill(const GemmArgs& a, int variant, int split_k, hipStream_t str
 bool prefill_wreg_supports(const GemmArgs& a);                  // K <= 16384, M * K * 2 < 4 GB
 int prefill_wreg_split(const GemmArgs& a, int requested);       // K slices per output tile the launch will use
 int prefill_lds_split(const GemmArgs& a, int requested, int bm = 256);   // the same for the LDS-staged kernel with blocks of bm rows
-// whether the default choice (variant 0, no split requested) is prefill_kernel_areg with blocks of 128 rows, and its split; no_w64: see there
+// whether the default choice (variant 0, no split requested) is prefill_kernel_areg with blocks of 128 rows, and its split, where prefill_r128_split does
+// not take the launch; no_w64: see there
 bool prefill_prefers_128_rows(const GemmArgs& a, int* split, bool no_w64 = false);
 double prefill_estimate(const GemmArgs& a);                                       // us the default choice is estimated to take at few rows
 double prefill_set_estimate(const GemmArgs& a, const int64_t* N, int count);      // the same for a set of weights of N[i] features
@@ -114,18 +115,30 @@ void launch_prefill_wreg(const GemmArgs& a, int split_k, hipStream_t stream);
 // part-filled last round is split as in launch_prefill_wreg).  All of the set must pass prefill_wreg_supports with
 // these M, K.
 void launch_prefill_wreg_set(const GemmArgs& a, const WeightSet& set, hipStream_t stream);
+int prefill_wreg_set_split(const GemmArgs& a, int blocks, int64_t N);   // K slices of such a launch over `blocks` output tiles, N features in all
+// Blocks of 256 features x 128 rows by wavefronts of 64 features; a, set as above; split > 1 needs a.ws with room for split x M x N floats of every
+// weight.  prefill_r128_split: the K slices in which the default choice (variant 0, no split requested) runs `count` weights of N[i] features this
+// way, 0 = it does not.
+int prefill_r128_split(const GemmArgs& a, const int64_t* N, int count);
+void launch_prefill_r128(const GemmArgs& a, const WeightSet& set, int split, hipStream_t stream);
 
 }  // namespace patch
 
 // Test hooks: exported like the interface in patch.h, but no part of it.
+struct patch_packed;
 struct patch_packed4;
 extern "C" {
+// The prefill product of `count` weights sharing X by prefill_kernel_r128 in `split` K slices, whatever the dispatch would take.
+int patch_test_prefill128(const void* X, int64_t M, const patch_packed* const* P, void* const* Y, int count, int split, int y_bf16, void* workspace,
+                          size_t workspace_bytes, void* stream);
 // What AUTO takes for M rows of `count` weights of N[i] x K features sharing X (sparse_pct per cent of the tiles 2:4) given ws_bytes of
-// workspace on 256 compute units: kernel (0 strip, 1 mid, 2 batch, 3 the prefill path, 4 that in blocks of 128 rows) and K chunks of every
-// pass (1 for kernel 3), at most 8; returns their number, -1 = bad arguments.  Runs on the host alone.
+// workspace on 256 compute units: kernel (0 strip, 1 mid, 2 batch, 3 the prefill path, 4 that in blocks of 128 rows by
+// prefill_prefers_128_rows) and K chunks of every pass (1 for kernel 3), at most 8; returns their number, -1 = bad arguments.  Runs on the host alone.
 int patch_test_schedule(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* kernel, int* chunks);
 // The same and, per pass, over how many workgroups per feature group its rows are dealt (rows_deals; 1 = not).
 int patch_test_schedule_deals(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* kernel, int* chunks, int* deals);
+// prefill_r128_split of the same, for the prefill path
+int patch_test_prefill128_split(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes);
 // deal_units: gridDim.x of a launch over `units` feature groups whose rows go over `deals` workgroups
 int patch_test_deal_units(int units, int deals, int n_cus);
 // The 4-bit product of `count` weights sharing X by one kernel, whatever the dispatch would take: 0 the strip kernel, 1 batch4_kernel, both in

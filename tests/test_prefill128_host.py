@@ -1,0 +1,37 @@
+"""When the default choice runs a prefill-shaped product in blocks of 128 rows by prefill_kernel_r128 (host only)."""
+import ctypes
+
+import pytest
+
+from paper_2509_23410_amd import binding as B
+
+
+def _split(M, N, K, tile, f, ws_bytes):
+    return B.lib().patch_test_prefill128_split(ctypes.c_int64(M), len(N), (ctypes.c_int64 * len(N))(*N), ctypes.c_int64(K), tile, round(100 * f), ctypes.c_size_t(ws_bytes))
+
+
+@pytest.mark.parametrize("N,K,tile,f,M,workspace,us,other", [
+    (5120, 5120, 128, 0.5, 512, True, {1: 61.0, 2: 42.7, 3: 38.0, 4: 50.4}, 43.6), (15360, 5120, 128, 0.5, 512, True, {1: 70.2, 2: 88.5}, 73.6),
+    (27648, 5120, 128, 0.5, 512, True, {1: 128.6}, 103.2), (11008, 4096, 128, 0.5, 1003, True, {1: 94.5}, 73.1), (4096, 4096, 128, 0.5, 2048, True, {1: 53.7}, 57.7),
+    (4096, 4096, 64, 0.5, 512, False, {1: 46.1}, 52.2), (5120, 5120, 128, 0.0, 512, True, {1: 66.0, 2: 46.9, 3: 40.8, 4: 54.3}, 47.9),
+    (11008, 4096, 128, 1.0, 2048, True, {1: 128.6}, 127.4), (2048, 5504, 64, 0.5, 1003, True, {1: 58.7, 2: 41.0, 3: 36.5, 4: 33.1, 5: 40.9, 8: 40.6}, 34.5),
+])
+def test_choice_is_no_slower_than_what_was_measured(N, K, tile, f, M, workspace, us, other):
+    s = _split(M, [N], K, tile, f, 384 << 20 if workspace else 0)
+    assert (us[s] if s else other) <= 1.05 * min([other] + [t for i, t in us.items() if workspace or i == 1])
+
+
+def test_limits_of_the_choice():
+    """One round of the chip; slices of at least 512 columns, at most 8, that the workspace holds; a set counts as one launch."""
+    taken = set()
+    for tile in (64, 128):
+        for N in ([tile], [896], [4096], [11008], [4096] * 3, [5120, 640], [32768]):
+            for K in (tile, 1024, 4096, 16384 + tile):
+                for M in (1, 17, 128, 129, 1000, 4096, 40000):
+                    for ws in (0, 1 << 20, 384 << 20):
+                        s = _split(M, N, K, tile, 0.5, ws)
+                        blocks = sum(-(-n // 256) for n in N) * -(-M // 128)
+                        assert 0 <= s <= 8 and (s == 0 or blocks * s <= 256)
+                        assert s < 2 or (4 * s * M * sum(N) <= ws and 512 * s <= K)
+                        taken.add(s)
+    assert {0, 1, 2, 8} <= taken
