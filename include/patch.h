@@ -118,7 +118,7 @@ patch_status patch_hard_masks(const float* P_tile, const void* P_24, int64_t N, 
  *   W_hat  DEVICE, N x K bf16, 16-byte aligned; either W itself (in place) or a buffer that does not overlap W;
  *          pruned entries are written as +0
  * Misaligned pointers: PATCH_ERR_ARG.
- * Synchronous: uploads the tile map, runs on `stream` and waits for it (a one-off conversion step).
+ * Synchronous: runs on `stream` and waits for it (a one-off conversion step).
  */
 patch_status patch_apply_mask(const void* W, const void* mask24, const uint8_t* tile_map, int64_t N,
                               int64_t K, int tile, void* W_hat, void* stream);

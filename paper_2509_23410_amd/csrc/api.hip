@@ -5,6 +5,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <condition_variable>
 #include <map>
 #include <mutex>
 #include <new>
@@ -12,6 +13,7 @@
 #include <vector>
 
 #include "../../include/patch.h"
+#include "host_word.h"
 #include "kernels.h"
 #include "layout.h"
 #include "saved.h"
@@ -24,9 +26,8 @@ struct patch_packed {
     int Tn = 0, Tk = 0;
     int64_t n_sparse = 0;
     size_t payload_bytes = 0;   // sum of tile payloads (no alignment slack: tiles are granule multiples)
-    // one allocation: payload | zeroed slack | status word of the 2:4 check | table | pairs
+    // one allocation: payload | zeroed slack | table | pairs
     uint8_t* d_payload = nullptr;
-    int* d_err = nullptr;
     uint32_t* d_table = nullptr;
     std::vector<uint8_t> tile_map;   // host copy, 1 = dense
     std::vector<uint32_t> table;     // host copy of the offset / type table
@@ -163,6 +164,48 @@ static patch_status static_scratch(void** out) {
     return PATCH_OK;
 }
 
+namespace {
+constexpr int kHostWords = 64, kHostWordStride = 16;   // a cache line each, one page
+std::mutex g_words_mutex;
+std::condition_variable g_words_free;
+uint32_t *g_words = nullptr, *g_words_device = nullptr;
+uint64_t g_words_held = 0;
+}  // namespace
+
+HostWord::HostWord() {
+    std::unique_lock<std::mutex> lock(g_words_mutex);
+    if (!g_words) {
+        void *host = nullptr, *device = nullptr;
+        if (hipHostMalloc(&host, kHostWords * kHostWordStride * sizeof(uint32_t), hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
+        if (hipHostGetDevicePointer(&device, host, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            (void)hipHostFree(host);
+            return;
+        }
+        g_words = static_cast<uint32_t*>(host);
+        g_words_device = static_cast<uint32_t*>(device);
+    }
+    g_words_free.wait(lock, [] { return g_words_held != ~0ull; });
+    slot_ = __builtin_ctzll(~g_words_held);
+    g_words_held |= 1ull << slot_;
+    __atomic_store_n(g_words + slot_ * kHostWordStride, 0u, __ATOMIC_RELEASE);
+}
+
+HostWord::~HostWord() {
+    if (slot_ < 0) return;
+    {
+        std::lock_guard<std::mutex> lock(g_words_mutex);
+        g_words_held &= ~(1ull << slot_);
+    }
+    g_words_free.notify_one();
+}
+
+uint32_t* HostWord::device() const { return g_words_device + slot_ * kHostWordStride; }
+uint32_t HostWord::value() const { return __atomic_load_n(g_words + slot_ * kHostWordStride, __ATOMIC_ACQUIRE); }
+
 extern "C" {
 
 const char* patch_version(void) { return "patch-mi355x 0.1 (gfx950)"; }
@@ -190,17 +233,10 @@ patch_status patch_apply_mask(const void* W, const void* mask24, const uint8_t* 
     if (st != PATCH_OK) return st;
     if (!aligned16(W) || !aligned16(W_hat) || (reinterpret_cast<uintptr_t>(mask24) & 7u)) return PATCH_ERR_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const size_t T = (size_t)(N / tile) * (size_t)(K / tile);
-    uint8_t* d_map = nullptr;
-    if (hipMalloc(&d_map, T) != hipSuccess) { (void)hipGetLastError(); return PATCH_ERR_ALLOC; }
-    hipError_t e = hipMemcpyAsync(d_map, tile_map, T, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) {
-        launch_apply_mask(static_cast<const uint16_t*>(W), static_cast<const uint8_t*>(mask24), d_map, N, K, tile,
-                          static_cast<uint16_t*>(W_hat), s);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    (void)hipFree(d_map);
+    launch_apply_mask(static_cast<const uint16_t*>(W), static_cast<const uint8_t*>(mask24), tile_map, N, K, tile, static_cast<uint16_t*>(W_hat), s);
+    hipError_t e = hipGetLastError();
+    const hipError_t e_sync = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = e_sync;
     if (e != hipSuccess) { g_last_hip_error = (int)e; return PATCH_ERR_HIP; }
     return PATCH_OK;
 }
@@ -224,23 +260,17 @@ void patch_free(patch_packed* P) {
     delete P;
 }
 
-// The host side of a packed weight (tile map, offset / type table) and its device buffers - one allocation, everything in
-// front of the tile-row pairs but the payload in one upload on `s` - the payload not yet written.  Shared by patch_pack (which
-// fills the payload from the matrix) and patch_deserialize (which copies a saved one).  `staging` is the upload's source:
-// it must live until `s` has been waited for.
-static patch_status new_packed(int64_t N, int64_t K, const uint8_t* tile_map, int tile, hipStream_t s, std::vector<uint32_t>& staging, patch_packed** out) {
+// The host side of a packed weight (tile map, offset / type table) and its device buffers, one allocation; nothing of it written yet: patch_pack's kernel
+// writes payload, slack and table, patch_deserialize copies them.
+static patch_status new_packed(int64_t N, int64_t K, const uint8_t* tile_map, int tile, patch_packed** out) {
     patch_packed* P = new (std::nothrow) patch_packed();
     if (!P) return PATCH_ERR_ALLOC;
     P->N = N; P->K = K; P->tile = tile;
     P->Tn = (int)(N / tile); P->Tk = (int)(K / tile);
     const size_t T = (size_t)P->Tn * (size_t)P->Tk;
-    // (a kilobyte of zeroed slack behind the payload keeps any over-read of the last tile inside the allocation; the
-    // status word has 16 bytes)
-    constexpr size_t kFront = kZeroPad / sizeof(uint32_t) + 4;
     try {
         P->tile_map.resize(T);
         P->table.resize(T);
-        staging.assign(kFront + T, 0);
     } catch (...) { delete P; return PATCH_ERR_ALLOC; }
     uint64_t off = 0;
     for (size_t i = 0; i < T; ++i) {
@@ -252,7 +282,6 @@ static patch_status new_packed(int64_t N, int64_t K, const uint8_t* tile_map, in
     }
     P->payload_bytes = off;
     if ((off / kGranule) >> 31) { delete P; return PATCH_ERR_SHAPE; }
-    memcpy(staging.data() + kFront, P->table.data(), T * sizeof(uint32_t));
 
     int dev = 0;
     hipDeviceProp_t prop;
@@ -265,20 +294,13 @@ static patch_status new_packed(int64_t N, int64_t K, const uint8_t* tile_map, in
     P->n_cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
 
     const size_t n_pairs = tile == 128 ? 2 * (((size_t)P->Tn + 1) / 2) : 0;
-    if (hipMalloc(&P->d_payload, P->payload_bytes + (kFront + T + n_pairs) * sizeof(uint32_t)) != hipSuccess) {
+    // (a kilobyte of zeroed slack behind the payload keeps any over-read of the last tile inside the allocation)
+    if (hipMalloc(&P->d_payload, P->payload_bytes + kZeroPad + (T + n_pairs) * sizeof(uint32_t)) != hipSuccess) {
         (void)hipGetLastError();
         patch_free(P);
         return PATCH_ERR_ALLOC;
     }
-    P->d_err = reinterpret_cast<int*>(P->d_payload + P->payload_bytes + kZeroPad);
-    P->d_table = reinterpret_cast<uint32_t*>(P->d_payload + P->payload_bytes) + kFront;
-    const hipError_t e = hipMemcpyAsync(P->d_payload + P->payload_bytes, staging.data(), staging.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s);
-    if (e != hipSuccess) {
-        g_last_hip_error = (int)e;
-        (void)hipStreamSynchronize(s);
-        patch_free(P);
-        return PATCH_ERR_HIP;
-    }
+    P->d_table = reinterpret_cast<uint32_t*>(P->d_payload + P->payload_bytes + kZeroPad);
     *out = P;
     return PATCH_OK;
 }
@@ -289,7 +311,8 @@ static patch_status add_pairs(patch_packed* P, hipStream_t s) {
     try {
         P->pairs = pair_tile_rows(P->tile_map, P->Tn, P->Tk);
     } catch (...) { return PATCH_ERR_ALLOC; }
-    HIP_TRY(hipMemcpyAsync(P->d_table + P->table.size(), P->pairs.data(), P->pairs.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    launch_put_words(P->d_table + P->table.size(), reinterpret_cast<const uint32_t*>(P->pairs.data()), P->pairs.size(), s);
+    HIP_TRY(hipGetLastError());
     return PATCH_OK;
 }
 
@@ -300,19 +323,19 @@ patch_status patch_pack(const void* W_hat, int64_t N, int64_t K, const uint8_t* 
     if (st != PATCH_OK) return st;
     if (!aligned16(W_hat)) return PATCH_ERR_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    HostWord not_24;
+    if (!not_24.valid()) return PATCH_ERR_ALLOC;
     patch_packed* P = nullptr;
-    std::vector<uint32_t> staging;
-    st = new_packed(N, K, tile_map, tile, s, staging, &P);
+    st = new_packed(N, K, tile_map, tile, &P);
     if (st != PATCH_OK) return st;
-    launch_pack(static_cast<const uint16_t*>(W_hat), K, P->d_table, (int)P->table.size(), P->Tk, tile, P->d_payload, P->d_err, s);
+    launch_pack(static_cast<const uint16_t*>(W_hat), K, P->tile_map.data(), (int)P->table.size(), P->Tk, tile, P->d_payload, P->d_table,
+                reinterpret_cast<uint32_t*>(P->d_payload + P->payload_bytes), not_24.device(), s);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) st = add_pairs(P, s);   // on the host while the kernel runs
-    int h_err = 0;
-    if (e == hipSuccess && st == PATCH_OK) e = hipMemcpyAsync(&h_err, P->d_err, sizeof(int), hipMemcpyDeviceToHost, s);
     const hipError_t e_sync = hipStreamSynchronize(s);
     if (e == hipSuccess) e = e_sync;
     if (e != hipSuccess && st == PATCH_OK) { g_last_hip_error = (int)e; st = PATCH_ERR_HIP; }
-    if (st == PATCH_OK && h_err) st = PATCH_ERR_NOT_24;
+    if (st == PATCH_OK && not_24.value()) st = PATCH_ERR_NOT_24;
     if (st != PATCH_OK) {
         patch_free(P);
         return st;
@@ -368,15 +391,17 @@ patch_status patch_deserialize(const void* buf, size_t bytes, void* stream, patc
     if (fnv1a(b + pay_at, (size_t)h.payload_bytes, fnv1a(b + map_at, (size_t)T, kFnvBasis)) != h.checksum) return PATCH_ERR_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
     patch_packed* P = nullptr;
-    std::vector<uint32_t> staging;
-    patch_status st = new_packed(h.N, h.K, b + map_at, (int)h.tile, s, staging, &P);
+    patch_status st = new_packed(h.N, h.K, b + map_at, (int)h.tile, &P);
     if (st != PATCH_OK) return st;
     if (P->payload_bytes != h.payload_bytes) {   // the map decides the size: a header that disagrees is not ours
-        (void)hipStreamSynchronize(s);
         patch_free(P);
         return PATCH_ERR_ARG;
     }
-    hipError_t e = hipMemcpyAsync(P->d_payload, b + pay_at, P->payload_bytes, hipMemcpyHostToDevice, s);
+    constexpr uint32_t kZeroes[kZeroPad / sizeof(uint32_t)] = {};
+    launch_put_words(reinterpret_cast<uint32_t*>(P->d_payload + P->payload_bytes), kZeroes, kZeroPad / sizeof(uint32_t), s);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpyAsync(P->d_table, P->table.data(), P->table.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(P->d_payload, b + pay_at, P->payload_bytes, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) st = add_pairs(P, s);
     const hipError_t e_sync = hipStreamSynchronize(s);   // the caller's buffer is free to go when the call returns
     if (e == hipSuccess) e = e_sync;

@@ -8,12 +8,27 @@ void patch_note_hip_error(int hip_error);
 
 namespace patch {
 
-void launch_apply_mask(const uint16_t* W, const uint8_t* mask24, const uint8_t* d_tile_map, int64_t N, int64_t K, int tile,
+// A part of a tile map as kernel arguments (4096 bytes at most, the hidden ones included), so that no launch has to wait for a copy of the map (and mask merge, pack and unpack of a
+// 4096 x 4096 matrix, 4-bit, took 170 us with one and a status word read back, 148 without): 64 tiles a group, bit set =
+// dense, and how many of the whole map's tiles before the group are.
+constexpr int kMapGroups = 304, kMapTiles = 64 * kMapGroups;
+struct TileMapArgs {
+    struct { uint32_t dense[2], before; } g[kMapGroups];
+};
+// `before` = dense tiles in front of map[0]; returns those in front of map[n]
+uint32_t fill_map_args(TileMapArgs* a, const uint8_t* map, int n, uint32_t before);
+
+// tile_map on the host; launches as many kernels as its tiles need
+void launch_apply_mask(const uint16_t* W, const uint8_t* mask24, const uint8_t* tile_map, int64_t N, int64_t K, int tile,
                        uint16_t* W_hat, hipStream_t stream);
 // mask24 (N x K keep bytes, 4-byte aligned) from the 6 x G pattern logits, G = N K / 4 groups
 void launch_hard_mask24(const float* P24, int64_t G, uint8_t* mask24, hipStream_t stream);
-void launch_pack(const uint16_t* W, int64_t K, const uint32_t* d_table, int n_tiles, int Tk, int tile, uint8_t* payload, int* d_err,
-                 hipStream_t stream);
+// tile_map on the host; also writes d_table (an entry per tile) and zeroes the kZeroPad bytes at `slack`.  *not_24 (device view of host memory) is set
+// to 1 if a group of four of a 2:4 tile holds more than two nonzeros.
+void launch_pack(const uint16_t* W, int64_t K, const uint8_t* tile_map, int n_tiles, int Tk, int tile, uint8_t* payload, uint32_t* d_table,
+                 uint32_t* slack, uint32_t* not_24, hipStream_t stream);
+// n words (any number) to dst by kernel arguments
+void launch_put_words(uint32_t* dst, const uint32_t* src, size_t n, hipStream_t stream);
 void launch_unpack(const uint8_t* payload, const uint32_t* d_table, int n_tiles, int Tk, int tile, int64_t K, uint16_t* W_out,
                    hipStream_t stream);
 

@@ -5,47 +5,89 @@
 // here is described in layout.h.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <string.h>
 
 #include "kernels.h"
 #include "layout.h"
+#include "map_args.h"
 
 namespace patch {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// ------------------------------------------------------------------ mask merge
-// One thread per 8 consecutive elements of a row (16 bytes of W, 8 bytes of mask).
-// W_hat may be W itself (in place): neither is declared restrict.
-__global__ __launch_bounds__(256) void apply_mask_kernel(const uint16_t* W, const uint8_t* __restrict__ mask24,
-                                                         const uint8_t* __restrict__ tile_map, int64_t N, int64_t K, int tile,
-                                                         uint16_t* W_hat) {
-    const int64_t chunks_per_row = K / 8;
-    const int64_t total = N * chunks_per_row;
-    const int64_t Tk = K / tile;
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < total; c += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t n = c / chunks_per_row, k = (c % chunks_per_row) * 8;
-        const int m_tile = tile_map[(n / tile) * Tk + k / tile] ? 1 : 0;
-        union { u32x4 v; uint16_t h[8]; } w;
-        w.v = *reinterpret_cast<const u32x4*>(W + n * K + k);
-        if (!m_tile) {
-            union { uint2 v; uint8_t b[8]; } m;
-            m.v = *reinterpret_cast<const uint2*>(mask24 + n * K + k);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                // M* = M_tile + (1 - M_tile) * M_24 with M_tile = 0 here
-                if (!m.b[e]) w.h[e] = 0;
-            }
-        }
-        *reinterpret_cast<u32x4*>(W_hat + n * K + k) = w.v;
+// ------------------------------------------------------------------ small data as kernel arguments
+uint32_t fill_map_args(TileMapArgs* a, const uint8_t* map, int n, uint32_t before) {
+    for (int g = 0; 64 * g < n; ++g) {
+        uint64_t bits = 0;
+        for (int i = 0; i < 64 && 64 * g + i < n; ++i) bits |= (uint64_t)(map[64 * g + i] != 0) << i;
+        a->g[g].dense[0] = (uint32_t)bits;
+        a->g[g].dense[1] = (uint32_t)(bits >> 32);
+        a->g[g].before = before;
+        before += (uint32_t)__builtin_popcountll(bits);
+    }
+    return before;
+}
+
+constexpr int kPutWords = 896;
+struct PutWords { uint32_t w[kPutWords]; };
+__global__ __launch_bounds__(64) void put_words_kernel(const PutWords words, uint32_t* __restrict__ dst, int n) {
+    for (int i = threadIdx.x; i < n; i += 64) dst[i] = words.w[i];
+}
+
+void launch_put_words(uint32_t* dst, const uint32_t* src, size_t n, hipStream_t stream) {
+    for (size_t at = 0; at < n; at += kPutWords) {
+        PutWords words;
+        const int part = (int)(n - at < (size_t)kPutWords ? n - at : (size_t)kPutWords);
+        memcpy(words.w, src + at, part * sizeof(uint32_t));
+        hipLaunchKernelGGL(put_words_kernel, dim3(1), dim3(64), 0, stream, words, dst + at, part);
     }
 }
 
-void launch_apply_mask(const uint16_t* W, const uint8_t* mask24, const uint8_t* d_tile_map, int64_t N, int64_t K, int tile,
+// ------------------------------------------------------------------ mask merge
+// A wavefront and step: up to 512 consecutive elements of a row, 8 per lane (16 bytes of W, 8 bytes of mask), whose tiles are at most eight
+// consecutive bits of the map.  W_hat may be W itself (in place): neither is declared restrict.  Bound by memory: 11008 x 4096, tile 128, f = 0.6
+// 35.6 us (5.8 TB/s), 4096 x 4096, tile 64, f = 1/2 13.0; with the map in device memory, a byte per tile, and a lookup per lane 38.2 and 15.1 - and about
+// 25 us of the call for the map's buffer and its copy.  The matrix passed here starts at the first tile of the map part: `rows` rows and Tk tiles of a matrix with K columns.
+__global__ __launch_bounds__(256) void apply_mask_kernel(const TileMapArgs map, const uint16_t* W, const uint8_t* __restrict__ mask24, int64_t K, int rows,
+                                                         int Tk, int tile_log2, uint16_t* W_hat) {
+    const int cols = Tk << tile_log2, per_row = (cols + 511) / 512, units = rows * per_row;
+    const int lane = threadIdx.x & 63;
+    for (int u = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + threadIdx.x / 64)); u < units; u += (int)gridDim.x * 4) {
+        const int n = u / per_row, k0 = 512 * (u % per_row), k = k0 + 8 * lane;
+        const int t = (n >> tile_log2) * Tk + (k0 >> tile_log2), w = t >> 5, w1 = w + 1 < 2 * kMapGroups ? w + 1 : w;
+        const uint64_t bits = (((uint64_t)map.g[w1 >> 1].dense[w1 & 1] << 32) | map.g[w >> 1].dense[w & 1]) >> (t & 31);
+        if (k >= cols) continue;
+        const int64_t at = n * K + k;
+        union { u32x4 v; uint16_t h[8]; } x;
+        x.v = *reinterpret_cast<const u32x4*>(W + at);
+        if (!((bits >> ((k - k0) >> tile_log2)) & 1)) {
+            union { uint2 v; uint8_t b[8]; } m;
+            m.v = *reinterpret_cast<const uint2*>(mask24 + at);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                // M* = M_tile + (1 - M_tile) * M_24 with M_tile = 0 here
+                if (!m.b[e]) x.h[e] = 0;
+            }
+        }
+        *reinterpret_cast<u32x4*>(W_hat + at) = x.v;
+    }
+}
+
+void launch_apply_mask(const uint16_t* W, const uint8_t* mask24, const uint8_t* tile_map, int64_t N, int64_t K, int tile,
                        uint16_t* W_hat, hipStream_t stream) {
-    const int64_t total = N * (K / 8);
-    int blocks = (int)((total + 255) / 256);
-    if (blocks > 256 * 32) blocks = 256 * 32;
-    hipLaunchKernelGGL(apply_mask_kernel, dim3(blocks), dim3(256), 0, stream, W, mask24, d_tile_map, N, K, tile, W_hat);
+    const int64_t Tn = N / tile, Tk = K / tile;
+    TileMapArgs map;
+    // parts of whole tile rows, or, where a single one is too long, pieces of it
+    const int64_t step_k = Tk < kMapTiles ? Tk : kMapTiles, step_n = kMapTiles / step_k;
+    for (int64_t tn = 0; tn < Tn; tn += step_n)
+        for (int64_t tk = 0; tk < Tk; tk += step_k) {
+            const int rn = (int)(Tn - tn < step_n ? Tn - tn : step_n), rk = (int)(Tk - tk < step_k ? Tk - tk : step_k);
+            fill_map_args(&map, tile_map + tn * Tk + tk, rn * rk, 0);   // (contiguous: rk = Tk or rn = 1)
+            const int64_t at = tn * tile * K + tk * tile;
+            const int64_t units = (int64_t)rn * tile * (((int64_t)rk * tile + 511) / 512), blocks = (units + 3) / 4;
+            hipLaunchKernelGGL(apply_mask_kernel, dim3((unsigned)(blocks < 256 * 32 ? blocks : 256 * 32)), dim3(256), 0, stream, map, W + at, mask24 + at, K,
+                               rn * tile, rk, tile == 128 ? 7 : 6, W_hat + at);
+        }
 }
 
 // ------------------------------------------------------------------ hard 2:4 mask from the pattern logits
@@ -135,12 +177,18 @@ __device__ __forceinline__ bool compress16(const uint16_t* in, uint16_t* out, ui
 // 33 us (4.8 TB/s) against 41 with a loop over the pieces and kept values picked by a computed index (which the compiler
 // sent through LDS); 4096 x 4096, tile 64, f = 0.5: 14 us against 25.
 template <int TILE>
-__global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ W, int64_t K, const uint32_t* __restrict__ table,
-                                                   int Tk, uint8_t* __restrict__ payload, int* __restrict__ err) {
+__global__ __launch_bounds__(256) void pack_kernel(const TileMapArgs map, int first, const uint16_t* __restrict__ W, int64_t K, int Tk,
+                                                   uint8_t* __restrict__ payload, uint32_t* __restrict__ table, uint32_t* __restrict__ slack,
+                                                   uint32_t* __restrict__ not_24) {
     constexpr int KPT = TILE / kStepCols, PIECES = TILE * TILE / 8 / 256;
-    const int t = blockIdx.x;
+    const int t = first + blockIdx.x;
     const int tn = t / Tk, tk = t % Tk;
-    const uint32_t e = table[t];
+    const uint32_t e = map_entry(map, blockIdx.x, t, dense_tile_bytes(TILE), sparse_tile_bytes(TILE));
+    if (threadIdx.x == 0) table[t] = e;
+    if (t == 0) {
+        static_assert(kZeroPad == 256 * sizeof(uint32_t), "one word a thread");
+        slack[threadIdx.x] = 0;
+    }
     uint8_t* base = payload + entry_offset(e);
     const int lane = threadIdx.x & 63, i = lane & 15, q = lane >> 4;
     const uint16_t* src = W + ((int64_t)tn * TILE + i) * K + (int64_t)tk * TILE;
@@ -175,13 +223,19 @@ __global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ 
             *reinterpret_cast<u32x4*>(base + (size_t)(threadIdx.x + 256 * p) * 16) = out.v;
             meta[(s * 64 + lane) * KPT + j] = (uint16_t)idx;
         }
-        if (!ok) atomicOr(err, 1);
+        if (!ok) report_not_24(not_24);
     }
 }
 
-void launch_pack(const uint16_t* W, int64_t K, const uint32_t* d_table, int n_tiles, int Tk, int tile, uint8_t* payload, int* d_err,
-                 hipStream_t stream) {
-    hipLaunchKernelGGL(tile == 128 ? &pack_kernel<128> : &pack_kernel<64>, dim3(n_tiles), dim3(256), 0, stream, W, K, d_table, Tk, payload, d_err);
+void launch_pack(const uint16_t* W, int64_t K, const uint8_t* tile_map, int n_tiles, int Tk, int tile, uint8_t* payload, uint32_t* d_table,
+                 uint32_t* slack, uint32_t* not_24, hipStream_t stream) {
+    TileMapArgs map;
+    uint32_t before = 0;
+    for (int first = 0; first < n_tiles; first += kMapTiles) {
+        const int n = n_tiles - first < kMapTiles ? n_tiles - first : kMapTiles;
+        before = fill_map_args(&map, tile_map + first, n, before);
+        hipLaunchKernelGGL(tile == 128 ? &pack_kernel<128> : &pack_kernel<64>, dim3(n), dim3(256), 0, stream, map, first, W, K, Tk, payload, d_table, slack, not_24);
+    }
 }
 
 // ------------------------------------------------------------------ decompression

@@ -33,8 +33,10 @@
 #include "../../include/patch.h"
 #include "batch_parts.h"
 #include "epilogue.h"
+#include "host_word.h"
 #include "kernels.h"
 #include "layout.h"
+#include "map_args.h"
 #include "prefill_parts.h"
 #include "saved.h"
 
@@ -109,14 +111,16 @@ __device__ __forceinline__ bool q4_nonzero(uint16_t h) { return (h & 0x7FFFu) !=
 // maximum, the tile read again in fragment order, a division per weight) took 76 us on 11008 x 4096, tile 128, f = 0.5, and 31 us on
 // 4096 x 4096, tile 64; this one 41 and 17 us (about half of that is arithmetic: eight instructions per code).
 template <int TILE>
-__global__ __launch_bounds__(256) void pack4_kernel(const uint16_t* __restrict__ W, int64_t K, const uint32_t* __restrict__ table, int Tk,
-                                                    uint8_t* __restrict__ payload, uint16_t* __restrict__ scales, int* __restrict__ err) {
+__global__ __launch_bounds__(256) void pack4_kernel(const TileMapArgs map, int first, const uint16_t* __restrict__ W, int64_t K, int Tk,
+                                                    uint8_t* __restrict__ payload, uint32_t* __restrict__ table, uint16_t* __restrict__ scales,
+                                                    uint32_t* __restrict__ not_24) {
     constexpr int KPT = TILE / kStepCols, SPT = TILE / kStripRows;
     constexpr int CPR = TILE / 8, RPP = 256 / CPR, PASSES = TILE / RPP;   // pieces per row, rows per pass, passes
     __shared__ __attribute__((aligned(16))) uint8_t stage[q4_dense_tile(TILE)];
-    const int t = blockIdx.x;
+    const int t = first + blockIdx.x;
     const int tn = t / Tk, tk = t % Tk;
-    const uint32_t e = table[t];
+    const uint32_t e = map_entry(map, blockIdx.x, t, q4_dense_tile(TILE), q4_sparse_tile(TILE));
+    if (threadIdx.x == 0) table[t] = e;
     const bool sparse = entry_sparse(e);
     const int kc = threadIdx.x % CPR, r0 = threadIdx.x / CPR;   // piece of the row, first row
     const int j = kc >> 3;                                      // K-step of the piece
@@ -177,7 +181,7 @@ __global__ __launch_bounds__(256) void pack4_kernel(const uint16_t* __restrict__
             stage[q4_sparse_codes(TILE) + ((strip * 64 + lane) * KPT + j) * 2 + half] = (uint8_t)idx;
         }
     }
-    if (!ok) atomicOr(err, 1);
+    if (!ok) report_not_24(not_24);
     __syncthreads();
     q4_u32x4* out = reinterpret_cast<q4_u32x4*>(payload + entry_offset(e));
     const int n16 = (sparse ? q4_sparse_tile(TILE) : q4_dense_tile(TILE)) / 16;
@@ -1159,7 +1163,6 @@ struct patch_packed4 {
     size_t payload_bytes = 0;
     // one allocation: payload | status word of the 2:4 check | table | scales
     uint8_t* d_payload = nullptr;   // codes and positions
-    int* d_err = nullptr;
     uint32_t* d_table = nullptr;
     uint16_t* d_scales = nullptr;   // N x Tk bf16, strip-major
     std::vector<uint8_t> tile_map;  // host copy, 1 = dense
@@ -1176,25 +1179,22 @@ void patch_free4(patch_packed4* P) {
     delete P;
 }
 
-// The host side of a 4-bit packed weight and its device buffers - one allocation, status word and table in one upload on `s` -
-// payload and scales not yet written (a tile has no alignment padding at either size, so that whoever fills them writes every
-// byte).  Shared by patch_pack4 and patch_deserialize4.  `staging` is the upload's source: it must live until `s` has been waited for.
+// The host side of a 4-bit packed weight and its device buffers, one allocation; nothing of it written yet (a tile has no alignment padding at either
+// size, so that whoever fills the payload writes every byte): patch_pack4's kernel writes payload, scales and table, patch_deserialize4 copies them.
 static_assert(q4_dense_tile(64) == q4_dense_codes(64) && q4_dense_tile(128) == q4_dense_codes(128) &&
               q4_sparse_tile(64) == q4_sparse_codes(64) + q4_sparse_pos(64) && q4_sparse_tile(128) == q4_sparse_codes(128) + q4_sparse_pos(128),
               "a tile with padding would have to be cleared");
-static patch_status new_packed4(int64_t N, int64_t K, const uint8_t* tile_map, int tile, hipStream_t s, std::vector<uint32_t>& staging, patch_packed4** out) {
+static patch_status new_packed4(int64_t N, int64_t K, const uint8_t* tile_map, int tile, patch_packed4** out) {
     patch_packed4* P = new (std::nothrow) patch_packed4();
     if (!P) return PATCH_ERR_ALLOC;
     P->N = N; P->K = K; P->tile = tile;
     P->Tn = (int)(N / tile); P->Tk = (int)(K / tile);
     const size_t T = (size_t)P->Tn * (size_t)P->Tk;
-    constexpr size_t kFront = 4;   // the status word, 16 bytes
-    try { staging.assign(kFront + T, 0); P->tile_map.resize(T); } catch (...) { delete P; return PATCH_ERR_ALLOC; }
+    try { P->tile_map.resize(T); } catch (...) { delete P; return PATCH_ERR_ALLOC; }
     uint64_t off = 0;
     for (size_t i = 0; i < T; ++i) {
         const bool sparse = tile_map[i] == 0;
         P->tile_map[i] = sparse ? 0 : 1;
-        staging[kFront + i] = make_entry(off, sparse);
         off += sparse ? q4_sparse_tile(tile) : q4_dense_tile(tile);
         P->algorithmic_bytes += sparse ? q4_sparse_codes(tile) + q4_sparse_pos(tile) + 2 * tile : q4_dense_codes(tile) + 2 * tile;
         if (sparse) ++P->n_sparse;
@@ -1209,22 +1209,14 @@ static patch_status new_packed4(int64_t N, int64_t K, const uint8_t* tile_map, i
         return PATCH_ERR_HIP;
     }
     P->n_cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-    const size_t scales_at = ((kFront + T) * sizeof(uint32_t) + kGranule - 1) / kGranule * kGranule;
+    const size_t scales_at = (T * sizeof(uint32_t) + kGranule - 1) / kGranule * kGranule;
     if (hipMalloc(&P->d_payload, P->payload_bytes + scales_at + (size_t)N * P->Tk * sizeof(uint16_t)) != hipSuccess) {
         (void)hipGetLastError();
         patch_free4(P);
         return PATCH_ERR_ALLOC;
     }
-    P->d_err = reinterpret_cast<int*>(P->d_payload + P->payload_bytes);
-    P->d_table = reinterpret_cast<uint32_t*>(P->d_err) + kFront;
+    P->d_table = reinterpret_cast<uint32_t*>(P->d_payload + P->payload_bytes);
     P->d_scales = reinterpret_cast<uint16_t*>(P->d_payload + P->payload_bytes + scales_at);
-    const hipError_t e = hipMemcpyAsync(P->d_err, staging.data(), staging.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s);
-    if (e != hipSuccess) {
-        patch_note_hip_error((int)e);
-        (void)hipStreamSynchronize(s);
-        patch_free4(P);
-        return PATCH_ERR_HIP;
-    }
     *out = P;
     return PATCH_OK;
 }
@@ -1234,15 +1226,20 @@ patch_status patch_pack4(const void* W_hat, int64_t N, int64_t K, const uint8_t*
     if ((tile != 64 && tile != 128) || N % tile || K % tile || N / tile > (1 << 20) || K / tile > (1 << 20)) return PATCH_ERR_SHAPE;
     if (!q4_aligned16(W_hat)) return PATCH_ERR_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    HostWord not_24;
+    if (!not_24.valid()) return PATCH_ERR_ALLOC;
     patch_packed4* P = nullptr;
-    std::vector<uint32_t> staging;
-    const patch_status st = new_packed4(N, K, tile_map, tile, s, staging, &P);
+    const patch_status st = new_packed4(N, K, tile_map, tile, &P);
     if (st != PATCH_OK) return st;
-    hipLaunchKernelGGL(tile == 128 ? &pack4_kernel<128> : &pack4_kernel<64>, dim3((unsigned)(P->Tn * P->Tk)), dim3(256), 0, s,
-                       static_cast<const uint16_t*>(W_hat), K, P->d_table, P->Tk, P->d_payload, P->d_scales, P->d_err);
+    TileMapArgs map;
+    uint32_t before = 0;
+    for (int n_tiles = P->Tn * P->Tk, first = 0; first < n_tiles; first += kMapTiles) {
+        const int n = n_tiles - first < kMapTiles ? n_tiles - first : kMapTiles;
+        before = fill_map_args(&map, P->tile_map.data() + first, n, before);
+        hipLaunchKernelGGL(tile == 128 ? &pack4_kernel<128> : &pack4_kernel<64>, dim3((unsigned)n), dim3(256), 0, s, map, first,
+                           static_cast<const uint16_t*>(W_hat), K, P->Tk, P->d_payload, P->d_table, P->d_scales, not_24.device());
+    }
     hipError_t e = hipGetLastError();
-    int h_err = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&h_err, P->d_err, sizeof(int), hipMemcpyDeviceToHost, s);
     const hipError_t e_sync = hipStreamSynchronize(s);
     if (e == hipSuccess) e = e_sync;
     if (e != hipSuccess) {
@@ -1250,7 +1247,7 @@ patch_status patch_pack4(const void* W_hat, int64_t N, int64_t K, const uint8_t*
         patch_free4(P);
         return PATCH_ERR_HIP;
     }
-    if (h_err) {
+    if (not_24.value()) {
         patch_free4(P);
         return PATCH_ERR_NOT_24;
     }
@@ -1317,15 +1314,21 @@ patch_status patch_deserialize4(const void* buf, size_t bytes, void* stream, pat
         return PATCH_ERR_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
     patch_packed4* P = nullptr;
-    std::vector<uint32_t> staging;
-    const patch_status st = new_packed4(h.N, h.K, b + map_at, (int)h.tile, s, staging, &P);
+    const patch_status st = new_packed4(h.N, h.K, b + map_at, (int)h.tile, &P);
     if (st != PATCH_OK) return st;
     if (P->payload_bytes != h.payload_bytes) {   // the map decides the size: a header that disagrees is not ours
-        (void)hipStreamSynchronize(s);
         patch_free4(P);
         return PATCH_ERR_ARG;
     }
-    hipError_t e = hipMemcpyAsync(P->d_payload, b + pay_at, P->payload_bytes, hipMemcpyHostToDevice, s);
+    std::vector<uint32_t> table;
+    try { table.resize(T); } catch (...) { patch_free4(P); return PATCH_ERR_ALLOC; }
+    uint64_t off = 0;
+    for (size_t i = 0; i < T; ++i) {
+        table[i] = make_entry(off, !P->tile_map[i]);
+        off += P->tile_map[i] ? q4_dense_tile(P->tile) : q4_sparse_tile(P->tile);
+    }
+    hipError_t e = hipMemcpyAsync(P->d_table, table.data(), T * sizeof(uint32_t), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(P->d_payload, b + pay_at, P->payload_bytes, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(P->d_scales, b + sc_at, (size_t)h.aux_bytes, hipMemcpyHostToDevice, s);
     const hipError_t e_sync = hipStreamSynchronize(s);   // the caller's buffer is free to go when the call returns
     if (e == hipSuccess) e = e_sync;
