@@ -598,27 +598,47 @@ int patch_test_prefill128_split(int64_t M, int count, const int64_t* N, int64_t 
     return prefill_r128_split(a, N, count);
 }
 
+// the set of a test hook's weights, by blocks of 256 features; false = bad arguments
+static bool test_prefill_set(const void* X, int64_t M, const patch_packed* const* P, void* const* Y, int count, int y_bf16, void* workspace,
+                             size_t workspace_bytes, GemmArgs* a, WeightSet* set) {
+    if (!X || !P || !Y || M < 1 || count < 1 || count > kMaxMany) return false;
+    *a = {};
+    *set = {};
+    a->X = static_cast<const uint16_t*>(X);
+    a->M = M; a->K = P[0]->K; a->tile = P[0]->tile; a->Tk = P[0]->Tk; a->n_cus = P[0]->n_cus;
+    a->ybf16 = y_bf16 ? 1 : 0;
+    a->ws = static_cast<float*>(workspace);
+    a->ws_bytes = workspace_bytes;
+    for (int i = 0; i < count; ++i) {
+        if (!P[i] || !Y[i] || P[i]->K != a->K || P[i]->tile != a->tile) return false;
+        set->payload[i] = P[i]->d_payload; set->table[i] = P[i]->d_table; set->Y[i] = static_cast<float*>(Y[i]); set->N[i] = P[i]->N;
+        set->first[i] = set->units;
+        set->units += (int)((P[i]->N + 255) / 256);
+        a->N += P[i]->N;
+    }
+    set->count = count;
+    return true;
+}
+
 int patch_test_prefill128(const void* X, int64_t M, const patch_packed* const* P, void* const* Y, int count, int split, int y_bf16, void* workspace,
                           size_t workspace_bytes, void* stream) {
-    if (!X || !P || !Y || M < 1 || count < 1 || count > kMaxMany || split < 1 || split > 16 || split > P[0]->Tk) return -1;
-    GemmArgs a = {};
-    a.X = static_cast<const uint16_t*>(X);
-    a.M = M; a.K = P[0]->K; a.tile = P[0]->tile; a.Tk = P[0]->Tk; a.n_cus = P[0]->n_cus;
-    a.ybf16 = y_bf16 ? 1 : 0;
-    a.ws = static_cast<float*>(workspace);
-    a.ws_bytes = workspace_bytes;
-    WeightSet set = {};
-    size_t need = 0;
-    for (int i = 0; i < count; ++i) {
-        if (!P[i] || !Y[i] || P[i]->K != a.K || P[i]->tile != a.tile) return -1;
-        set.payload[i] = P[i]->d_payload; set.table[i] = P[i]->d_table; set.Y[i] = static_cast<float*>(Y[i]); set.N[i] = P[i]->N;
-        set.first[i] = set.units;
-        set.units += (int)((P[i]->N + 255) / 256);
-        need += (size_t)split * (size_t)M * (size_t)P[i]->N * sizeof(float);
-    }
-    set.count = count;
-    if (split > 1 && (!workspace || workspace_bytes < need)) return -1;
+    GemmArgs a;
+    WeightSet set;
+    if (!test_prefill_set(X, M, P, Y, count, y_bf16, workspace, workspace_bytes, &a, &set) || split < 1 || split > 16 || split > a.Tk) return -1;
+    if (split > 1 && (!workspace || workspace_bytes / sizeof(float) / (size_t)split < (size_t)M * (size_t)a.N)) return -1;
     launch_prefill_r128(a, set, split, static_cast<hipStream_t>(stream));
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int patch_test_prefill_last_round(const void* X, int64_t M, const patch_packed* const* P, void* const* Y, int count, int halves, int slices, int y_bf16,
+                                  void* workspace, size_t workspace_bytes, void* stream) {
+    GemmArgs a;
+    WeightSet set;
+    if (!test_prefill_set(X, M, P, Y, count, y_bf16, workspace, workspace_bytes, &a, &set) || !prefill_wreg_supports(a)) return -1;
+    const int tiles_m = (int)((M + 255) / 256), tail = set.units * tiles_m % a.n_cus;
+    if (halves >= 0 && (slices < 1 || slices > 8 || slices > a.Tk || (halves == 0 && slices == 1) || tail == 0 || set.units * tiles_m < a.n_cus)) return -1;
+    if (halves >= 0 && slices > 1 && (!workspace || workspace_bytes < (size_t)tail * slices * 256 * 256 * sizeof(float))) return -1;
+    launch_prefill_wreg_rounds(a, set, tiles_m, halves < 0 ? LastRound{0, 1, false} : LastRound{tail, slices, halves != 0}, static_cast<hipStream_t>(stream));
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -952,9 +972,8 @@ static size_t workspace_need(int64_t M, const patch_packed* P, const patch_gemm_
     const int s = prefill_wreg_split(a, split_k);
     if (s > 1) return std::max(least, (size_t)s * (size_t)M * (size_t)P->N * sizeof(float));
     if (split_k != 0) return 0;
-    int tail = 0;
-    const int ts = prefill_wreg_tail(a, &tail);   // K slices for the part-filled last round only
-    return std::max(least, ts > 1 ? (size_t)ts * (size_t)tail * 256 * 256 * sizeof(float) : (size_t)0);
+    const LastRound last = prefill_wreg_tail(a);   // K slices for the part-filled last round only
+    return std::max(least, last.slices > 1 ? (size_t)last.slices * (size_t)last.tail * 256 * 256 * sizeof(float) : (size_t)0);
 }
 
 size_t patch_gemm_workspace_bytes(int64_t M, const patch_packed* P, const patch_gemm_opts* opts) { return workspace_need(M, P, opts, false); }

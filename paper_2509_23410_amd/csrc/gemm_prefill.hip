@@ -769,10 +769,7 @@ double prefill_estimate(const GemmArgs& a) {
 // 0.87 (4096 x 4096, 512 rows 49.9 -> 45.9; 11008 x 4096, 512 rows 65.2 -> 54.9); at worst 4.5 % behind (4096 x 4096, f = 0, 512 rows 31.8 -> 33.2).
 // The best choice of each would be 0.95 and 0.90.  Whether the decode path's passes run instead is decided by the prices above, as if this kernel
 // did not exist.
-struct PrefillPrice { double base, begin, t0, t1, g1, g2, second, rate; };
-constexpr PrefillPrice kPriceR128 = {6.7, 2.3, 0.682, 0.171, 0.365, 0.0, 2.2, 10.3e6}, kPriceAreg128 = {4.6, 3.2, 0.864, 0.199, 0.347, 0.0, 3.3, 13.0e6},
-                       kPriceWreg = {10.6, 0.5, 0.841, 0.411, 0.017, 0.364, 1.6, 8.4e6};
-static double pf_price(const PrefillPrice& p, const GemmArgs& a, int64_t N, int64_t blocks, int split) {
+double pf_price(const PrefillPrice& p, const GemmArgs& a, int64_t N, int64_t blocks, int split) {
     const int64_t wgs = blocks * split, rounds = (wgs + a.n_cus - 1) / a.n_cus, steps = (int64_t)((a.Tk + split - 1) / split) * (a.tile / kStepCols);
     const double fill = wgs < a.n_cus ? (double)wgs / a.n_cus : 1.0, f = 0.01 * a.sparse_pct, y = (double)a.M * (double)N * 4.0;
     return p.base + p.begin * fill + (double)rounds * (double)steps * (p.t0 + p.t1 * fill) * (1.0 - p.g1 * f - p.g2 * f * f) +

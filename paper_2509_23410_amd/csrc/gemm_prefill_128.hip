@@ -23,6 +23,7 @@
 #include "kernels.h"
 #include "layout.h"
 #include "prefill_parts.h"
+#include "tile_order.h"
 
 namespace patch {
 
@@ -109,36 +110,27 @@ __device__ __forceinline__ void rh_half(f32x16 (&acc)[2][4], int sparse, uint32_
 
 template <int TILE, bool SPLIT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void prefill_kernel_r128(
-    const uint16_t* __restrict__ X, int64_t M, int64_t K, int Tk_all, int tiles_n, int tiles_m, const WeightSet set, int ybf16) {
+    const uint16_t* __restrict__ X, int64_t M, int64_t K, int Tk_all, int tiles_n, int tiles_m, int t0, int cnt, const WeightSet set, int ybf16) {
     constexpr int KPT = TILE / kStepCols;  // K-steps per tile: 2 or 1
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tr = TILE == 128 ? w >> 1 : w, sh = TILE == 128 ? w & 1 : 0;   // tile row of the block, half of the tile
-    // block -> (n, m): one contiguous run of the grouped order (4 row blocks x all feature blocks) per XCD
-    const int nblk = tiles_n * tiles_m;
+    // Block -> (n, m): one contiguous run of the order per XCD.  t0 < 0: the launch is a grid of tiles_n x tiles_m blocks.  Otherwise it covers tiles
+    // t0 .. of a grid of 256 x 256 tiles, two blocks each.
+    const bool tail = t0 >= 0;
     int bid = blockIdx.x;
     {
-        const int per = (nblk + 7) / 8;
+        const int per = (cnt + 7) / 8;
         const int x = bid & 7, i = bid >> 3;
         const int t = x * per + i;
-        bid = (i < per && t < nblk) ? t : -1;
+        bid = (i < per && t < cnt) ? t : -1;
     }
     if (bid < 0) return;
     int bn, bm;
-    {
-        constexpr int GM = 4;
-        const int full = (tiles_m / GM) * GM * tiles_n;
-        if (bid < full) {
-            const int g = bid / (GM * tiles_n), rem = bid % (GM * tiles_n);
-            bn = rem / GM;
-            bm = g * GM + rem % GM;
-        } else {
-            const int gm = tiles_m % GM, rem = bid - full;
-            bn = rem / gm;
-            bm = (tiles_m / GM) * GM + rem % gm;
-        }
-    }
+    tile_of(tail ? t0 + (bid >> 1) : bid, tiles_n, tiles_m, bn, bm);
+    const int64_t m0 = tail ? (int64_t)bm * 256 + (bid & 1) * kRhBM : (int64_t)bm * kRhBM;
+    if (m0 >= M) return;
     // the weight of the set that the feature block belongs to
     uint64_t payload_ = reinterpret_cast<uint64_t>(set.payload[0]), table_ = reinterpret_cast<uint64_t>(set.table[0]), Y_ = reinterpret_cast<uint64_t>(set.Y[0]);
     int64_t N = set.N[0];
@@ -159,7 +151,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     float* const Y = reinterpret_cast<float*>(Y_);
     typedef const __attribute__((address_space(4))) int32_t* pairs_t;
     typedef const __attribute__((address_space(1))) uint32_t* table_t;
-    const int64_t m0 = (int64_t)bm * kRhBM;
     // Mask tile 128: the two tile rows that the packer put together (so that both are 2:4 in as many steps as possible), -1 = no second one.  Mask
     // tile 64: four adjacent tile rows, of which the last block may lack up to three.  A wavefront without a tile row works on another one's
     // weights (valid addresses) and stores nothing.
@@ -280,12 +271,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // left the loop.
     __syncthreads();
     if (live) {
+        // (a slot of 256 x 256 floats per tile and slice, a part of the workspace per slice, or Y)
+        const bool slots = SPLIT && tail;
+        const int64_t stride = slots ? 256 : N;
+        const int64_t at = slots ? (((int64_t)(bid >> 1) * gridDim.y + blockIdx.y) * 256 + (bid & 1) * kRhBM) * 256 + 64 * w
+                                 : (SPLIT ? (int64_t)blockIdx.y * M * N : 0) + m0 * N + nrow + 64 * sh;
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
             for (int b = 0; b < 4; ++b)
-                store_block_rows(lds + w * 4096, acc[a][b], lane, Y, (SPLIT ? (int64_t)blockIdx.y * M * N : 0) + (m0 + 32 * b) * N + nrow + 64 * sh + 32 * a, N,
-                                 M - (m0 + 32 * b), SPLIT ? 0 : ybf16);
+                store_block_rows(lds + w * 4096, acc[a][b], lane, Y, at + 32 * b * stride + 32 * a, stride, M - (m0 + 32 * b), SPLIT ? 0 : ybf16);
     }
 }
 
@@ -293,7 +288,7 @@ void launch_prefill_r128(const GemmArgs& a, const WeightSet& set, int split, hip
     const int tiles_m = (int)((a.M + kRhBM - 1) / kRhBM), nblk = set.units * tiles_m, grid = ((nblk + 7) / 8) * 8;
     if (split < 2) {
         const auto kernel = a.tile == 128 ? &prefill_kernel_r128<128, false> : &prefill_kernel_r128<64, false>;
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), kRhLds, stream, a.X, a.M, a.K, a.Tk, set.units, tiles_m, set, a.ybf16);
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), kRhLds, stream, a.X, a.M, a.K, a.Tk, set.units, tiles_m, -1, nblk, set, a.ybf16);
         return;
     }
     WeightSet part = set;
@@ -307,9 +302,16 @@ void launch_prefill_r128(const GemmArgs& a, const WeightSet& set, int split, hip
         off += (size_t)split * (size_t)a.M * (size_t)set.N[i];
     }
     const auto kernel = a.tile == 128 ? &prefill_kernel_r128<128, true> : &prefill_kernel_r128<64, true>;
-    hipLaunchKernelGGL(kernel, dim3(grid, split), dim3(256), kRhLds, stream, a.X, a.M, a.K, a.Tk, set.units, tiles_m, part, 0);
+    hipLaunchKernelGGL(kernel, dim3(grid, split), dim3(256), kRhLds, stream, a.X, a.M, a.K, a.Tk, set.units, tiles_m, -1, nblk, part, 0);
     if (set.count == 1) wr_reduce(a.ws, red.n4[0], split, set.Y[0], a.ybf16, stream);
     else wr_reduce_set(red, set.count, split, a.ybf16, stream);
+}
+
+void launch_prefill_r128_tail(const GemmArgs& a, const WeightSet& set, int tiles_m, int t0, int tail, int slices, hipStream_t stream) {
+    const dim3 grid((unsigned)((2 * tail + 7) / 8 * 8), (unsigned)slices);
+    const auto kernel = slices > 1 ? a.tile == 128 ? &prefill_kernel_r128<128, true> : &prefill_kernel_r128<64, true>
+                                   : a.tile == 128 ? &prefill_kernel_r128<128, false> : &prefill_kernel_r128<64, false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(256), kRhLds, stream, a.X, a.M, a.K, a.Tk, set.units, tiles_m, t0, 2 * tail, set, a.ybf16);
 }
 
 }  // namespace patch

@@ -38,9 +38,12 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "epilogue.h"
 #include "kernels.h"
 #include "layout.h"
+#include "tile_order.h"
 
 namespace patch {
 
@@ -540,30 +543,13 @@ __device__ __forceinline__ uint64_t wr_uniform64(uint64_t v) {
     return ((uint64_t)hi << 32) | lo;
 }
 
-// Tile t of the launch order -> feature block bn (256 features), row block bm (256 rows): groups of 4 row blocks x
-// all feature blocks, so that the workgroups an XCD runs at a time cover about 8 feature blocks x 4 row blocks
-// and share both operands in its L2.
-__device__ __forceinline__ void wr_tile_of(int t, int tiles_n, int tiles_m, int& bn, int& bm) {
-    constexpr int GM = 4;
-    const int full = (tiles_m / GM) * GM * tiles_n;
-    if (t < full) {
-        const int g = t / (GM * tiles_n), rem = t % (GM * tiles_n);
-        bn = rem / GM;
-        bm = g * GM + rem % GM;
-    } else {
-        const int gm = tiles_m % GM, rem = t - full;
-        bn = rem / gm;
-        bm = (tiles_m / GM) * GM + rem % gm;
-    }
-}
-
 // Sum of the partial tiles of a MODE 2 launch (slot (t - t0) * slices + y, 256 rows x 256 features each, slice 0
 // first) into Y.  Block = 16 rows of one tile; thread = 4 x 4 features of one row.
 __global__ __launch_bounds__(256) void wr_tail_reduce_kernel(const float* __restrict__ ws, int slices, int t0, int tiles_n, int tiles_m,
                                                              int64_t M, int Tk_all, int tile, const WeightSet set, int ybf16) {
     const int j = blockIdx.x >> 4, chunk = blockIdx.x & 15;
     int bn, bm;
-    wr_tile_of(t0 + j, tiles_n, tiles_m, bn, bm);
+    tile_of(t0 + j, tiles_n, tiles_m, bn, bm);
     const uint32_t* table = set.table[0];
     float* Y = set.Y[0];
     int64_t N = set.N[0];
@@ -627,7 +613,7 @@ __device__ __forceinline__ void wr_body(const uint16_t* __restrict__ X, int64_t 
     }
     if (bid < 0) return;
     int bn, bm;
-    wr_tile_of(bid, tiles_n, tiles_m, bn, bm);
+    tile_of(bid, tiles_n, tiles_m, bn, bm);
     // which weight of the set the feature block belongs to: scalar selects, made explicitly uniform, so that the
     // weight addresses stay in scalar registers
     const uint8_t* __restrict__ payload = set.payload[0];
@@ -1057,37 +1043,37 @@ int prefill_wreg_split(const GemmArgs& a, int requested) {
     return s < 2 ? 1 : s;
 }
 
-// A launch whose tile count is a little more than a multiple of the CU count ends with a part-filled round that
-// lasts as long as a full one.  With a workspace the last `tail` tiles (at most half a round) are cut into K slices
-// that fill the chip once: returns the slice count (1 = no such split) and sets *tail.  It pays when the part of a
-// round it saves outweighs writing and re-reading the partial tiles (an estimate from measured rates: 0.9 - 1.25 us
-// per step depending on how full the chip is, 3 TB/s for the partials, 8 us for the two extra launches).
-int prefill_wreg_tail(const GemmArgs& a, int* tail) {
-    return prefill_wreg_tail_of((int)(((a.N + kWrBN - 1) / kWrBN) * ((a.M + kWrBM - 1) / kWrBM)), a, tail);
+// A launch whose tile count is a little more than a multiple of the compute units ends with a part-filled round that lasts almost as long as a full one.
+// Its tiles can be a launch of their own: in halves of 128 rows by prefill_kernel_r128, which takes three quarters of the time, needs no workspace where
+// it leaves K whole, and has the lower start-up, or in 256-row tiles of this kernel, both with K in slices while they fill the chip at most once.  Priced as
+// in prefill_r128_split (less 5 us for a round that follows others, 2 us to be gained at least).  Over 85 launches (13 weights, 700 - 6872 rows, both mask tiles,
+// f = 0, 1/2 and 1) the choice takes 0.90 of the launch without a last round of its own, the best of all slices 0.895, the best without halves 0.915.  us,
+// whole -> best 256-row slices -> choice: 22016 x 4096, f = 1/2, mask tile 64, 1003 rows (344 tiles) 154.8 -> 148.7 -> 145.1 (this one without a workspace);
+// 700 rows (258) 141.6 -> 121.3 -> 120.0; 4096 x 4096, mask tile 128, 4200 rows (272) 136.4 -> 114.7 -> 109.5; 256-row slices are still the better ones where
+// they fill the chip and halves would not: 5120 x 13824, 4096 rows (320) 440.4 -> 363.4 in four slices, 408.2 in halves.  After more than four full rounds the
+// workgroups are far out of step and the part-filled round costs little: 22016 x 4096, f = 1/2, 1376 tiles 476.5, in halves 494.6; 1118 tiles 432.2 and 409.2.
+LastRound prefill_wreg_last_round(int tiles, const GemmArgs& a) {
+    const int t = tiles % a.n_cus;
+    LastRound best = {0, 1, false};
+    if (tiles < a.n_cus || tiles / a.n_cus > 4 || t == 0 || 2 * t > a.n_cus) return best;
+    const double slot = (double)t * kWrBM * kWrBN * sizeof(float);
+    const auto priced = [&](const PrefillPrice& p, int blocks, int slices, double launches) {
+        return pf_price(p, a, 0, blocks, slices) + launches + (slices > 1 ? (2.0 * slices + 1.0) * slot / p.rate : 0.0);
+    };
+    double us = priced(kPriceWreg, t, 1, -5.0) - 2.0;
+    const auto consider = [&](const LastRound& r, double price) {
+        if (price < us) { us = price; best = r; }
+    };
+    const int fit = a.ws ? (int)std::min<size_t>(8, a.ws_bytes / (size_t)slot) : 1;
+    for (int s = 1; s <= 8 && (s == 1 || (s <= fit && s <= wr_longest(a))); ++s) {
+        if (2 * t * s <= a.n_cus) consider({t, s, true}, priced(kPriceR128, 2 * t, s, 0.0));
+        if (s > 1 && t * s <= a.n_cus) consider({t, s, false}, priced(kPriceWreg, t, s, 0.0));
+    }
+    return best;
 }
 
-int prefill_wreg_tail_of(int tiles, const GemmArgs& a, int* tail) {
-    const int t = tiles % a.n_cus;
-    *tail = 0;
-    if (!a.ws || tiles < a.n_cus || t == 0 || 2 * t > a.n_cus) return 1;
-    int s = a.n_cus / t;
-    if (s > 8) s = 8;
-    if (s > wr_longest(a)) s = wr_longest(a);
-    const size_t per_slot = (size_t)kWrBM * kWrBN * sizeof(float);
-    while (s >= 2 && (size_t)t * (size_t)s * per_slot > a.ws_bytes) --s;
-    if (s < 2) return 1;
-    // after more than three full rounds the workgroups are far out of step and a part-filled round costs much less
-    // than a full one (gate + up in one launch, 5.4 rounds: splitting the last 96 tiles measured 4 % slower)
-    // a K-step costs 0.9 us on a nearly empty chip and 1.25 us on a full one: the part-filled round is shorter than a
-    // full round to begin with, and its slices run on a fuller chip
-    const double fill = (double)t / a.n_cus, fill_s = (double)t * s / a.n_cus;
-    const double steps = (double)a.Tk * (a.tile / kStepCols);
-    const double round_us = steps * (0.9 + 0.35 * fill) * (tiles / a.n_cus > 3 ? 0.4 : 1.0);
-    const double gain_us = round_us - steps / s * (0.9 + 0.35 * (fill_s < 1.0 ? fill_s : 1.0)) * (tiles / a.n_cus > 3 ? 0.4 : 1.0);
-    const double cost_us = 2.0 * (double)t * s * per_slot / 3.0e6 + 8.0;
-    if (gain_us <= cost_us) return 1;
-    *tail = t;
-    return s;
+LastRound prefill_wreg_tail(const GemmArgs& a) {
+    return prefill_wreg_last_round((int)(((a.N + kWrBN - 1) / kWrBN) * ((a.M + kWrBM - 1) / kWrBM)), a);
 }
 
 // One launch of the kernel of a.tile: tiles t0 .. t0 + cnt - 1 of the order, `slices` K slices each (MODE 1, 2).
@@ -1124,23 +1110,23 @@ void wr_reduce_set(const WrReduceSet& red, int count, int slices, int ybf16, hip
                        ybf16);
 }
 
-// An unsplit launch; with a.ws and a part-filled last round worth it, all full rounds unsplit, then the last tiles in K
-// slices over the whole chip, then their sum.
-static void wr_launch_whole(const GemmArgs& a, const WeightSet& set, int tiles_m, bool may_split_tail, hipStream_t stream) {
-    const int nblk = set.units * tiles_m;
-    int tail = 0;
-    const int tail_split = may_split_tail ? prefill_wreg_tail_of(nblk, a, &tail) : 1;   // 1 without a.ws
-    if (tail_split < 2) {
-        wr_launch<0>(a, set, tiles_m, 0, nblk, 1, a.ybf16, stream);
-        return;
-    }
-    const int body = nblk - tail;
+// An unsplit launch whose last round (r.tail tiles; 0 = as the rest) is a launch of its own, where split followed by one that sums it.
+void launch_prefill_wreg_rounds(const GemmArgs& a, const WeightSet& set, int tiles_m, const LastRound& r, hipStream_t stream) {
+    const int nblk = set.units * tiles_m, body = nblk - r.tail;
     wr_launch<0>(a, set, tiles_m, 0, body, 1, a.ybf16, stream);
-    WeightSet part = set;
-    for (int i = 0; i < kMaxMany; ++i) part.Y[i] = a.ws;   // partial tiles go to workspace slots, whatever the weight
-    wr_launch<2>(a, part, tiles_m, body, tail, tail_split, 0, stream);
-    hipLaunchKernelGGL(wr_tail_reduce_kernel, dim3(tail * 16), dim3(256), 0, stream, a.ws, tail_split, body, set.units, tiles_m, a.M, a.Tk,
-                       a.tile, set, a.ybf16);
+    if (r.tail == 0) return;
+    WeightSet out = set;
+    if (r.slices > 1)
+        for (int i = 0; i < kMaxMany; ++i) out.Y[i] = a.ws;   // partial tiles go to workspace slots, whatever the weight
+    if (r.halves) launch_prefill_r128_tail(a, out, tiles_m, body, r.tail, r.slices, stream);
+    else wr_launch<2>(a, out, tiles_m, body, r.tail, r.slices, 0, stream);
+    if (r.slices > 1)
+        hipLaunchKernelGGL(wr_tail_reduce_kernel, dim3(r.tail * 16), dim3(256), 0, stream, a.ws, r.slices, body, set.units, tiles_m, a.M, a.Tk, a.tile, set,
+                           a.ybf16);
+}
+
+static void wr_launch_whole(const GemmArgs& a, const WeightSet& set, int tiles_m, bool may_split_tail, hipStream_t stream) {
+    launch_prefill_wreg_rounds(a, set, tiles_m, may_split_tail ? prefill_wreg_last_round(set.units * tiles_m, a) : LastRound{0, 1, false}, stream);
 }
 
 void launch_prefill_wreg(const GemmArgs& a, int split_k, hipStream_t stream) {

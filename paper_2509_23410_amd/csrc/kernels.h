@@ -122,9 +122,17 @@ bool prefill_prefers_128_rows(const GemmArgs& a, int* split, bool no_w64 = false
 double prefill_estimate(const GemmArgs& a);                                       // us the default choice is estimated to take at few rows
 double prefill_set_estimate(const GemmArgs& a, const int64_t* N, int count);      // the same for a set of weights of N[i] features
 double pf_few_rows(const GemmArgs& a, int64_t N, int blocks, int split, bool rows128, bool whole_blocks);   // what both go by
-// K slices for the last *tail tiles of an unsplit launch with a part-filled last round (needs a.ws); 1 = none
-int prefill_wreg_tail(const GemmArgs& a, int* tail);
-int prefill_wreg_tail_of(int tiles, const GemmArgs& a, int* tail);   // the same for a given tile count (sets of weights)
+// How an unsplit launch of 256 x 256 tiles runs its part-filled last round: the last `tail` tiles (0: as the others) in `slices` K slices (more than one
+// needs a.ws with a slot of 256 x 256 floats per tile and slice), by prefill_kernel_r128 (`halves`: 128 rows a workgroup) or by the kernel of the rest.
+struct LastRound { int tail, slices; bool halves; };
+LastRound prefill_wreg_tail(const GemmArgs& a);
+LastRound prefill_wreg_last_round(int tiles, const GemmArgs& a);   // the same for a given tile count (sets of weights)
+void launch_prefill_wreg_rounds(const GemmArgs& a, const WeightSet& set, int tiles_m, const LastRound& r, hipStream_t stream);
+// Price of a prefill launch in us (prefill_r128_split has the formula and what it was fitted to)
+struct PrefillPrice { double base, begin, t0, t1, g1, g2, second, rate; };
+constexpr PrefillPrice kPriceR128 = {6.7, 2.3, 0.682, 0.171, 0.365, 0.0, 2.2, 10.3e6}, kPriceAreg128 = {4.6, 3.2, 0.864, 0.199, 0.347, 0.0, 3.3, 13.0e6},
+                       kPriceWreg = {10.6, 0.5, 0.841, 0.411, 0.017, 0.364, 1.6, 8.4e6};
+double pf_price(const PrefillPrice& p, const GemmArgs& a, int64_t N, int64_t blocks, int split);
 void launch_prefill_wreg(const GemmArgs& a, int split_k, hipStream_t stream);
 // The same for a set of weights; a supplies X, M, K, tile, Tk, n_cus and, optionally, ws / ws_bytes (then a
 // part-filled last round is split as in launch_prefill_wreg).  All of the set must pass prefill_wreg_supports with
@@ -136,6 +144,8 @@ int prefill_wreg_set_split(const GemmArgs& a, int blocks, int64_t N);   // K sli
 // way, 0 = it does not.
 int prefill_r128_split(const GemmArgs& a, const int64_t* N, int count);
 void launch_prefill_r128(const GemmArgs& a, const WeightSet& set, int split, hipStream_t stream);
+// Tiles t0 .. t0 + tail - 1 of a launch over 256 x 256 tiles, two workgroups each; slices > 1: partial tiles to slots of 256 x 256 floats at set.Y
+void launch_prefill_r128_tail(const GemmArgs& a, const WeightSet& set, int tiles_m, int t0, int tail, int slices, hipStream_t stream);
 
 }  // namespace patch
 
@@ -152,6 +162,10 @@ int patch_test_prefill128(const void* X, int64_t M, const patch_packed* const* P
 int patch_test_schedule(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* kernel, int* chunks);
 // The same and, per pass, over how many workgroups per feature group its rows are dealt (rows_deals; 1 = not).
 int patch_test_schedule_deals(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* kernel, int* chunks, int* deals);
+// The prefill product of `count` weights by the 256-row register-weight kernel, its last round (the tiles beyond a multiple of the compute units) in
+// `slices` K slices, `halves` as in LastRound; halves = -1: as the rest of the launch.
+int patch_test_prefill_last_round(const void* X, int64_t M, const patch_packed* const* P, void* const* Y, int count, int halves, int slices, int y_bf16,
+                                  void* workspace, size_t workspace_bytes, void* stream);
 // prefill_r128_split of the same, for the prefill path
 int patch_test_prefill128_split(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes);
 // deal_units: gridDim.x of a launch over `units` feature groups whose rows go over `deals` workgroups

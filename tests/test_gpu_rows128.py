@@ -107,3 +107,61 @@ def test_the_default_choice_takes_it(tile, Ns, K, M, workspace):
             assert torch.equal(Y, Z)
     for P in Ps:
         P.close()
+
+
+@pytest.mark.parametrize("tile,Ns,K", [(128, [384], 384), (128, [128, 256], 640), (64, [320], 192), (64, [320, 64], 448)])
+def test_last_round_in_halves(tile, Ns, K):
+    """The tiles beyond 256 of a launch over 256 x 256 tiles, 128 rows a workgroup: whole K and slices in workspace slots, last row blocks whose second half
+    is part-filled or empty, feature blocks that lack tile rows, sets."""
+    stream = torch.cuda.current_stream().cuda_stream
+    Ps, Ws = zip(*[_weight(N, K, tile, 0.5, 5 + i) for i, N in enumerate(Ns)])
+    units = sum(-(-N // 256) for N in Ns)
+    for missing in (200, 40):
+        M = 256 * (-(-258 // units)) - missing
+        tail = units * -(-M // 256) - 256
+        X = _x(M, K)
+        refs = [_ref(X, W) for W in Ws]
+        for slices in sorted({1, 2, 3, K // tile} & set(range(1, min(8, K // tile) + 1))):
+            for dt in (torch.float32, torch.bfloat16):
+                print(f"last round tile={tile} N={Ns} K={K} M={M} tail={tail} slices={slices} {dt}", flush=True)
+                ends = np.cumsum([1024] + [M * N + 1024 for N in Ns])
+                buf = torch.full((int(ends[-1]),), 7.0, device="cuda", dtype=dt)
+                Ys = [buf[e:e + M * N].view(M, N) for e, N in zip(ends, Ns)]
+                for Y in Ys:
+                    Y.fill_(float("nan"))
+                ws = torch.full((slices * tail * 65536 + 1024,), float("nan"), device="cuda")
+                ws[slices * tail * 65536:] = 7.0
+                st = B.lib().patch_test_prefill_last_round(vp(X.data_ptr()), ctypes.c_int64(M), (vp * len(Ns))(*[P.handle for P in Ps]),
+                                                           (vp * len(Ns))(*[Y.data_ptr() for Y in Ys]), len(Ns), 1, slices, int(dt == torch.bfloat16),
+                                                           vp(ws.data_ptr()), ctypes.c_size_t(4 * slices * tail * 65536), vp(stream))
+                assert st == B.OK, st
+                for Y, (ref, bound) in zip(Ys, refs):
+                    allowed = bound if dt == torch.float32 else bound + 2.0 ** -8 * (ref.abs() + bound)
+                    assert ((Y.double() - ref).abs() / allowed).max().item() <= 1.0
+                assert bool((torch.cat([buf[e - 1024:e] for e in ends]) == 7.0).all()), "wrote outside Y"
+                assert bool((ws[slices * tail * 65536:] == 7.0).all()), "wrote behind the workspace"
+    for P in Ps:
+        P.close()
+
+
+@pytest.mark.parametrize("workspace", [False, True])
+def test_the_last_round_of_the_default_choice(workspace):
+    N, K, M = 640, 2048, 256 * 86 - 100     # 258 tiles
+    stream = torch.cuda.current_stream().cuda_stream
+    P, W = _weight(N, K, 128, 0.5, 21)
+    X = _x(M, K)
+    need = B.patch_gemm_workspace_bytes(M, P, path=B.PATH_PREFILL)
+    slices = need // (2 * 65536 * 4) if workspace else 1
+    assert need % (2 * 65536 * 4) == 0 and (slices > 1) == workspace
+    ws = torch.full((need // 4,), float("nan"), device="cuda")
+    Y, Z, whole = (torch.full((M, N), float("nan"), device="cuda") for _ in range(3))
+    B.patch_gemm(X, M, P, Y, stream, path=B.PATH_PREFILL, workspace=ws if workspace else None)
+    for out, halves, n in ((Z, 1, slices), (whole, -1, 1)):
+        assert B.lib().patch_test_prefill_last_round(vp(X.data_ptr()), ctypes.c_int64(M), (vp * 1)(P.handle), (vp * 1)(out.data_ptr()), 1, halves, n, 0,
+                                                     vp(ws.data_ptr()), ctypes.c_size_t(need), vp(stream)) == B.OK
+    ref, bound = _ref(X, W)
+    assert ((Y.double() - ref).abs() / bound).max().item() <= 1.0
+    assert torch.equal(Y, Z)
+    # whole K in halves adds up in the order of the 256-row kernel; slices do not
+    assert torch.equal(Y, whole) != workspace
+    P.close()
