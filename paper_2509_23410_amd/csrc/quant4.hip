@@ -21,13 +21,12 @@
 // partial sums meet in LDS in wavefront order (bit-reproducible); several weights sharing X run as one launch
 // (patch_gemm4_many).  That kernel takes up to 64 rows of X (one, two or four blocks of 16) per pass over the weight;
 // for more rows there are prefill-shaped kernels that keep the weight in 4 bits (prefill4_kernel below, prefill4_kgroups_kernel in
-// quant4_kgroups.h; patch_gemm4_ex), and any weight can be dequantized once and packed as bf16 (patch_pack_from4).
+// quant4_kgroups.hip; patch_gemm4_ex), and any weight can be dequantized once and packed as bf16 (patch_pack_from4).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <string.h>
 
 #include <new>
-#include <type_traits>
 #include <vector>
 
 #include "../../include/patch.h"
@@ -38,6 +37,7 @@
 #include "layout.h"
 #include "map_args.h"
 #include "prefill_parts.h"
+#include "quant4_layout.h"
 #include "saved.h"
 
 namespace patch {
@@ -50,15 +50,6 @@ typedef unsigned int q4_u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int q4_pair_t __attribute__((ext_vector_type(2), aligned(4)));   // two at a dword's
 union Q4A { q4_u32x4 raw; q4_bf16x8 v; };
 union Q4B { q4_u32x4 raw[2]; q4_bf16x8 h[2]; q4_bf16x16 v; };
-
-__host__ __device__ constexpr int q4_dense_codes(int t) { return t * t / 2; }
-__host__ __device__ constexpr int q4_sparse_codes(int t) { return t * t / 4; }
-__host__ __device__ constexpr int q4_sparse_pos(int t) { return t * t / 8; }
-__host__ __device__ constexpr int q4_round_up(int b) { return (b + kGranule - 1) / kGranule * kGranule; }
-__host__ __device__ constexpr int q4_dense_tile(int t) { return q4_round_up(q4_dense_codes(t)); }
-__host__ __device__ constexpr int q4_sparse_tile(int t) { return q4_round_up(q4_sparse_codes(t) + q4_sparse_pos(t)); }
-// scale of row r (0..15) of strip `strip` (over the whole matrix) for tile column tk
-__host__ __device__ constexpr int64_t q4_scale_index(int64_t strip, int Tk, int tk, int r) { return (strip * Tk + tk) * 16 + r; }
 
 __device__ __forceinline__ float q4_bf16_to_float(uint32_t bits) { return __uint_as_float(bits << 16); }
 
@@ -1151,8 +1142,6 @@ __global__ __launch_bounds__(512) void prefill4_kernel(const uint16_t* __restric
 
 }  // namespace patch
 
-#include "quant4_kgroups.h"
-
 using namespace patch;
 
 struct patch_packed4 {
@@ -1536,10 +1525,6 @@ struct Q4PrefillPrice { int bm; double base, start, round, t0, t1, tile64, spars
 constexpr Q4PrefillPrice kQ4PrefillPrice[] = {{128, 4.6, 0.0, 0.0, 0.766, 0.076, 1.065, -0.30, 1.0}, {256, 6.1, 0.0, 0.0, 1.22, 0.142, 1.054, -0.387, 1.0},
                                               {128, 8.1, 1.5, 4.1, 0.489, 0.142, 1.023, -0.255, 0.91}};
 
-static hipError_t q4_grant(decltype(&prefill4_kgroups_kernel<128, false>) kernel) {   // more LDS than a launch gets without asking
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kKgLds);
-}
-
 static int q4_prefill_split(int64_t M, const Q4Shape& d, Q4PrefillKernel* kernel) {
     *kernel = kQ4Rows128;
     if (M <= 16) return 0;
@@ -1604,7 +1589,7 @@ static patch_status q4_prefill(const uint16_t* X, int64_t M, const patch_packed4
     const int bm = kernel == kQ4Rows256 ? 256 : 128;
     const int tiles_n = (int)((P->N + kP4BN - 1) / kP4BN), tiles_m = (int)((M + bm - 1) / bm);
     const int grid = ((tiles_n * tiles_m + 7) / 8) * 8;
-    const int lds_bytes = kernel == kQ4Groups ? kKgLds : 2 * bm * 128;
+    const int lds_bytes = 2 * bm * 128;
     auto launch = [&](auto whole, auto sliced) {
         if (split == 1) {
             hipLaunchKernelGGL(whole, dim3(grid), dim3(512), lds_bytes, s, X, M, P->N, P->K, P->d_payload, P->d_scales, P->d_table, P->Tk, tiles_n,
@@ -1616,11 +1601,8 @@ static patch_status q4_prefill(const uint16_t* X, int64_t M, const patch_packed4
         }
     };
     if (kernel == kQ4Groups) {
-        static const hipError_t granted[] = {q4_grant(prefill4_kgroups_kernel<128, false>), q4_grant(prefill4_kgroups_kernel<128, true>),
-                                             q4_grant(prefill4_kgroups_kernel<64, false>), q4_grant(prefill4_kgroups_kernel<64, true>)};
-        (void)granted;
-        if (P->tile == 128) launch(prefill4_kgroups_kernel<128, false>, prefill4_kgroups_kernel<128, true>);
-        else launch(prefill4_kgroups_kernel<64, false>, prefill4_kgroups_kernel<64, true>);
+        launch_prefill4_kgroups({X, M, P->N, P->K, P->tile, P->Tk, P->d_payload, P->d_scales, P->d_table, split == 1 ? Y : ws}, split, s);
+        if (split > 1) wr_reduce(ws, (size_t)M * (size_t)P->N / 4, split, Y, 0, s);
     } else if (P->tile == 128 && bm == 128) launch(prefill4_kernel<128, 128, false>, prefill4_kernel<128, 128, true>);
     else if (P->tile == 128) launch(prefill4_kernel<128, 256, false>, prefill4_kernel<128, 256, true>);
     else if (bm == 128) launch(prefill4_kernel<64, 128, false>, prefill4_kernel<64, 128, true>);

@@ -1,5 +1,5 @@
-// Prefill-shaped product from the 4-bit storage with K divided between two groups of wavefronts of a workgroup (included by quant4.hip, whose layout and
-// rounding it uses; Section 5.2 of the paper).
+// Prefill-shaped product from the 4-bit storage with K divided between two groups of wavefronts of a workgroup (layout and
+// rounding: quant4.hip; Section 5.2 of the paper).
 //
 // Workgroup = 256 features x 128 rows of X, 8 wavefronts.  Wavefronts 0 - 3 (group 0) own 64 features x all 128 rows each and take the even 64-column
 // K-steps, wavefronts 4 - 7 the same features and the odd ones; the two halves meet in LDS at the end (group 0's sum + group 1's: a fixed order).
@@ -13,14 +13,21 @@
 // 2048 cycles of that.  Measured and not taken: a unit as one branch-free statement per tile type (1.02 - 1.05 times as long), a barrier every two
 // units (1.07), 16-bit position loads that need no shift (1.02 - 1.03), operands converted in one piece between phases (1.2 - 1.3).  A wavefront lowers its
 // priority from phase to phase, so that of two that share a SIMD the one behind goes first (dense steps 4 % shorter).
-#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <type_traits>
+
+#include "epilogue.h"
+#include "layout.h"
+#include "prefill_parts.h"
+#include "quant4_layout.h"
 
 namespace patch {
 
 constexpr int kKgBN = 256, kKgBM = 128;
 constexpr int kKgStep = kKgBM * 128;       // X of one K-step: 128 rows x 64 columns, swizzled (xs_off)
 constexpr int kKgLds = 4 * 2 * kKgStep;    // 128 KB: four stages of two K-steps
-constexpr int64_t kKgMaxK = 1 << 24;       // lane offsets into the 128 rows of X have 32 bits
 
 typedef const __attribute__((address_space(1))) uint32_t* kg_g4_t;
 
@@ -342,6 +349,21 @@ __global__ __launch_bounds__(512) void prefill4_kgroups_kernel(const uint16_t* _
     } else {
         finish(acc[0][2], 0, 0, 2); finish(acc[0][3], 1, 0, 3); finish(acc[1][2], 2, 1, 2); finish(acc[1][3], 3, 1, 3);
     }
+}
+
+static hipError_t kg_grant(decltype(&prefill4_kgroups_kernel<128, false>) kernel) {   // more LDS than a launch gets without asking
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kKgLds);
+}
+
+void launch_prefill4_kgroups(const Q4Prefill& a, int split, hipStream_t stream) {
+    static const hipError_t granted[] = {kg_grant(prefill4_kgroups_kernel<128, false>), kg_grant(prefill4_kgroups_kernel<128, true>),
+                                         kg_grant(prefill4_kgroups_kernel<64, false>), kg_grant(prefill4_kgroups_kernel<64, true>)};
+    (void)granted;
+    const int tiles_n = (int)((a.N + kKgBN - 1) / kKgBN), tiles_m = (int)((a.M + kKgBM - 1) / kKgBM);
+    const auto kernel = split > 1 ? a.tile == 128 ? &prefill4_kgroups_kernel<128, true> : &prefill4_kgroups_kernel<64, true>
+                                  : a.tile == 128 ? &prefill4_kgroups_kernel<128, false> : &prefill4_kgroups_kernel<64, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((tiles_n * tiles_m + 7) / 8 * 8), (unsigned)split), dim3(512), kKgLds, stream, a.X, a.M, a.N, a.K, a.payload,
+                       a.scales, a.table, a.Tk, tiles_n, tiles_m, a.Y);
 }
 
 }  // namespace patch

@@ -6,7 +6,7 @@ import pytest
 from paper_2509_23410_amd import build
 
 
-@pytest.mark.parametrize("source,kernel,first,count", [("quant4.hip", "prefill4_kgroups_kernel", 161, 4), ("gemm_prefill_128.hip", "prefill_kernel_r128", 160, 4)])
+@pytest.mark.parametrize("source,kernel,first,count", [("quant4_kgroups.hip", "prefill4_kgroups_kernel", 161, 4), ("gemm_prefill_128.hip", "prefill_kernel_r128", 160, 4)])
 def test_named_registers_are_left_alone(tmp_path, source, kernel, first, count):
     """From the first asm statement that names them to the wait in front of the output stage, loads are in flight into registers v<first> and up
     and the statements hand values on in them: compiler-generated code may touch none of them, nor m0, may issue no vector memory instruction but
