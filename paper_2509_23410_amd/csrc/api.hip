@@ -972,7 +972,9 @@ static size_t workspace_need(int64_t M, const patch_packed* P, const patch_gemm_
     const int s = prefill_wreg_split(a, split_k);
     if (s > 1) return std::max(least, (size_t)s * (size_t)M * (size_t)P->N * sizeof(float));
     if (split_k != 0) return 0;
-    const LastRound last = prefill_wreg_tail(a);   // K slices for the part-filled last round only
+    least = std::max(least, prefill_wreg_tail_bytes(a));   // K slices for the part-filled last round only
+    if (slices_only) return least;
+    const LastRound last = prefill_wreg_tail(a);
     return std::max(least, last.slices > 1 ? (size_t)last.slices * (size_t)last.tail * 256 * 256 * sizeof(float) : (size_t)0);
 }
 

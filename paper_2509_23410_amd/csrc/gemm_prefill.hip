@@ -433,7 +433,7 @@ __global__ __launch_bounds__(512) void prefill_kernel_lds(const uint16_t* __rest
 
 // ------------------------------------------------------------------------------------------------------
 // Blocks of 256 features x BM rows with the weights straight into registers ("areg"): BM = 128 on both mask tiles (the
-// 128-row kernel of the default choice), BM = 256 on mask tile 64 (its 256-row kernel; variant 6).
+// 128-row kernel of the default choice where prefill_kernel_r128 does not take the launch; variant 5), BM = 256 on mask tile 64 (its 256-row kernel; variant 6).
 //
 // The LDS-staged kernel is bound by what a compute unit can fetch per K-step, and the global -> LDS path is the
 // slower way in (patch_probe_lds_fill).  Here only X goes that way (BM x 128 bytes per step, two LDS stages); a

@@ -1076,6 +1076,20 @@ LastRound prefill_wreg_tail(const GemmArgs& a) {
     return prefill_wreg_last_round((int)(((a.N + kWrBN - 1) / kWrBN) * ((a.M + kWrBM - 1) / kWrBM)), a);
 }
 
+// The workspace that the last round was given before prefill_kernel_r128 took part in it, by the estimate of that time: patch_gemm_static goes on
+// accepting and refusing by it, and a caller that asks for a size gets no smaller one.
+size_t prefill_wreg_tail_bytes(const GemmArgs& a) {
+    const int tiles = (int)(((a.N + kWrBN - 1) / kWrBN) * ((a.M + kWrBM - 1) / kWrBM)), t = tiles % a.n_cus;
+    if (tiles < a.n_cus || t == 0 || 2 * t > a.n_cus) return 0;
+    const int s = std::min({a.n_cus / t, 8, wr_longest(a)});
+    if (s < 2) return 0;
+    const size_t bytes = (size_t)t * (size_t)s * kWrBM * kWrBN * sizeof(float);
+    const double fill = (double)t / a.n_cus, fill_s = (double)t * s / a.n_cus, late = tiles / a.n_cus > 3 ? 0.4 : 1.0;
+    const double steps = (double)a.Tk * (a.tile / kStepCols);
+    const double gain_us = steps * late * (0.9 + 0.35 * fill - (0.9 + 0.35 * (fill_s < 1.0 ? fill_s : 1.0)) / s);
+    return gain_us <= 2.0 * (double)bytes / 3.0e6 + 8.0 ? 0 : bytes;
+}
+
 // One launch of the kernel of a.tile: tiles t0 .. t0 + cnt - 1 of the order, `slices` K slices each (MODE 1, 2).
 template <int MODE>
 static void wr_launch(const GemmArgs& a, const WeightSet& set, int tiles_m, int t0, int cnt, int slices, int ybf16, hipStream_t stream) {

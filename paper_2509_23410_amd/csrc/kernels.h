@@ -126,6 +126,7 @@ double pf_few_rows(const GemmArgs& a, int64_t N, int blocks, int split, bool row
 // needs a.ws with a slot of 256 x 256 floats per tile and slice), by prefill_kernel_r128 (`halves`: 128 rows a workgroup) or by the kernel of the rest.
 struct LastRound { int tail, slices; bool halves; };
 LastRound prefill_wreg_tail(const GemmArgs& a);
+size_t prefill_wreg_tail_bytes(const GemmArgs& a);   // see there
 LastRound prefill_wreg_last_round(int tiles, const GemmArgs& a);   // the same for a given tile count (sets of weights)
 void launch_prefill_wreg_rounds(const GemmArgs& a, const WeightSet& set, int tiles_m, const LastRound& r, hipStream_t stream);
 // Price of a prefill launch in us (prefill_r128_split has the formula and what it was fitted to)
