@@ -1525,8 +1525,9 @@ struct Q4PrefillPrice { int bm; double base, start, round, t0, t1, tile64, spars
 constexpr Q4PrefillPrice kQ4PrefillPrice[] = {{128, 4.6, 0.0, 0.0, 0.766, 0.076, 1.065, -0.30, 1.0}, {256, 6.1, 0.0, 0.0, 1.22, 0.142, 1.054, -0.387, 1.0},
                                               {128, 8.1, 1.5, 4.1, 0.489, 0.142, 1.023, -0.255, 0.91}};
 
-static int q4_prefill_split(int64_t M, const Q4Shape& d, Q4PrefillKernel* kernel) {
+static int q4_prefill_split(int64_t M, const Q4Shape& d, Q4PrefillKernel* kernel, int* tail) {
     *kernel = kQ4Rows128;
+    *tail = 0;
     if (M <= 16) return 0;
     const int kpt = d.tile / kStepCols, Tk = (int)(d.K / d.tile);
     const int64_t full = M / kQ4Rows;
@@ -1553,7 +1554,24 @@ static int q4_prefill_split(int64_t M, const Q4Shape& d, Q4PrefillKernel* kernel
     take(kQ4Rows128);
     take(kQ4Rows256);
     if (best >= passes_us) return 0;
-    if (d.K <= kKgMaxK) take(kQ4Groups);
+    if (d.K > kKgMaxK) return best_split;
+    take(kQ4Groups);
+    // ... and, with a workspace, the blocks beyond a multiple of the compute units in a launch of their own, K in slices that fill the chip at most once and are
+    // summed by a third: up to four full rounds, up to half a round left, 4 % and 4 us below.  60 launches of 7 weights at 640 - 4200 rows: 0.908 of the
+    // best undivided launch over all, none slower; us, undivided -> so: 11008 x 4096, f = 1/2, 800 rows (301 blocks) 94.1 -> 83.4, 1536 rows (516) 144.3 -> 131.6;
+    // 4096 x 11008, 2100 rows (272) 223.8 -> 166.5; half a round left gains least (4096 x 4096, 3000 rows, 384 blocks 92.5 and 96.5: not taken).
+    const Q4PrefillPrice& p = kQ4PrefillPrice[kQ4Groups];
+    const int64_t blocks = ((d.N + kP4BN - 1) / kP4BN) * ((M + p.bm - 1) / p.bm), whole = blocks / d.n_cus, t = blocks % d.n_cus;
+    if (whole < 1 || whole > 4 || t == 0 || 2 * t > d.n_cus) return best_split;
+    const double step = (d.tile == 64 ? p.tile64 : 1.0) * (1.0 + p.sparse * (d.f - 0.5));
+    for (int sp = 2; sp <= 8 && sp * t <= d.n_cus && sp * 512 <= d.K && (size_t)sp * (size_t)t * kKgSlotBytes <= d.ws_bytes; ++sp) {
+        const double fill = (double)(sp * t) / d.n_cus;
+        const int steps = (((Tk + sp - 1) / sp) * kpt + 1) / 2 * 2;
+        const double body = p.base + p.start + p.round * (double)(whole - 1) + (double)(whole * Tk * kpt) * (p.t0 + p.t1) * step;
+        const double last = p.base + p.start * fill + (double)steps * (p.t0 + p.t1 * fill) * step + p.second * (3.0 + (2.0 * sp + 1.0) * (double)t * (double)kKgSlotBytes / 8.3e6);
+        const double us = 1.04 * (body + last) + 4.0;
+        if (us < best) { best = us; best_split = sp; *kernel = kQ4Groups; *tail = (int)t; }
+    }
     return best_split;
 }
 
@@ -1569,9 +1587,10 @@ int patch_test_schedule4(int64_t M, int count, const int64_t* N, int64_t K, int 
     }
     if (count == 1 && ws_bytes >= 2 * (size_t)M * (size_t)d.N * sizeof(float)) d.ws_bytes = ws_bytes;
     Q4PrefillKernel which;
-    if (const int split = count == 1 ? q4_prefill_split(M, d, &which) : 0) {
+    int tail;
+    if (const int split = count == 1 ? q4_prefill_split(M, d, &which, &tail) : 0) {
         kernel[0] = 2 + which;
-        chunks[0] = split;
+        chunks[0] = tail ? 1 : split;
         return 1;
     }
     if (M > 8 * kQ4Rows) return -1;
@@ -1584,8 +1603,8 @@ int patch_test_schedule4(int64_t M, int count, const int64_t* N, int64_t K, int 
     return n;
 }
 
-// One prefill-shaped launch; split > 1: K slices, partial sums in ws (split x M x N floats).
-static patch_status q4_prefill(const uint16_t* X, int64_t M, const patch_packed4* P, float* Y, int split, Q4PrefillKernel kernel, float* ws, hipStream_t s) {
+// One prefill-shaped launch; split > 1: K slices, partial sums in ws (split x M x N floats); tail > 0: of the last blocks alone (launch_prefill4_kgroups).
+static patch_status q4_prefill(const uint16_t* X, int64_t M, const patch_packed4* P, float* Y, int split, Q4PrefillKernel kernel, int tail, float* ws, hipStream_t s) {
     const int bm = kernel == kQ4Rows256 ? 256 : 128;
     const int tiles_n = (int)((P->N + kP4BN - 1) / kP4BN), tiles_m = (int)((M + bm - 1) / bm);
     const int grid = ((tiles_n * tiles_m + 7) / 8) * 8;
@@ -1601,8 +1620,8 @@ static patch_status q4_prefill(const uint16_t* X, int64_t M, const patch_packed4
         }
     };
     if (kernel == kQ4Groups) {
-        launch_prefill4_kgroups({X, M, P->N, P->K, P->tile, P->Tk, P->d_payload, P->d_scales, P->d_table, split == 1 ? Y : ws}, split, s);
-        if (split > 1) wr_reduce(ws, (size_t)M * (size_t)P->N / 4, split, Y, 0, s);
+        launch_prefill4_kgroups({X, M, P->N, P->K, P->tile, P->Tk, P->d_payload, P->d_scales, P->d_table, Y}, split, tail, ws, s);
+        if (split > 1 && tail == 0) wr_reduce(ws, (size_t)M * (size_t)P->N / 4, split, Y, 0, s);
     } else if (P->tile == 128 && bm == 128) launch(prefill4_kernel<128, 128, false>, prefill4_kernel<128, 128, true>);
     else if (P->tile == 128) launch(prefill4_kernel<128, 256, false>, prefill4_kernel<128, 256, true>);
     else if (bm == 128) launch(prefill4_kernel<64, 128, false>, prefill4_kernel<64, 128, true>);
@@ -1621,16 +1640,17 @@ patch_status patch_gemm4_ex(const void* X, int64_t M, const patch_packed4* P, vo
     float* const part = ws ? static_cast<float*>(workspace) : nullptr;
     const size_t part_bytes = ws ? workspace_bytes : 0;
     Q4PrefillKernel kernel;
-    const int split = q4_prefill_split(M, q4_shape(&P, 1, part_bytes), &kernel);
+    int tail;
+    const int split = q4_prefill_split(M, q4_shape(&P, 1, part_bytes), &kernel, &tail);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (split == 0) return q4_passes(X, M, &P, &Y, 1, part, part_bytes, s);
-    return q4_prefill(static_cast<const uint16_t*>(X), M, P, static_cast<float*>(Y), split, kernel, part, s);
+    return q4_prefill(static_cast<const uint16_t*>(X), M, P, static_cast<float*>(Y), split, kernel, tail, part, s);
 }
 
 // Test hook (kernels.h)
 int patch_test_gemm4(const void* X, int64_t M, const patch_packed4* const* P, void* const* Y, int count, int kernel, int chunks,
                               void* workspace, size_t workspace_bytes, void* stream) {
-    if (!X || !P || !Y || M < 1 || count < 1 || count > kMaxMany || kernel < 0 || kernel > 4 || !q4_aligned16(X)) return PATCH_ERR_ARG;
+    if (!X || !P || !Y || M < 1 || count < 1 || count > kMaxMany || kernel < 0 || kernel > 5 || !q4_aligned16(X)) return PATCH_ERR_ARG;
     for (int i = 0; i < count; ++i) {
         if (!P[i] || !Y[i] || !q4_aligned16(Y[i])) return PATCH_ERR_ARG;
         if (P[i]->K != P[0]->K || P[i]->tile != P[0]->tile) return PATCH_ERR_SHAPE;
@@ -1638,12 +1658,18 @@ int patch_test_gemm4(const void* X, int64_t M, const patch_packed4* const* P, vo
     const int longest = kernel == 1 ? (int)((P[0]->K + kBtUnit - 1) / kBtUnit) : kernel == 0 ? 1 : P[0]->Tk;
     const int64_t rows = kernel == 1 && M > kQ4Rows ? kQ4Rows : M;
     if (chunks < 1 || chunks > longest || (count > 1 && (chunks > 1 || kernel > 1))) return PATCH_ERR_ARG;
+    const int64_t blocks = ((P[0]->N + 255) / 256) * ((M + 127) / 128);
+    const int tail = kernel == 5 ? (int)(blocks % P[0]->n_cus) : 0;
+    if (kernel == 5) {
+        if (chunks < 2 || blocks < P[0]->n_cus || tail == 0) return PATCH_ERR_ARG;
+        if (!workspace || !q4_aligned16(workspace) || workspace_bytes < (size_t)chunks * (size_t)tail * kKgSlotBytes) return PATCH_ERR_SIZE;
+    } else
     if (chunks > 1 && (!workspace || !q4_aligned16(workspace) || workspace_bytes < (size_t)chunks * (size_t)rows * (size_t)P[0]->N * sizeof(float)))
         return PATCH_ERR_SIZE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (kernel == 4 && P[0]->K > kKgMaxK) return PATCH_ERR_SHAPE;
+    if (kernel >= 4 && P[0]->K > kKgMaxK) return PATCH_ERR_SHAPE;
     if (kernel > 1)
-        return q4_prefill(static_cast<const uint16_t*>(X), M, P[0], static_cast<float*>(Y[0]), chunks, (Q4PrefillKernel)(kernel - 2), static_cast<float*>(workspace), s);
+        return q4_prefill(static_cast<const uint16_t*>(X), M, P[0], static_cast<float*>(Y[0]), chunks, kernel == 5 ? kQ4Groups : (Q4PrefillKernel)(kernel - 2), tail, static_cast<float*>(workspace), s);
     const Q4Plan plan = {kernel == 1, chunks, 0.0};
     return q4_passes(X, M, P, Y, count, static_cast<float*>(workspace), workspace_bytes, s, &plan);
 }

@@ -22,6 +22,7 @@
 #include "layout.h"
 #include "prefill_parts.h"
 #include "quant4_layout.h"
+#include "tile_order.h"
 
 namespace patch {
 
@@ -178,38 +179,25 @@ __device__ __forceinline__ void kg_fetch(uint32_t r0, uint32_t r1) {
 template <int TILE, bool SPLIT>
 __global__ __launch_bounds__(512) void prefill4_kgroups_kernel(const uint16_t* __restrict__ X, int64_t M, int64_t N, int64_t K,
                                                                const uint8_t* __restrict__ payload, const uint16_t* __restrict__ scales,
-                                                               const uint32_t* __restrict__ table, int Tk_all, int tiles_n, int tiles_m,
-                                                               float* __restrict__ Y) {
+                                                               const uint32_t* __restrict__ table, int Tk_all, int tiles_n, int tiles_m, int t0,
+                                                               int cnt, int slots, float* __restrict__ Y) {
     constexpr int KPT = TILE / kStepCols;      // K-steps per tile: 2 or 1
     extern __shared__ __attribute__((aligned(256))) uint8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = w >> 2, fw = w & 3;                                        // K group, 64-feature group
     const int tr = TILE == 128 ? fw >> 1 : fw, sh = TILE == 128 ? fw & 1 : 0;   // tile row of the block, half of the tile
-    // block -> (n, m): one contiguous run of the grouped order (4 row blocks x all feature blocks) per XCD
-    const int nblk = tiles_n * tiles_m;
+    // blocks t0 .. t0 + cnt - 1 of the order, one contiguous run of it per XCD
     int bid = blockIdx.x;
     {
-        const int per = (nblk + 7) / 8;
+        const int per = (cnt + 7) / 8;
         const int x = bid & 7, i = bid >> 3;
         const int t = x * per + i;
-        bid = (i < per && t < nblk) ? t : -1;
+        bid = (i < per && t < cnt) ? t : -1;
     }
     if (bid < 0) return;
     int bn, bm;
-    {
-        constexpr int GM = 4;
-        const int full = (tiles_m / GM) * GM * tiles_n;
-        if (bid < full) {
-            const int gi = bid / (GM * tiles_n), rem = bid % (GM * tiles_n);
-            bn = rem / GM;
-            bm = gi * GM + rem % GM;
-        } else {
-            const int gm = tiles_m % GM, rem = bid - full;
-            bn = rem / gm;
-            bm = (tiles_m / GM) * GM + rem % gm;
-        }
-    }
+    tile_of(t0 + bid, tiles_n, tiles_m, bn, bm);
     const int64_t n0 = (int64_t)bn * kKgBN, m0 = (int64_t)bm * kKgBM;
     // N is a multiple of the tile, not necessarily of 256: a wavefront of a missing tile row works on the last live one's
     // weights (valid addresses) and stores nothing
@@ -334,9 +322,10 @@ __global__ __launch_bounds__(512) void prefill4_kgroups_kernel(const uint16_t* _
 #pragma unroll
             for (int i = 0; i < 4; ++i) v[4 * r + i] += o[i];
         }
-        if (tr < rows_here)
-            store_block_rows(mine + k * 4096, v, lane, Y, (SPLIT ? (int64_t)blockIdx.y * M * N : 0) + (m0 + 32 * b) * N + n0 + 64 * fw + 32 * a, N,
-                             M - (m0 + 32 * b), 0);
+        // to Y, to a part of the workspace per slice, or to a slot of 128 x 256 floats per block and slice
+        const int64_t stride = SPLIT && slots ? kKgBN : N;
+        const int64_t at = SPLIT && slots ? ((int64_t)bid * gridDim.y + blockIdx.y) * (kKgBM * kKgBN) : (SPLIT ? (int64_t)blockIdx.y * M * N : 0) + m0 * N + n0;
+        if (tr < rows_here) store_block_rows(mine + k * 4096, v, lane, Y, at + 32 * b * stride + 64 * fw + 32 * a, stride, M - (m0 + 32 * b), 0);
     };
     if (g == 0) {
         put(0, acc[0][2]); put(1, acc[0][3]); put(2, acc[1][2]); put(3, acc[1][3]);
@@ -355,15 +344,44 @@ static hipError_t kg_grant(decltype(&prefill4_kgroups_kernel<128, false>) kernel
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kKgLds);
 }
 
-void launch_prefill4_kgroups(const Q4Prefill& a, int split, hipStream_t stream) {
+// Sum of the slots of the last `cnt` blocks (slice 0 first) into Y.  Workgroup = 16 rows of a block; thread = 4 x 4 features of one row.
+__global__ __launch_bounds__(256) void kgroups_last_round_kernel(const float* __restrict__ ws, int slices, int t0, int tiles_n, int tiles_m, int64_t M, int64_t N,
+                                                                 float* __restrict__ Y) {
+    const int j = blockIdx.x >> 3, r = 16 * (blockIdx.x & 7) + (threadIdx.x >> 4);
+    int bn, bm;
+    tile_of(t0 + j, tiles_n, tiles_m, bn, bm);
+    const int64_t m = (int64_t)bm * kKgBM + r;
+    if (m >= M) return;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int f = (threadIdx.x & 15) * 4 + 64 * u;
+        const int64_t n = (int64_t)bn * kKgBN + f;
+        if (n >= N) continue;
+        const float* src = ws + (int64_t)j * slices * (kKgBM * kKgBN) + r * kKgBN + f;
+        f32x4 sum = *reinterpret_cast<const f32x4*>(src);
+        for (int y = 1; y < slices; ++y) sum += *reinterpret_cast<const f32x4*>(src + (int64_t)y * (kKgBM * kKgBN));
+        *reinterpret_cast<f32x4*>(Y + m * N + n) = sum;
+    }
+}
+
+void launch_prefill4_kgroups(const Q4Prefill& a, int split, int tail, float* ws, hipStream_t stream) {
     static const hipError_t granted[] = {kg_grant(prefill4_kgroups_kernel<128, false>), kg_grant(prefill4_kgroups_kernel<128, true>),
                                          kg_grant(prefill4_kgroups_kernel<64, false>), kg_grant(prefill4_kgroups_kernel<64, true>)};
     (void)granted;
-    const int tiles_n = (int)((a.N + kKgBN - 1) / kKgBN), tiles_m = (int)((a.M + kKgBM - 1) / kKgBM);
-    const auto kernel = split > 1 ? a.tile == 128 ? &prefill4_kgroups_kernel<128, true> : &prefill4_kgroups_kernel<64, true>
-                                  : a.tile == 128 ? &prefill4_kgroups_kernel<128, false> : &prefill4_kgroups_kernel<64, false>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((tiles_n * tiles_m + 7) / 8 * 8), (unsigned)split), dim3(512), kKgLds, stream, a.X, a.M, a.N, a.K, a.payload,
-                       a.scales, a.table, a.Tk, tiles_n, tiles_m, a.Y);
+    const int tiles_n = (int)((a.N + kKgBN - 1) / kKgBN), tiles_m = (int)((a.M + kKgBM - 1) / kKgBM), nblk = tiles_n * tiles_m;
+    const auto launch = [&](int t0, int cnt, int slices, int slots, float* Y) {
+        const auto kernel = slices > 1 ? a.tile == 128 ? &prefill4_kgroups_kernel<128, true> : &prefill4_kgroups_kernel<64, true>
+                                       : a.tile == 128 ? &prefill4_kgroups_kernel<128, false> : &prefill4_kgroups_kernel<64, false>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((cnt + 7) / 8 * 8), (unsigned)slices), dim3(512), kKgLds, stream, a.X, a.M, a.N, a.K, a.payload, a.scales,
+                           a.table, a.Tk, tiles_n, tiles_m, t0, cnt, slots, Y);
+    };
+    if (tail == 0) {
+        launch(0, nblk, split, 0, split > 1 ? ws : a.Y);
+        return;
+    }
+    launch(0, nblk - tail, 1, 0, a.Y);
+    launch(nblk - tail, tail, split, 1, ws);
+    hipLaunchKernelGGL(kgroups_last_round_kernel, dim3((unsigned)(8 * tail)), dim3(256), 0, stream, ws, split, nblk - tail, tiles_n, tiles_m, a.M, a.N, a.Y);
 }
 
 }  // namespace patch

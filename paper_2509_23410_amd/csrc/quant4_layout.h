@@ -24,8 +24,11 @@ struct Q4Prefill {
     const uint8_t* payload;
     const uint16_t* scales;
     const uint32_t* table;
-    float* Y;   // split > 1: room for split x M x N
+    float* Y;
 };
-void launch_prefill4_kgroups(const Q4Prefill& a, int split, hipStream_t stream);
+constexpr size_t kKgSlotBytes = 128 * 256 * sizeof(float);
+// tail = 0: the whole product in `split` K slices, more than one to ws (split x M x N floats, to be summed).  tail > 0: all blocks of 256 features x 128 rows but the
+// last `tail` whole, those in `split` (at least two) slices over slots of kKgSlotBytes each at ws, and their sum.
+void launch_prefill4_kgroups(const Q4Prefill& a, int split, int tail, float* ws, hipStream_t stream);
 
 }  // namespace patch

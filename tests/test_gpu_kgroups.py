@@ -45,3 +45,34 @@ def test_two_k_groups(tile, N, K, f):
                 assert first is None or torch.equal(Y, first), "launches of one configuration must be bit-equal"
                 first = Y.clone()
     P.close()
+
+
+@pytest.mark.parametrize("tile,N,K", [(128, 384, 512), (128, 128, 896), (64, 320, 192), (64, 192, 832)])
+def test_last_round_in_slices(tile, N, K):
+    """The blocks beyond 256 of a launch in K slices over slots of the workspace: part-filled last rows, a feature block that lacks tile rows."""
+    vp = ctypes.c_void_p
+    c = synth.make_case("kgroups", N, K, 1, tile, 0.5, seed=7)
+    Wd = torch.from_numpy(c.W.view(np.int16)).cuda().view(torch.bfloat16)
+    stream = torch.cuda.current_stream().cuda_stream
+    B.patch_apply_mask(Wd, torch.from_numpy(c.mask24).cuda(), c.tile_map, N, K, tile, Wd, stream)
+    P = B.patch_pack4(Wd, N, K, c.tile_map, tile, stream)
+    B.patch_unpack4(P, W_deq=Wd, stream=stream)
+    W, units = Wd.double(), -(-N // 256)
+    M = 128 * -(-259 // units) - 40
+    tail = units * -(-M // 128) - 256
+    X = torch.randn(M, K, device="cuda", generator=torch.Generator(device="cuda").manual_seed(M)).to(torch.bfloat16)
+    ref, bound = X.double() @ W.T, 2 * K ** 0.5 * 2.0 ** -24 * X.double().norm(dim=1)[:, None] * W.norm(dim=1)[None, :]
+    for chunks in (2, 3, min(7, K // tile)):
+        print(f"kgroups last round tile={tile} N={N} K={K} M={M} tail={tail} chunks={chunks}", flush=True)
+        buf = torch.full((M * N + 2048,), 7.0, device="cuda")
+        Y = buf[1024:1024 + M * N].view(M, N)
+        Y.fill_(float("nan"))
+        ws = torch.full((chunks * tail * 32768 + 1024,), float("nan"), device="cuda")
+        ws[chunks * tail * 32768:] = 7.0
+        st = B.lib().patch_test_gemm4(vp(X.data_ptr()), ctypes.c_int64(M), (vp * 1)(P.handle), (vp * 1)(Y.data_ptr()), 1, 5, chunks, vp(ws.data_ptr()),
+                                      ctypes.c_size_t(4 * chunks * tail * 32768), vp(stream))
+        assert st == B.OK, st
+        assert ((Y.double() - ref).abs() / bound).max().item() <= 1.0
+        assert bool((buf[:1024] == 7.0).all()) and bool((buf[1024 + M * N:] == 7.0).all()), "wrote outside Y"
+        assert bool((ws[chunks * tail * 32768:] == 7.0).all()), "wrote behind the workspace"
+    P.close()
