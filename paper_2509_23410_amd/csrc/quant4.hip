@@ -1150,7 +1150,7 @@ struct patch_packed4 {
     int64_t n_sparse = 0;
     size_t algorithmic_bytes = 0;   // codes + positions + scales, without alignment padding
     size_t payload_bytes = 0;
-    // one allocation: payload | status word of the 2:4 check | table | scales
+    // one allocation: payload | table | scales
     uint8_t* d_payload = nullptr;   // codes and positions
     uint32_t* d_table = nullptr;
     uint16_t* d_scales = nullptr;   // N x Tk bf16, strip-major
