@@ -763,7 +763,8 @@ double prefill_estimate(const GemmArgs& a) {
 //     us = base + begin fill + rounds x K-steps per workgroup x (t0 + t1 fill) x g(f) + (split > 1 ? second + (2 split + 1) M N 4 B / rate : 0)
 // (prices below; rms error 6 % for blocks of 128 rows, 7 % for 256).  A second workgroup on a compute unit gains little - the matrix cores and the
 // path from the L2 are shared: 11008 x 4096, f = 1/2, 172 / 344 workgroups 55 / 95 us, where 256-row blocks take 73 - so that the blocks, times the
-// slices, must not be more than the compute units.  Split: at most 8 slices of at least 512 columns that the workspace holds.  Taken where the price is
+// slices, must not be more than the compute units of any die (the launch deals the blocks out in eight equal runs, a die each: 84 blocks x 3 slices, 33
+// workgroups on seven dies of 32 compute units and 21 on the eighth, took 72.9 us, 3072 x 8192, f = 0, 805 rows, where the 256-row kernel takes 53.7).  Split: at most 8 slices of at least 512 columns that the workspace holds.  Taken where the price is
 // at least 3 % below: with a workspace 279 of 618 launches, 0.96 of the earlier time over all of them and 0.95 over those of 20 us and more
 // (4096 x 4096, f = 1/2, 2048 rows 57.7 -> 53.7 us; 15360 x 5120, 200 rows 58.1 -> 45.7; 5120 x 5120, 512 rows 43.6 -> 38.0), without one 381, 0.90 and
 // 0.87 (4096 x 4096, 512 rows 49.9 -> 45.9; 11008 x 4096, 512 rows 65.2 -> 54.9); at worst 4.5 % behind (4096 x 4096, f = 0, 512 rows 31.8 -> 33.2).
@@ -788,7 +789,7 @@ int prefill_r128_split(const GemmArgs& a, const int64_t* N, int count) {
     const size_t per_slice = (size_t)a.M * (size_t)total * sizeof(float);
     double best = 0.0;
     int split = 1;
-    for (int s = 1; s <= 8 && (s == 1 || (b128 * s <= a.n_cus && (int64_t)s * 512 <= a.K && a.ws && a.ws_bytes / per_slice >= (size_t)s)); ++s) {
+    for (int s = 1; s <= 8 && (s == 1 || ((b128 + 7) / 8 * 8 * s <= a.n_cus && (int64_t)s * 512 <= a.K && a.ws && a.ws_bytes / per_slice >= (size_t)s)); ++s) {
         const double us = pf_price(kPriceR128, a, total, b128, s);
         if (s == 1 || us < best) { best = us; split = s; }
     }

@@ -21,6 +21,14 @@ def test_choice_is_no_slower_than_what_was_measured(N, K, tile, f, M, workspace,
     assert (us[s] if s else other) <= 1.05 * min([other] + [t for i, t in us.items() if workspace or i == 1])
 
 
+@pytest.mark.parametrize("N,K,tile,f,M", [(3072, 8192, 128, 0.0, 805), (3072, 8192, 64, 1.0, 813), (896, 4864, 128, 0.5, 1073), (3584, 3584, 128, 0.0, 321), (1536, 8960, 128, 0.5, 702)])
+def test_no_die_gets_more_slices_than_compute_units(N, K, tile, f, M):
+    """The blocks go to eight dies of 32 compute units in runs of equal length, a slice of each block with it: the longest run counts, not the mean."""
+    blocks = -(-N // 256) * -(-M // 128)
+    s = _split(M, [N], K, tile, f, 384 << 20)
+    assert s < 2 or -(-blocks // 8) * s <= 32
+
+
 def test_limits_of_the_choice():
     """One round of the chip; slices of at least 512 columns, at most 8, that the workspace holds; a set counts as one launch."""
     taken = set()
