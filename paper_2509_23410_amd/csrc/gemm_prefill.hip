@@ -761,17 +761,23 @@ double prefill_estimate(const GemmArgs& a) {
 // One round of prefill_kernel_r128, or what the launch took without it?  Priced by launches of 100 .. 4096 rows of 13 weights at f = 0, 1/2 and 1, both
 // mask tiles, with and without a workspace (4718 timings):
 //     us = base + begin fill + rounds x K-steps per workgroup x (t0 + t1 fill) x g(f) + (split > 1 ? second + (2 split + 1) M N 4 B / rate : 0)
-// (prices below; rms error 6 % for blocks of 128 rows, 7 % for 256).  A second workgroup on a compute unit gains little - the matrix cores and the
+// (prices below; rms error 6 % for blocks of 128 rows, 7 % for 256; rounds = those of the die that gets most).  A second workgroup on a compute unit gains little - the matrix cores and the
 // path from the L2 are shared: 11008 x 4096, f = 1/2, 172 / 344 workgroups 55 / 95 us, where 256-row blocks take 73 - so that the blocks, times the
 // slices, must not be more than the compute units of any die (the launch deals the blocks out in eight equal runs, a die each: 84 blocks x 3 slices, 33
-// workgroups on seven dies of 32 compute units and 21 on the eighth, took 72.9 us, 3072 x 8192, f = 0, 805 rows, where the 256-row kernel takes 53.7).  Split: at most 8 slices of at least 512 columns that the workspace holds.  Taken where the price is
-// at least 3 % below: with a workspace 279 of 618 launches, 0.96 of the earlier time over all of them and 0.95 over those of 20 us and more
-// (4096 x 4096, f = 1/2, 2048 rows 57.7 -> 53.7 us; 15360 x 5120, 200 rows 58.1 -> 45.7; 5120 x 5120, 512 rows 43.6 -> 38.0), without one 381, 0.90 and
-// 0.87 (4096 x 4096, 512 rows 49.9 -> 45.9; 11008 x 4096, 512 rows 65.2 -> 54.9); at worst 4.5 % behind (4096 x 4096, f = 0, 512 rows 31.8 -> 33.2).
-// The best choice of each would be 0.95 and 0.90.  Whether the decode path's passes run instead is decided by the prices above, as if this kernel
-// did not exist.
+// workgroups on seven dies of 32 compute units and 21 on the eighth, took 72.9 us, 3072 x 8192, f = 0, 805 rows, where the 256-row kernel takes 53.7).
+// Split: at most 8 slices of at least 512 columns that the workspace holds.
+// Taken where the price is 3 % below; in slices against a launch without them 3 % and 1.5 us (1280 x 1280, f = 1/2, 1003 rows 20.0 us in two slices, 19.1
+// unsplit by prefill_kernel_areg); unsplit 3 % and 0.6 us (calls of 15 - 18 us are dearer than priced: 1024 x 1024, f = 1/2, 2960 rows 17.8 us, 17.2
+// without), against a launch in s slices 6 s % and 0.6 us (the price of long unsplit workgroups is low on a full chip: 3072 x 8192, f = 0.7, mask tile
+// 64, 2231 rows 92.3 us, in two slices by the 256-row kernel 85.9).  Held against the launches without this kernel, timed in turn: 10 hidden sizes of
+// 896 - 5120 with their weights and sets, 80 - 4096 rows, both mask tiles, f from 0 to 1: with a workspace 1217 of 1919 taken, 0.903 of the time over
+// all of them, the worst 1.011; without one 1582 of 1763, 0.840, none slower (4096 x 4096, f = 1/2, 2048 rows 57.7 -> 53.7 us; 5120 x 5120, 512 rows
+// 43.6 -> 38.0; without a workspace 11008 x 4096, 512 rows 65.2 -> 54.9).  The best choice of each would be 0.896 and 0.838.  Of 2772
+// launches of 8 hidden sizes that the rule was not fitted to 7 were more than 1 % slower, the worst 1.022.  Beyond the limits of the
+// register-weight kernels the other side is pf_estimate, which knows no f: 70 of these launches, 3584 x 18944, 0.81 and 0.78, none slower.  Whether the
+// decode path's passes run instead is decided by the prices above, as if this kernel did not exist.
 double pf_price(const PrefillPrice& p, const GemmArgs& a, int64_t N, int64_t blocks, int split) {
-    const int64_t wgs = blocks * split, rounds = (wgs + a.n_cus - 1) / a.n_cus, steps = (int64_t)((a.Tk + split - 1) / split) * (a.tile / kStepCols);
+    const int64_t wgs = blocks * split, die = a.n_cus / 8, rounds = ((blocks + 7) / 8 * split + die - 1) / die, steps = (int64_t)((a.Tk + split - 1) / split) * (a.tile / kStepCols);
     const double fill = wgs < a.n_cus ? (double)wgs / a.n_cus : 1.0, f = 0.01 * a.sparse_pct, y = (double)a.M * (double)N * 4.0;
     return p.base + p.begin * fill + (double)rounds * (double)steps * (p.t0 + p.t1 * fill) * (1.0 - p.g1 * f - p.g2 * f * f) +
            (split > 1 ? p.second + (2.0 * split + 1.0) * y / p.rate : 0.0);
@@ -793,12 +799,18 @@ int prefill_r128_split(const GemmArgs& a, const int64_t* N, int count) {
         const double us = pf_price(kPriceR128, a, total, b128, s);
         if (s == 1 || us < best) { best = us; split = s; }
     }
-    int split128 = 1;
+    int other_split = 1;
     double other;
-    if (count == 1 && prefill_prefers_128_rows(a, &split128)) other = pf_price(kPriceAreg128, a, total, b128, split128);
-    else if (prefill_wreg_supports(a)) other = pf_price(kPriceWreg, a, total, b256, count == 1 ? prefill_wreg_split(a, 0) : prefill_wreg_set_split(a, b256, total));
-    else other = pf_estimate(a, b256, prefill_lds_split(a, 0, 256), 1.26, 0.33);
-    return 1.03 * best < other ? split : 0;
+    if (count == 1 && prefill_prefers_128_rows(a, &other_split)) other = pf_price(kPriceAreg128, a, total, b128, other_split);
+    else if (prefill_wreg_supports(a)) {
+        other_split = count == 1 ? prefill_wreg_split(a, 0) : prefill_wreg_set_split(a, b256, total);
+        other = pf_price(kPriceWreg, a, total, b256, other_split);
+    } else {
+        other_split = prefill_lds_split(a, 0, 256);
+        other = pf_estimate(a, b256, other_split, 1.26, 0.33);
+    }
+    if (split > 1) return 1.03 * best + (other_split == 1 ? 1.5 : 0.0) < other ? split : 0;
+    return (other_split > 1 ? 1.0 + 0.06 * other_split : 1.03) * best + 0.6 < other ? 1 : 0;
 }
 
 // Kernel choice.  variant 0 (default): prefill_kernel_r128 where prefill_r128_split says so, prefill_kernel_areg with blocks of 128 rows where
