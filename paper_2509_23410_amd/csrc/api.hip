@@ -585,17 +585,34 @@ int patch_test_schedule_deals(int64_t M, int count, const int64_t* N, int64_t K,
     return n;
 }
 
-int patch_test_prefill128_split(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes) {
-    if (!N || M < 1 || count < 1 || count > kMaxMany || sparse_pct < 0 || sparse_pct > 100) return -1;
+// a prefill-path launch as patch_test_schedule describes it; false = bad arguments
+static bool test_prefill_args(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, GemmArgs* a) {
+    if (!N || M < 1 || count < 1 || count > kMaxMany || sparse_pct < 0 || sparse_pct > 100) return false;
     for (int i = 0; i < count; ++i)
-        if (check_shape(N[i], K, tile) != PATCH_OK) return -1;
-    GemmArgs a = {};
-    a.M = M; a.N = N[0]; a.K = K;
-    a.tile = tile; a.Tk = (int)(K / tile);
-    a.n_cus = 256;
-    a.sparse_pct = sparse_pct;
-    if (ws_bytes) { a.ws = reinterpret_cast<float*>(16); a.ws_bytes = ws_bytes; }
-    return prefill_r128_split(a, N, count);
+        if (check_shape(N[i], K, tile) != PATCH_OK) return false;
+    *a = {};
+    a->M = M; a->N = N[0]; a->K = K;
+    a->tile = tile; a->Tk = (int)(K / tile);
+    a->n_cus = 256;
+    a->sparse_pct = sparse_pct;
+    if (ws_bytes) { a->ws = reinterpret_cast<float*>(16); a->ws_bytes = ws_bytes; }
+    return true;
+}
+
+int patch_test_prefill128_split(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes) {
+    GemmArgs a;
+    return test_prefill_args(M, count, N, K, tile, sparse_pct, ws_bytes, &a) ? prefill_r128_split(a, N, count) : -1;
+}
+
+int patch_test_last_round(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* slices, int* halves) {
+    GemmArgs a;
+    if (!slices || !halves || !test_prefill_args(M, count, N, K, tile, sparse_pct, ws_bytes, &a) || !prefill_wreg_supports(a)) return -1;
+    int64_t tiles = 0;
+    for (int i = 0; i < count; ++i) tiles += (N[i] + 255) / 256 * ((M + 255) / 256);
+    const LastRound r = prefill_wreg_last_round((int)tiles, a);
+    *slices = r.slices;
+    *halves = r.halves;
+    return r.tail;
 }
 
 // the set of a test hook's weights, by blocks of 256 features; false = bad arguments

@@ -777,7 +777,7 @@ double prefill_estimate(const GemmArgs& a) {
 // register-weight kernels the other side is pf_estimate, which knows no f: 70 of these launches, 3584 x 18944, 0.81 and 0.78, none slower.  Whether the
 // decode path's passes run instead is decided by the prices above, as if this kernel did not exist.
 double pf_price(const PrefillPrice& p, const GemmArgs& a, int64_t N, int64_t blocks, int split) {
-    const int64_t wgs = blocks * split, die = a.n_cus / 8, rounds = ((blocks + 7) / 8 * split + die - 1) / die, steps = (int64_t)((a.Tk + split - 1) / split) * (a.tile / kStepCols);
+    const int64_t wgs = blocks * split, die = a.n_cus < 8 ? 1 : a.n_cus / 8, rounds = ((blocks + 7) / 8 * split + die - 1) / die, steps = (int64_t)((a.Tk + split - 1) / split) * (a.tile / kStepCols);
     const double fill = wgs < a.n_cus ? (double)wgs / a.n_cus : 1.0, f = 0.01 * a.sparse_pct, y = (double)a.M * (double)N * 4.0;
     return p.base + p.begin * fill + (double)rounds * (double)steps * (p.t0 + p.t1 * fill) * (1.0 - p.g1 * f - p.g2 * f * f) +
            (split > 1 ? p.second + (2.0 * split + 1.0) * y / p.rate : 0.0);

@@ -1043,32 +1043,49 @@ int prefill_wreg_split(const GemmArgs& a, int requested) {
     return s < 2 ? 1 : s;
 }
 
+// Slices of 256 rows for the last round by what they save alone: its K-steps, 0.9 - 1.25 us each by how full the chip is (a part of that behind more than three
+// full rounds), against the partial tiles' way through memory (3 TB/s) and two more launches.  1 = none.
+static int wr_tail_slices(int tiles, const GemmArgs& a, size_t slots) {
+    const int t = tiles % a.n_cus;
+    if (tiles < a.n_cus || t == 0 || 2 * t > a.n_cus) return 1;
+    const int s = (int)std::min<size_t>(std::min({a.n_cus / t, 8, wr_longest(a)}), slots / t);
+    if (s < 2) return 1;
+    const double fill = (double)t / a.n_cus, fill_s = (double)t * s / a.n_cus, late = tiles / a.n_cus > 3 ? 0.4 : 1.0, steps = (double)a.Tk * (a.tile / kStepCols);
+    const double gain_us = steps * late * (0.9 + 0.35 * fill - (0.9 + 0.35 * (fill_s < 1.0 ? fill_s : 1.0)) / s);
+    return gain_us <= 2.0 * (double)t * s * kWrBM * kWrBN * sizeof(float) / 3.0e6 + 8.0 ? 1 : s;
+}
+
 // A launch whose tile count is a little more than a multiple of the compute units ends with a part-filled round that lasts almost as long as a full one.
 // Its tiles can be a launch of their own: in halves of 128 rows by prefill_kernel_r128, which takes three quarters of the time, needs no workspace where
 // it leaves K whole, and has the lower start-up, or in 256-row tiles of this kernel, both with K in slices while they fill the chip at most once.  Priced as
 // in prefill_r128_split (less 5 us for a round that follows others, 2 us to be gained at least).  Over 85 launches (13 weights, 700 - 6872 rows, both mask tiles,
-// f = 0, 1/2 and 1) the choice takes 0.90 of the launch without a last round of its own, the best of all slices 0.895, the best without halves 0.915.  us,
-// whole -> best 256-row slices -> choice: 22016 x 4096, f = 1/2, mask tile 64, 1003 rows (344 tiles) 154.8 -> 148.7 -> 145.1 (this one without a workspace);
-// 700 rows (258) 141.6 -> 121.3 -> 120.0; 4096 x 4096, mask tile 128, 4200 rows (272) 136.4 -> 114.7 -> 109.5; 256-row slices are still the better ones where
-// they fill the chip and halves would not: 5120 x 13824, 4096 rows (320) 440.4 -> 363.4 in four slices, 408.2 in halves.  After more than four full rounds the
-// workgroups are far out of step and the part-filled round costs little: 22016 x 4096, f = 1/2, 1376 tiles 476.5, in halves 494.6; 1118 tiles 432.2 and 409.2.
+// f = 0, 1/2 and 1) the choice takes 0.90 of the launch without a last round of its own, the best of all slices 0.895, the best without halves 0.915.  us, whole -> best
+// 256-row slices -> choice: 22016 x 4096, f = 1/2, mask tile 64, 1003 rows (344 tiles) 154.8 -> 148.7 -> 145.1 (this one without a workspace); 700 rows (258) 141.6 -> 121.3 -> 120.0; 4096 x 4096, mask tile 128,
+// 4200 rows (272) 136.4 -> 114.7 -> 109.5; 256-row slices are still the better ones where they fill the chip and halves would not: 5120 x 13824, 4096 rows
+// (320) 440.4 -> 363.4 in four slices, 408.2 in halves.  After more than four full rounds the part-filled one costs little where K is short
+// (22016 x 4096, f = 1/2, 1376 tiles 476.5, in halves 494.6), and there only wr_tail_slices is asked: 5120 x 13824, f = 1/2, 16640 rows (1300 tiles) in 8 slices 1363,
+// as one launch 1489.
 LastRound prefill_wreg_last_round(int tiles, const GemmArgs& a) {
-    const int t = tiles % a.n_cus;
+    const int t = tiles % a.n_cus, full = tiles / a.n_cus;
     LastRound best = {0, 1, false};
-    if (tiles < a.n_cus || tiles / a.n_cus > 4 || t == 0 || 2 * t > a.n_cus) return best;
+    if (full < 1 || t == 0 || 2 * t > a.n_cus) return best;
     const double slot = (double)t * kWrBM * kWrBN * sizeof(float);
-    const auto priced = [&](const PrefillPrice& p, int blocks, int slices, double launches) {
-        return pf_price(p, a, 0, blocks, slices) + launches + (slices > 1 ? (2.0 * slices + 1.0) * slot / p.rate : 0.0);
+    const size_t slots = a.ws ? a.ws_bytes / ((size_t)kWrBM * kWrBN * sizeof(float)) : 0;
+    const auto priced = [&](const PrefillPrice& p, int blocks, int slices) {
+        return pf_price(p, a, 0, blocks, slices) + (slices > 1 ? (2.0 * slices + 1.0) * slot / p.rate : 0.0);
     };
-    double us = priced(kPriceWreg, t, 1, -5.0) - 2.0;
+    double us = priced(kPriceWreg, t, 1) - 5.0 - 2.0;
     const auto consider = [&](const LastRound& r, double price) {
         if (price < us) { us = price; best = r; }
     };
-    const int fit = a.ws ? (int)std::min<size_t>(8, a.ws_bytes / (size_t)slot) : 1;
-    for (int s = 1; s <= 8 && (s == 1 || (s <= fit && s <= wr_longest(a))); ++s) {
-        if (2 * t * s <= a.n_cus) consider({t, s, true}, priced(kPriceR128, 2 * t, s, 0.0));
-        if (s > 1 && t * s <= a.n_cus) consider({t, s, false}, priced(kPriceWreg, t, s, 0.0));
+    const auto fits = [&](int blocks, int slices) { return blocks * slices <= a.n_cus; };
+    const int most = full > 4 ? 0 : std::max(1, (int)std::min<size_t>(std::min(8, wr_longest(a)), slots / t));
+    for (int s = 1; s <= most; ++s) {
+        if (fits(2 * t, s)) consider({t, s, true}, priced(kPriceR128, 2 * t, s));
+        if (s > 1 && fits(t, s)) consider({t, s, false}, priced(kPriceWreg, t, s));
     }
+    if (full > 4)
+        if (const int s = wr_tail_slices(tiles, a, slots); s > 1) best = {t, s, false};
     return best;
 }
 
@@ -1076,18 +1093,11 @@ LastRound prefill_wreg_tail(const GemmArgs& a) {
     return prefill_wreg_last_round((int)(((a.N + kWrBN - 1) / kWrBN) * ((a.M + kWrBM - 1) / kWrBM)), a);
 }
 
-// The workspace that the last round was given before prefill_kernel_r128 took part in it, by the estimate of that time: patch_gemm_static goes on
-// accepting and refusing by it, and a caller that asks for a size gets no smaller one.
+// The workspace that the last round is given by wr_tail_slices: patch_gemm_static accepts and refuses by it, and a caller that asks for a size gets no
+// smaller one.
 size_t prefill_wreg_tail_bytes(const GemmArgs& a) {
-    const int tiles = (int)(((a.N + kWrBN - 1) / kWrBN) * ((a.M + kWrBM - 1) / kWrBM)), t = tiles % a.n_cus;
-    if (tiles < a.n_cus || t == 0 || 2 * t > a.n_cus) return 0;
-    const int s = std::min({a.n_cus / t, 8, wr_longest(a)});
-    if (s < 2) return 0;
-    const size_t bytes = (size_t)t * (size_t)s * kWrBM * kWrBN * sizeof(float);
-    const double fill = (double)t / a.n_cus, fill_s = (double)t * s / a.n_cus, late = tiles / a.n_cus > 3 ? 0.4 : 1.0;
-    const double steps = (double)a.Tk * (a.tile / kStepCols);
-    const double gain_us = steps * late * (0.9 + 0.35 * fill - (0.9 + 0.35 * (fill_s < 1.0 ? fill_s : 1.0)) / s);
-    return gain_us <= 2.0 * (double)bytes / 3.0e6 + 8.0 ? 0 : bytes;
+    const int tiles = (int)(((a.N + kWrBN - 1) / kWrBN) * ((a.M + kWrBM - 1) / kWrBM)), s = wr_tail_slices(tiles, a, ~(size_t)0);
+    return s < 2 ? 0 : (size_t)(tiles % a.n_cus) * (size_t)s * kWrBM * kWrBN * sizeof(float);
 }
 
 // One launch of the kernel of a.tile: tiles t0 .. t0 + cnt - 1 of the order, `slices` K slices each (MODE 1, 2).

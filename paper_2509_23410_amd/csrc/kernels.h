@@ -167,6 +167,8 @@ int patch_test_schedule_deals(int64_t M, int count, const int64_t* N, int64_t K,
 // `slices` K slices, `halves` as in LastRound; halves = -1: as the rest of the launch.
 int patch_test_prefill_last_round(const void* X, int64_t M, const patch_packed* const* P, void* const* Y, int count, int halves, int slices, int y_bf16,
                                   void* workspace, size_t workspace_bytes, void* stream);
+// prefill_wreg_last_round for such a launch (arguments as in patch_test_schedule): returns its tail, -1 = bad arguments
+int patch_test_last_round(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* slices, int* halves);
 // prefill_r128_split of the same, for the prefill path
 int patch_test_prefill128_split(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes);
 // deal_units: gridDim.x of a launch over `units` feature groups whose rows go over `deals` workgroups

@@ -54,3 +54,43 @@ def test_limits_of_the_choice():
                         assert s < 2 or (4 * s * M * sum(N) <= ws and 512 * s <= K)
                         taken.add(s)
     assert {0, 1, 2, 8} <= taken
+
+
+def _last_round(M, N, K, tile, f, ws_bytes):
+    slices, halves = ctypes.c_int(), ctypes.c_int()
+    tail = B.lib().patch_test_last_round(ctypes.c_int64(M), len(N), (ctypes.c_int64 * len(N))(*N), ctypes.c_int64(K), tile, round(100 * f), ctypes.c_size_t(ws_bytes),
+                                         ctypes.byref(slices), ctypes.byref(halves))
+    return tail, slices.value, bool(halves.value)
+
+
+@pytest.mark.parametrize("N,K,tile,f,M,workspace", [([11008] * 2, 4096, 64, 0.6, 1003, False), ([4096], 4096, 128, 0.5, 4200, True), ([5120], 13824, 128, 0.5, 4096, True),
+                                                    ([5120], 5120, 128, 0.0, 3248, False), ([11008], 4096, 128, 0.0, 3035, True),
+                                                    ([13824] * 2, 5120, 64, 1.0, 768, True)])
+def test_a_last_round_that_lasts_is_a_launch_of_its_own(N, K, tile, f, M, workspace):
+    assert _last_round(M, N, K, tile, f, 384 << 20 if workspace else 0)[0] > 0
+
+
+def test_limits_of_the_last_round():
+    """At most half a round, halves behind one to four full ones; slots that the workspace holds, slices that the dies hold at once and that K has."""
+    taken = set()
+    for tile in (64, 128):
+        for N in ([1024], [4096], [11008, 11008], [5120] * 3, [640, 128]):
+            for K in (tile, 512, 4096, 13824):
+                for M in (1003, 2048, 3035, 4200, 6000, 21916, 40000):
+                    for f in (0.0, 0.5, 1.0):
+                        for ws in (0, 4 << 20, 384 << 20):
+                            tail, slices, halves = _last_round(M, N, K, tile, f, ws)
+                            tiles = sum(-(-n // 256) for n in N) * -(-M // 256)
+                            assert tail in (0, tiles % 256) and (tail == 0 or (256 <= tiles and 2 * tail <= 256 and (halves or slices > 1)))
+                            assert not halves or tiles < 5 * 256
+                            assert slices == 1 or (1 < slices <= 8 and slices * tail * (256 << 10) <= ws and slices <= K // tile)
+                            assert tail * slices * (2 if halves else 1) <= 256
+                            taken.add((slices > 1, halves))
+    assert taken == {(False, False), (False, True), (True, False), (True, True)}
+
+
+@pytest.mark.parametrize("N,K,tile,f,M,slices", [(5120, 13824, 128, 0.5, 16640, 8), (4096, 14336, 128, 0.0, 20736, 8), (4096, 11008, 64, 1.0, 20736, 8)])
+def test_a_long_last_round_after_more_than_four_is_sliced(N, K, tile, f, M, slices):
+    """1.09 - 1.11 times as long in one launch; without a workspace, and where K is short, one launch it is."""
+    assert _last_round(M, [N], K, tile, f, 384 << 20) == (N // 256 * (M // 256) % 256, slices, False)
+    assert _last_round(M, [N], K, tile, f, 0)[0] == 0 and _last_round(M, [N], 4096, tile, f, 384 << 20)[0] == 0
