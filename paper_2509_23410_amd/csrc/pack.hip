@@ -45,19 +45,23 @@ void launch_put_words(uint32_t* dst, const uint32_t* src, size_t n, hipStream_t 
 
 // ------------------------------------------------------------------ mask merge
 // A wavefront and step: up to 512 consecutive elements of a row, 8 per lane (16 bytes of W, 8 bytes of mask), whose tiles are at most eight
-// consecutive bits of the map.  W_hat may be W itself (in place): neither is declared restrict.  Bound by memory: 11008 x 4096, tile 128, f = 0.6
-// 35.6 us (5.8 TB/s), 4096 x 4096, tile 64, f = 1/2 13.0; with the map in device memory, a byte per tile, and a lookup per lane 38.2 and 15.1 - and about
-// 25 us of the call for the map's buffer and its copy.  The matrix passed here starts at the first tile of the map part: `rows` rows and Tk tiles of a matrix with K columns.
+// consecutive bits of the map; or, where a row is at most 256 long (ROW_LANES < 64 lanes of 8 elements), of 64 / ROW_LANES rows, which are of one tile row.
+// W_hat may be W itself (in place): neither is declared restrict.  Bound by memory.  Calls with the host's part, us,
+// a thread per 8 elements with the map in device memory -> this: 11008 x 4096, tile 128, f = 1/2 48.0 -> 43.6, 4096 x 4096, tile 64 32.9 -> 27.7, 13824 x 640, tile 128 25.7 -> 20.8;
+// 1048576 x 64 70.7 -> 66.4, where a wavefront per row took 153.
+// The matrix passed here starts at the first tile of the map part: `rows` rows and Tk tiles of a matrix with K columns.
+template <int ROW_LANES>
 __global__ __launch_bounds__(256) void apply_mask_kernel(const TileMapArgs map, const uint16_t* W, const uint8_t* __restrict__ mask24, int64_t K, int rows,
                                                          int Tk, int tile_log2, uint16_t* W_hat) {
-    const int cols = Tk << tile_log2, per_row = (cols + 511) / 512, units = rows * per_row;
+    constexpr int ROWS = 64 / ROW_LANES, COLS = 8 * ROW_LANES;
+    const int cols = Tk << tile_log2, per_row = (cols + COLS - 1) / COLS, units = rows / ROWS * per_row;
     const int lane = threadIdx.x & 63;
     for (int u = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + threadIdx.x / 64)); u < units; u += (int)gridDim.x * 4) {
-        const int n = u / per_row, k0 = 512 * (u % per_row), k = k0 + 8 * lane;
+        const int n = ROWS * (u / per_row), k0 = COLS * (u % per_row), k = k0 + 8 * (lane % ROW_LANES);
         const int t = (n >> tile_log2) * Tk + (k0 >> tile_log2), w = t >> 5, w1 = w + 1 < 2 * kMapGroups ? w + 1 : w;
         const uint64_t bits = (((uint64_t)map.g[w1 >> 1].dense[w1 & 1] << 32) | map.g[w >> 1].dense[w & 1]) >> (t & 31);
         if (k >= cols) continue;
-        const int64_t at = n * K + k;
+        const int64_t at = (n + lane / ROW_LANES) * K + k;
         union { u32x4 v; uint16_t h[8]; } x;
         x.v = *reinterpret_cast<const u32x4*>(W + at);
         if (!((bits >> ((k - k0) >> tile_log2)) & 1)) {
@@ -83,9 +87,11 @@ void launch_apply_mask(const uint16_t* W, const uint8_t* mask24, const uint8_t* 
         for (int64_t tk = 0; tk < Tk; tk += step_k) {
             const int rn = (int)(Tn - tn < step_n ? Tn - tn : step_n), rk = (int)(Tk - tk < step_k ? Tk - tk : step_k);
             fill_map_args(&map, tile_map + tn * Tk + tk, rn * rk, 0);   // (contiguous: rk = Tk or rn = 1)
-            const int64_t at = tn * tile * K + tk * tile;
-            const int64_t units = (int64_t)rn * tile * (((int64_t)rk * tile + 511) / 512), blocks = (units + 3) / 4;
-            hipLaunchKernelGGL(apply_mask_kernel, dim3((unsigned)(blocks < 256 * 32 ? blocks : 256 * 32)), dim3(256), 0, stream, map, W + at, mask24 + at, K,
+            const int64_t at = tn * tile * K + tk * tile, cols = (int64_t)rk * tile;
+            const int row_lanes = cols <= 64 ? 8 : cols <= 128 ? 16 : cols <= 256 ? 32 : 64;
+            const int64_t units = (int64_t)rn * tile * row_lanes / 64 * ((cols + 511) / 512), blocks = (units + 3) / 4;
+            const auto kernel = row_lanes == 8 ? &apply_mask_kernel<8> : row_lanes == 16 ? &apply_mask_kernel<16> : row_lanes == 32 ? &apply_mask_kernel<32> : &apply_mask_kernel<64>;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(blocks < 256 * 32 ? blocks : 256 * 32)), dim3(256), 0, stream, map, W + at, mask24 + at, K,
                                rn * tile, rk, tile == 128 ? 7 : 6, W_hat + at);
         }
 }
