@@ -659,6 +659,14 @@ int patch_test_prefill_last_round(const void* X, int64_t M, const patch_packed* 
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
+int64_t patch_test_map_args(const uint8_t* map, int n, uint32_t before, uint32_t* out) {
+    if (!map || !out || n < 1 || n > kMapTiles) return -1;
+    TileMapArgs a;
+    before = fill_map_args(&a, map, n, before);
+    memcpy(out, a.g, (size_t)(n + 63) / 64 * sizeof a.g[0]);
+    return before;
+}
+
 int patch_test_deal_units(int units, int deals, int n_cus) { return units < 1 || deals < 1 || n_cus < 8 ? -1 : (int)deal_units(units, (unsigned)deals, n_cus); }
 
 patch_status patch_gemm_ex(const void* X, int64_t M, const patch_packed* P, void* Y, void* stream, const patch_gemm_opts* opts) {

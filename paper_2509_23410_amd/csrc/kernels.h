@@ -171,6 +171,8 @@ int patch_test_prefill_last_round(const void* X, int64_t M, const patch_packed* 
 int patch_test_last_round(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes, int* slices, int* halves);
 // prefill_r128_split of the same, for the prefill path
 int patch_test_prefill128_split(int64_t M, int count, const int64_t* N, int64_t K, int tile, int sparse_pct, size_t ws_bytes);
+// fill_map_args of n <= 19456 tiles, `before` dense ones in front of them: three words per 64 tiles to out; returns the dense tiles up to the end, -1 = bad arguments
+int64_t patch_test_map_args(const uint8_t* map, int n, uint32_t before, uint32_t* out);
 // deal_units: gridDim.x of a launch over `units` feature groups whose rows go over `deals` workgroups
 int patch_test_deal_units(int units, int deals, int n_cus);
 // The 4-bit product of `count` weights sharing X by one kernel, whatever the dispatch would take: 0 the strip kernel, 1 batch4_kernel, both in

@@ -16,10 +16,23 @@ namespace patch {
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // ------------------------------------------------------------------ small data as kernel arguments
+// Eight bytes to eight bits, nonzero = 1, the first byte lowest
+static inline uint64_t nonzero_bits(const uint8_t* bytes) {
+    constexpr uint64_t low7 = 0x7f7f7f7f7f7f7f7full;
+    uint64_t x;
+    memcpy(&x, bytes, 8);
+    x = (((x & low7) + low7) | x) & ~low7;            // the top bit of every nonzero byte
+    return ((x >> 7) * 0x0102040810204080ull) >> 56;   // byte i's bit to bit 56 + i, without carries
+}
+
+// (on the way of every call that has a map: 19456 tiles byte by byte took 18.5 us, eight at a time 3.6)
 uint32_t fill_map_args(TileMapArgs* a, const uint8_t* map, int n, uint32_t before) {
     for (int g = 0; 64 * g < n; ++g) {
+        const int here = n - 64 * g < 64 ? n - 64 * g : 64;
         uint64_t bits = 0;
-        for (int i = 0; i < 64 && 64 * g + i < n; ++i) bits |= (uint64_t)(map[64 * g + i] != 0) << i;
+        int i = 0;
+        for (; i + 8 <= here; i += 8) bits |= nonzero_bits(map + 64 * g + i) << i;
+        for (; i < here; ++i) bits |= (uint64_t)(map[64 * g + i] != 0) << i;
         a->g[g].dense[0] = (uint32_t)bits;
         a->g[g].dense[1] = (uint32_t)(bits >> 32);
         a->g[g].before = before;
