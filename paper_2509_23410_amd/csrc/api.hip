@@ -5,7 +5,6 @@
 #include <string.h>
 
 #include <algorithm>
-#include <condition_variable>
 #include <map>
 #include <mutex>
 #include <new>
@@ -163,48 +162,6 @@ static patch_status static_scratch(void** out) {
     *out = g_scratch_ptr[dev];
     return PATCH_OK;
 }
-
-namespace {
-constexpr int kHostWords = 64, kHostWordStride = 16;   // a cache line each, one page
-std::mutex g_words_mutex;
-std::condition_variable g_words_free;
-uint32_t *g_words = nullptr, *g_words_device = nullptr;
-uint64_t g_words_held = 0;
-}  // namespace
-
-HostWord::HostWord() {
-    std::unique_lock<std::mutex> lock(g_words_mutex);
-    if (!g_words) {
-        void *host = nullptr, *device = nullptr;
-        if (hipHostMalloc(&host, kHostWords * kHostWordStride * sizeof(uint32_t), hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
-            (void)hipGetLastError();
-            return;
-        }
-        if (hipHostGetDevicePointer(&device, host, 0) != hipSuccess) {
-            (void)hipGetLastError();
-            (void)hipHostFree(host);
-            return;
-        }
-        g_words = static_cast<uint32_t*>(host);
-        g_words_device = static_cast<uint32_t*>(device);
-    }
-    g_words_free.wait(lock, [] { return g_words_held != ~0ull; });
-    slot_ = __builtin_ctzll(~g_words_held);
-    g_words_held |= 1ull << slot_;
-    __atomic_store_n(g_words + slot_ * kHostWordStride, 0u, __ATOMIC_RELEASE);
-}
-
-HostWord::~HostWord() {
-    if (slot_ < 0) return;
-    {
-        std::lock_guard<std::mutex> lock(g_words_mutex);
-        g_words_held &= ~(1ull << slot_);
-    }
-    g_words_free.notify_one();
-}
-
-uint32_t* HostWord::device() const { return g_words_device + slot_ * kHostWordStride; }
-uint32_t HostWord::value() const { return __atomic_load_n(g_words + slot_ * kHostWordStride, __ATOMIC_ACQUIRE); }
 
 extern "C" {
 
