@@ -790,7 +790,7 @@ int prefill_r128_split(const GemmArgs& a, const int64_t* N, int count) {
         total += N[i];
     }
     const int64_t b128 = units * ((a.M + 127) / 128);
-    if (b128 > a.n_cus) return 0;
+    if (b128 > a.n_cus || (count > 1 && !prefill_wreg_supports(a))) return 0;   // (such a set runs weight by weight)
     const int b256 = (int)(units * ((a.M + 255) / 256));
     const size_t per_slice = (size_t)a.M * (size_t)total * sizeof(float);
     double best = 0.0;

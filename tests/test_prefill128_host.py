@@ -51,6 +51,7 @@ def test_limits_of_the_choice():
                         s = _split(M, N, K, tile, 0.5, ws)
                         blocks = sum(-(-n // 256) for n in N) * -(-M // 128)
                         assert 0 <= s <= 8 and (s == 0 or blocks * s <= 256)
+                        assert s == 0 or len(N) == 1 or (K <= 16384 and 2 * M * K < 2 ** 32)    # beyond them a set runs weight by weight
                         assert s < 2 or (4 * s * M * sum(N) <= ws and 512 * s <= K)
                         taken.add(s)
     assert {0, 1, 2, 8} <= taken
