@@ -176,9 +176,9 @@ int64_t patch_test_map_args(const uint8_t* map, int n, uint32_t before, uint32_t
 // deal_units: gridDim.x of a launch over `units` feature groups whose rows go over `deals` workgroups
 int patch_test_deal_units(int units, int deals, int n_cus);
 // The 4-bit product of `count` weights sharing X by one kernel, whatever the dispatch would take: 0 the strip kernel, 1 batch4_kernel, both in
-// passes of up to 64 rows, 2 / 3 the prefill-shaped kernel in blocks of 128 / 256 rows, 4 the one with two K groups (a single weight), 5 the same with the blocks beyond a multiple of the compute units
-// in `chunks` K slices (slots of 128 KB).  chunks > 1 (a
-// single weight, kernels 1 - 4): K in that many chunks over the workspace.
+// passes of up to 64 rows, 2 / 3 the prefill-shaped kernel in blocks of 128 / 256 rows, 4 the one with two K groups, 5 the same with the blocks
+// beyond a multiple of the compute units in `chunks` K slices (slots of 128 KB).  2 - 5: a single weight.  chunks > 1 (a single weight,
+// kernels 1 - 4): K in that many chunks over the workspace.
 int patch_test_gemm4(const void* X, int64_t M, const patch_packed4* const* P, void* const* Y, int count, int kernel, int chunks,
                      void* workspace, size_t workspace_bytes, void* stream);
 // patch_test_schedule for patch_gemm4_ex (count 1) and patch_gemm4_many: kernels as in patch_test_gemm4.

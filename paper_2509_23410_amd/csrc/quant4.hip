@@ -1589,8 +1589,8 @@ int patch_test_schedule4(int64_t M, int count, const int64_t* N, int64_t K, int 
     Q4PrefillKernel which;
     int tail;
     if (const int split = count == 1 ? q4_prefill_split(M, d, &which, &tail) : 0) {
-        kernel[0] = 2 + which;
-        chunks[0] = tail ? 1 : split;
+        kernel[0] = tail ? 5 : 2 + which;
+        chunks[0] = split;
         return 1;
     }
     if (M > 8 * kQ4Rows) return -1;
@@ -1663,13 +1663,14 @@ int patch_test_gemm4(const void* X, int64_t M, const patch_packed4* const* P, vo
     if (kernel == 5) {
         if (chunks < 2 || blocks < P[0]->n_cus || tail == 0) return PATCH_ERR_ARG;
         if (!workspace || !q4_aligned16(workspace) || workspace_bytes < (size_t)chunks * (size_t)tail * kKgSlotBytes) return PATCH_ERR_SIZE;
-    } else
-    if (chunks > 1 && (!workspace || !q4_aligned16(workspace) || workspace_bytes < (size_t)chunks * (size_t)rows * (size_t)P[0]->N * sizeof(float)))
+    } else if (chunks > 1 && (!workspace || !q4_aligned16(workspace) || workspace_bytes < (size_t)chunks * (size_t)rows * (size_t)P[0]->N * sizeof(float))) {
         return PATCH_ERR_SIZE;
+    }
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (kernel >= 4 && P[0]->K > kKgMaxK) return PATCH_ERR_SHAPE;
     if (kernel > 1)
-        return q4_prefill(static_cast<const uint16_t*>(X), M, P[0], static_cast<float*>(Y[0]), chunks, kernel == 5 ? kQ4Groups : (Q4PrefillKernel)(kernel - 2), tail, static_cast<float*>(workspace), s);
+        return q4_prefill(static_cast<const uint16_t*>(X), M, P[0], static_cast<float*>(Y[0]), chunks, kernel == 5 ? kQ4Groups : (Q4PrefillKernel)(kernel - 2), tail,
+                          static_cast<float*>(workspace), s);
     const Q4Plan plan = {kernel == 1, chunks, 0.0};
     return q4_passes(X, M, P, Y, count, static_cast<float*>(workspace), workspace_bytes, s, &plan);
 }

@@ -76,3 +76,36 @@ def test_last_round_in_slices(tile, N, K):
         assert bool((buf[:1024] == 7.0).all()) and bool((buf[1024 + M * N:] == 7.0).all()), "wrote outside Y"
         assert bool((ws[chunks * tail * 32768:] == 7.0).all()), "wrote behind the workspace"
     P.close()
+
+
+@pytest.mark.parametrize("tile,N,K,M,kernel", [(128, 640, 4224, 1112, 4), (128, 1408, 4224, 600, 4), (64, 640, 4160, 1112, 4), (64, 1344, 4224, 600, 4),
+                                               (128, 640, 4096, 10968, 5), (128, 1408, 4224, 5464, 5), (64, 640, 4160, 10968, 5), (64, 1344, 4160, 5464, 5)])
+def test_the_default_choice_in_slices(tile, N, K, M, kernel):
+    """Through the public call, where it takes this kernel with K in slices (4) and with the last round alone in slices (5): equal to the launch called for by
+    name, and nothing written behind a workspace of just the size that allows it."""
+    vp = ctypes.c_void_p
+    c = synth.make_case("kgroups", N, K, 1, tile, 0.5, seed=9)
+    Wd = torch.from_numpy(c.W.view(np.int16)).cuda().view(torch.bfloat16)
+    stream = torch.cuda.current_stream().cuda_stream
+    B.patch_apply_mask(Wd, torch.from_numpy(c.mask24).cuda(), c.tile_map, N, K, tile, Wd, stream)
+    P = B.patch_pack4(Wd, N, K, c.tile_map, tile, stream)
+    B.patch_unpack4(P, W_deq=Wd, stream=stream)
+    W, floats = Wd.double(), (4 if kernel == 4 else 2) * M * N
+    X = torch.randn(M, K, device="cuda", generator=torch.Generator(device="cuda").manual_seed(M)).to(torch.bfloat16)
+    which, chunks = (ctypes.c_int * 8)(), (ctypes.c_int * 8)()
+    pct = round(100 * (c.tile_map == 0).sum() / c.tile_map.size)
+    assert B.lib().patch_test_schedule4(ctypes.c_int64(M), 1, (ctypes.c_int64 * 1)(N), ctypes.c_int64(K), tile, pct, ctypes.c_size_t(4 * floats), which, chunks) == 1
+    assert which[0] == kernel and chunks[0] > 1, (which[0], chunks[0])
+    ws = torch.full((floats + 1024,), float("nan"), device="cuda")
+    ws[floats:] = 7.0
+    Y, Z = (torch.full((M, N), float("nan"), device="cuda") for _ in range(2))
+    B.patch_gemm4(X, M, P, Y, stream, workspace=ws[:floats])
+    assert bool((ws[floats:] == 7.0).all()), "wrote behind the workspace"
+    for m in range(0, M, 4096):
+        ref, bound = X[m:m + 4096].double() @ W.T, 2 * K ** 0.5 * 2.0 ** -24 * X[m:m + 4096].double().norm(dim=1)[:, None] * W.norm(dim=1)[None, :]
+        assert ((Y[m:m + 4096].double() - ref).abs() / bound).max().item() <= 1.0
+    named = torch.full((max(floats, chunks[0] * M * N),), float("nan"), device="cuda")
+    assert B.lib().patch_test_gemm4(vp(X.data_ptr()), ctypes.c_int64(M), (vp * 1)(P.handle), (vp * 1)(Z.data_ptr()), 1, kernel, chunks[0], vp(named.data_ptr()),
+                                    ctypes.c_size_t(4 * named.numel()), vp(stream)) == B.OK
+    assert torch.equal(Y, Z)
+    P.close()

@@ -171,3 +171,29 @@ def test_choice_from_the_4_bit_storage(N, K, tile, f, M, workspace, us):
     chosen = "prefill" if kernel[0] > 1 else "+".join("strip" if kernel[i] == 0 else f"b{chunks[i]}" for i in range(n))
     assert chosen in us, (chosen, us)
     assert us[chosen] <= 1.03 * min(us.values()) + 0.3, (chosen, us)
+
+
+def test_limits_of_the_4_bit_prefill_choice():
+    """K slices: at most 8 of at least 512 columns, partial sums that the workspace holds; of the last round alone, blocks that fill the chip at most once behind
+    one to four full rounds, slots of 128 KB."""
+    kernel, chunks, taken = (ctypes.c_int * 8)(), (ctypes.c_int * 8)(), set()
+    for tile in (64, 128):
+        for N in (640, 1024, 4096, 11008):
+            for K in (384, 1024, 4096, 13824):
+                for M in (129, 300, 600, 800, 1536, 2100, 4096, 10968, 20000):
+                    for f in (0.0, 0.5, 1.0):
+                        for slices in (0, 2, 5):
+                            ws = 4 * slices * M * N
+                            n = B.lib().patch_test_schedule4(ctypes.c_int64(M), 1, (ctypes.c_int64 * 1)(N), ctypes.c_int64(K), tile, round(100 * f), ctypes.c_size_t(ws), kernel, chunks)
+                            if n != 1 or kernel[0] < 2:
+                                continue
+                            k, c = kernel[0], chunks[0]
+                            assert 1 <= c <= 8 and (c == 1 or (512 * c <= K and ws > 0))
+                            if k == 5:
+                                blocks = -(-N // 256) * -(-M // 128)
+                                assert c > 1 and 256 < blocks < 5 * 256 and 2 * (blocks % 256) <= 256 and c * (blocks % 256) <= 256
+                                assert c * (blocks % 256) * (128 << 10) <= ws
+                            else:
+                                assert c == 1 or 4 * c * M * N <= ws
+                            taken.add((k, c > 1))
+    assert {(2, False), (2, True), (4, False), (4, True), (5, True)} <= taken, taken
