@@ -157,10 +157,13 @@ patch_status patch_gemm_ex(const void* X, int64_t M, const patch_packed* P, void
  * allocating routine; the first call on a device looks the array's address up (hipGetSymbolAddress).
  *   X, M, P, Y, stream   as for patch_gemm
  * The schedule is the one patch_gemm_ex picks when given a workspace of that size, so results are bit-equal to
- * patch_gemm_ex with such a caller workspace.  Returns PATCH_ERR_SIZE - nothing is launched - when that schedule
- * would want more scratch than the array holds (patch_gemm_workspace_bytes(M, P, NULL) > PATCH_STATIC_SCRATCH_BYTES;
- * e.g. split launches of large M x N; on tile 64 only the slices of whole launches count, and a part-filled last round is
- * split as far as the array allows); use patch_gemm_ex with a workspace of your own then.  Every partial sum the
+ * patch_gemm_ex with such a caller workspace.  Returns PATCH_ERR_SIZE - nothing is launched - where K slices of
+ * the whole product (slices x M x N x 4 bytes, large M x N) or, on mask tile 128, 256-row slices of the part-filled last
+ * round of its 256 x 256 tiles (slices x tiles x 256 KB) would be more than the array holds; use patch_gemm_ex with a
+ * workspace of your own then.  The rule is this call's own and goes by M, the weight's sizes and its share of 2:4 tiles alone: the
+ * launch may need less than what was counted, or nothing, and a last round that would like more slices than the array holds runs in
+ * fewer.  So patch_gemm_workspace_bytes does not tell: its answer may be more than PATCH_STATIC_SCRATCH_BYTES for a call that is
+ * accepted (last rounds of either mask tile).  Every partial sum the
  * kernels read from the scratch is written by the same call first, so nothing needs clearing between calls, but
  * all calls on one GPU share the one array: calls that overlap in time on the same GPU (different streams or
  * threads) race on it.  Errors otherwise as patch_gemm_ex.
@@ -247,8 +250,9 @@ patch_status patch_tune_layer(patch_tune_table* t, const void* X_decode, int64_t
 /* Bytes of patch_gemm_opts.workspace that let the product with these M, P and opts (path, split_k, variant; NULL =
  * defaults) run as if given any amount: slices x M x N x 4 for a split prefill launch, slices x tiles x 256 KB when only
  * the part-filled last round of a prefill launch is split, chunks x rows x N x 4 for decode passes of `rows` rows (up
- * to 64; 128 in variant 7 and where AUTO takes 65 .. 128 rows in one pass) whose K is split, and 0 where nothing is split -
- * then the workspace stays untouched.  For a single weight; a set: see patch_gemm_many. */
+ * to 64; 128 in variant 7 and where AUTO takes 65 .. 128 rows in one pass) whose K is split.  An upper bound: where the schedule is
+ * automatic it also covers the splits of the kernels that the chosen one was weighed against, so that the launch may write less, or
+ * nothing.  0: the workspace stays untouched.  For a single weight; a set: see patch_gemm_many. */
 size_t patch_gemm_workspace_bytes(int64_t M, const patch_packed* P, const patch_gemm_opts* opts);
 
 /*

@@ -894,8 +894,9 @@ patch_status patch_tune_layer(patch_tune_table* t, const void* X_decode, int64_t
     return PATCH_OK;
 }
 
-// Bytes of workspace a product uses given any amount.  slices_only: of a prefill launch on mask tile 64 only the split of whole launches,
-// as prefill_kernel_areg would make it - by which patch_gemm_static accepts or refuses; prefill_kernel_w64 runs in what the array holds.
+// Bytes of workspace that let a product run as if given any amount; no less than the kernels in 256-row tiles would use in place of
+// prefill_kernel_r128.  slices_only: what patch_gemm_static accepts and refuses by, whatever it launches: the slices of 256-row tiles - mask tile 128: of
+// the whole product or of the last round (prefill_wreg_tail_bytes); mask tile 64: of the whole product, as prefill_kernel_areg would make them.
 static size_t workspace_need(int64_t M, const patch_packed* P, const patch_gemm_opts* opts, bool slices_only) {
     if (!P || M <= 0) return 0;
     int path = PATCH_PATH_AUTO, split_k = 0, variant = 0;
@@ -1077,7 +1078,7 @@ patch_status patch_gemm(const void* X, int64_t M, const patch_packed* P, void* Y
 
 patch_status patch_gemm_static(const void* X, int64_t M, const patch_packed* P, void* Y, void* stream) {
     if (!X || !P || !Y || M < 0) return PATCH_ERR_ARG;
-    // what the automatic schedule would use given any amount of workspace: beyond the static array, refuse
+    // (a rule of its own beside what the launch below uses: the calls that were refused or accepted once stay so)
     const size_t need = workspace_need(M, P, nullptr, true);
     if (need > kStaticScratchBytes) return PATCH_ERR_SIZE;
     void* ws = nullptr;

@@ -78,6 +78,31 @@ def test_static_scratch_takes_a_part_filled_last_round_of_mask_tile_64():
     P.close()
 
 
+def test_static_scratch_and_last_rounds_of_mask_tile_128():
+    """324 tiles, the last 68 in slices of 51 MB where there is a workspace for them: accepted, since slices of 256-row tiles alone would not be made, and run in
+    what the array holds.  384 tiles of a longer K, whose last 128 would be 64 MB in two slices: refused, though the launch takes halves and writes no
+    scratch; the size asked for is those 64 MB."""
+    stream = torch.cuda.current_stream().cuda_stream
+    P, M = _weight(4608, 4096, 128, 0.0), 4608
+    assert B.patch_gemm_workspace_bytes(M, P) == 3 * 68 * (256 << 10) > B.STATIC_SCRATCH_BYTES
+    X = torch.randn(M, 4096, device="cuda", generator=torch.Generator(device="cuda").manual_seed(M)).to(torch.bfloat16)
+    Y, E = (torch.full((M, 4608), float("nan"), device="cuda") for _ in range(2))
+    B.patch_gemm_static(X, M, P, Y, stream)
+    B.patch_gemm(X, M, P, E, stream, workspace=torch.empty(B.STATIC_SCRATCH_BYTES // 4, device="cuda"))
+    assert torch.equal(Y, E)
+    P.close()
+    P, M = _weight(4096, 11008, 128, 0.5), 6144
+    assert B.patch_gemm_workspace_bytes(M, P) == 2 * 128 * (256 << 10)
+    X = torch.randn(M, 11008, device="cuda", generator=torch.Generator(device="cuda").manual_seed(M)).to(torch.bfloat16)
+    Y, ws = torch.full((M, 4096), 7.0, device="cuda"), torch.full((16 << 20,), 7.0, device="cuda")
+    with pytest.raises(B.PatchError) as e:
+        B.patch_gemm_static(X, M, P, Y, stream)
+    assert e.value.status == B.ERR_SIZE and bool((Y == 7.0).all())
+    B.patch_gemm(X, M, P, Y, stream, workspace=ws)
+    assert bool((ws == 7.0).all())
+    P.close()
+
+
 @pytest.mark.parametrize("tile,N,K,f", [(128, 640, 4096, 0.5), (64, 448, 4160, 0.5)])
 def test_sets_write_what_the_header_says(tile, N, K, f):
     """patch_gemm_many at any M, few rows included: at most max(8, split_k) x M x (sum of N) floats of the workspace, or 64 MB where the
