@@ -109,3 +109,32 @@ def test_the_default_choice_in_slices(tile, N, K, M, kernel):
                                     ctypes.c_size_t(4 * named.numel()), vp(stream)) == B.OK
     assert torch.equal(Y, Z)
     P.close()
+
+
+@pytest.mark.parametrize("tile,N,K,chunks", [(128, 384, 640, 1), (128, 384, 640, 3), (64, 320, 448, 1), (64, 320, 448, 2)])
+def test_infinities_and_nan_in_x(tile, N, K, chunks):
+    """Infinities and NaN in X reach the outputs of their rows that they reach in the kernel with one K group, and no others."""
+    vp = ctypes.c_void_p
+    c = synth.make_case("kgroups", N, K, 1, tile, 0.5, seed=13)
+    Wd = torch.from_numpy(c.W.view(np.int16)).cuda().view(torch.bfloat16)
+    stream = torch.cuda.current_stream().cuda_stream
+    B.patch_apply_mask(Wd, torch.from_numpy(c.mask24).cuda(), c.tile_map, N, K, tile, Wd, stream)
+    P = B.patch_pack4(Wd, N, K, c.tile_map, tile, stream)
+    B.patch_unpack4(P, W_deq=Wd, stream=stream)
+    M, W = 200, Wd.double()
+    X = torch.randn(M, K, device="cuda", generator=torch.Generator(device="cuda").manual_seed(M)).to(torch.bfloat16)
+    clean = X.clone()
+    X[3, 5], X[64, K - 1], X[64, 1], X[130, K // 2], X[M - 1, 7] = float("inf"), float("inf"), float("-inf"), float("nan"), float("-inf")
+    out = []
+    for kernel in (4, 2):
+        Y, ws = torch.zeros(M, N, device="cuda"), torch.full((chunks * M * N,), float("nan"), device="cuda")
+        assert B.lib().patch_test_gemm4(vp(X.data_ptr()), ctypes.c_int64(M), (vp * 1)(P.handle), (vp * 1)(Y.data_ptr()), 1, kernel, chunks, vp(ws.data_ptr()),
+                                        ctypes.c_size_t(4 * ws.numel()), vp(stream)) == B.OK
+        out.append(Y)
+    Y, Z = out
+    assert torch.equal(torch.isnan(Y), torch.isnan(Z)) and torch.equal(torch.isinf(Y), torch.isinf(Z)) and torch.equal(Y[torch.isinf(Y)], Z[torch.isinf(Z)])
+    assert bool(torch.isnan(Y[130]).any()) and bool((~torch.isfinite(Y[3])).any()) and bool((~torch.isfinite(Y[M - 1])).any())
+    rows = [m for m in range(M) if m not in (3, 64, 130, M - 1)]
+    ref, bound = clean.double() @ W.T, 2 * K ** 0.5 * 2.0 ** -24 * clean.double().norm(dim=1)[:, None] * W.norm(dim=1)[None, :]
+    assert ((Y.double() - ref).abs() / bound)[rows].max().item() <= 1.0
+    P.close()

@@ -171,3 +171,42 @@ def test_the_last_round_of_the_default_choice(workspace):
         B.patch_gemm(X, M, P, Z, stream, path=B.PATH_PREFILL, workspace=torch.full((need // 4,), float("nan"), device="cuda"))
         assert torch.equal(Y, Z)
     P.close()
+
+
+@pytest.mark.parametrize("tile,N,K,split", [(128, 384, 640, 1), (128, 384, 640, 3), (64, 320, 448, 1), (64, 320, 448, 2)])
+def test_infinities_and_nan_in_x(tile, N, K, split):
+    """Infinities and NaN in X reach the outputs of their rows that they reach in the earlier kernel of 128 rows, and no others."""
+    stream = torch.cuda.current_stream().cuda_stream
+    P, W = _weight(N, K, tile, 0.5, 17)
+    M = 200
+    X = _x(M, K)
+    clean = X.clone()
+    X[3, 5], X[64, K - 1], X[64, 1], X[130, K // 2], X[M - 1, 7] = float("inf"), float("inf"), float("-inf"), float("nan"), float("-inf")
+    Y, Z, ws = torch.zeros(M, N, device="cuda"), torch.zeros(M, N, device="cuda"), torch.full((split * M * N,), float("nan"), device="cuda")
+    assert B.lib().patch_test_prefill128(vp(X.data_ptr()), ctypes.c_int64(M), (vp * 1)(P.handle), (vp * 1)(Y.data_ptr()), 1, split, 0, vp(ws.data_ptr()),
+                                         ctypes.c_size_t(4 * ws.numel()), vp(stream)) == B.OK
+    B.patch_gemm(X, M, P, Z, stream, path=B.PATH_PREFILL, variant=5)
+    assert torch.equal(torch.isnan(Y), torch.isnan(Z)) and torch.equal(torch.isinf(Y), torch.isinf(Z)) and torch.equal(Y[torch.isinf(Y)], Z[torch.isinf(Z)])
+    assert bool(torch.isnan(Y[130]).any()) and bool(torch.isinf(Y[3]).any()) and bool(torch.isinf(Y[M - 1]).any())
+    rows = [m for m in range(M) if m not in (3, 64, 130, M - 1)]
+    ref, bound = _ref(clean, W)
+    assert ((Y.double() - ref).abs() / bound)[rows].max().item() <= 1.0
+    P.close()
+
+
+def test_x_of_more_than_4_gb():
+    """Rows of X beyond 32-bit byte offsets, through the public call: the first, the last and those around the middle and each 4 GB."""
+    stream = torch.cuda.current_stream().cuda_stream
+    N, K, M = 128, 65664, 32768
+    P, W = _weight(N, K, 128, 0.5, 19)
+    pct = 100 * P.dims()[3] // (K // 128)
+    assert B.lib().patch_test_prefill128_split(ctypes.c_int64(M), 1, (ctypes.c_int64 * 1)(N), ctypes.c_int64(K), 128, pct, ctypes.c_size_t(0)) == 1
+    X = torch.randn(M, K, device="cuda", dtype=torch.bfloat16, generator=torch.Generator(device="cuda").manual_seed(1))
+    Y = torch.full((M, N), float("nan"), device="cuda")
+    B.patch_gemm(X, M, P, Y, stream, path=B.PATH_PREFILL)
+    edge = 2 ** 32 // (2 * K)
+    for r in (0, M // 2 - 32, edge - 32, M - 64):
+        ref, bound = _ref(X[r:r + 64], W)
+        assert ((Y[r:r + 64].double() - ref).abs() / bound).max().item() <= 1.0, r
+    assert bool(torch.isfinite(Y).all())
+    P.close()
