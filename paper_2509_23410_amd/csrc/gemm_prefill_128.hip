@@ -1,19 +1,21 @@
 // Prefill-shaped hybrid GEMM in blocks of 256 features x 128 rows (Section 4 / Appendix A of the paper: the product for the prefill input,
 // dense and 2:4 tiles mixed inside one launch): the kernel of a few hundred rows, where blocks of 256 rows are too few to fill the chip.
 //
-// What bounds it: the loop.  A K-step is 16 matrix instructions (dense; 8 sparse) per wavefront of 32 - 34 cycles each, and per compute unit 16 KB of X
-// and 32 KB (18) of weights from the L2, which sends about 32 - 38 bytes per clock and unit with all of them busy.  prefill_kernel_areg runs the same
-// block with eight wavefronts of 32 features: each 16 bytes of X read from LDS serve one matrix instruction, two wavefronts of a SIMD wait at the same
-// two barriers of every step, and its loads are one step ahead.  Here four wavefronts own 64 features x 128 rows each, so that an X operand read from LDS
-// serves two matrix instructions; the weights of two steps are in flight or in use in registers that the asm statements name (v192 - v255, two buffers)
-// and the X of three more in four LDS stages (64 KB); and the operands of the next half-step are read between the matrix instructions of this one, over the
-// barrier: one barrier per step.  Waits are counted by hand (vmcnt), since loads into LDS and into registers share the counter and the compiler would
-// wait for all of them.  64 KB of LDS and at most 256 registers leave room for a second workgroup on the compute unit.
+// What bounds it: the loop.  A K-step is 32 matrix instructions (dense; 16 sparse) per wavefront of 32 cycles each, and per compute unit 16 KB of X
+// and 32 KB (18) of weights from the L2.  Counted on 15360 x 5120, 512 rows (240 workgroups, 70 us at f = 1/2), f = 0 / 1/2 / 1: the matrix pipes are busy 60 / 51 / 41 %
+// of a wavefront's life and a compute unit draws 30 / 29 / 29 bytes per clock from the L2, whatever f; wavefronts wait 50 / 42 / 34 % of the time.
+// prefill_kernel_areg runs the same block with eight wavefronts of 32 features: each 16 bytes of X read from LDS serve one matrix instruction, two wavefronts of
+// a SIMD wait at the same two barriers of every step, and its loads are one step ahead.  Here four wavefronts own 64 features x 128 rows each, so that an X
+// operand read from LDS serves two matrix instructions; the weights of two steps are in flight or in use in registers that the asm statements name (v192 -
+// v255, two buffers) and the X of three more in four LDS stages (64 KB); and the operands of the next half-step are read between the matrix instructions of
+// this one, over the barrier: one barrier per step.  Waits are counted by hand (vmcnt), since loads into LDS and into registers share the counter and the
+// compiler would wait for all of them.  64 KB of LDS and at most 256 registers leave room for a second workgroup on the compute unit.
 //
 // Measured against prefill_kernel_areg, unsplit, f = 1/2, mask tile 128: 4096 x 4096, 128 rows 63.6 -> 52.0 us; 4096 x 8192, 128 rows 123 -> 96 (f = 0
-// 144 -> 106, f = 1 107 -> 87); 15360 x 5120, 512 rows 86.7 -> 70.2; 5120 x 5120, 512 rows in three slices 43.6 -> 38.0; mask tile 64, 4096 x 8192, 128 rows
-// 122 -> 93.  Against the 256-row kernels it gains only while its blocks are one round of the chip (see prefill_r128_split).  Tried and slower: areg's eight
-// wavefronts with X in a ring of four stages (52.3 / 99.4 us for the first two).
+// 144 -> 106, f = 1 107 -> 87); mask tile 64, 4096 x 8192, 128 rows 122 -> 93.  Against what a call with a workspace took before, weights from memory: 5120 x
+// 5120, 512 rows in three slices with their sum 44.0 -> 38.1; three of them sharing X 73.1 -> 70.6.  Against the 256-row kernels it gains only while its
+// blocks are one round of the chip (see prefill_r128_split).  Tried and slower: areg's eight wavefronts with X in a ring of four stages (52.3 / 99.4 us for
+// the first two).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

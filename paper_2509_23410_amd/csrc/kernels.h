@@ -8,9 +8,8 @@ void patch_note_hip_error(int hip_error);
 
 namespace patch {
 
-// A part of a tile map as kernel arguments (4096 bytes at most, the hidden ones included), so that no launch has to wait for a copy of the map (and mask merge, pack and unpack of a
-// 4096 x 4096 matrix, 4-bit, took 170 us with one and a status word read back, 148 without): 64 tiles a group, bit set =
-// dense, and how many of the whole map's tiles before the group are.
+// A part of a tile map as kernel arguments (4096 bytes at most, the hidden ones included), so that no launch has to wait for a copy of the map: 64
+// tiles a group, bit set = dense, and how many of the whole map's tiles before the group are.
 constexpr int kMapGroups = 304, kMapTiles = 64 * kMapGroups;
 struct TileMapArgs {
     struct { uint32_t dense[2], before; } g[kMapGroups];

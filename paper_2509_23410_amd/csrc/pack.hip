@@ -60,8 +60,8 @@ void launch_put_words(uint32_t* dst, const uint32_t* src, size_t n, hipStream_t 
 // A wavefront and step: up to 512 consecutive elements of a row, 8 per lane (16 bytes of W, 8 bytes of mask), whose tiles are at most eight
 // consecutive bits of the map; or, where a row is at most 256 long (ROW_LANES < 64 lanes of 8 elements), of 64 / ROW_LANES rows, which are of one tile row.
 // W_hat may be W itself (in place): neither is declared restrict.  Bound by memory.  Calls with the host's part, us,
-// a thread per 8 elements with the map in device memory -> this: 11008 x 4096, tile 128, f = 1/2 48.0 -> 43.6, 4096 x 4096, tile 64 32.9 -> 27.7, 13824 x 640, tile 128 25.7 -> 20.8;
-// 1048576 x 64 70.7 -> 66.4, where a wavefront per row took 153.
+// a thread per 8 elements with the map in device memory -> this: 11008 x 4096, tile 128, f = 1/2 47.0 -> 42.6, 4096 x 4096, tile 64 31.7 -> 26.4, 13824 x 640, tile 128 25.3 -> 20.5;
+// 1048576 x 64 69.9 -> 60.7, where a wavefront per row took 153.
 // The matrix passed here starts at the first tile of the map part: `rows` rows and Tk tiles of a matrix with K columns.
 template <int ROW_LANES>
 __global__ __launch_bounds__(256) void apply_mask_kernel(const TileMapArgs map, const uint16_t* W, const uint8_t* __restrict__ mask24, int64_t K, int rows,

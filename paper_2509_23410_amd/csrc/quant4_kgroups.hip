@@ -9,10 +9,12 @@
 // requested three steps and X three units (of two K-steps) ahead and counted, and one barrier joins two K-steps.  Cycles a K-step, one
 // workgroup, cache-resident, f = 0 / 1/2 / 1: 1365 / 1285 / 1066, prefill4_kernel 1900 and more; 11008 x 4096, 500 rows, f = 0 / 1/2 / 1 66.2 / 59.9 / 49.0 ->
 // 53.5 / 48.2 / 41.0 us, mask tile 64 67.2 -> 48.5.
-// What bounds it: a SIMD's two wavefronts issue about 490 (2:4) or 670 (dense) instructions a unit, one every four cycles; matrix instructions take 1024 /
-// 2048 cycles of that.  Measured and not taken: a unit as one branch-free statement per tile type (1.02 - 1.05 times as long), a barrier every two
-// units (1.07), 16-bit position loads that need no shift (1.02 - 1.03), operands converted in one piece between phases (1.2 - 1.3).  A wavefront lowers its
-// priority from phase to phase, so that of two that share a SIMD the one behind goes first (dense steps 4 % shorter).
+// What bounds it: a SIMD's two wavefronts issue about 490 (2:4) or 670 (dense) instructions a unit, and its matrix instructions take 1024 / 2048
+// cycles.  Counted on 11008 x 4096, 500 rows, f = 0 / 1/2 / 1: matrix pipes busy 63 / 50 / 38 % of a wavefront's life, vector instructions issued in
+// 57 / 48 / 41 % of it, wavefronts waiting 35 / 33 / 36 %; a compute unit draws 17 - 19 bytes per clock from the L2, which sends prefill_kernel_r128 29.
+// Measured and not taken: a unit as one branch-free statement per tile type (1.02 - 1.05 times as long), a barrier every two units (1.07), 16-bit
+// position loads that need no shift (1.02 - 1.03), operands converted in one piece between phases (1.2 - 1.3).  A wavefront lowers its priority from
+// phase to phase, so that of two that share a SIMD the one behind goes first (dense steps 4 % shorter).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -237,12 +239,12 @@ __global__ __launch_bounds__(512) void prefill4_kgroups_kernel(const uint16_t* _
     int ent_base = 0;
     uint32_t ent = trow[lane < Tk ? lane : Tk - 1];   // table entries of 64 tiles, one per lane
     asm volatile("" : "+v"(ent));
-    auto tile_of = [&](int n) __attribute__((always_inline)) {
+    auto tile_at = [&](int n) __attribute__((always_inline)) {   // tile of this group's K-step of unit n
         const int t = KPT == 2 ? n : 2 * n + g;
         return t < Tk ? t : Tk - 1;
     };
     auto entry = [&](int n) __attribute__((always_inline)) {
-        const int t = tile_of(n);
+        const int t = tile_at(n);
         if (t >= ent_base + 64) {
             ent_base += 64;
             ent = trow[ent_base + lane < Tk ? ent_base + lane : Tk - 1];
@@ -254,7 +256,7 @@ __global__ __launch_bounds__(512) void prefill4_kgroups_kernel(const uint16_t* _
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)lds;
     const uint32_t lds_x = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + g * kKgStep + fw * 1024));
     auto load_x = [&](int n) __attribute__((always_inline)) {
-        const int t = KPT == 2 ? 2 * (n < U ? n : U - 1) + g : tile_of(n);   // K-step
+        const int t = KPT == 2 ? 2 * (n < U ? n : U - 1) + g : tile_at(n);   // K-step
         kg_load_x(xbase + (size_t)t * 128, xoff, lds_x + (uint32_t)(n & 3) * (2 * kKgStep));
     };
     auto load_w = [&](auto buf, int n) __attribute__((always_inline)) {
@@ -262,7 +264,7 @@ __global__ __launch_bounds__(512) void prefill4_kgroups_kernel(const uint16_t* _
         const uint32_t e = eb[B] = entry(n);
         const bool sp = entry_sparse(e);
         const uint32_t v = sp ? v_spa : v_den, gap = sp ? 128 : 256, next = sp ? 2 * KPT * 256 : 2 * KPT * 512;
-        kg_load<B, KPT>(payload + entry_offset(e), v, v + gap, v + next, v + next + gap, v_pos, sc + (size_t)tile_of(n) * 16, v_sc, v_sc + 64 * Tk_all, sp);
+        kg_load<B, KPT>(payload + entry_offset(e), v, v + gap, v + next, v + next + gap, v_pos, sc + (size_t)tile_at(n) * 16, v_sc, v_sc + 64 * Tk_all, sp);
     };
     const uint32_t xr = lds0 + g * kKgStep + xs_off(i32, q);   // chunk 2 c + q of the row is at xr ^ 32 c
     auto at = [&](int n, int c) __attribute__((always_inline)) { return (xr ^ (32u * c)) + (uint32_t)(n & 3) * (2 * kKgStep); };

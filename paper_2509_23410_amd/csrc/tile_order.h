@@ -4,9 +4,9 @@
 
 namespace patch {
 
-// Tile t of the launch order -> feature block bn (256 features), row block bm (256 rows): groups of 4 row blocks x
-// all feature blocks, so that the workgroups an XCD runs at a time cover about 8 feature blocks x 4 row blocks
-// and share both operands in its L2.
+// Tile t of the launch order -> feature block bn (256 features), row block bm (256 rows, or 128 in the kernels of such blocks): groups of 4 row
+// blocks x all feature blocks, so that the workgroups an XCD runs at a time cover about 8 feature blocks x 4 row blocks and share both
+// operands in its L2.
 __device__ __forceinline__ void tile_of(int t, int tiles_n, int tiles_m, int& bn, int& bm) {
     constexpr int GM = 4;
     const int full = (tiles_m / GM) * GM * tiles_n;
