@@ -761,23 +761,24 @@ double prefill_estimate(const GemmArgs& a) {
 // One round of prefill_kernel_r128, or what the launch took without it?  Priced by launches of 100 .. 4096 rows of 13 weights at f = 0, 1/2 and 1, both
 // mask tiles, with and without a workspace (4718 timings):
 //     us = base + begin fill + rounds x K-steps per workgroup x (t0 + t1 fill) x g(f) + (split > 1 ? second + (2 split + 1) M N 4 B / rate : 0)
-// (prices below; rms error 6 % for blocks of 128 rows, 7 % for 256; rounds = those of the die that gets most).  A second workgroup on a compute unit gains little - the matrix cores and the
-// path from the L2 are shared: 11008 x 4096, f = 1/2, 172 / 344 workgroups 55 / 95 us, where 256-row blocks take 73 - so that the blocks, times the
-// slices, must not be more than the compute units of any die (the launch deals the blocks out in eight equal runs, a die each: 84 blocks x 3 slices, 33
-// workgroups on seven dies of 32 compute units and 21 on the eighth, took 72.9 us, 3072 x 8192, f = 0, 805 rows, where the 256-row kernel takes 53.7).
-// Split: at most 8 slices of at least 512 columns that the workspace holds.
-// Taken where the price is 3 % below; in slices against a launch without them 3 % and 1.5 us (1280 x 1280, f = 1/2, 1003 rows 20.0 us in two slices, 19.1
-// unsplit by prefill_kernel_areg); unsplit 3 % and 0.6 us (calls of 15 - 18 us are dearer than priced: 1024 x 1024, f = 1/2, 2960 rows 17.8 us, 17.2
-// without), against a launch in s slices 6 s % and 0.6 us (the price of long unsplit workgroups is low on a full chip: 3072 x 8192, f = 0.7, mask tile
-// 64, 2231 rows 92.3 us, in two slices by the 256-row kernel 85.9).  Held against the launches without this kernel, timed in turn: 10 hidden sizes of
-// 896 - 5120 with their weights and sets, 80 - 4096 rows, both mask tiles, f from 0 to 1: with a workspace 1217 of 1919 taken, 0.903 of the time over
-// all of them, the worst 1.011; without one 1582 of 1763, 0.840, none slower (4096 x 4096, f = 1/2, 2048 rows 57.7 -> 53.7 us; 5120 x 5120, 512 rows
-// 43.6 -> 38.0; without a workspace 11008 x 4096, 512 rows 65.2 -> 54.9).  The best choice of each would be 0.896 and 0.838.  Of 2772
-// launches of 8 hidden sizes that the rule was not fitted to 7 were more than 1 % slower, the worst 1.022.  Beyond the limits of the
-// register-weight kernels the other side is pf_estimate, which knows no f: 70 of these launches, 3584 x 18944, 0.81 and 0.78, none slower.  Whether the
-// decode path's passes run instead is decided by the prices above, as if this kernel did not exist.
+// (prices below; rms error 6 % for blocks of 128 rows, 7 % for 256; rounds = those of the die that gets most).  A second workgroup on a compute unit
+// gains little - the matrix cores and the path from the L2 are shared: 11008 x 4096, f = 1/2, 172 / 344 workgroups 55 / 95 us, where 256-row blocks take
+// 73 - so that the blocks, times the slices, must not be more than the compute units of any die (the launch deals the blocks out in eight equal runs, a
+// die each: 84 blocks x 3 slices, 33 workgroups on seven dies of 32 compute units and 21 on the eighth, took 72.9 us, 3072 x 8192, f = 0, 805 rows,
+// where the 256-row kernel takes 53.7). Split: at most 8 slices of at least 512 columns that the workspace holds. Taken where the price is 3 % below; in
+// slices against a launch without them 3 % and 1.5 us (1280 x 1280, f = 1/2, 1003 rows 20.0 us in two slices, 19.1 unsplit by prefill_kernel_areg);
+// unsplit 3 % and 0.6 us (calls of 15 - 18 us are dearer than priced: 1024 x 1024, f = 1/2, 2960 rows 17.8 us, 17.2 without), against a launch in s
+// slices 6 s % and 0.6 us (the price of long unsplit workgroups is low on a full chip: 3072 x 8192, f = 0.7, mask tile 64, 2231 rows 92.3 us, in two
+// slices by the 256-row kernel 85.9).  Held against the launches without this kernel, timed in turn: 10 hidden sizes of 896 - 5120 with their weights
+// and sets, 80 - 4096 rows, both mask tiles, f from 0 to 1: with a workspace 1217 of 1919 taken, 0.903 of the time over all of them, the worst 1.011;
+// without one 1582 of 1763, 0.840, none slower (4096 x 4096, f = 1/2, 2048 rows 57.7 -> 53.7 us; 5120 x 5120, 512 rows 43.6 -> 38.0; without a workspace
+// 11008 x 4096, 512 rows 65.2 -> 54.9).  The best choice of each would be 0.896 and 0.838.  Of 2772 launches of 8 hidden sizes that the rule was not
+// fitted to 7 were more than 1 % slower, the worst 1.022.  Beyond the limits of the register-weight kernels the other side is pf_estimate, which knows
+// no f: 70 of these launches, 3584 x 18944, 0.81 and 0.78, none slower.  Whether the decode path's passes run instead is decided by the prices above, as
+// if this kernel did not exist.
 double pf_price(const PrefillPrice& p, const GemmArgs& a, int64_t N, int64_t blocks, int split) {
-    const int64_t wgs = blocks * split, die = a.n_cus < 8 ? 1 : a.n_cus / 8, rounds = ((blocks + 7) / 8 * split + die - 1) / die, steps = (int64_t)((a.Tk + split - 1) / split) * (a.tile / kStepCols);
+    const int64_t die = a.n_cus < 8 ? 1 : a.n_cus / 8, rounds = ((blocks + 7) / 8 * split + die - 1) / die;
+    const int64_t wgs = blocks * split, steps = (int64_t)((a.Tk + split - 1) / split) * (a.tile / kStepCols);
     const double fill = wgs < a.n_cus ? (double)wgs / a.n_cus : 1.0, f = 0.01 * a.sparse_pct, y = (double)a.M * (double)N * 4.0;
     return p.base + p.begin * fill + (double)rounds * (double)steps * (p.t0 + p.t1 * fill) * (1.0 - p.g1 * f - p.g2 * f * f) +
            (split > 1 ? p.second + (2.0 * split + 1.0) * y / p.rate : 0.0);

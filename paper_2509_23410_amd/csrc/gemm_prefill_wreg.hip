@@ -1057,20 +1057,19 @@ static int wr_tail_slices(int tiles, const GemmArgs& a, size_t slots) {
 
 // A launch whose tile count is a little more than a multiple of the compute units ends with a part-filled round that lasts almost as long as a full one.
 // Its tiles can be a launch of their own: in halves of 128 rows by prefill_kernel_r128, which takes three quarters of the time, needs no workspace where
-// it leaves K whole, and has the lower start-up, or in 256-row tiles of this kernel, both with K in slices while no die gets more of them than it holds.  Priced as
-// in prefill_r128_split, less 5 us for a round that follows others, with 2 us to be gained at least and 1 us more in slices, and less what the round hides among
-// the others: workgroups of 2:4 tiles are out of step at the end of a round, and the first to finish begin with the tiles that are left: 4 us per 64 K-steps
-// and full round, at f = 0 1 us for all full rounds but one.  (Three 4096 x 4096, f = 1, 2741 rows, 528 tiles: 169 us as one launch, 185 with the last 16 tiles in
-// halves.)  Where that leaves nothing to gain, wr_tail_slices still may.  Over 1266 launches (10 hidden sizes of 896 - 5120 with their weights and sets, one to
-// four full rounds, both mask tiles, f from 0 to 1) against launches of 256-row tiles and slices alone, with a workspace 0.964 of the time, without 0.976; 21 and 36 of
-// them took more than 1.5 % longer, as did 55 of the same launches timed against
-// themselves; over 1126 launches taken of 8 other hidden sizes 0.941 and 0.951, 14 of them more than 2 % slower, as were 14 of 672 not taken (the weights' place in
-// memory).  us, whole -> best 256-row slices -> choice: 22016 x 4096, f = 1/2,
-// mask tile 64, 1003 rows (344 tiles) 154.8 -> 148.7 -> 145.1 (this one without a workspace); 700 rows (258) 141.6 -> 121.3 -> 120.0; 4096 x 4096, mask tile 128,
-// 4200 rows (272) 136.4 -> 114.7 -> 109.5; 256-row slices are still the better ones where they fill the chip and halves would not: 5120 x 13824, 4096 rows
-// (320) 440.4 -> 363.4 in four slices, 408.2 in halves.  After more than four full rounds the part-filled one costs little where K is short
-// (22016 x 4096, f = 1/2, 1376 tiles 476.5, in halves 494.6), and there only wr_tail_slices is asked: 5120 x 13824, f = 1/2, 16640 rows (1300 tiles) in 8 slices 1363,
-// as one launch 1489.
+// it leaves K whole, and has the lower start-up, or in 256-row tiles of this kernel, both with K in slices while no die gets more of them than it holds.
+// Priced as in prefill_r128_split, less 5 us for a round that follows others, with 2 us to be gained at least and 1 us more in slices, and less what the
+// round hides among the others: workgroups of 2:4 tiles are out of step at the end of a round, and the first to finish begin with the tiles that are
+// left: 4 us per 64 K-steps and full round, at f = 0 1 us for all full rounds but one.  (Three 4096 x 4096, f = 1, 2741 rows, 528 tiles: 169 us as one
+// launch, 185 with the last 16 tiles in halves.)  Where that leaves nothing to gain, wr_tail_slices still may.  Over 1266 launches (10 hidden sizes of
+// 896 - 5120 with their weights and sets, one to four full rounds, both mask tiles, f from 0 to 1) against launches of 256-row tiles and slices alone,
+// with a workspace 0.964 of the time, without 0.976; 21 and 36 of them took more than 1.5 % longer, as did 55 of the same launches timed against
+// themselves; over 1126 launches taken of 8 other hidden sizes 0.941 and 0.951, 14 of them more than 2 % slower, as were 14 of 672 not taken (the
+// weights' place in memory).  us, whole -> best 256-row slices -> choice: 22016 x 4096, f = 1/2, mask tile 64, 1003 rows (344 tiles) 154.8 -> 148.7 ->
+// 145.1 (this one without a workspace); 700 rows (258) 141.6 -> 121.3 -> 120.0; 4096 x 4096, mask tile 128, 4200 rows (272) 136.4 -> 114.7 -> 109.5;
+// 256-row slices are still the better ones where they fill the chip and halves would not: 5120 x 13824, 4096 rows (320) 440.4 -> 363.4 in four slices,
+// 408.2 in halves.  After more than four full rounds the part-filled one costs little where K is short (22016 x 4096, f = 1/2, 1376 tiles 476.5, in
+// halves 494.6), and there only wr_tail_slices is asked: 5120 x 13824, f = 1/2, 16640 rows (1300 tiles) in 8 slices 1363, as one launch 1489.
 LastRound prefill_wreg_last_round(int tiles, const GemmArgs& a) {
     const int t = tiles % a.n_cus, full = tiles / a.n_cus;
     LastRound best = {0, 1, false};

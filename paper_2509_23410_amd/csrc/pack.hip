@@ -57,12 +57,12 @@ void launch_put_words(uint32_t* dst, const uint32_t* src, size_t n, hipStream_t 
 }
 
 // ------------------------------------------------------------------ mask merge
-// A wavefront and step: up to 512 consecutive elements of a row, 8 per lane (16 bytes of W, 8 bytes of mask), whose tiles are at most eight
-// consecutive bits of the map; or, where a row is at most 256 long (ROW_LANES < 64 lanes of 8 elements), of 64 / ROW_LANES rows, which are of one tile row.
-// W_hat may be W itself (in place): neither is declared restrict.  Bound by memory.  Calls with the host's part, us,
-// a thread per 8 elements with the map in device memory -> this: 11008 x 4096, tile 128, f = 1/2 47.0 -> 42.6, 4096 x 4096, tile 64 31.7 -> 26.4, 13824 x 640, tile 128 25.3 -> 20.5;
-// 1048576 x 64 69.9 -> 60.7, where a wavefront per row took 153.
-// The matrix passed here starts at the first tile of the map part: `rows` rows and Tk tiles of a matrix with K columns.
+// A wavefront and step: up to 512 consecutive elements of a row, 8 per lane (16 bytes of W, 8 bytes of mask), whose tiles are at most eight consecutive
+// bits of the map; or, where a row is at most 256 long (ROW_LANES < 64 lanes of 8 elements), of 64 / ROW_LANES rows, which are of one tile row. W_hat
+// may be W itself (in place): neither is declared restrict.  Bound by memory.  Calls with the host's part, us, a thread per 8 elements with the map in
+// device memory -> this: 11008 x 4096, tile 128, f = 1/2 47.0 -> 42.6, 4096 x 4096, tile 64 31.7 -> 26.4, 13824 x 640, tile 128 25.3 -> 20.5; 1048576 x
+// 64 69.9 -> 60.7, where a wavefront per row took 153. The matrix passed here starts at the first tile of the map part: `rows` rows and Tk tiles of a
+// matrix with K columns.
 template <int ROW_LANES>
 __global__ __launch_bounds__(256) void apply_mask_kernel(const TileMapArgs map, const uint16_t* W, const uint8_t* __restrict__ mask24, int64_t K, int rows,
                                                          int Tk, int tile_log2, uint16_t* W_hat) {
@@ -103,7 +103,8 @@ void launch_apply_mask(const uint16_t* W, const uint8_t* mask24, const uint8_t* 
             const int64_t at = tn * tile * K + tk * tile, cols = (int64_t)rk * tile;
             const int row_lanes = cols <= 64 ? 8 : cols <= 128 ? 16 : cols <= 256 ? 32 : 64;
             const int64_t units = (int64_t)rn * tile * row_lanes / 64 * ((cols + 511) / 512), blocks = (units + 3) / 4;
-            const auto kernel = row_lanes == 8 ? &apply_mask_kernel<8> : row_lanes == 16 ? &apply_mask_kernel<16> : row_lanes == 32 ? &apply_mask_kernel<32> : &apply_mask_kernel<64>;
+            const auto kernel = row_lanes == 8 ? &apply_mask_kernel<8> : row_lanes == 16 ? &apply_mask_kernel<16> : row_lanes == 32 ? &apply_mask_kernel<32>
+                                                                                                                              : &apply_mask_kernel<64>;
             hipLaunchKernelGGL(kernel, dim3((unsigned)(blocks < 256 * 32 ? blocks : 256 * 32)), dim3(256), 0, stream, map, W + at, mask24 + at, K,
                                rn * tile, rk, tile == 128 ? 7 : 6, W_hat + at);
         }

@@ -12,7 +12,7 @@ def _fill(tiles, before=0):
     fn.restype = ctypes.c_int64
     out = np.full(3 * -(-len(tiles) // 64), 7, np.uint32)
     args, best = (ctypes.c_void_p(tiles.ctypes.data), len(tiles), ctypes.c_uint32(before), ctypes.c_void_p(out.ctypes.data)), 1.0
-    for _ in range(30):
+    for _ in range(100):
         t = time.perf_counter()
         total = fn(*args)
         best = min(best, time.perf_counter() - t)
